@@ -303,8 +303,7 @@ int compress_blocks(kv_cache *c, const __half *ksrc, const __half *vsrc, int64_t
         vjob.page_list = static_cast<uint32_t *>(c->buf.v_pages);
         vjob.max_pages = c->max_pages_v;
         int rc;
-        if ((rc = launch_token_params(c, kjob, s))) return rc;
-        if ((rc = launch_token_params(c, vjob, s))) return rc;
+        if ((rc = launch_token_params(c, kjob, vjob, s))) return rc;
         if (c->cfg.repack == KV_REPACK_V_MEDIAN) {
             uint8_t *order = static_cast<uint8_t *>(c->buf.token_order);
             if ((rc = launch_v_median_order(c, vjob, kjob.meta, order, s))) return rc;
@@ -312,8 +311,7 @@ int compress_blocks(kv_cache *c, const __half *ksrc, const __half *vsrc, int64_t
         }
         kjob.fill_bound16 = c->fill_bound16[0];
         vjob.fill_bound16 = c->fill_bound16[1];
-        if ((rc = launch_pack(c, kjob, s))) return rc;
-        if ((rc = launch_pack(c, vjob, s))) return rc;
+        if ((rc = launch_pack(c, kjob, vjob, s))) return rc;
         c->fill_bound16[0] += uint64_t(nb) * B * H * (chunk_max_bytes(c->cfg.pack_size, c->wide_k) / 16);
         c->fill_bound16[1] += uint64_t(nb) * B * H * (chunk_max_bytes(c->cfg.pack_size, c->wide_v) / 16);
         c->packed_tokens += int64_t(nb) * N;

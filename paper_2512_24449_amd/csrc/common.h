@@ -216,18 +216,6 @@ struct StagedRound {
     uint64_t arena_cap16;
 };
 
-// A staged part: chunks in their slots, to be copied to the arena once the part's scan has set
-// their index words.
-struct StagedPart {
-    const uint8_t *staging;   // slot i holds chunk first_chunk + i
-    const uint32_t *index;
-    int64_t first_chunk;      // absolute chunk number
-    int n;
-    uint8_t *arena;
-    StagedRound round;        // of the part's tensor
-};
-
-
 struct kv_cache {
     kv_config_t cfg;
     kv_buffers_t buf;
@@ -306,8 +294,9 @@ struct CompressJob {
     uint64_t fill_bound16;    // the arena holds at most this much before the round (every chunk so far at its largest)
 };
 
-int launch_token_params(const kv_cache *c, const CompressJob &job, hipStream_t s);
-int launch_pack(const kv_cache *c, const CompressJob &job, hipStream_t s);
+// Both tensors of a round (they share every launch).
+int launch_token_params(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s);
+int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s);
 // V-median order of the job's blocks (job describes V); permutes the token metadata of both
 // tensors into storage order and fills `order`.
 int launch_v_median_order(const kv_cache *c, const CompressJob &vjob, uint32_t *k_meta, uint8_t *order,

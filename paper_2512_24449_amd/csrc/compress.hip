@@ -20,7 +20,7 @@
 // No atomics in either path: the arena bytes are a pure function of the input.
 #include <algorithm>
 
-#include "common.h"
+#include "unpack.h"
 
 namespace packkv {
 
@@ -48,18 +48,42 @@ __device__ inline uint4 load8_as_fp16(const __half *p, bool bf16) {
     return as_fp16(make_uint4(v.x, v.y, v.z, v.w), bf16);
 }
 
+// A token's metadata word from its smallest and largest value: fp16 scale | fp16 minimum << 16.
+__device__ inline uint32_t token_meta_word(float mn, float mx, float rel) {
+    mn = mn + 0.0f;  // a zero minimum or maximum is stored as +0
+    mx = mx + 0.0f;
+    float range = mx - mn;
+    float s = rel * range;
+    // The product is rounded to fp32 first and to fp16 second; keep the
+    // compiler from fusing both into one mixed-precision FMA (one rounding).
+    asm volatile("" : "+v"(s));
+    __half s16 = __float2half_rn(s);
+    __half m16 = __float2half_rn(mn);  // exact: mn is an fp16 value
+    return uint32_t(__half_as_ushort(s16)) | (uint32_t(__half_as_ushort(m16)) << 16);
+}
+
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void token_params_kernel(const __half *__restrict__ src,
-                                                           int64_t batch_stride,
-                                                           int64_t token_stride, int row_elems,
-                                                           float rel, uint32_t *__restrict__ meta,
-                                                           int64_t meta_stride,
-                                                           int64_t first_token, bool bf16) {
+// Both tensors of an append share every launch (blockIdx.z or the item number says which): the
+// launches of a small round cost more than its work.
+struct ParamTensor {
+    const __half *src;
+    float rel;
+    uint32_t *meta;
+};
+struct ParamArgs {
+    ParamTensor t[2];
+    int64_t batch_stride, token_stride, meta_stride, first_token;
+    int row_elems;
+    bool bf16;
+};
+
+__global__ __launch_bounds__(256) void token_params_kernel(ParamArgs a) {
     const int t = blockIdx.x, b = blockIdx.y;
-    const __half *row = src + b * batch_stride + t * token_stride;
+    const ParamTensor &pt = a.t[blockIdx.z];
+    const __half *row = pt.src + b * a.batch_stride + t * a.token_stride;
     float mn = INFINITY, mx = -INFINITY;
-    for (int i = threadIdx.x * 8; i < row_elems; i += 256 * 8) {
-        uint4 raw = load8_as_fp16(row + i, bf16);
+    for (int i = threadIdx.x * 8; i < a.row_elems; i += 256 * 8) {
+        uint4 raw = load8_as_fp16(row + i, a.bf16);
         const __half *h = reinterpret_cast<const __half *>(&raw);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -82,17 +106,7 @@ __global__ __launch_bounds__(256) void token_params_kernel(const __half *__restr
     if (threadIdx.x == 0) {
         mn = fminf(fminf(smn[0], smn[1]), fminf(smn[2], smn[3]));
         mx = fmaxf(fmaxf(smx[0], smx[1]), fmaxf(smx[2], smx[3]));
-        mn = mn + 0.0f;  // a zero minimum or maximum is stored as +0
-        mx = mx + 0.0f;
-        float range = mx - mn;
-        float s = rel * range;
-        // The product is rounded to fp32 first and to fp16 second; keep the
-        // compiler from fusing both into one mixed-precision FMA (one rounding).
-        asm volatile("" : "+v"(s));
-        __half s16 = __float2half_rn(s);
-        __half m16 = __float2half_rn(mn);  // exact: mn is an fp16 value
-        uint32_t word = uint32_t(__half_as_ushort(s16)) | (uint32_t(__half_as_ushort(m16)) << 16);
-        meta[b * meta_stride + first_token + t] = word;
+        pt.meta[b * a.meta_stride + a.first_token + t] = token_meta_word(mn, mx, pt.rel);
     }
 }
 
@@ -165,12 +179,7 @@ __device__ inline PackBits make_pack(const __half *tile, int g, int d, const flo
 __device__ inline int block_exclusive_scan(int v, int *total) {
     __shared__ int wave_sum[4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int inc = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int n = __shfl_up(inc, o);
-        if (lane >= o) inc += n;
-    }
+    const int inc = wave_inclusive_scan(v);
     __syncthreads();  // protects wave_sum against a previous call
     if (lane == 63) wave_sum[wave] = inc;
     __syncthreads();
@@ -180,54 +189,79 @@ __device__ inline int block_exclusive_scan(int v, int *total) {
     return base + inc - v;
 }
 
+struct ChunkSource {
+    const __half *src;
+    int64_t batch_stride, token_stride;
+    int B, H, qmax;
+    uint64_t magic_h, magic_hb;  // floor(2^32 / H) + 1, floor(2^32 / (H * B)) + 1
+    const uint32_t *meta;
+    int64_t meta_stride, first_token;
+    const uint8_t *order;
+    bool bf16;
+    int pack_order;
+};
+
+// One tensor's side of a round or part.
+struct PackTensor {
+    ChunkSource cs;
+    StagedRound round;
+    uint32_t *index;
+    uint8_t *arena;
+    uint32_t *sizes16;      // sizes of this part's (two-pass: round's) chunks, 16-byte units
+    uint64_t arena_cap16;
+    uint32_t *status;       // set when the round does not fit
+    uint32_t *page_list;    // paged arena
+    int64_t max_pages;
+};
+struct PackArgs {
+    PackTensor t[2];        // K, V
+    int part_first, n;      // chunks part_first .. part_first + n - 1 of the round, in both tensors
+    int index_words;
+    int first_tensor;       // a launch whose grid covers one tensor: which (else 0)
+    uint32_t *pool_state;   // paged arena
+    uint8_t *staging;       // K chunk i of the part in slot i, V chunk i in slot n + i
+};
+
 // One workgroup per new chunk; packs of PK = 8 tokens (Sec. IV-B; packs of 16 have their own
 // kernel below): the chunk has 64/PK token groups of 128 packs, thread tau owns packs tau + 256k
 // (token group (tau >> 7) + 2k, channel tau & 127).  A pack takes PK*w/8 payload bytes.  WIDE (codes above 15, packs of 8): the
 // header is a width byte per pack followed by a minimum byte per pack, widths go up to 8.
 template <bool WRITE, int PK, bool WIDE = false>
-__global__ __launch_bounds__(256) void chunk_kernel(const __half *__restrict__ src,
-                                                    int64_t batch_stride, int64_t token_stride,
-                                                    int B, int H, int qmax,
-                                                    const uint32_t *__restrict__ meta,
-                                                    int64_t meta_stride, int64_t first_token,
-                                                    int64_t first_chunk,
-                                                    uint32_t *__restrict__ sizes16,
-                                                    const uint32_t *__restrict__ index,
-                                                    int index_words,
-                                                    uint8_t *__restrict__ arena,
-                                                    const uint8_t *__restrict__ order, bool bf16) {
+__global__ __launch_bounds__(256) void chunk_kernel(PackArgs a) {
     static_assert(PK == 8, "contiguous packs are packs of 8 tokens");
     constexpr int NPACKS = N / PK * D;
     constexpr int HDR = WIDE ? 2 * NPACKS : NPACKS;  // header bytes
     constexpr int PER = N / PK * D / 256;  // packs per thread
+    const PackTensor &t = a.t[a.first_tensor + blockIdx.y];
+    const ChunkSource &cs = t.cs;
     const int cl = blockIdx.x;  // chunk within this round: (blk*B + b)*H + h
-    const int h = cl % H;
-    const int b = (cl / H) % B;
-    const int blk = cl / (H * B);
+    const int h = cl % cs.H;
+    const int b = (cl / cs.H) % cs.B;
+    const int blk = cl / (cs.H * cs.B);
     const int tau = threadIdx.x;
     const int d = tau & 127;
 
     uint8_t *dst = nullptr;
     if (WRITE) {
-        const int64_t e = (first_chunk + cl) * index_words;
-        uint32_t o0 = index[e], o1 = index[e + 1];
+        const int64_t e = (t.round.first_chunk + cl) * a.index_words;
+        uint32_t o0 = t.index[e], o1 = t.index[e + 1];
         if (o1 == o0) return;  // dropped: the arena was full
-        dst = arena + size_t(o0) * 16;
+        dst = t.arena + size_t(o0) * 16;
     }
 
     // stage the block's 64 x 128 values in LDS with 16-byte loads, rows in storage order, and the
     // tokens' scales and minimums as floats (every thread needs all 64 of them)
     __shared__ __attribute__((aligned(16))) __half tile[N * D];
     __shared__ float4 sm[N];
-    if (tau < N) sm[tau] = token_scale_min(meta[b * meta_stride + first_token + int64_t(blk) * N + tau]);
+    if (tau < N) sm[tau] = token_scale_min(cs.meta[b * cs.meta_stride + cs.first_token + int64_t(blk) * N + tau]);
     {
-        const __half *x_blk = src + b * batch_stride + int64_t(blk) * N * token_stride + h * D;
-        const uint8_t *ord = order ? order + b * meta_stride + first_token + int64_t(blk) * N : nullptr;
+        const __half *x_blk = cs.src + b * cs.batch_stride + int64_t(blk) * N * cs.token_stride + h * D;
+        const uint8_t *ord = cs.order ? cs.order + b * cs.meta_stride + cs.first_token + int64_t(blk) * N : nullptr;
 #pragma unroll
         for (int pass = 0; pass < 4; ++pass) {
             const int row = pass * 16 + (tau >> 4), c8 = (tau & 15) * 8;
             const int src_row = ord ? ord[row] : row;
-            *reinterpret_cast<uint4 *>(tile + row * D + c8) = load8_as_fp16(x_blk + src_row * token_stride + c8, bf16);
+            *reinterpret_cast<uint4 *>(tile + row * D + c8) = load8_as_fp16(x_blk + src_row * cs.token_stride + c8, cs.bf16);
         }
     }
     __syncthreads();
@@ -236,7 +270,7 @@ __global__ __launch_bounds__(256) void chunk_kernel(const __half *__restrict__ s
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int g = (tau >> 7) + 2 * k;
-        pb[k] = make_pack<PK>(tile, g, d, sm, qmax);
+        pb[k] = make_pack<PK>(tile, g, d, sm, cs.qmax);
     }
     // all packs are quantized before the first barrier of the scans
     int off[PER];
@@ -250,7 +284,7 @@ __global__ __launch_bounds__(256) void chunk_kernel(const __half *__restrict__ s
     const int padded = (HDR + payload + 15) & ~15;
 
     if (!WRITE) {
-        if (tau == 0) sizes16[cl] = uint32_t(padded >> 4);
+        if (tau == 0) t.sizes16[cl] = uint32_t(padded >> 4);
         return;
     }
 #pragma unroll
@@ -335,18 +369,6 @@ struct PlaneChunk {
 struct ChunkInput {
     uint4 raw[4];
     uint32_t mt[4];
-};
-
-struct ChunkSource {
-    const __half *src;
-    int64_t batch_stride, token_stride;
-    int B, H, qmax;
-    uint64_t magic_h, magic_hb;  // floor(2^32 / H) + 1, floor(2^32 / (H * B)) + 1
-    const uint32_t *meta;
-    int64_t meta_stride, first_token;
-    const uint8_t *order;
-    bool bf16;
-    int pack_order;
 };
 
 // Chunk cl of the round is (blk*B + b)*H + h.  cl is the same for the whole workgroup, so the
@@ -528,86 +550,118 @@ __device__ inline bool staged_round(const StagedRound &r, const uint32_t *index)
 }
 
 // Two-pass path, packs of 16: WRITE false = sizes only, true = bytes at the offsets of the index.
+// blockIdx.y: tensor.
 template <bool WRITE>
-__global__ __launch_bounds__(256) void chunk16_kernel(ChunkSource cs, int64_t first_chunk,
-                                                      uint32_t *__restrict__ sizes16,
-                                                      const uint32_t *__restrict__ index, int index_words,
-                                                      uint8_t *__restrict__ arena, StagedRound round) {
-    if (staged_round(round, index)) return;  // the staged path writes this round
+__global__ __launch_bounds__(256) void chunk16_kernel(PackArgs a) {
+    const PackTensor &t = a.t[a.first_tensor + blockIdx.y];
+    if (staged_round(t.round, t.index)) return;  // the staged path writes this round
     const int cl = blockIdx.x;
     uint8_t *dst = nullptr;
     if (WRITE) {
-        const int64_t e = (first_chunk + cl) * index_words;
-        uint32_t o0 = index[e], o1 = index[e + 1];
+        const int64_t e = (t.round.first_chunk + cl) * a.index_words;
+        uint32_t o0 = t.index[e], o1 = t.index[e + 1];
         if (o1 == o0) return;  // dropped: the arena was full
-        dst = arena + size_t(o0) * 16;
+        dst = t.arena + size_t(o0) * 16;
     }
     __shared__ uint32_t codes[CODE_TILE_WORDS];
-    const PlaneChunk c = make_plane_chunk(cs, load_chunk_input(cs, cl, load_chunk_rows(cs, cl)), codes);
+    const PlaneChunk c = make_plane_chunk(t.cs, load_chunk_input(t.cs, cl, load_chunk_rows(t.cs, cl)), codes);
     if (!WRITE) {
-        if (threadIdx.x == 0) sizes16[cl] = uint32_t(c.padded >> 4);
+        if (threadIdx.x == 0) t.sizes16[cl] = uint32_t(c.padded >> 4);
         return;
     }
     write_plane_chunk(c, dst);
 }
 
-// Chunks part_first .. part_first + n - 1 of the round, chunk part_first + i into slot i.  A
-// workgroup takes every gridDim.x-th chunk and has the loads of its next one in flight while it
+// The part's chunks of both tensors, item i = K chunk i (i < n) or V chunk i - n, into slot i.  A
+// workgroup takes every gridDim.x-th item and has the loads of its next one in flight while it
 // works on the current one.
-__global__ __launch_bounds__(256) void chunk16_stage_kernel(ChunkSource cs, const uint32_t *__restrict__ index,
-                                                            int part_first, int n,
-                                                            uint32_t *__restrict__ sizes16,
-                                                            uint8_t *__restrict__ staging, StagedRound round) {
-    if (!staged_round(round, index)) return;
+__global__ __launch_bounds__(256) void chunk16_stage_kernel(PackArgs a) {
+    const int lo = staged_round(a.t[0].round, a.t[0].index) ? 0 : a.n;
+    const int hi = staged_round(a.t[1].round, a.t[1].index) ? 2 * a.n : a.n;
     // the chunk's bytes are put together in the memory of the code tile (8704 bytes, a chunk has at most 4608)
     __shared__ __attribute__((aligned(16))) uint32_t codes[CODE_TILE_WORDS];
     static_assert(CODE_TILE_WORDS * 4 >= CHUNK_MAX, "the chunk image lives in the code tile");
     static_assert(CHUNK_MAX <= 2 * 256 * 16, "two 16-byte units per thread move a chunk");
     const int tau = threadIdx.x;
     const int stride = int(gridDim.x);
-    int cl = blockIdx.x;
-    if (cl >= n) return;
+    int item = lo + int(blockIdx.x);
+    if (item >= hi) return;
+    const int last = hi - 1;
+    auto rows_of = [&](int i) {
+        const int v = i >= a.n;
+        return load_chunk_rows(a.t[v].cs, a.part_first + i - (v ? a.n : 0));
+    };
+    auto input_of = [&](int i, const ChunkRows &rows) {
+        const int v = i >= a.n;
+        return load_chunk_input(a.t[v].cs, a.part_first + i - (v ? a.n : 0), rows);
+    };
     // The loads of the next chunk and the token order of the one after it are always issued (of
     // the last chunk again where there is no next one): the count of loads in flight is then the
     // same on every path, and the waits of the current chunk do not wait for them.
-    ChunkInput in = load_chunk_input(cs, part_first + cl, load_chunk_rows(cs, part_first + cl));
-    ChunkRows rows_next = load_chunk_rows(cs, part_first + min(cl + stride, n - 1));
+    ChunkInput in = input_of(item, rows_of(item));
+    ChunkRows rows_next = rows_of(min(item + stride, last));
     for (;;) {
-        const int next = cl + stride;
-        const ChunkInput in_next = load_chunk_input(cs, part_first + min(next, n - 1), rows_next);
-        rows_next = load_chunk_rows(cs, part_first + min(next + stride, n - 1));
-        const PlaneChunk c = make_plane_chunk(cs, in, codes);
+        const int next = item + stride;
+        const ChunkInput in_next = input_of(min(next, last), rows_next);
+        rows_next = rows_of(min(next + stride, last));
+        const int v = item >= a.n;
+        const PlaneChunk c = make_plane_chunk(a.t[v].cs, in, codes);
         write_plane_chunk(c, reinterpret_cast<uint8_t *>(codes));
         __syncthreads();
-        if (tau == 0) sizes16[cl] = uint32_t(c.padded >> 4);
+        if (tau == 0) a.t[v].sizes16[item - (v ? a.n : 0)] = uint32_t(c.padded >> 4);
         const uint4 *image = reinterpret_cast<const uint4 *>(codes);
-        uint4 *slot = reinterpret_cast<uint4 *>(staging + size_t(cl) * CHUNK_MAX);
+        uint4 *slot = reinterpret_cast<uint4 *>(a.staging + size_t(item) * CHUNK_MAX);
         const int n16 = c.padded >> 4;
         if (tau < n16) slot[tau] = image[tau];
         if (tau + 256 < n16) slot[tau + 256] = image[tau + 256];
-        if (next >= n) break;
+        if (next >= hi) break;
         __syncthreads();  // the image is read: the next code tile may take its place
         in = in_next;
-        cl = next;
+        item = next;
     }
 }
 
-// One wave per chunk of a staged part (its index words are set: the part's scan has run): staged
-// bytes to their place.
-__global__ __launch_bounds__(256) void chunk16_compact_kernel(StagedPart waiting) {
-    if (!staged_round(waiting.round, waiting.index)) return;
-    const int lane = threadIdx.x & 63;
-    const int cl = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (cl >= waiting.n) return;
-    const uint32_t start = waiting.index[waiting.first_chunk + cl], end = waiting.index[waiting.first_chunk + cl + 1];
-    const int n16 = int(end - start);
-    const uint4 *from = reinterpret_cast<const uint4 *>(waiting.staging + size_t(cl) * CHUNK_MAX);
-    uint4 *to = reinterpret_cast<uint4 *>(waiting.arena + size_t(start) * 16);
+// Sum over the 256 threads of a workgroup, in every thread.
+__device__ inline uint32_t block_sum(uint32_t v) {
+    __shared__ uint32_t wave_sum[4];
+    const int inc = wave_inclusive_scan(int(v));
+    if ((threadIdx.x & 63) == 63) wave_sum[threadIdx.x >> 6] = uint32_t(inc);
+    __syncthreads();
+    return wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3];
+}
+
+// Staged bytes of a part to their place, and its index words.  blockIdx.y: tensor; a wave takes
+// one chunk, so a workgroup four.  Every workgroup adds up the sizes of the part's chunks before
+// its own by itself (at most 32 KB, in the L2 cache of its die after the first): no launch of a scan
+// between staging and compaction, which cost a launch gap and 7 us for 16384 chunks.
+__global__ __launch_bounds__(256) void chunk16_compact_kernel(PackArgs a) {
+    const PackTensor &t = a.t[blockIdx.y];
+    if (!staged_round(t.round, t.index)) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wg_first = blockIdx.x * 4, cl = wg_first + wave;
+    const uint32_t start0 = t.index[t.round.first_chunk + a.part_first];
+    uint32_t before = 0;
+    for (int i = 4 * tid; i < wg_first; i += 1024) {
+        const uint4 q = *reinterpret_cast<const uint4 *>(t.sizes16 + i);
+        before += q.x + q.y + q.z + q.w;
+    }
+    uint32_t mine = 0, own = 0;  // this wave's chunk, and those of the workgroup before it
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t sz = wg_first + k < a.n ? t.sizes16[wg_first + k] : 0u;
+        if (k < wave) own += sz;
+        if (k == wave) mine = sz;
+    }
+    const uint32_t start = start0 + block_sum(before) + own;
+    if (cl >= a.n) return;
+    const int n16 = int(mine);
+    if (lane == 0) t.index[t.round.first_chunk + a.part_first + cl + 1] = start + mine;
+    const uint8_t *slot = a.staging + size_t(blockIdx.y * a.n + cl) * CHUNK_MAX;
     constexpr int STEPS = (CHUNK_MAX / 16 + 63) / 64;
     // read once and written once: both with the non-temporal hint (6 % of the whole compression)
     typedef uint32_t u32x4n __attribute__((ext_vector_type(4)));
-    const u32x4n *src = reinterpret_cast<const u32x4n *>(from);
-    u32x4n *dst = reinterpret_cast<u32x4n *>(to);
+    const u32x4n *src = reinterpret_cast<const u32x4n *>(slot);
+    u32x4n *dst = reinterpret_cast<u32x4n *>(t.arena + size_t(start) * 16);
     u32x4n v[STEPS];
 #pragma unroll
     for (int i = 0; i < STEPS; ++i)
@@ -617,16 +671,17 @@ __global__ __launch_bounds__(256) void chunk16_compact_kernel(StagedPart waiting
         if (lane + 64 * i < n16) __builtin_nontemporal_store(v[i], dst + lane + 64 * i);
 }
 
-// Single workgroup: index[first+i+1] = index[first] + sum_{j<=i} sizes16[j].
+// Two-pass rounds, one workgroup per tensor (blockIdx.x): index[first+i+1] = index[first] + sum_{j<=i} sizes16[j].
 // If the new chunks do not fit, all of them get size 0 and the flag is set.
 // Wave w owns a run of `per` consecutive sizes (a multiple of 256) and walks it 256 at a time,
 // four per lane, so loads and stores of a wave cover consecutive memory.
-__global__ __launch_bounds__(1024) void scan_offsets_kernel(const uint32_t *__restrict__ sizes16,
-                                                            int n, uint32_t *__restrict__ index,
-                                                            int64_t first_chunk,
-                                                            uint64_t arena_cap16,
-                                                            uint32_t *__restrict__ status,
-                                                            StagedRound round, bool staged_part) {
+__global__ __launch_bounds__(1024) void scan_offsets_kernel(PackArgs a) {
+    const PackTensor &t = a.t[a.first_tensor + blockIdx.x];
+    const uint32_t *sizes16 = t.sizes16;
+    uint32_t *index = t.index;
+    const int64_t first_chunk = t.round.first_chunk;
+    const int n = a.n;
+    if (staged_round(t.round, index)) return;  // the staged path writes this round
     __shared__ uint32_t wsum[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int per = ((n + 15) / 16 + 255) & ~255;
@@ -653,8 +708,6 @@ __global__ __launch_bounds__(1024) void scan_offsets_kernel(const uint32_t *__re
         const uint4 q = load4(r);
         local += q.x + q.y + q.z + q.w;
     }
-    // serves a part of a staged round (staged_part) or a whole two-pass round: whichever path runs
-    if (staged_round(round, index) != staged_part) return;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) local += __shfl_xor(local, o);
     if (lane == 0) wsum[wave] = local;
@@ -664,8 +717,8 @@ __global__ __launch_bounds__(1024) void scan_offsets_kernel(const uint32_t *__re
         if (k < wave) run += wsum[k];
         total += wsum[k];
     }
-    const bool fits = uint64_t(start) + total <= arena_cap16;
-    if (!fits && tid == 0) status[0] = 1;
+    const bool fits = uint64_t(start) + total <= t.arena_cap16;
+    if (!fits && tid == 0) t.status[0] = 1;
     auto place = [&](int r, uint4 q) {
         const uint32_t mine = q.x + q.y + q.z + q.w;
         uint32_t inc = mine;
@@ -702,12 +755,9 @@ __global__ __launch_bounds__(1024) void scan_offsets_kernel(const uint32_t *__re
 // that does not fit the newest page -- one LDS step per fresh page, not per chunk -- and marks
 // the chunks that start a page; (4) in parallel again, every chunk finds its page (a count of the
 // marks before it) and its offset inside it (S[j] - S[page start]).
-__global__ __launch_bounds__(1024) void place_chunks_kernel(uint32_t *__restrict__ sizes16, int n,
-                                                            uint32_t *__restrict__ index2,
-                                                            int64_t first_chunk,
-                                                            uint32_t *__restrict__ page_list,
-                                                            int64_t max_pages, uint32_t *pool_state,
-                                                            uint32_t *__restrict__ status) {
+__global__ __launch_bounds__(1024) void place_chunks_kernel(PackArgs a, int n_tensors) {
+    uint32_t *const pool_state = a.pool_state;
+    const int n = a.n;
     // bit 7: the chunk starts a fresh page; bits 0..6: chunks that fit a page starting here, minus 1
     // (a chunk is at least 512 bytes, so a page holds at most 128)
     __shared__ uint8_t step[MAX_NEW_CHUNKS];
@@ -717,6 +767,20 @@ __global__ __launch_bounds__(1024) void place_chunks_kernel(uint32_t *__restrict
     const int per = (n + 1023) / 1024;
     const int lo = min(tid * per, n), hi = min(lo + per, n);
     constexpr uint32_t P = PAGE16;
+    constexpr int WAVES = 16, ENTRIES = 128;
+    __shared__ uint32_t seg_exit[WAVES][ENTRIES];
+    __shared__ uint16_t seg_pages[WAVES][ENTRIES];
+    __shared__ uint32_t seg_entry[WAVES];
+
+    // the tensors one after the other: V's fresh pages are the ones below K's on the pool's stack
+    for (int tensor = 0; tensor < n_tensors; ++tensor) {
+    const PackTensor &pt = a.t[a.first_tensor + tensor];
+    uint32_t *const sizes16 = pt.sizes16;
+    uint32_t *const index2 = pt.index;
+    const int64_t first_chunk = pt.round.first_chunk;
+    uint32_t *const page_list = pt.page_list;
+    const int64_t max_pages = pt.max_pages;
+    if (tensor) __syncthreads();  // the shared arrays and the pool's state of the tensor before are done with
 
     // (1) exclusive prefix sums, in place
     uint32_t local = 0;
@@ -759,10 +823,6 @@ __global__ __launch_bounds__(1024) void place_chunks_kernel(uint32_t *__restrict
     // the chain from each of these 128 possible entries to the segment's end (lanes in parallel)
     // and notes where it leaves and how many pages it starts; thread 0 then hops through the
     // sixteen tables, and every wave marks its own segment from its true entry.
-    constexpr int WAVES = 16, ENTRIES = 128;
-    __shared__ uint32_t seg_exit[WAVES][ENTRIES];
-    __shared__ uint16_t seg_pages[WAVES][ENTRIES];
-    __shared__ uint32_t seg_entry[WAVES];
     const int seg = (n + WAVES - 1) / WAVES;
     const bool segmented = seg >= ENTRIES;
     const int seg_a = min(wave * seg, n), seg_e = min(seg_a + seg, n);
@@ -827,12 +887,12 @@ __global__ __launch_bounds__(1024) void place_chunks_kernel(uint32_t *__restrict
     }
     __syncthreads();
     if (!sh_ok) {
-        if (tid == 0) status[0] = 1;
+        if (tid == 0) pt.status[0] = 1;
         for (int i = lo; i < hi; ++i) {
             index2[2 * (first_chunk + i)] = 0;
             index2[2 * (first_chunk + i) + 1] = 0;
         }
-        return;
+        continue;
     }
     const uint32_t top = sh_top;
 
@@ -872,6 +932,7 @@ __global__ __launch_bounds__(1024) void place_chunks_kernel(uint32_t *__restrict
         for (int k = 0; k < 16; ++k) l = max(l, wave_b[k]);
         page_list[0] = held + ord;
         page_list[1] = l ? total - S(int(l) - 1) : fill0 + total;
+    }
     }
 }
 
@@ -1049,13 +1110,20 @@ int launch_tail_copy(const kv_cache *c, const __half *ksrc, const __half *vsrc, 
     return KV_OK;
 }
 
-int launch_token_params(const kv_cache *c, const CompressJob &job, hipStream_t s) {
+int launch_token_params(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s) {
     const int B = c->cfg.batch, H = c->cfg.n_kv_heads;
-    const int n_tokens = job.n_blocks * N;
+    const int n_tokens = kjob.n_blocks * N;
     if (n_tokens <= 0) return KV_ERR_ARG;
-    hipLaunchKernelGGL(token_params_kernel, dim3(n_tokens, B), dim3(256), 0, s, job.src,
-                       job.batch_stride, job.token_stride, H * D, job.rel, job.meta,
-                       c->max_tokens, job.first_token, job.bf16);
+    ParamArgs a;
+    a.t[0] = ParamTensor{kjob.src, kjob.rel, kjob.meta};
+    a.t[1] = ParamTensor{vjob.src, vjob.rel, vjob.meta};
+    a.batch_stride = kjob.batch_stride;
+    a.token_stride = kjob.token_stride;
+    a.meta_stride = c->max_tokens;
+    a.first_token = kjob.first_token;
+    a.row_elems = H * D;
+    a.bf16 = kjob.bf16;
+    hipLaunchKernelGGL(token_params_kernel, dim3(n_tokens, B, 2), dim3(256), 0, s, a);
     KV_HIP_CHECK(hipGetLastError());
     return KV_OK;
 }
@@ -1074,86 +1142,97 @@ int launch_v_median_order(const kv_cache *c, const CompressJob &vjob, uint32_t *
     return KV_OK;
 }
 
-int launch_pack(const kv_cache *c, const CompressJob &job, hipStream_t s) {
+int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s) {
     const int B = c->cfg.batch, H = c->cfg.n_kv_heads;
-    const int n_chunks = job.n_blocks * B * H;
+    const int n_chunks = kjob.n_blocks * B * H;
     if (n_chunks <= 0 || n_chunks > MAX_NEW_CHUNKS) return KV_ERR_ARG;
     uint8_t *ws = static_cast<uint8_t *>(c->buf.workspace);
     uint32_t *sizes16 = reinterpret_cast<uint32_t *>(ws + WS_SIZES);
-    const bool planes = !job.wide && c->cfg.pack_size == 16;
-    auto sizes_kernel = job.wide ? chunk_kernel<false, 8, true> : chunk_kernel<false, 8>;
-    auto write_kernel = job.wide ? chunk_kernel<true, 8, true> : chunk_kernel<true, 8>;
+    const bool planes = c->cfg.pack_size == 16;
     // packs of 16, contiguous arena: the staged path when even the largest chunks fit (decided on
     // the device, where the fill level is); the kernels of the other path return at once.  The
     // host knows an upper bound of the fill level: where that already says "fits", the two-pass
     // kernels are not launched at all.
-    ChunkSource cs;
-    cs.src = job.src;
-    cs.batch_stride = job.batch_stride;
-    cs.token_stride = job.token_stride;
-    cs.B = B;
-    cs.H = H;
-    cs.qmax = job.qmax;
-    cs.magic_h = (uint64_t(1) << 32) / uint64_t(H) + 1;
-    cs.magic_hb = (uint64_t(1) << 32) / (uint64_t(H) * uint64_t(B)) + 1;
-    cs.meta = job.meta;
-    cs.meta_stride = c->max_tokens;
-    cs.first_token = job.first_token;
-    cs.order = job.order;
-    cs.bf16 = job.bf16;
-    cs.pack_order = job.pack_order;
-    StagedRound round;
-    round.first_chunk = job.first_chunk;
-    round.worst16 = 0;
-    round.arena_cap16 = job.arena_cap16;
-    bool two_pass = true;
-    // (a small round is bound by its launches, not by reading the input twice: two passes, three kernels)
-    constexpr int STAGED_MIN_CHUNKS = 1024;
-    if (planes && !c->pool && n_chunks >= STAGED_MIN_CHUNKS) {
-        round.worst16 = uint32_t(n_chunks) * uint32_t(CHUNK_MAX / 16);
-        two_pass = job.fill_bound16 + round.worst16 > job.arena_cap16;
-        uint8_t *staging = ws + c->stage_offset;
-        for (int part = 0; part < n_chunks; part += c->stage_chunks) {
-            const int n = std::min(c->stage_chunks, n_chunks - part);
+    const bool staged = planes && !c->pool;
+    bool two_pass = !staged;
+    PackArgs a;
+    for (int i = 0; i < 2; ++i) {
+        const CompressJob &job = i ? vjob : kjob;
+        PackTensor &t = a.t[i];
+        t.cs.src = job.src;
+        t.cs.batch_stride = job.batch_stride;
+        t.cs.token_stride = job.token_stride;
+        t.cs.B = B;
+        t.cs.H = H;
+        t.cs.qmax = job.qmax;
+        t.cs.magic_h = (uint64_t(1) << 32) / uint64_t(H) + 1;
+        t.cs.magic_hb = (uint64_t(1) << 32) / (uint64_t(H) * uint64_t(B)) + 1;
+        t.cs.meta = job.meta;
+        t.cs.meta_stride = c->max_tokens;
+        t.cs.first_token = job.first_token;
+        t.cs.order = job.order;
+        t.cs.bf16 = job.bf16;
+        t.cs.pack_order = job.pack_order;
+        t.round.first_chunk = job.first_chunk;
+        t.round.worst16 = staged ? uint32_t(n_chunks) * uint32_t(CHUNK_MAX / 16) : 0;
+        t.round.arena_cap16 = job.arena_cap16;
+        t.index = job.index;
+        t.arena = job.arena;
+        t.arena_cap16 = job.arena_cap16;
+        t.status = job.status;
+        t.page_list = job.page_list;
+        t.max_pages = job.max_pages;
+        if (staged && job.fill_bound16 + t.round.worst16 > job.arena_cap16) two_pass = true;
+    }
+    a.index_words = c->index_words;
+    a.first_tensor = 0;
+    a.pool_state = c->pool ? c->pool->state : nullptr;
+    a.staging = ws + c->stage_offset;
+    if (staged) {
+        // equal parts that fit the staging area, half of its slots for each tensor
+        const int most = c->stage_chunks / 2;
+        const int parts = (n_chunks + most - 1) / most, per_part = (n_chunks + parts - 1) / parts;
+        for (int part = 0; part < n_chunks; part += per_part) {
+            a.part_first = part;
+            a.n = std::min(per_part, n_chunks - part);
+            a.t[0].sizes16 = sizes16;
+            a.t[1].sizes16 = sizes16 + ((a.n + 3) & ~3);
             static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(chunk16_stage_kernel));
-            const int groups = flat_groups_for(int64_t(n) * 4, per_cu, n);  // all resident, at most one per chunk
-            hipLaunchKernelGGL(chunk16_stage_kernel, dim3(groups), dim3(256), 0, s, cs, job.index, part, n,
-                               sizes16, staging, round);
-            hipLaunchKernelGGL(scan_offsets_kernel, dim3(1), dim3(1024), 0, s, sizes16, n, job.index,
-                               job.first_chunk + part, job.arena_cap16, job.status, round, true);
-            StagedPart staged;
-            staged.staging = staging;
-            staged.index = job.index;
-            staged.first_chunk = job.first_chunk + part;
-            staged.n = n;
-            staged.arena = job.arena;
-            staged.round = round;
-            hipLaunchKernelGGL(chunk16_compact_kernel, dim3((n + 3) / 4), dim3(256), 0, s, staged);
+            const int groups = flat_groups_for(int64_t(a.n) * 8, per_cu, 2 * a.n);  // all resident, at most one per chunk
+            hipLaunchKernelGGL(chunk16_stage_kernel, dim3(groups), dim3(256), 0, s, a);
+            hipLaunchKernelGGL(chunk16_compact_kernel, dim3((a.n + 3) / 4, 2), dim3(256), 0, s, a);
         }
     }
     if (two_pass) {
-        if (planes)
-            hipLaunchKernelGGL(chunk16_kernel<false>, dim3(n_chunks), dim3(256), 0, s, cs, job.first_chunk,
-                               sizes16, job.index, c->index_words, job.arena, round);
-        else
-            hipLaunchKernelGGL(sizes_kernel, dim3(n_chunks), dim3(256), 0, s, job.src,
-                               job.batch_stride, job.token_stride, B, H, job.qmax, job.meta, c->max_tokens,
-                               job.first_token, job.first_chunk, sizes16, job.index, c->index_words, job.arena,
-                               job.order, job.bf16);
-        if (c->pool)
-            hipLaunchKernelGGL(place_chunks_kernel, dim3(1), dim3(1024), 0, s, sizes16, n_chunks, job.index,
-                               job.first_chunk, job.page_list, job.max_pages, c->pool->state, job.status);
-        else
-            hipLaunchKernelGGL(scan_offsets_kernel, dim3(1), dim3(1024), 0, s, sizes16, n_chunks,
-                               job.index, job.first_chunk, job.arena_cap16, job.status, round, false);
-        if (planes)
-            hipLaunchKernelGGL(chunk16_kernel<true>, dim3(n_chunks), dim3(256), 0, s, cs, job.first_chunk,
-                               sizes16, job.index, c->index_words, job.arena, round);
-        else
-            hipLaunchKernelGGL(write_kernel, dim3(n_chunks), dim3(256), 0, s, job.src,
-                               job.batch_stride, job.token_stride, B, H, job.qmax, job.meta, c->max_tokens,
-                               job.first_token, job.first_chunk, sizes16, job.index, c->index_words, job.arena,
-                               job.order, job.bf16);
+        // both tensors per launch where the sizes area takes both (and, packs of 8, the layouts agree)
+        a.part_first = 0;
+        a.n = n_chunks;
+        const bool both = 2 * ((n_chunks + 3) & ~3) <= MAX_NEW_CHUNKS;
+        const bool same = planes || kjob.wide == vjob.wide;
+        for (int i = 0; i < 2; i += both ? 2 : 1) {
+            a.first_tensor = i;
+            a.t[0].sizes16 = sizes16;
+            a.t[1].sizes16 = both ? sizes16 + ((n_chunks + 3) & ~3) : sizes16;
+            const int n_tensors = both ? 2 : 1;
+            auto pass = [&](bool write) {
+                for (int j = i; j < i + n_tensors; j += same ? n_tensors : 1) {
+                    a.first_tensor = j;
+                    const dim3 grid(n_chunks, same ? n_tensors : 1);
+                    const bool wide = j ? vjob.wide : kjob.wide;
+                    auto kernel = planes ? (write ? chunk16_kernel<true> : chunk16_kernel<false>)
+                                  : wide ? (write ? chunk_kernel<true, 8, true> : chunk_kernel<false, 8, true>)
+                                         : (write ? chunk_kernel<true, 8> : chunk_kernel<false, 8>);
+                    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a);
+                }
+                a.first_tensor = i;
+            };
+            pass(false);
+            if (c->pool)
+                hipLaunchKernelGGL(place_chunks_kernel, dim3(1), dim3(1024), 0, s, a, n_tensors);
+            else
+                hipLaunchKernelGGL(scan_offsets_kernel, dim3(n_tensors), dim3(1024), 0, s, a);
+            pass(true);
+        }
     }
     KV_HIP_CHECK(hipGetLastError());
     return KV_OK;
