@@ -302,6 +302,8 @@ int compress_blocks(kv_cache *c, const __half *ksrc, const __half *vsrc, int64_t
         vjob.status = status + ST_OVERFLOW_V;
         vjob.page_list = static_cast<uint32_t *>(c->buf.v_pages);
         vjob.max_pages = c->max_pages_v;
+        kjob.fill_bound16 = c->fill_bound16[0];
+        vjob.fill_bound16 = c->fill_bound16[1];
         int rc;
         if ((rc = launch_token_params(c, kjob, vjob, s))) return rc;
         if (c->cfg.repack == KV_REPACK_V_MEDIAN) {
@@ -309,8 +311,6 @@ int compress_blocks(kv_cache *c, const __half *ksrc, const __half *vsrc, int64_t
             if ((rc = launch_v_median_order(c, vjob, kjob.meta, order, s))) return rc;
             kjob.order = vjob.order = order;
         }
-        kjob.fill_bound16 = c->fill_bound16[0];
-        vjob.fill_bound16 = c->fill_bound16[1];
         if ((rc = launch_pack(c, kjob, vjob, s))) return rc;
         c->fill_bound16[0] += uint64_t(nb) * B * H * (chunk_max_bytes(c->cfg.pack_size, c->wide_k) / 16);
         c->fill_bound16[1] += uint64_t(nb) * B * H * (chunk_max_bytes(c->cfg.pack_size, c->wide_v) / 16);
@@ -506,6 +506,10 @@ extern "C" int kv_cache_restore(kv_cache_t *c, int64_t tokens) {
     if (!c || tokens < 0 || tokens > c->max_tokens) return KV_ERR_ARG;
     c->packed_tokens = tokens / N * N;
     c->tail_tokens = int(tokens - c->packed_tokens);
+    // what the adopted arenas hold is known to the device only: every chunk at its largest
+    const uint64_t n_chunks = uint64_t(c->packed_tokens / N) * c->cfg.batch * c->cfg.n_kv_heads;
+    c->fill_bound16[0] = n_chunks * (chunk_max_bytes(c->cfg.pack_size, c->wide_k) / 16);
+    c->fill_bound16[1] = n_chunks * (chunk_max_bytes(c->cfg.pack_size, c->wide_v) / 16);
     return KV_OK;
 }
 
