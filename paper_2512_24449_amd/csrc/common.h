@@ -73,12 +73,13 @@ struct FlatPlan {
 int resident_workgroups(const void *kernel);
 int flat_groups_for(int64_t total, int per_cu, int64_t most);
 
-// Staging area of the compressor (packs of 16): chunks it holds, each in a slot of the largest
-// chunk's size.  64 blocks of the cache at a time, within 256 .. 16384 chunks (1.2 .. 75 MB):
-// large enough to fill the chip, small enough to stay in the last-level cache until it is read back.
+// Staging area of the compressor (packs of 16): chunks it holds, half of them for each tensor, each in
+// a slot of the largest chunk's size.  64 blocks of the cache at a time, within 512 .. 16384 chunks
+// (2.4 .. 75 MB): large enough to fill the chip, small enough to stay in the last-level cache until
+// it is read back.
 inline int stage_chunks_for(int batch, int n_kv_heads) {
-    const int64_t want = int64_t(batch) * n_kv_heads * 64;
-    return int(want < 256 ? 256 : want > 16384 ? 16384 : want);
+    const int64_t want = int64_t(batch) * n_kv_heads * 128;
+    return int(want < 512 ? 512 : want > 16384 ? 16384 : want);
 }
 
 inline size_t v_partial_bytes(int batch, int n_q_heads) {

@@ -42,11 +42,12 @@ __device__ inline uint4 as_fp16(uint4 raw, bool bf16) {
 }
 // (The input is read once per kernel and is larger than the caches: the non-temporal hint keeps it
 // from pushing out what is read again, the staged chunks for one.)
-__device__ inline uint4 load8_as_fp16(const __half *p, bool bf16) {
+__device__ inline uint4 load8_nt(const __half *p) {
     typedef uint32_t u32x4n __attribute__((ext_vector_type(4)));
     const u32x4n v = __builtin_nontemporal_load(reinterpret_cast<const u32x4n *>(p));
-    return as_fp16(make_uint4(v.x, v.y, v.z, v.w), bf16);
+    return make_uint4(v.x, v.y, v.z, v.w);
 }
+__device__ inline uint4 load8_as_fp16(const __half *p, bool bf16) { return as_fp16(load8_nt(p), bf16); }
 
 // A token's metadata word from its smallest and largest value: fp16 scale | fp16 minimum << 16.
 __device__ inline uint32_t token_meta_word(float mn, float mx, float rel) {
@@ -301,74 +302,75 @@ __global__ __launch_bounds__(256) void chunk_kernel(PackArgs a) {
     if (tau < padded - HDR - payload) dst[HDR + payload + tau] = 0;
 }
 
-// Packs of 16 tokens in the plane layout (packkv.h): header bytes in pack-list order, region E
-// with a 32-bit word of low code bits per pack of width >= 2 (and a second word of high bits
-// for width 4), region O with a 16-bit word of top bits per pack of odd width.  One workgroup
-// per new chunk; thread tau owns packs tau and tau + 256 of the pack list (order 0: pack
-// p = g*128 + d, order 1: p = d*4 + g).
+// ---- packs of 16 tokens, plane layout (packkv.h) --------------------------------------------
+// One workgroup per chunk, wave w = token group w.  Lane (cg = lane % 16, q = lane / 16) loads the
+// channels 8 cg .. 8 cg + 7 of the four tokens 16 w + 8 (q / 2) + q % 2 + 2 i and quantizes them; a
+// 4 x 4 exchange between the lanes of one cg (eight row swaps) then leaves each lane all sixteen
+// tokens of the channels 8 cg + 2 q and 8 cg + 2 q + 1: its two packs.  No LDS tile and no barrier
+// on the way; the waves meet once for the byte counts of their packs and once when the chunk's
+// bytes are complete in LDS.
+
+// Rows of 16 lanes: of x keep the even rows and take the odd rows from x's odd rows into y's even
+// rows' place and the other way round (odd rows of x <-> even rows of y).
+__device__ inline void swap_rows16(uint32_t &x, uint32_t &y) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    x = r[0];
+    y = r[1];
+}
+// The upper 32 lanes of x <-> the lower 32 lanes of y.
+__device__ inline void swap_rows32(uint32_t &x, uint32_t &y) {
+    const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+    x = r[0];
+    y = r[1];
+}
+
 struct PlaneBits {
-    uint32_t low, high, top;
+    uint32_t low, high, top;  // top: in the low 16 bits
     int w, m;
 };
 
 // n0, n1: the 16 codes of a pack as nibbles (tokens 0..7, 8..15); lo, hi: their minimum and maximum.
-__device__ inline PlaneBits planes_from_nibbles(uint32_t n0, uint32_t n1, int lo, int hi) {
+__device__ inline PlaneBits planes_from_nibbles(uint32_t n0, uint32_t n1, uint32_t lo, uint32_t hi) {
     PlaneBits pb;
-    const int range = hi - lo;
-    pb.w = range == 0 ? 0 : 32 - __clz(range);
-    pb.m = lo;
+    pb.w = 32 - __clz(int(hi - lo));  // 0 for equal codes
+    pb.m = int(lo);
     // codes minus the pack minimum: no nibble borrows (every code is at least the minimum)
-    n0 -= uint32_t(lo) * 0x11111111u;
-    n1 -= uint32_t(lo) * 0x11111111u;
+    uint32_t all = lo | (lo << 4);
+    all |= all << 8;
+    all |= all << 16;
+    n0 -= all;
+    n1 -= all;
     // planes of two-bit fields: token i at bits [4i, 4i+2) for i < 8, at [4(i-8)+2, 4(i-8)+4) for i >= 8
-    pb.low = (n0 & 0x33333333u) | ((n1 & 0x33333333u) << 2);
+    pb.low = (n0 & 0x33333333u) | ((n1 << 2) & 0xCCCCCCCCu);
     pb.high = ((n0 >> 2) & 0x33333333u) | (n1 & 0xCCCCCCCCu);
     // top bit of every code, token i at bit 4 (i % 4) + i / 4
-    const int top_bit = pb.w > 0 ? pb.w - 1 : 0;
+    const int top_bit = max(pb.w - 1, 0);
     const uint32_t t0 = (n0 >> top_bit) & 0x11111111u, t1 = (n1 >> top_bit) & 0x11111111u;
-    pb.top = (t0 & 0xFFFFu) | ((t0 >> 16) << 1) | ((t1 & 0xFFFFu) << 2) | ((t1 >> 16) << 3);
+    const uint32_t y0 = t0 | (t0 >> 15), y1 = t1 | (t1 >> 15);
+    pb.top = y0 | (y1 << 2);
     return pb;
 }
 
-// Code tile of a chunk in LDS: channel d has a row of 16 words (and one word of padding, which
-// spreads the rows over the banks); word 4g + q of it holds four codes of token group g, one per
-// byte: q = 0: tokens 0, 2, 4, 6; q = 1: tokens 1, 3, 5, 7; q = 2: tokens 8, 10, 12, 14; q = 3:
-// tokens 9, 11, 13, 15.  So word 0 | word 1 << 4 is the nibble string of tokens 0..7 and
-// word 2 | word 3 << 4 that of tokens 8..15 (codes of packs of 16 are below 16).
-constexpr int CODE_ROW_WORDS = 17;
-constexpr int CODE_TILE_WORDS = D * CODE_ROW_WORDS;
 typedef unsigned short pk_u16 __attribute__((ext_vector_type(2)));
-
-__device__ inline PlaneBits planes_from_codes(const uint32_t *words) {
-    const uint32_t w0 = words[0], w1 = words[1], w2 = words[2], w3 = words[3];
-    // minimum and maximum of the 16 bytes, two 16-bit lanes at a time
-    constexpr uint32_t EVEN = 0x00FF00FFu;
-    const uint32_t v[8] = {w0 & EVEN, (w0 >> 8) & EVEN, w1 & EVEN, (w1 >> 8) & EVEN,
-                           w2 & EVEN, (w2 >> 8) & EVEN, w3 & EVEN, (w3 >> 8) & EVEN};
-    pk_u16 mn = __builtin_bit_cast(pk_u16, v[0]), mx = mn;
-#pragma unroll
-    for (int i = 1; i < 8; ++i) {
-        mn = __builtin_elementwise_min(mn, __builtin_bit_cast(pk_u16, v[i]));
-        mx = __builtin_elementwise_max(mx, __builtin_bit_cast(pk_u16, v[i]));
-    }
-    const int lo = min(int(mn.x), int(mn.y)), hi = max(int(mx.x), int(mx.y));
-    return planes_from_nibbles(w0 | (w1 << 4), w2 | (w3 << 4), lo, hi);
+__device__ inline uint32_t pk_min(uint32_t x, uint32_t y) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(pk_u16, x), __builtin_bit_cast(pk_u16, y)));
+}
+__device__ inline uint32_t pk_max(uint32_t x, uint32_t y) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(pk_u16, x), __builtin_bit_cast(pk_u16, y)));
 }
 
-// One chunk of packs of 16 in a workgroup's registers: thread tau holds packs 2 tau and 2 tau + 1
-// of the pack list; off: the bytes of the packs before them in region E (low half) and region O
-// (high half).
-struct PlaneChunk {
-    PlaneBits pb[2];
-    int off;
-    int e_bytes, o_bytes, padded;
-};
-
-// What a thread loads of a chunk: eight channels (8 * (tau % 16) ...) of the four tokens that
-// share a word of the code tile (word tau / 16 of each of those channels), and the tokens' metadata.
+// What a lane loads of a chunk: eight channels of its four tokens, and the metadata word of token
+// 16 w + lane % 16 of the block (storage order).
 struct ChunkInput {
     uint4 raw[4];
-    uint32_t mt[4];
+    uint32_t mt;
+};
+
+// LDS of a workgroup that builds chunks; the image of one chunk is copied out while the next is built.
+struct ChunkLds {
+    float4 tok[N];              // token_quant of the block's tokens
+    uint32_t counts[2][4][64];  // per wave: byte counts of the packs (see build_plane_chunk)
+    __attribute__((aligned(16))) uint8_t image[2][CHUNK_MAX];
 };
 
 // Chunk cl of the round is (blk*B + b)*H + h.  cl is the same for the whole workgroup, so the
@@ -388,14 +390,14 @@ __device__ inline ChunkCoord chunk_coord(const ChunkSource &cs, int cl) {
     return k;
 }
 
-// Where chunk cl of the round ((blk*B + b)*H + h) finds the four tokens of thread tau: rows
-// row0 + 2i of the block in storage order, at the source positions the token order gives.
+// Where chunk cl of the round ((blk*B + b)*H + h) finds the lane's four tokens: rows row0 + 2i of
+// the block in storage order, at the source positions the token order gives.
 struct ChunkRows {
     int src_row[4];
 };
 __device__ inline int chunk_row0() {
-    const int word = threadIdx.x >> 4;  // word = 4g + q
-    return 16 * (word >> 2) + 8 * ((word >> 1) & 1) + (word & 1);
+    const int q = threadIdx.x >> 4;  // 4 * wave + q
+    return 16 * (q >> 2) + 8 * ((q >> 1) & 1) + (q & 1);
 }
 __device__ inline ChunkRows load_chunk_rows(const ChunkSource &cs, int cl) {
     const ChunkCoord k = chunk_coord(cs, cl);
@@ -413,124 +415,236 @@ __device__ inline ChunkRows load_chunk_rows(const ChunkSource &cs, int cl) {
     return r;
 }
 
-// Issues the loads of chunk cl.
+// Issues the loads of chunk cl.  STREAM: with the non-temporal hint.
+template <bool STREAM>
 __device__ inline ChunkInput load_chunk_input(const ChunkSource &cs, int cl, const ChunkRows &rows) {
     const ChunkCoord k = chunk_coord(cs, cl);
     const int h = k.h, b = k.b, blk = k.blk;
     const int cg = threadIdx.x & 15;
-    const int row0 = chunk_row0();
     const __half *x_blk = cs.src + b * cs.batch_stride + int64_t(blk) * N * cs.token_stride + h * D + cg * 8;
     const uint32_t *meta_blk = cs.meta + b * cs.meta_stride + cs.first_token + int64_t(blk) * N;
     ChunkInput in;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        in.raw[i] = *reinterpret_cast<const uint4 *>(x_blk + rows.src_row[i] * cs.token_stride);  // converted where it is used
-        in.mt[i] = meta_blk[row0 + 2 * i];
-    }
+    for (int i = 0; i < 4; ++i)
+        in.raw[i] = STREAM ? load8_nt(x_blk + rows.src_row[i] * cs.token_stride)
+                           : *reinterpret_cast<const uint4 *>(x_blk + rows.src_row[i] * cs.token_stride);  // converted where it is used
+    in.mt = meta_blk[16 * (threadIdx.x >> 6) + cg];
     return in;
 }
 
-// The eight values of one token a thread holds, quantized (Sec. III-B.2: clamp(rint(fl((x - mn) / s)),
-// 0, qmax), the quotient rounded to fp32 as an IEEE divide does) into byte `slot` of out[0..7];
-// qmax < 16.  Fast path: q = (x - mn) * r with r = 1 / s to within an ulp, rounded to the nearest
-// integer (ties to even) and clamped to 0 .. 255 by the conversion that also places the byte; a token
-// with a quotient that could round above qmax takes the slow path, which clamps.
-// q lies within 2^-22 relative of the rounded quotient (an ulp for r, half for the product, half
-// for the quotient's own rounding): within 2^-16 for quotients below 64, and from 64 on both sides
-// are clamped to qmax anyway.  So unless q is within 2^-15 of a rounding tie k + 1/2, it rounds as
-// the quotient does.  `clear` collects how far the eight values stay from a tie; the rare token
-// with a value near one takes the divide for all eight.
-constexpr float TIE_GUARD = 1.0f / 32768.0f;
-
-// x - mn in fp32 for the low (HI = false) or high half of a word of two fp16 values: the mixed-
-// precision fused multiply-add x * 1 + (-mn) rounds the exact difference once, as the conversion
-// to fp32 (exact) followed by the subtraction does, and saves the conversion.
-template <bool HI>
-__device__ inline float half_minus(uint32_t two_halves, float neg_mn) {
-    float a;
-    if (HI)
-        asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(a) : "v"(two_halves), "v"(neg_mn));
-    else
-        asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(a) : "v"(two_halves), "v"(neg_mn));
-    return a;
-}
-
-__device__ inline void quantize_token8(uint4 values, uint32_t mt, int qmax, int slot, uint32_t *out) {
+// Quantization (Sec. III-B.2: clamp(rint(fl((x - mn) / s)), 0, qmax), the quotient rounded to fp32
+// as an IEEE divide does), qmax < 16.  Fast path, one fused multiply-add per value:
+//     t = fl(x * r + c),   r = 1 / s to within an ulp,   c = fl(128 + 1/2 + g * 2^-16 - mn * r)
+// The quotient (x - mn) * r is below 24 (the largest value over an fp16 scale that may have been
+// rounded down from half a subnormal step more), so t lies in [128, 256), where a float is a fixed-
+// point number with 16 fraction bits: bits 16.. of its pattern are 0x4300 + floor(quotient + 1/2 + g).
+// Error of t against quotient + 1/2 + g, in units of 2^-16: half for t's own rounding, half an ulp
+// of c (half a unit for |c| < 256, 2^(e-8) for |c| below 2^(e+1)), 0.19 for r, 0.16 for the roundings of
+// the subtraction and the quotient in the definition: below 1.4 + 2^(e-8).  With g = 3 (+ 2^(e-7) for
+// e >= 8) the quotient can only be on the other side of a rounding tie, or on one, if the fraction
+// field of t is below 2g: then the token's eight values take the divide.  A token whose offset is so
+// large against its scale that g reaches 1/2 always does, and so does every NaN (its low pattern
+// bits are zero) -- infinite inputs end there.  s = 0: r = 0, code 0.
+struct TokenQuant {
+    float r, c;
+    uint32_t guard;  // 2g
+    uint32_t mt;     // fp16 scale | fp16 minimum << 16
+};
+__device__ inline float4 token_quant(uint32_t mt) {
     const float s = __half2float(__ushort_as_half(uint16_t(mt & 0xFFFFu)));
     const float mn = __half2float(__ushort_as_half(uint16_t(mt >> 16)));
-    const float r = s != 0.0f ? __builtin_amdgcn_rcpf(s) : 0.0f;  // s = 0: every code is 0
-    const float top = float(qmax);
+    const float r = s != 0.0f ? __builtin_amdgcn_rcpf(s) : 0.0f;
+    const int e = int((__float_as_uint(fmaf(-mn, r, 128.5f)) >> 23) & 0xFFu) - 127;
+    const uint32_t g = 3u + (e >= 8 ? 2u << min(e - 8, 14) : 0u);
+    const float c = fmaf(-mn, r, 128.5f + float(g) * (1.0f / 65536.0f));
+    return make_float4(r, c, __uint_as_float(2u * g), __uint_as_float(mt));
+}
+
+// x * r + c for the low (HI = false) or high half x of a word of two fp16 values, rounded once.
+template <bool HI>
+__device__ inline float half_mul_add(uint32_t two_halves, float r, float c) {
+    float t;
+    if (HI)
+        asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(t) : "v"(two_halves), "v"(r), "v"(c));
+    else
+        asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(t) : "v"(two_halves), "v"(r), "v"(c));
+    return t;
+}
+
+// The eight values of one token a lane holds: pair[k] = 0x4300 + code of values 2k (low half) and 2k + 1.
+__device__ inline void quantize_token8(uint4 values, float4 tq, uint32_t qmax, uint32_t (&pair)[4]) {
     const uint32_t w[4] = {values.x, values.y, values.z, values.w};
-    float clear = 1.0f, most = 0.0f;
-    float q[8];
+    const uint32_t cap = (0x4300u + qmax) * 0x10001u;
+    uint32_t t[8];
+    unsigned short near = 0xFFFF;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const float a = (j & 1) ? half_minus<true>(w[j >> 1], -mn) : half_minus<false>(w[j >> 1], -mn);
-        q[j] = a * r;
-        clear = fminf(clear, fabsf(__builtin_amdgcn_fractf(q[j]) - 0.5f));
-        most = fmaxf(most, q[j]);
-        out[j] = __builtin_amdgcn_cvt_pk_u8_f32(q[j], uint32_t(slot), out[j]);  // rounds to nearest even, 0 .. 255
+    for (int k = 0; k < 4; ++k) {
+        t[2 * k] = __float_as_uint(half_mul_add<false>(w[k], tq.x, tq.y));
+        t[2 * k + 1] = __float_as_uint(half_mul_add<true>(w[k], tq.x, tq.y));
+        near = min(min(near, (unsigned short)t[2 * k]), (unsigned short)t[2 * k + 1]);
+        pair[k] = pk_min(__builtin_amdgcn_perm(t[2 * k + 1], t[2 * k], 0x07060302u), cap);
     }
-    // rare: a value near a rounding tie (the divide decides), or one that rounds above qmax (the
-    // scale is an fp16 rounding of rel * range, so the largest quotient can pass qmax + 1/2; an
-    // infinite quotient lands here too, and a NaN converts to code 0)
-    if (clear < TIE_GUARD || most >= top + 0.5f - TIE_GUARD) {
+    if (near < __float_as_uint(tq.z)) {  // rare: a value near a rounding tie: the divide decides
+        const uint32_t mt = __float_as_uint(tq.w);
+        const float s = __half2float(__ushort_as_half(uint16_t(mt & 0xFFFFu)));
+        const float mn = __half2float(__ushort_as_half(uint16_t(mt >> 16)));
+        const float top = float(qmax);
         const __half *x = reinterpret_cast<const __half *>(&values);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float qd = s != 0.0f ? (__half2float(x[j]) - mn) / s : 0.0f;  // IEEE fp32 divide
-            out[j] = __builtin_amdgcn_cvt_pk_u8_f32(fminf(qd, top), uint32_t(slot), out[j]);
+        for (int k = 0; k < 4; ++k) {
+            uint32_t code[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float qd = s != 0.0f ? (__half2float(x[2 * k + j]) - mn) / s : 0.0f;  // IEEE fp32 divide
+                code[j] = __builtin_amdgcn_cvt_pk_u8_f32(fminf(qd, top), 0u, 0u);            // to nearest even, 0 .. 255
+            }
+            pair[k] = 0x43004300u + (code[0] | (code[1] << 16));
         }
     }
 }
 
-// Quantizes a chunk and lays out its regions.  Every value is quantized by the thread that loaded
-// it, with its token's scale and minimum, so the code tile is written a word at a time.
-// Ends behind a barrier that all threads pass after their last read of the tile.
-__device__ inline PlaneChunk make_plane_chunk(const ChunkSource &cs, const ChunkInput &in, uint32_t *codes) {
-    const int tau = threadIdx.x;
-    {
-        const int cg = tau & 15, word = tau >> 4;
-        uint32_t out[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) quantize_token8(as_fp16(in.raw[i], cs.bf16), in.mt[i], cs.qmax, i, out);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) codes[(cg * 8 + j) * CODE_ROW_WORDS + word] = out[j];
-    }
-    __syncthreads();
-    PlaneChunk c;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int p = 2 * tau + k;
-        const int g = cs.pack_order ? (p & 3) : (p >> 7);
-        const int d = cs.pack_order ? (p >> 2) : (p & 127);
-        c.pb[k] = planes_from_codes(codes + d * CODE_ROW_WORDS + 4 * g);
-    }
-    // one scan carries both regions: E bytes in the low half, O bytes in the high half
-    int total;
-    const int w0 = c.pb[0].w, w1 = c.pb[1].w;
-    c.off = block_exclusive_scan(4 * ((w0 >> 1) + (w1 >> 1)) + ((2 * ((w0 & 1) + (w1 & 1))) << 16), &total);
-    c.e_bytes = total & 0xFFFF;
-    c.o_bytes = total >> 16;
-    c.padded = (HEADER + c.e_bytes + c.o_bytes + 15) & ~15;
-    return c;
+// Sum over the four lanes of one cg (rows 0..3) of x, and the part of it in the rows before this one.
+__device__ inline void rows4_sum(uint32_t x, uint32_t &before, uint32_t &total) {
+    const int q = (threadIdx.x >> 4) & 3;
+    uint32_t a = x, b = x;
+    swap_rows16(a, b);  // a: the even row's value, b: the odd row's, in both rows of a pair
+    uint32_t c = a + b, d = c;
+    swap_rows32(c, d);  // c: the lower pair's sum, d: the upper pair's
+    total = c + d;
+    before = ((q & 1) ? a : 0u) + ((q & 2) ? c : 0u);
 }
 
-__device__ inline void write_plane_chunk(const PlaneChunk &c, uint8_t *__restrict__ dst) {
+// Inclusive prefix sum over the 16 lanes of a row.
+__device__ inline uint32_t row_inclusive_scan(uint32_t x) {
+    int v = int(x);
+    v += dpp_shift0<DPP_ROW_SHR1, 0xF>(v);
+    v += dpp_shift0<DPP_ROW_SHR2, 0xF>(v);
+    v += dpp_shift0<DPP_ROW_SHR4, 0xF>(v);
+    v += dpp_shift0<DPP_ROW_SHR8, 0xF>(v);
+    return uint32_t(v);
+}
+
+// Quantizes a chunk and, if WRITE, puts its bytes together in lds.image[slot] (complete in every
+// thread's view on return).  Returns the chunk's size in 16-byte units.  All 256 threads call;
+// contains workgroup barriers (one without WRITE).  Consecutive calls alternate `slot`: the bytes
+// of the call before may still be read while this one runs.
+//
+// Bound by vector instructions next to memory (the input is read once here): per value one fused
+// multiply-add, half a byte permute, half a clamp, a third of a minimum for the tie test.
+template <bool WRITE>
+__device__ inline int build_plane_chunk(const ChunkSource &cs, const ChunkInput &in, ChunkLds &lds, int slot) {
+    const int tau = threadIdx.x, lane = tau & 63, cg = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tau >> 6);
+    if (lane < 16) lds.tok[16 * wave + lane] = token_quant(in.mt);
+    wave_lds_fence();
+    // codes of the lane's 8 channels x 4 tokens: word[j] = channel 8 cg + j, token i in byte i
+    uint32_t word[8], mn2[4], mx2[4];
+    {
+        const int tok0 = 16 * wave + 8 * (q >> 1) + (q & 1);
+        uint32_t pair[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) quantize_token8(as_fp16(in.raw[i], cs.bf16), lds.tok[tok0 + 2 * i], uint32_t(cs.qmax), pair[i]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            mn2[k] = pk_min(pk_min(pair[0][k], pair[1][k]), pk_min(pair[2][k], pair[3][k]));
+            mx2[k] = pk_max(pk_max(pair[0][k], pair[1][k]), pk_max(pair[2][k], pair[3][k]));
+            const uint32_t p01 = __builtin_amdgcn_perm(pair[1][k], pair[0][k], 0x06020400u);  // even ch. tokens 0 1, odd ch. tokens 0 1
+            const uint32_t p23 = __builtin_amdgcn_perm(pair[3][k], pair[2][k], 0x06020400u);
+            word[2 * k] = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
+            word[2 * k + 1] = __builtin_amdgcn_perm(p23, p01, 0x07060302u);
+        }
+    }
+    // 4 x 4 exchange between rows: rows 0, 1 keep channels 0..3, rows 2, 3 channels 4..7; then even
+    // rows the lower pair of those, odd rows the upper.  Row q ends with channels 2q, 2q + 1; word
+    // 2q + j of row q' goes to: j (from row 0), j + 2 (row 1), j + 4 (row 2), j + 6 (row 3).
+#pragma unroll
+    for (int j = 0; j < 4; ++j) swap_rows32(word[j], word[j + 4]);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) swap_rows16(word[j], word[j + 2]), swap_rows16(word[j + 4], word[j + 6]);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        swap_rows32(mn2[k], mn2[k + 2]);
+        swap_rows32(mx2[k], mx2[k + 2]);
+        mn2[k] = pk_min(mn2[k], mn2[k + 2]);
+        mx2[k] = pk_max(mx2[k], mx2[k + 2]);
+    }
+    swap_rows16(mn2[0], mn2[1]);
+    swap_rows16(mx2[0], mx2[1]);
+    const uint32_t mn = pk_min(mn2[0], mn2[1]), mx = pk_max(mx2[0], mx2[1]);
+    PlaneBits pb[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const uint32_t lo = (mn >> (16 * j)) & 0xFFu, hi = (mx >> (16 * j)) & 0xFFu;
+        pb[j] = planes_from_nibbles(word[j] | (word[j + 2] << 4), word[j + 4] | (word[j + 6] << 4), lo, hi);
+    }
+    const int w0 = pb[0].w, w1 = pb[1].w;
+    // Bytes of the lane's packs in the two regions.  Where a pack's planes go: behind those of all
+    // packs before it in the list.  Sums carry region E in the low half and region O in the high half.
+    const uint32_t e0 = 4u * uint32_t(w0 >> 1), e1 = 4u * uint32_t(w1 >> 1), o0 = 2u * uint32_t(w0 & 1), o1 = 2u * uint32_t(w1 & 1);
+    uint32_t off0, off1, total;
+    if (cs.pack_order == 0) {
+        // group-major (V): wave after wave, channels ascending inside a wave
+        const uint32_t mine = (e0 + e1) | ((o0 + o1) << 16);
+        uint32_t before, four;
+        rows4_sum(mine, before, four);
+        const uint32_t inc = row_inclusive_scan(four);
+        if (lane == 15) lds.counts[slot][0][wave] = inc;
+        __syncthreads();
+        const uint4 t = *reinterpret_cast<const uint4 *>(&lds.counts[slot][0][0]);
+        total = (t.x + t.y) + (t.z + t.w);
+        off0 = inc - four + before + (wave > 0 ? t.x : 0u) + (wave > 1 ? t.y : 0u) + (wave > 2 ? t.z : 0u);
+        off1 = off0 + (e0 | (o0 << 16));
+    } else {
+        // channel-major (K): for every channel the four groups, i.e. the four waves
+        lds.counts[slot][wave][lane] = e0 | (o0 << 8) | (e1 << 16) | (o1 << 24);  // sums of four stay below 256
+        __syncthreads();
+        const uint32_t n0 = lds.counts[slot][0][lane], n1 = lds.counts[slot][1][lane];
+        const uint32_t n2 = lds.counts[slot][2][lane], n3 = lds.counts[slot][3][lane];
+        const uint32_t all = (n0 + n1) + (n2 + n3);
+        const uint32_t earlier = (wave > 0 ? n0 : 0u) + (wave > 1 ? n1 : 0u) + (wave > 2 ? n2 : 0u);
+        const uint32_t all0 = (all & 0xFFu) | ((all & 0xFF00u) << 8), all1 = ((all >> 16) & 0xFFu) | ((all >> 8) & 0xFF0000u);
+        uint32_t before, four;
+        rows4_sum(all0 + all1, before, four);
+        const uint32_t inc = row_inclusive_scan(four);
+        total = uint32_t(__builtin_amdgcn_readlane(int(inc), 15));
+        off0 = inc - four + before;
+        off1 = off0 + all0 + (((earlier >> 16) & 0xFFu) | ((earlier >> 8) & 0xFF0000u));
+        off0 += (earlier & 0xFFu) | ((earlier & 0xFF00u) << 8);
+    }
+    const int e_bytes = int(total & 0xFFFFu), used = HEADER + e_bytes + int(total >> 16);
+    const int padded = (used + 15) & ~15;
+    if constexpr (WRITE) {
+        uint8_t *img = lds.image[slot];
+        const int d = 8 * cg + 2 * q;
+        const uint32_t h0 = uint32_t((w0 << 4) | pb[0].m), h1 = uint32_t((w1 << 4) | pb[1].m);
+        if (cs.pack_order == 0) {
+            *reinterpret_cast<uint16_t *>(img + 128 * wave + d) = uint16_t(h0 | (h1 << 8));
+        } else {
+            img[4 * d + wave] = uint8_t(h0);
+            img[4 * d + 4 + wave] = uint8_t(h1);
+        }
+        uint32_t *ea = reinterpret_cast<uint32_t *>(img + HEADER + (off0 & 0xFFFFu));
+        uint32_t *eb = reinterpret_cast<uint32_t *>(img + HEADER + (off1 & 0xFFFFu));
+        if (w0 >= 2) ea[0] = pb[0].low;
+        if (w0 == 4) ea[1] = pb[0].high;
+        if (w1 >= 2) eb[0] = pb[1].low;
+        if (w1 == 4) eb[1] = pb[1].high;
+        if (w0 & 1) *reinterpret_cast<uint16_t *>(img + HEADER + e_bytes + (off0 >> 16)) = uint16_t(pb[0].top);
+        if (w1 & 1) *reinterpret_cast<uint16_t *>(img + HEADER + e_bytes + (off1 >> 16)) = uint16_t(pb[1].top);
+        if (tau < padded - used) img[used + tau] = 0;
+        __syncthreads();
+    }
+    return padded >> 4;
+}
+
+// The finished bytes of a chunk to global memory.
+__device__ inline void copy_image(const ChunkLds &lds, int slot, int n16, uint8_t *__restrict__ to) {
+    static_assert(CHUNK_MAX <= 2 * 256 * 16, "two 16-byte units per thread move a chunk");
     const int tau = threadIdx.x;
-    const int w0 = c.pb[0].w, w1 = c.pb[1].w;
-    reinterpret_cast<uint16_t *>(dst)[tau] = uint16_t(((w0 << 4) | c.pb[0].m) | (((w1 << 4) | c.pb[1].m) << 8));
-    uint32_t *e = reinterpret_cast<uint32_t *>(dst + HEADER + (c.off & 0xFFFF));
-    if (w0 >= 2) e[0] = c.pb[0].low;
-    if (w0 == 4) e[1] = c.pb[0].high;
-    e += w0 >> 1;
-    if (w1 >= 2) e[0] = c.pb[1].low;
-    if (w1 == 4) e[1] = c.pb[1].high;
-    uint16_t *o = reinterpret_cast<uint16_t *>(dst + HEADER + c.e_bytes + (c.off >> 16));
-    if (w0 & 1) o[0] = uint16_t(c.pb[0].top);
-    o += w0 & 1;
-    if (w1 & 1) o[0] = uint16_t(c.pb[1].top);
-    if (tau < c.padded - HEADER - c.e_bytes - c.o_bytes) dst[HEADER + c.e_bytes + c.o_bytes + tau] = 0;
+    const uint4 *image = reinterpret_cast<const uint4 *>(lds.image[slot]);
+    uint4 *dst = reinterpret_cast<uint4 *>(to);
+    if (tau < n16) dst[tau] = image[tau];
+    if (tau + 256 < n16) dst[tau + 256] = image[tau + 256];
 }
 
 // Staged path, packs of 16, contiguous arena: the input is quantized once.
@@ -563,26 +677,24 @@ __global__ __launch_bounds__(256) void chunk16_kernel(PackArgs a) {
         if (o1 == o0) return;  // dropped: the arena was full
         dst = t.arena + size_t(o0) * 16;
     }
-    __shared__ uint32_t codes[CODE_TILE_WORDS];
-    const PlaneChunk c = make_plane_chunk(t.cs, load_chunk_input(t.cs, cl, load_chunk_rows(t.cs, cl)), codes);
-    if (!WRITE) {
-        if (threadIdx.x == 0) t.sizes16[cl] = uint32_t(c.padded >> 4);
-        return;
-    }
-    write_plane_chunk(c, dst);
+    __shared__ ChunkLds lds;
+    const int n16 = build_plane_chunk<WRITE>(t.cs, load_chunk_input<false>(t.cs, cl, load_chunk_rows(t.cs, cl)), lds, 0);
+    if (WRITE)
+        copy_image(lds, 0, n16, dst);
+    else if (threadIdx.x == 0)
+        t.sizes16[cl] = uint32_t(n16);
 }
 
 // The part's chunks of both tensors, item i = K chunk i (i < n) or V chunk i - n, into slot i.  A
 // workgroup takes every gridDim.x-th item and has the loads of its next one in flight while it
-// works on the current one.
+// works on the current one.  STREAM: the round's input is larger than the caches (last-level cache
+// 256 MB): read with the non-temporal hint, 3.56 -> 3.47 ms for a prompt of 6.8 GB; a smaller
+// input is still there from the token parameter pass, which the hint would not make use of (67 MB: 51 -> 54 us).
+template <bool STREAM>
 __global__ __launch_bounds__(256) void chunk16_stage_kernel(PackArgs a) {
     const int lo = staged_round(a.t[0].round, a.t[0].index) ? 0 : a.n;
     const int hi = staged_round(a.t[1].round, a.t[1].index) ? 2 * a.n : a.n;
-    // the chunk's bytes are put together in the memory of the code tile (8704 bytes, a chunk has at most 4608)
-    __shared__ __attribute__((aligned(16))) uint32_t codes[CODE_TILE_WORDS];
-    static_assert(CODE_TILE_WORDS * 4 >= CHUNK_MAX, "the chunk image lives in the code tile");
-    static_assert(CHUNK_MAX <= 2 * 256 * 16, "two 16-byte units per thread move a chunk");
-    const int tau = threadIdx.x;
+    __shared__ ChunkLds lds;
     const int stride = int(gridDim.x);
     int item = lo + int(blockIdx.x);
     if (item >= hi) return;
@@ -593,29 +705,22 @@ __global__ __launch_bounds__(256) void chunk16_stage_kernel(PackArgs a) {
     };
     auto input_of = [&](int i, const ChunkRows &rows) {
         const int v = i >= a.n;
-        return load_chunk_input(a.t[v].cs, a.part_first + i - (v ? a.n : 0), rows);
+        return load_chunk_input<STREAM>(a.t[v].cs, a.part_first + i - (v ? a.n : 0), rows);
     };
     // The loads of the next chunk and the token order of the one after it are always issued (of
     // the last chunk again where there is no next one): the count of loads in flight is then the
     // same on every path, and the waits of the current chunk do not wait for them.
     ChunkInput in = input_of(item, rows_of(item));
     ChunkRows rows_next = rows_of(min(item + stride, last));
-    for (;;) {
+    for (int slot = 0;; slot ^= 1) {
         const int next = item + stride;
         const ChunkInput in_next = input_of(min(next, last), rows_next);
         rows_next = rows_of(min(next + stride, last));
         const int v = item >= a.n;
-        const PlaneChunk c = make_plane_chunk(a.t[v].cs, in, codes);
-        write_plane_chunk(c, reinterpret_cast<uint8_t *>(codes));
-        __syncthreads();
-        if (tau == 0) a.t[v].sizes16[item - (v ? a.n : 0)] = uint32_t(c.padded >> 4);
-        const uint4 *image = reinterpret_cast<const uint4 *>(codes);
-        uint4 *slot = reinterpret_cast<uint4 *>(a.staging + size_t(item) * CHUNK_MAX);
-        const int n16 = c.padded >> 4;
-        if (tau < n16) slot[tau] = image[tau];
-        if (tau + 256 < n16) slot[tau + 256] = image[tau + 256];
+        const int n16 = build_plane_chunk<true>(a.t[v].cs, in, lds, slot);
+        if (threadIdx.x == 0) a.t[v].sizes16[item - (v ? a.n : 0)] = uint32_t(n16);
+        copy_image(lds, slot, n16, a.staging + size_t(item) * CHUNK_MAX);
         if (next >= hi) break;
-        __syncthreads();  // the image is read: the next code tile may take its place
         in = in_next;
         item = next;
     }
@@ -634,38 +739,41 @@ __device__ inline uint32_t block_sum(uint32_t v) {
 // one chunk, so a workgroup four.  Every workgroup adds up the sizes of the part's chunks before
 // its own by itself (at most 32 KB, in the L2 cache of its die after the first): no launch of a scan
 // between staging and compaction, which cost a launch gap and 7 us for 16384 chunks.
-__global__ __launch_bounds__(256) void chunk16_compact_kernel(PackArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void chunk16_compact_kernel(PackArgs a) {
     const PackTensor &t = a.t[blockIdx.y];
     if (!staged_round(t.round, t.index)) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wg_first = blockIdx.x * 4, cl = wg_first + wave;
+    const bool present = cl < a.n;
+    // the four sizes of the workgroup in one read (the sizes area goes on behind the last one)
+    const uint4 sz = *reinterpret_cast<const uint4 *>(t.sizes16 + wg_first);
     const uint32_t start0 = t.index[t.round.first_chunk + a.part_first];
-    uint32_t before = 0;
-    for (int i = 4 * tid; i < wg_first; i += 1024) {
-        const uint4 q = *reinterpret_cast<const uint4 *>(t.sizes16 + i);
-        before += q.x + q.y + q.z + q.w;
-    }
-    uint32_t mine = 0, own = 0;  // this wave's chunk, and those of the workgroup before it
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const uint32_t sz = wg_first + k < a.n ? t.sizes16[wg_first + k] : 0u;
-        if (k < wave) own += sz;
-        if (k == wave) mine = sz;
-    }
-    const uint32_t start = start0 + block_sum(before) + own;
-    if (cl >= a.n) return;
-    const int n16 = int(mine);
-    if (lane == 0) t.index[t.round.first_chunk + a.part_first + cl + 1] = start + mine;
-    const uint8_t *slot = a.staging + size_t(blockIdx.y * a.n + cl) * CHUNK_MAX;
+    const uint32_t mine = wave == 0 ? sz.x : wave == 1 ? sz.y : wave == 2 ? sz.z : sz.w;
+    const uint32_t own = (wave > 0 ? sz.x : 0u) + (wave > 1 ? sz.y : 0u) + (wave > 2 ? sz.z : 0u);
+    const int n16 = present ? int(mine) : 0;
+    // the chunk's bytes are on their way while its place is found
     constexpr int STEPS = (CHUNK_MAX / 16 + 63) / 64;
     // read once and written once: both with the non-temporal hint (6 % of the whole compression)
     typedef uint32_t u32x4n __attribute__((ext_vector_type(4)));
-    const u32x4n *src = reinterpret_cast<const u32x4n *>(slot);
-    u32x4n *dst = reinterpret_cast<u32x4n *>(t.arena + size_t(start) * 16);
+    const u32x4n *src = reinterpret_cast<const u32x4n *>(a.staging + size_t(blockIdx.y * a.n + cl) * CHUNK_MAX);
     u32x4n v[STEPS];
 #pragma unroll
     for (int i = 0; i < STEPS; ++i)
         if (lane + 64 * i < n16) v[i] = __builtin_nontemporal_load(src + lane + 64 * i);
+    uint32_t before = 0;
+#pragma unroll 1
+    for (int i = 4 * tid; i < wg_first; i += 4096) {
+        uint4 q[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            q[k] = i + 1024 * k < wg_first ? *reinterpret_cast<const uint4 *>(t.sizes16 + i + 1024 * k) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) before += q[k].x + q[k].y + q[k].z + q[k].w;
+    }
+    const uint32_t start = start0 + block_sum(before) + own;
+    if (!present) return;
+    if (lane == 0) t.index[t.round.first_chunk + a.part_first + cl + 1] = start + mine;
+    u32x4n *dst = reinterpret_cast<u32x4n *>(t.arena + size_t(start) * 16);
 #pragma unroll
     for (int i = 0; i < STEPS; ++i)
         if (lane + 64 * i < n16) __builtin_nontemporal_store(v[i], dst + lane + 64 * i);
@@ -1190,6 +1298,7 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
     a.staging = ws + c->stage_offset;
     if (staged) {
         // equal parts that fit the staging area, half of its slots for each tensor
+        const bool stream = int64_t(n_chunks) * 2 * (N * D * 2) > (int64_t(192) << 20);
         const int most = c->stage_chunks / 2;
         const int parts = (n_chunks + most - 1) / most, per_part = (n_chunks + parts - 1) / parts;
         for (int part = 0; part < n_chunks; part += per_part) {
@@ -1197,9 +1306,9 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
             a.n = std::min(per_part, n_chunks - part);
             a.t[0].sizes16 = sizes16;
             a.t[1].sizes16 = sizes16 + ((a.n + 3) & ~3);
-            static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(chunk16_stage_kernel));
+            static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(chunk16_stage_kernel<false>));
             const int groups = flat_groups_for(int64_t(a.n) * 8, per_cu, 2 * a.n);  // all resident, at most one per chunk
-            hipLaunchKernelGGL(chunk16_stage_kernel, dim3(groups), dim3(256), 0, s, a);
+            hipLaunchKernelGGL(stream ? chunk16_stage_kernel<true> : chunk16_stage_kernel<false>, dim3(groups), dim3(256), 0, s, a);
             hipLaunchKernelGGL(chunk16_compact_kernel, dim3((a.n + 3) / 4, 2), dim3(256), 0, s, a);
         }
     }
