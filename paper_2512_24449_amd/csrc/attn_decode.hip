@@ -36,13 +36,13 @@ struct AArgs {
     const uint32_t *k_index, *v_index;
     const uint32_t *k_meta, *v_meta;  // [B][meta_stride]
     const __half *q;                  // [B][Hq][128]
-    float *partial;                   // [splits][B*Hq][V_PART_STRIDE]
+    float *partial;                   // [row sets][G][V_PART_STRIDE], see FlatPlan
     int64_t meta_stride;
     int B, H;
     int index_words;        // index words per chunk: 1 back to back, 2 with a paged arena
     int dup;                // H counts every kv-head dup times (query groups above 8 are split): kv-head = h / dup
     int n_blocks;                     // packed blocks per stream
-    int blocks_per_split;
+    int blocks_per_split;             // not FLAT: blocks of a workgroup
     float sm_log2;                    // sm_scale * log2(e)
 };
 
@@ -131,12 +131,13 @@ __device__ inline void attn_store_state(const VPlaneState<G> &st, float (*red)[D
     v_planes_store<G>(st, red, lane);
 }
 
-// End of a fused attention workgroup: merges the four waves' running sums (each with its own
-// softmax reference) and writes the split's partial row.  red aliases the chunk buffers.
+// End of a workgroup's part of a stream: merges the four waves' running sums (each with its own
+// softmax reference) and writes the partial rows.  red aliases the chunk buffers, which are free again
+// on return.
 template <int G, class State>
 __device__ inline void attn_store_partial(const AArgs &a, const State &st, const float (&l_lane)[G],
                                           const float (&m_ref)[G], float (*red)[G][D + 4], int wave,
-                                          int lane, int split, int64_t head0,
+                                          int lane, int64_t row_set,
                                           float code_scale = CODE_SCALE_LIFTED) {
     __syncthreads();  // every wave is done with its chunk buffers: reuse them as red[][][]
 
@@ -155,7 +156,7 @@ __device__ inline void attn_store_partial(const AArgs &a, const State &st, const
         const float m0 = red[0][g][D + 2], m1 = red[1][g][D + 2], m2 = red[2][g][D + 2], m3 = red[3][g][D + 2];
         const float M = fmaxf(fmaxf(m0, m1), fmaxf(m2, m3));
         const float f0 = exp2_diff(m0, M), f1 = exp2_diff(m1, M), f2 = exp2_diff(m2, M), f3 = exp2_diff(m3, M);
-        float *dst = a.partial + (int64_t(split) * a.B * a.H * G + head0 + g) * V_PART_STRIDE;
+        float *dst = a.partial + (row_set * G + g) * V_PART_STRIDE;
         if (d < D) {
             // outputs carry the per-head sum p*min term
             dst[d] = (f0 * (red[0][g][d] + red[0][g][D]) + f1 * (red[1][g][d] + red[1][g][D])) +
@@ -166,13 +167,17 @@ __device__ inline void attn_store_partial(const AArgs &a, const State &st, const
             dst[A_M] = M;
         }
     }
+    __syncthreads();  // red[][][] has been read: the buffers may be filled again
 }
 
-// HIGH: the V codes of the cache may need four bits (a plane H exists).
-template <int G, bool HIGH>
-__global__ __launch_bounds__(256) void attn_kernel(AArgs a) {
+// HIGH: the V codes of the cache may need four bits (a plane H exists).  The blocks of all streams form
+// one work list cut into equal ranges, one per workgroup and one round of resident workgroups
+// (FlatPlan), so no last round runs nearly empty; a workgroup whose range crosses a stream
+// boundary writes a partial row set per stream.
+template <int G, bool HIGH, bool FLAT>
+__global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
     // per wave: buffer 0 holds the K chunk (and then its tiles, k_planes.h), buffer 1 the V chunk of
-    // the block in flight; after the main loop the same memory holds the cross-wave reduction array
+    // the block in flight; between two streams the same memory holds the cross-wave reduction array
     // red[4][G][D + 4]
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * 2 * CHUNK_LDS + LDS_TAIL_PAD];
     constexpr int VB = vb_bytes<G>();
@@ -189,74 +194,101 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a) {
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int split = blockIdx.x;
-    const int bh = blockIdx.y;
-    const int h = bh % a.H, b = bh / a.H;
+    const int grp = blockIdx.x;
     const int col = lane & 15;
     const int kbuf = wave * 2 * CHUNK_LDS, vbuf = kbuf + CHUNK_LDS;
-    const int64_t head0 = int64_t(b) * a.H * G + h * G;
-
-    KQueryPlanes<G> kq;
-    kq.load(a.q + head0 * D, lane);
     uint8_t *vb = vb_all + wave * VB;
-    VPlaneState<G> st;
-    st.clear();
-    float m_ref[G], l_lane[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) m_ref[g] = -INFINITY, l_lane[g] = 0.0f;
+    const int64_t range_end = FLAT ? plan.begin(grp + 1) : 1;
 
-    const int blk_begin = split * a.blocks_per_split;
-    const int blk_end = min(blk_begin + a.blocks_per_split, a.n_blocks);
-    for (int first = blk_begin + wave; first < blk_end; first += 4 * 64) {
-        IndexBatch ik, iv;
-        ik.load(a.k_index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
-        iv.load(a.v_index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
-        const int n_it = min(64, (blk_end - first + 3) / 4);
-        chunk_issue_lds<CHUNK_MAX, HEADER, true>(a.k_arena, ik.start16(0), ik.end16(0), lds_all + kbuf, lane);
-        const int64_t tok0 = b * a.meta_stride + int64_t(first) * N + lane;
-        uint32_t kmt_next = a.k_meta[tok0], vmt_next = a.v_meta[tok0];
-        for (int it = 0; it < n_it; ++it) {
-            // a block dropped by an arena overflow (in either tensor) takes no part
-            const bool valid = ik.end16(it) - ik.start16(it) >= uint32_t(HEADER / 16) &&
-                               iv.end16(it) - iv.start16(it) >= uint32_t(HEADER / 16);
-            wait_chunk_landed();  // K chunk of this block
-            uint32_t kmt = kmt_next, vmt = vmt_next;
-            consume_here(kmt), consume_here(vmt);
-            lds_reads_returned();  // the previous V chunk has been read completely
-            chunk_issue_lds<CHUNK_MAX, HEADER, true>(a.v_arena, iv.start16(it), iv.end16(it), lds_all + vbuf, lane);
-            if (it + 1 < n_it) {
-                const int64_t tok = b * a.meta_stride + int64_t(first + 4 * (it + 1)) * N + lane;
-                kmt_next = a.k_meta[tok];
-                vmt_next = a.v_meta[tok];
-            }
-
-            float s[G];  // scores of token `lane` in log2 units
-            if (valid) {
-                float u[G];
-                k_planes_chunk<G>(lds_all, kbuf, ktable, lds_all + kbuf, kq, u, []() {});
-                const float kscale = __half2float(__ushort_as_half(uint16_t(kmt & 0xFFFFu)));
-                const float kmn = __half2float(__ushort_as_half(uint16_t(kmt >> 16)));
-#pragma unroll
-                for (int g = 0; g < G; ++g) s[g] = a.sm_log2 * fmaf(kscale, u[g], kmn * kq.qsum[g]);
-
-                attn_raise_reference<G>(s, m_ref, l_lane, st, col);
-            }
-            wait_chunk_landed();  // V chunk of this block
-            lds_reads_returned();  // the K tiles have been read completely before the next chunk overwrites them
-            if (it + 1 < n_it)
-                chunk_issue_lds<CHUNK_MAX, HEADER, true>(a.k_arena, ik.start16(it + 1), ik.end16(it + 1), lds_all + kbuf, lane);
-            if (!valid) continue;
-            float pt[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                pt[g] = exp2f(s[g] - m_ref[g]);
-                l_lane[g] += pt[g];
-            }
-            v_planes_chunk<G, HIGH>(lds_all, vbuf, vtable, vhighs, vb, vmt, pt, st);
+    for (int64_t f = FLAT ? plan.begin(grp) : 0; f < range_end;) {
+        FlatPlan::Segment seg;
+        int64_t row_set;
+        if constexpr (FLAT) {
+            seg = plan.segment(f, range_end);
+            row_set = int64_t(grp) + seg.stream;
+            f += seg.blk_end - seg.blk_begin;
+        } else {
+            seg.stream = blockIdx.y;
+            seg.b = seg.stream / a.H, seg.h = seg.stream % a.H;
+            seg.blk_begin = grp * a.blocks_per_split;
+            seg.blk_end = min(seg.blk_begin + a.blocks_per_split, a.n_blocks);
+            row_set = int64_t(grp) * gridDim.y + seg.stream;
+            f = 1;
         }
-        wait_chunk_landed();
+        const int stream = seg.stream, b = seg.b, h = seg.h, blk_begin = seg.blk_begin, blk_end = seg.blk_end;
+        const int64_t head0 = int64_t(stream) * G;
+
+        KQueryPlanes<G> kq;
+        kq.fetch(a.q + head0 * D, lane);
+        VPlaneState<G> st;
+        st.clear();
+        float m_ref[G], l_lane[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) m_ref[g] = -INFINITY, l_lane[g] = 0.0f;
+
+        IndexBatch ik, iv;
+        uint32_t kmt_next = 0, vmt_next = 0;
+        // index words of up to 64 blocks of this wave, then both chunks of the first of them
+        auto start_batch = [&](int first) {
+            if (first >= blk_end) return;
+            ik.load(a.k_index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
+            iv.load(a.v_index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
+            const int64_t tok0 = b * a.meta_stride + int64_t(first) * N + lane;
+            kmt_next = a.k_meta[tok0], vmt_next = a.v_meta[tok0];
+            chunk_issue_lds<CHUNK_MAX, HEADER, true>(a.k_arena, ik.start16(0), ik.end16(0), lds_all + kbuf, lane);
+            if (FLAT) chunk_issue_lds<CHUNK_MAX, HEADER, true>(a.v_arena, iv.start16(0), iv.end16(0), lds_all + vbuf, lane);
+        };
+        start_batch(blk_begin + wave);
+        kq.build(lane);  // while the first chunks are on their way
+        for (int first = blk_begin + wave; first < blk_end; first += 4 * 64) {
+            const int n_it = min(64, (blk_end - first + 3) / 4);
+            for (int it = 0; it < n_it; ++it) {
+                // a block dropped by an arena overflow (in either tensor) takes no part
+                const bool valid = ik.end16(it) - ik.start16(it) >= uint32_t(HEADER / 16) &&
+                                   iv.end16(it) - iv.start16(it) >= uint32_t(HEADER / 16);
+                wait_chunk_landed();  // K chunk of this block
+                uint32_t kmt = kmt_next, vmt = vmt_next;
+                consume_here(kmt), consume_here(vmt);
+                if (!FLAT || it > 0) {
+                    lds_reads_returned();  // the previous V chunk has been read completely
+                    chunk_issue_lds<CHUNK_MAX, HEADER, true>(a.v_arena, iv.start16(it), iv.end16(it), lds_all + vbuf, lane);
+                }
+                if (it + 1 < n_it) {
+                    const int64_t tok = b * a.meta_stride + int64_t(first + 4 * (it + 1)) * N + lane;
+                    kmt_next = a.k_meta[tok];
+                    vmt_next = a.v_meta[tok];
+                }
+
+                float s[G];  // scores of token `lane` in log2 units
+                if (valid) {
+                    float u[G];
+                    k_planes_chunk<G>(lds_all, kbuf, ktable, lds_all + kbuf, kq, u, []() {});
+                    const float kscale = __half2float(__ushort_as_half(uint16_t(kmt & 0xFFFFu)));
+                    const float kmn = __half2float(__ushort_as_half(uint16_t(kmt >> 16)));
+#pragma unroll
+                    for (int g = 0; g < G; ++g) s[g] = a.sm_log2 * fmaf(kscale, u[g], kmn * kq.qsum[g]);
+
+                    attn_raise_reference<G>(s, m_ref, l_lane, st, col);
+                }
+                wait_chunk_landed();  // V chunk of this block
+                lds_reads_returned();  // the K tiles have been read completely before the next chunk overwrites them
+                if (it + 1 < n_it)
+                    chunk_issue_lds<CHUNK_MAX, HEADER, true>(a.k_arena, ik.start16(it + 1), ik.end16(it + 1), lds_all + kbuf, lane);
+                if (!valid) continue;
+                float pt[G];
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    pt[g] = __builtin_amdgcn_exp2f(s[g] - m_ref[g]);  // below 2^-126: 0, nothing next to the block's largest
+                    l_lane[g] += pt[g];
+                }
+                v_planes_chunk<G, HIGH>(lds_all, vbuf, vtable, vhighs, vb, vmt, pt, st);
+            }
+            wait_chunk_landed();
+            lds_reads_returned();  // the last V chunk has been read before the next batch's first overwrites it
+            start_batch(first + 4 * 64);
+        }
+        attn_store_partial<G>(a, st, l_lane, m_ref, red, wave, lane, row_set);
     }
-    attn_store_partial<G>(a, st, l_lane, m_ref, red, wave, lane, split, head0);
 }
 
 // The same for chunks with packs of 8 tokens (Sec. IV-B; pack8.h): the K phase runs the
@@ -379,7 +411,7 @@ __global__ __launch_bounds__(256) void attn8_kernel(AArgs a) {
                 float pt[G];
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
-                    pt[g] = exp2f(s[g] - m_ref[g]);
+                    pt[g] = __builtin_amdgcn_exp2f(s[g] - m_ref[g]);  // below 2^-126: 0, nothing next to the block's largest
                     l_lane[g] += pt[g];
                 }
                 if constexpr (VW)
@@ -396,13 +428,13 @@ __global__ __launch_bounds__(256) void attn8_kernel(AArgs a) {
         wait_chunk_landed();
     }
     // wide V codes enter the matrix cores as the numbers themselves
-    attn_store_partial<G>(a, st, l_lane, m_ref, red, wave, lane, split, head0, VW ? 1.0f : CODE_SCALE_LIFTED);
+    attn_store_partial<G>(a, st, l_lane, m_ref, red, wave, lane, int64_t(split) * gridDim.y + bh, VW ? 1.0f : CODE_SCALE_LIFTED);
 }
 
 // Merges the splits of one (batch, query head) row in a fixed order and adds the raw fp16
 // tail tokens (Sec. III-B.1 buffer), whose scores are plain dot products.
 __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restrict__ partial,
-                                                           int n_splits, int n_rows,
+                                                           int n_splits, FlatPlan plan,
                                                            const __half *__restrict__ q,
                                                            const __half *__restrict__ k_tail,
                                                            const __half *__restrict__ v_tail,
@@ -418,10 +450,22 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
     // every global load of the kernel is issued before the first result is needed
     SplitRows rows;
     TailRows trows;
-    rows.load(partial, n_splits, n_rows, r);
+    // the row sets of stream r / Gk are those of the workgroups that hold one of its blocks
+    // the row sets of the row's stream: one per split, or with a flat plan (one head per kv-head: row =
+    // stream) those of the workgroups that hold one of its blocks
+    int64_t first_row = r, row_stride = gridDim.x;
+    if (plan.n_groups > 0) {
+        const int w_lo = plan.group_of(int64_t(r) * plan.n_blocks);
+        const int w_hi = plan.group_of(int64_t(r + 1) * plan.n_blocks - 1);
+        n_splits = w_hi - w_lo + 1;
+        first_row = w_lo + r;
+        row_stride = 1;
+    }
+    partial += first_row * V_PART_STRIDE;
+    rows.load_strided(partial, n_splits, row_stride);
     trows.load(v_tail + (int64_t(b) * tail_cap * H + h) * D, int64_t(H) * D, n_tail);
     if (int(threadIdx.x) < n_splits)
-        ms[threadIdx.x] = partial[(int64_t(threadIdx.x) * n_rows + r) * V_PART_STRIDE + A_M];
+        ms[threadIdx.x] = partial[int64_t(threadIdx.x) * row_stride * V_PART_STRIDE + A_M];
     // tail scores: thread (t, seg) takes 32 channels of tail token t, four threads per token
     {
         const int t = threadIdx.x >> 2, seg = threadIdx.x & 3;
@@ -472,9 +516,9 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
     uint8_t *ws = static_cast<uint8_t *>(c->buf.workspace);
     float *partial = reinterpret_cast<float *>(ws + WS_VPART);
     const float sm_log2 = sm_scale * LOG2E;
+    FlatPlan plan = FlatPlan::make(n_blocks, B, Hs);
     int n_splits = 0;
     if (n_blocks > 0) {
-        n_splits = v_splits_for(n_blocks, B * Hs);
         AArgs a;
         a.k_arena = static_cast<const uint8_t *>(c->buf.k_arena);
         a.v_arena = static_cast<const uint8_t *>(c->buf.v_arena);
@@ -490,17 +534,40 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         a.H = Hs;
         a.dup = c->head_split;
         a.n_blocks = n_blocks;
-        a.blocks_per_split = (n_blocks + n_splits - 1) / n_splits;
         a.sm_log2 = sm_log2;
+        n_splits = v_splits_for(n_blocks, B * Hs);
+        a.blocks_per_split = (n_blocks + n_splits - 1) / n_splits;
         n_splits = (n_blocks + a.blocks_per_split - 1) / a.blocks_per_split;
-        dim3 grid(n_splits, B * Hs);
-        if (c->cfg.pack_size == 8) {
+        const dim3 grid(n_splits, B * Hs);
 #define PACKKV_LAUNCH_A8NN(g) hipLaunchKernelGGL((attn8_kernel<g, false, false>), grid, dim3(256), 0, s, a)
 #define PACKKV_LAUNCH_A8WN(g) hipLaunchKernelGGL((attn8_kernel<g, true, false>), grid, dim3(256), 0, s, a)
 #define PACKKV_LAUNCH_A8NW(g) hipLaunchKernelGGL((attn8_kernel<g, false, true>), grid, dim3(256), 0, s, a)
 #define PACKKV_LAUNCH_A8WW(g) hipLaunchKernelGGL((attn8_kernel<g, true, true>), grid, dim3(256), 0, s, a)
-#define PACKKV_LAUNCH_A(g) hipLaunchKernelGGL((attn_kernel<g, false>), grid, dim3(256), 0, s, a)
-#define PACKKV_LAUNCH_AH(g) hipLaunchKernelGGL((attn_kernel<g, true>), grid, dim3(256), 0, s, a)
+#define PACKKV_LAUNCH_A(g) hipLaunchKernelGGL((attn_kernel<g, false, false>), grid, dim3(256), 0, s, a, plan)
+#define PACKKV_LAUNCH_AH(g) hipLaunchKernelGGL((attn_kernel<g, true, false>), grid, dim3(256), 0, s, a, plan)
+        // One head per kv-head and at least eight blocks for every wave of one round of resident workgroups:
+        // a flat plan (8 x 52 streams of 500 blocks: 4160 workgroups at 768 resident ended in a round that was
+        // two fifths full; 258 -> 239 us, 1 x 32 of 1000: 55 -> 49).  Below that the longer start-up of the plan
+        // shows (1 x 32 streams of 250 blocks: 21.7 / 23.5 us).  With more heads the sums of a second stream's
+        // part do not fit the registers next to the loop (4 x 8 streams of 512, four heads: 46 -> 50 us), and
+        // packs of 8 gain nothing (30.1 / 30.6 us, wide 35.3 / 35.2).
+        bool flat = false;
+#define PACKKV_LAUNCH_FLAT(...)                                                                        \
+    {                                                                                                  \
+        static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(__VA_ARGS__));    \
+        const int groups = plan_groups_for(n_blocks, B * Hs, per_cu, int64_t(V_SPLITS_MAX - 2) * B * Hs); \
+        flat = plan.total >= int64_t(groups) * 4 * 8;                                                  \
+        if (flat) {                                                                                    \
+            plan.split(groups);                                                                        \
+            hipLaunchKernelGGL((__VA_ARGS__), dim3(groups), dim3(256), 0, s, a, plan);                 \
+        }                                                                                              \
+    }
+        if (c->cfg.pack_size == 16 && G == 1) {
+            if (c->qmax_v > 7) PACKKV_LAUNCH_FLAT(attn_kernel<1, true, true>)
+            else PACKKV_LAUNCH_FLAT(attn_kernel<1, false, true>)
+        }
+        if (flat) {
+        } else if (c->cfg.pack_size == 8) {
             if (c->wide_k && c->wide_v) {
                 PACKKV_DISPATCH_GROUP(G, PACKKV_LAUNCH_A8WW)
             } else if (c->wide_k) {
@@ -521,9 +588,10 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
 #undef PACKKV_LAUNCH_A8WW
 #undef PACKKV_LAUNCH_A
 #undef PACKKV_LAUNCH_AH
+#undef PACKKV_LAUNCH_FLAT
     }
     hipLaunchKernelGGL(attn_combine_kernel, dim3(B * H * Gq), dim3(256), 0, s, partial, n_splits,
-                       B * H * Gq, q, static_cast<const __half *>(c->buf.k_tail),
+                       plan, q, static_cast<const __half *>(c->buf.k_tail),
                        static_cast<const __half *>(c->buf.v_tail), c->tail_tokens,
                        c->cfg.tail_capacity, H, Gq, sm_log2, out);
     KV_HIP_CHECK(hipGetLastError());

@@ -216,11 +216,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     const int64_t range_end = plan.begin(grp + 1);
 
     for (int64_t f = plan.begin(grp); f < range_end;) {
-        const int stream = int(f / plan.n_blocks);
-        const int blk_begin = int(f - int64_t(stream) * plan.n_blocks);
-        const int blk_end = int(min<int64_t>(plan.n_blocks, blk_begin + (range_end - f)));
+        const FlatPlan::Segment seg = plan.segment(f, range_end);
+        const int stream = seg.stream, b = seg.b, h = seg.h, blk_begin = seg.blk_begin, blk_end = seg.blk_end;
         f += blk_end - blk_begin;
-        const int h = stream % a.H, b = stream / a.H;
         const uint32_t *meta = a.meta + b * a.meta_stride;
         const int64_t head0 = int64_t(stream) * G;
         KQueryPlanes<G> kq;
@@ -354,14 +352,12 @@ int launch_k_matvec(const kv_cache *c, const __half *q, float sm_scale, float *s
     } else if (c->cfg.pack_size == 8) {
         PACKKV_DISPATCH_GROUP(c->group, PACKKV_LAUNCH_K8)
     } else {
-        FlatPlan plan;
-        plan.n_blocks = a.n_blocks;
-        plan.total = int64_t(a.n_blocks) * streams;
+        FlatPlan plan = FlatPlan::make(a.n_blocks, a.B, a.H);
         // one round of resident workgroups, never less than one block per wave
 #define PACKKV_LAUNCH_KP(g)                                                                                   \
     {                                                                                                         \
         static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(k_planes_kernel<g>));    \
-        plan.n_groups = plan.total > 0 ? flat_groups_for(plan.total, per_cu, int64_t(1) << 30) : 0;  \
+        if (plan.total > 0) plan.split(plan_groups_for(a.n_blocks, streams, per_cu, int64_t(1) << 30));       \
         hipLaunchKernelGGL(k_planes_kernel<g>, dim3(plan.n_groups + tail_groups), dim3(256), 0, s, a, plan); \
     }
         PACKKV_DISPATCH_GROUP4(c->group, PACKKV_LAUNCH_KP)

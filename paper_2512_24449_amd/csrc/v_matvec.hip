@@ -75,11 +75,9 @@ __global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
     const int64_t range_end = plan.begin(grp + 1);
 
     for (int64_t f = plan.begin(grp); f < range_end;) {
-        const int stream = int(f / plan.n_blocks);
-        const int blk_begin = int(f - int64_t(stream) * plan.n_blocks);
-        const int blk_end = int(min<int64_t>(plan.n_blocks, blk_begin + (range_end - f)));
+        const FlatPlan::Segment seg = plan.segment(f, range_end);
+        const int stream = seg.stream, b = seg.b, h = seg.h, blk_begin = seg.blk_begin, blk_end = seg.blk_end;
         f += blk_end - blk_begin;
-        const int h = stream % a.H, b = stream / a.H;
         const uint32_t *meta = a.meta + b * a.meta_stride;
         const float *prow = a.p + int64_t(stream) * G * a.ld;
         VPlaneState<G> st;
@@ -344,6 +342,32 @@ int flat_groups_for(int64_t total, int per_cu, int64_t most) {
     return int(std::max<int64_t>(w, 1));
 }
 
+// Workgroups for a flat plan over `streams` streams of n_blocks chunks, at most `most`.  Either one round
+// of resident workgroups that cut the list as it comes, or a whole number of workgroups per
+// stream: then none has parts of two streams, each of which costs its start-up (query, index, first
+// chunk) and its end (merge, store) -- about the time of PART_COST chunks of a wave.  The cheaper one by the
+// chunks its longest wave walks: 256 streams of 7 blocks run as 512 workgroups of one stream each (fused
+// attention 21 us; 448 that cross the boundaries 29 us), 416 streams of 500 blocks as one round of 768.
+int plan_groups_for(int n_blocks, int streams, int per_cu, int64_t most) {
+    constexpr int64_t PART_COST = 2;
+    const int64_t total = int64_t(n_blocks) * streams;
+    const int64_t room = flat_groups_for(int64_t(1) << 40, per_cu, int64_t(1) << 30);
+    auto waves = [](int64_t blocks) { return (blocks + 3) / 4; };
+    const int64_t flat = flat_groups_for(total, per_cu, most);
+    int64_t best = flat;
+    int64_t best_cost = waves((total + flat - 1) / flat) * 4 + 4 * PART_COST * (flat + streams - 1) / flat;
+    const int64_t most_per_stream = std::max<int64_t>(1, std::min<int64_t>(waves(n_blocks), most / streams));
+    for (int64_t want : {int64_t(1), room / streams, most_per_stream}) {
+        const int64_t per_stream = std::max<int64_t>(1, std::min<int64_t>(want, most_per_stream));
+        const int64_t groups = per_stream * streams;
+        if (groups > most) continue;
+        const int64_t rounds = (groups + room - 1) / room;
+        const int64_t cost = 4 * rounds * (waves((n_blocks + per_stream - 1) / per_stream) + PART_COST);
+        if (cost < best_cost || (cost == best_cost && best == flat)) best = groups, best_cost = cost;
+    }
+    return int(best);
+}
+
 // partial: [row sets][V_PART_STRIDE] floats for the split sums; max_split_rows: how many rows
 // (one per query head and split or row set) it can take.
 static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p, float *out, float *partial,
@@ -356,7 +380,7 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
     if (rows > max_split_rows) return KV_ERR_CAPACITY;
     const bool planes = !c->wide_v && c->cfg.pack_size == PACK;
     int n_splits = 0;
-    FlatPlan plan = {n_blocks, 0, int64_t(B) * Hs * n_blocks};
+    FlatPlan plan = FlatPlan::make(n_blocks, B, Hs);
     VArgs a;
     a.arena = static_cast<const uint8_t *>(c->buf.v_arena);
     a.index = static_cast<const uint32_t *>(c->buf.v_index);
@@ -380,7 +404,7 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
 #define PACKKV_LAUNCH_VX(g, high)                                                                          \
     {                                                                                                      \
         static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(v_matvec_kernel<g, high>)); \
-        plan.n_groups = flat_groups_for(plan.total, per_cu, most_groups);                                 \
+        plan.split(plan_groups_for(n_blocks, B * Hs, per_cu, most_groups));                               \
         hipLaunchKernelGGL((v_matvec_kernel<g, high>), dim3(plan.n_groups), dim3(256), 0, s, a, plan);      \
     }
 #define PACKKV_LAUNCH_V(g) PACKKV_LAUNCH_VX(g, false)
