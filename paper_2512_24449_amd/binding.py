@@ -124,13 +124,19 @@ def _check(rc: int, what: str) -> None:
         raise PackKVError("%s: %s (%d)" % (what, lib().kv_strerror(rc).decode(), rc), rc)
 
 
+# torch's current stream as a raw pointer, without building a Stream object around it (2 us per call
+# of the decode entry points, which launch kernels of a few microseconds)
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_ptr(stream=None):
-    """stream: None (torch's current stream), a torch stream, or a raw hipStream_t as int
-    (looking up the current stream costs microseconds; hot loops pass the integer)."""
-    if isinstance(stream, int):
-        return C.c_void_p(stream)
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    """stream: None (torch's current stream), a torch stream, or a raw hipStream_t as int."""
+    if stream is None:
+        if _current_raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _current_raw_stream(_current_device())
+        return torch.cuda.current_stream().cuda_stream
+    return stream if isinstance(stream, int) else stream.cuda_stream
 
 
 def make_config(batch, n_kv_heads, n_q_heads, max_tokens, k_rel_scale=0.1, v_rel_scale=0.2,
@@ -217,6 +223,8 @@ class PackedKVCache:
                                              C.byref(handle)), "kv_cache_create")
         self.handle = handle
         self.batch, self.n_kv_heads, self.n_q_heads = batch, n_kv_heads, n_q_heads
+        self._q_shape, self._row_shape = (batch, n_q_heads, HEAD_DIM), (batch, n_q_heads)
+        self._token_shape = (n_kv_heads, HEAD_DIM)
 
     def close(self):
         if getattr(self, "handle", None) and _lib is not None:
@@ -234,41 +242,48 @@ class PackedKVCache:
 
     @property
     def tokens(self) -> int:
-        return int(lib().kv_cache_tokens(self.handle))
+        return _lib.kv_cache_tokens(self.handle)
 
     def kv_compress_append(self, k_new: torch.Tensor, v_new: torch.Tensor, stream=None):
         """k_new, v_new: fp16 (or both bf16: kv_compress_append_bf16) [B, n, H_kv, 128] contiguous device tensors."""
-        assert k_new.dtype == v_new.dtype and k_new.dtype in (torch.float16, torch.bfloat16)
-        assert k_new.is_contiguous() and v_new.is_contiguous() and k_new.shape == v_new.shape
-        assert k_new.shape[0] == self.batch and tuple(k_new.shape[2:]) == (self.n_kv_heads, HEAD_DIM)
-        if k_new.dtype == torch.bfloat16:
-            _check(lib().kv_compress_append_bf16(self.handle, k_new.data_ptr(), v_new.data_ptr(),
-                                                 k_new.shape[1], _stream_ptr(stream)), "kv_compress_append_bf16")
+        dtype, shape = k_new.dtype, k_new.shape
+        assert dtype == v_new.dtype and dtype in (torch.float16, torch.bfloat16)
+        assert k_new.is_contiguous() and v_new.is_contiguous() and shape == v_new.shape
+        assert shape[0] == self.batch and shape[2:] == self._token_shape
+        if dtype == torch.bfloat16:
+            rc = _lib.kv_compress_append_bf16(self.handle, k_new.data_ptr(), v_new.data_ptr(), shape[1],
+                                              _stream_ptr(stream))
+            if rc != KV_OK:
+                _check(rc, "kv_compress_append_bf16")
             return
-        _check(lib().kv_compress_append(self.handle, k_new.data_ptr(), v_new.data_ptr(),
-                                        k_new.shape[1], _stream_ptr(stream)), "kv_compress_append")
+        rc = _lib.kv_compress_append(self.handle, k_new.data_ptr(), v_new.data_ptr(), shape[1], _stream_ptr(stream))
+        if rc != KV_OK:
+            _check(rc, "kv_compress_append")
 
     def kv_k_matvec(self, q: torch.Tensor, sm_scale: float, scores: torch.Tensor = None, stream=None):
         """q: fp16 [B, Hq, 128] -> scores fp32 [B, Hq, ld] (ld >= tokens)."""
         assert q.dtype == torch.float16 and q.is_contiguous()
-        assert tuple(q.shape) == (self.batch, self.n_q_heads, HEAD_DIM)
+        assert q.shape == self._q_shape
         if scores is None:
             scores = torch.empty(self.batch, self.n_q_heads, self.tokens, dtype=torch.float32,
                                  device=self.device)
-        assert scores.dtype == torch.float32 and scores.is_contiguous()
-        _check(lib().kv_k_matvec(self.handle, q.data_ptr(), sm_scale, scores.data_ptr(),
-                                 scores.shape[2], _stream_ptr(stream)), "kv_k_matvec")
+        else:
+            assert scores.dtype == torch.float32 and scores.is_contiguous()
+        rc = _lib.kv_k_matvec(self.handle, q.data_ptr(), sm_scale, scores.data_ptr(), scores.shape[2],
+                              _stream_ptr(stream))
+        if rc != KV_OK:
+            _check(rc, "kv_k_matvec")
         return scores
 
     def kv_v_matvec(self, p: torch.Tensor, out: torch.Tensor = None, stream=None):
         """p: fp32 [B, Hq, ld] -> out fp32 [B, Hq, 128]."""
         assert p.dtype == torch.float32 and p.is_contiguous()
-        assert tuple(p.shape[:2]) == (self.batch, self.n_q_heads)
+        assert p.shape[:2] == self._row_shape
         if out is None:
-            out = torch.empty(self.batch, self.n_q_heads, HEAD_DIM, dtype=torch.float32,
-                              device=self.device)
-        _check(lib().kv_v_matvec(self.handle, p.data_ptr(), p.shape[2], out.data_ptr(),
-                                 _stream_ptr(stream)), "kv_v_matvec")
+            out = torch.empty(self._q_shape, dtype=torch.float32, device=self.device)
+        rc = _lib.kv_v_matvec(self.handle, p.data_ptr(), p.shape[2], out.data_ptr(), _stream_ptr(stream))
+        if rc != KV_OK:
+            _check(rc, "kv_v_matvec")
         return out
 
     def kv_v_matvec_noalloc(self, p: torch.Tensor, out: torch.Tensor, stream=None):
@@ -284,20 +299,21 @@ class PackedKVCache:
     def kv_softmax(self, scores: torch.Tensor, stream=None):
         """In-place softmax over the cached tokens of scores fp32 [B, Hq, ld]; returns scores."""
         assert scores.dtype == torch.float32 and scores.is_contiguous()
-        assert tuple(scores.shape[:2]) == (self.batch, self.n_q_heads)
-        _check(lib().kv_softmax(self.handle, scores.data_ptr(), scores.shape[2], _stream_ptr(stream)),
-               "kv_softmax")
+        assert scores.shape[:2] == self._row_shape
+        rc = _lib.kv_softmax(self.handle, scores.data_ptr(), scores.shape[2], _stream_ptr(stream))
+        if rc != KV_OK:
+            _check(rc, "kv_softmax")
         return scores
 
     def kv_decode_attention(self, q: torch.Tensor, sm_scale: float, out: torch.Tensor = None, stream=None):
         """q: fp16 [B, Hq, 128] -> out fp32 [B, Hq, 128] = softmax(sm_scale * q K^T) V over the whole cache."""
         assert q.dtype == torch.float16 and q.is_contiguous()
-        assert tuple(q.shape) == (self.batch, self.n_q_heads, HEAD_DIM)
+        assert q.shape == self._q_shape
         if out is None:
-            out = torch.empty(self.batch, self.n_q_heads, HEAD_DIM, dtype=torch.float32,
-                              device=self.device)
-        _check(lib().kv_decode_attention(self.handle, q.data_ptr(), sm_scale, out.data_ptr(),
-                                         _stream_ptr(stream)), "kv_decode_attention")
+            out = torch.empty(self._q_shape, dtype=torch.float32, device=self.device)
+        rc = _lib.kv_decode_attention(self.handle, q.data_ptr(), sm_scale, out.data_ptr(), _stream_ptr(stream))
+        if rc != KV_OK:
+            _check(rc, "kv_decode_attention")
         return out
 
     def kv_cache_stats(self, stream=None) -> kv_stats_t:
@@ -306,10 +322,14 @@ class PackedKVCache:
         return st
 
     def kv_cache_release(self, stream=None):
-        _check(lib().kv_cache_release(self.handle, _stream_ptr(stream)), "kv_cache_release")
+        rc = _lib.kv_cache_release(self.handle, _stream_ptr(stream))
+        if rc != KV_OK:
+            _check(rc, "kv_cache_release")
 
     def kv_cache_restore(self, tokens: int):
-        _check(lib().kv_cache_restore(self.handle, tokens), "kv_cache_restore")
+        rc = _lib.kv_cache_restore(self.handle, tokens)
+        if rc != KV_OK:
+            _check(rc, "kv_cache_restore")
 
     # typed views of the raw buffers, for tests and tools
     def view(self, name, dtype):
