@@ -36,3 +36,21 @@ def test_fused_attention_on_the_flat_plan_equals_the_three_steps(B, H, blocks, t
     # outputs are a few hundredths of sum(p |v|) at these lengths
     rel = (fused.double() - steps).norm(dim=-1) / steps.norm(dim=-1)
     assert float(rel.max()) < 1e-4, float(rel.max())
+
+
+# segments in registers (up to 64 of 4096 tokens) and beyond them; a row of 16 segments with an odd stride
+@pytest.mark.parametrize("Hq,tokens,ld", [(1, 64 * 4096, 64 * 4096), (1, 64 * 4096 + 1, 64 * 4096 + 3), (3, 8192, 8193),
+                                          (3, 12289, 12289), (32, 65537, 65539), (2, 300001, 300001)])
+def test_softmax_of_few_long_rows(Hq, tokens, ld):
+    cache = binding.PackedKVCache(1, 1, Hq, tokens)
+    cache.kv_cache_restore(tokens)
+    gen = torch.Generator(device="cuda:0").manual_seed(tokens)
+    s = 3.0 * torch.randn(1, Hq, ld, device="cuda:0", generator=gen)
+    s[0, 0, 100:5000] = -math.inf   # a dropped range
+    s[0, Hq - 1, tokens - 1] = 40.0
+    want = torch.softmax(s[..., :tokens].double(), -1)
+    rest = s[..., tokens:].clone()
+    got = cache.kv_softmax(s)
+    # exp2 of an argument rounded to 24 bits: up to 2^-24 * |argument| (under 100) relative, plus the fp32 sum
+    assert float(((got[..., :tokens].double() - want).abs() / (want + 1e-30)).max()) < 2e-5
+    assert torch.equal(got[..., tokens:], rest)
