@@ -488,19 +488,23 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
         if (seg == 0 && t < n_tail) st[t] = sm_log2 * s;
     }
     __syncthreads();
-    float M = -INFINITY;
-    for (int s = 0; s < n_splits; ++s) M = fmaxf(M, ms[s]);
-    for (int t = 0; t < n_tail; ++t) M = fmaxf(M, st[t]);
+    // at most 64 splits and 64 tail tokens: one of each per lane; every wave finds the row's reference and the
+    // tail's weight sum by itself (element after element from LDS they took 3 us with 62 tail tokens)
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const float my_split = lane < n_splits ? ms[lane] : -INFINITY, my_tail = lane < n_tail ? st[lane] : -INFINITY;
+    const float M = wave_all_max(fmaxf(my_split, my_tail));
+    const float tail_weight = lane < n_tail ? exp2f(my_tail - M) : 0.0f;
+    const float tail_sum = wave_all_sum(tail_weight);
     __syncthreads();
-    if (int(threadIdx.x) < n_splits) ms[threadIdx.x] = exp2_diff(ms[threadIdx.x], M);
-    if (threadIdx.x >= 64 && int(threadIdx.x) - 64 < n_tail) st[threadIdx.x - 64] = exp2f(st[threadIdx.x - 64] - M);
+    if (wave == 0 && lane < n_splits) ms[lane] = exp2_diff(my_split, M);
+    if (wave == 1 && lane < n_tail) st[lane] = tail_weight;
     __syncthreads();
     // weighted sum of the split rows (column 128 = the splits' weight sums), then the tail tokens
     float l;
     float o = rows.sum(n_splits, red, &l, ms);
     if (n_tail > 0) {
         o += trows.sum(st, n_tail, red);
-        for (int t = 0; t < n_tail; ++t) l += st[t];
+        l += tail_sum;
     }
     const int d = threadIdx.x;
     if (d < D) out[int64_t(r) * D + d] = l > 0.0f ? o / l : 0.0f;  // every block dropped and no tail: defined output
