@@ -78,12 +78,18 @@ struct ParamArgs {
     bool bf16;
 };
 
-__global__ __launch_bounds__(256) void token_params_kernel(ParamArgs a) {
-    const int t = blockIdx.x, b = blockIdx.y;
+// A workgroup per token, or (WAVE: rows of up to 2048 values, which would leave lanes of a workgroup
+// idle) a wave per token, four tokens to a workgroup.
+template <bool WAVE>
+__global__ __launch_bounds__(256) void token_params_kernel(ParamArgs a, int n_tokens) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int t = WAVE ? blockIdx.x * 4 + wave : blockIdx.x, b = blockIdx.y;
+    if (WAVE && t >= n_tokens) return;
     const ParamTensor &pt = a.t[blockIdx.z];
     const __half *row = pt.src + b * a.batch_stride + t * a.token_stride;
     float mn = INFINITY, mx = -INFINITY;
-    for (int i = threadIdx.x * 8; i < a.row_elems; i += 256 * 8) {
+    constexpr int STEP = (WAVE ? 64 : 256) * 8;
+    for (int i = (WAVE ? lane : int(threadIdx.x)) * 8; i < a.row_elems; i += STEP) {
         uint4 raw = load8_as_fp16(row + i, a.bf16);
         const __half *h = reinterpret_cast<const __half *>(&raw);
 #pragma unroll
@@ -98,17 +104,18 @@ __global__ __launch_bounds__(256) void token_params_kernel(ParamArgs a) {
         mn = fminf(mn, __shfl_xor(mn, o));
         mx = fmaxf(mx, __shfl_xor(mx, o));
     }
-    __shared__ float smn[4], smx[4];
-    if ((threadIdx.x & 63) == 0) {
-        smn[threadIdx.x >> 6] = mn;
-        smx[threadIdx.x >> 6] = mx;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
+    if constexpr (!WAVE) {
+        __shared__ float smn[4], smx[4];
+        if (lane == 0) {
+            smn[wave] = mn;
+            smx[wave] = mx;
+        }
+        __syncthreads();
         mn = fminf(fminf(smn[0], smn[1]), fminf(smn[2], smn[3]));
         mx = fmaxf(fmaxf(smx[0], smx[1]), fmaxf(smx[2], smx[3]));
-        pt.meta[b * a.meta_stride + a.first_token + t] = token_meta_word(mn, mx, pt.rel);
     }
+    if (WAVE ? lane == 0 : threadIdx.x == 0)
+        pt.meta[b * a.meta_stride + a.first_token + t] = token_meta_word(mn, mx, pt.rel);
 }
 
 // Quantize the PK tokens of one pack (channel d of token group g) and derive
@@ -1044,6 +1051,136 @@ __global__ __launch_bounds__(1024) void place_chunks_kernel(PackArgs a, int n_te
     }
 }
 
+// The same for rounds of up to PLACE_SMALL_CHUNKS chunks per tensor: sizes and prefix sums stay in LDS, the
+// two tensors run side by side in half a workgroup each (only the pages are taken one after the other, K
+// first), and the one thread that follows the chain of page starts marks them on the way.  This
+// kernel is one chain of latencies: 2 x 1504 chunks took 33 us through the general one.
+constexpr int PLACE_SMALL_CHUNKS = 8192;
+__global__ __launch_bounds__(1024) void place_small_kernel(PackArgs a) {
+    constexpr int T = 512;
+    constexpr uint32_t P = PAGE16;
+    __shared__ uint32_t sums[2][PLACE_SMALL_CHUNKS + 1];
+    __shared__ uint8_t steps[2][PLACE_SMALL_CHUNKS];
+    __shared__ uint32_t wave_a[2][T / 64], wave_b[2][T / 64];
+    __shared__ uint32_t sh_need[2], sh_top[2], sh_ok[2];
+    const int half = __builtin_amdgcn_readfirstlane(threadIdx.x / T);
+    const int tid = threadIdx.x % T, lane = tid & 63, wave = tid >> 6, n = a.n;
+    const PackTensor &t = a.t[half];
+    uint32_t *const S = sums[half];
+    uint8_t *const step = steps[half];
+    const uint32_t held = t.page_list[0], newest_fill = t.page_list[1];
+    const uint32_t newest = held ? t.page_list[1 + held] : 0u;
+    const uint32_t fill0 = held ? newest_fill : P;  // no page yet: like a full one
+    for (int i = tid; i < n; i += T) S[i] = t.sizes16[i];
+    __syncthreads();
+    // exclusive prefix sums, S[n] = total
+    const int per = (n + T - 1) / T, lo = min(tid * per, n), hi = min(lo + per, n);
+    uint32_t local = 0;
+    for (int i = lo; i < hi; ++i) local += S[i];
+    const uint32_t inc = uint32_t(wave_inclusive_scan(int(local)));
+    if (lane == 63) wave_a[half][wave] = inc;
+    __syncthreads();
+    uint32_t run = inc - local;
+    for (int k = 0; k < wave; ++k) run += wave_a[half][k];
+    for (int i = lo; i < hi; ++i) {
+        const uint32_t sz = S[i];
+        S[i] = run;
+        run += sz;
+    }
+    if (tid == T - 1) S[n] = run;
+    __syncthreads();
+    // chunks (minus one) that a page holds which starts with chunk j
+    for (int j = lo, k = lo; j < hi; ++j) {
+        k = max(k, j + 1);
+        const uint32_t limit = S[j] + P;
+        while (k < n && S[k + 1] <= limit) ++k;
+        step[j] = uint8_t(k - j - 1);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        // chunks 0 .. j - 1 still go into the newest page: the largest j with fill0 + S[j] <= P
+        int j = 0, above = n + 1;
+        while (above - j > 1) {
+            const int mid = (j + above) >> 1;
+            if (fill0 + S[mid] <= P) j = mid; else above = mid;
+        }
+        uint32_t need = 0;
+        while (j < n) {
+            const uint32_t c = step[j];
+            step[j] = uint8_t(c | 0x80u);
+            ++need;
+            j += int(c) + 1;
+        }
+        sh_need[half] = need;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int v = 0; v < 2; ++v) {  // K's pages come first
+            const uint32_t need = sh_need[v];
+            uint32_t ok = a.t[v].page_list[0] + need <= uint64_t(a.t[v].max_pages), top = 0;
+            if (ok && need) {
+                uint32_t old = __atomic_load_n(&a.pool_state[0], __ATOMIC_RELAXED);
+                while (true) {
+                    if (old < need) {
+                        ok = 0;
+                        break;
+                    }
+                    const uint32_t seen = atomicCAS(&a.pool_state[0], old, old - need);
+                    if (seen == old) break;
+                    old = seen;
+                }
+                top = old;
+            }
+            sh_ok[v] = ok;
+            sh_top[v] = top;
+        }
+    }
+    __syncthreads();
+    uint32_t *const index2 = t.index + 2 * t.round.first_chunk;
+    const bool ok = sh_ok[half] != 0;
+    const uint32_t top = sh_top[half];
+    // page starts before this thread's slice, and the last of them (+1; 0 = none)
+    uint32_t marks = 0, last = 0;
+    for (int j = lo; j < hi; ++j)
+        if (step[j] & 0x80u) ++marks, last = uint32_t(j) + 1;
+    uint32_t marks_inc = marks, last_inc = last;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t x = __shfl_up(marks_inc, o), y = __shfl_up(last_inc, o);
+        if (lane >= o) marks_inc += x, last_inc = max(last_inc, y);
+    }
+    __syncthreads();
+    if (lane == 63) wave_a[half][wave] = marks_inc, wave_b[half][wave] = last_inc;
+    __syncthreads();
+    if (!ok) {
+        if (tid == 0) t.status[0] = 1;
+        for (int i = tid; i < 2 * n; i += T) index2[i] = 0;
+        return;
+    }
+    uint32_t ord = marks_inc - marks, start_j = __shfl_up(last_inc, 1);
+    if (lane == 0) start_j = 0;
+    for (int k = 0; k < wave; ++k) ord += wave_a[half][k], start_j = max(start_j, wave_b[half][k]);
+    uint32_t page = 0, page_s = 0;  // the page the slice starts in, S of the chunk that starts it
+    if (start_j) page = a.pool_state[top - (ord - 1)], page_s = S[start_j - 1];
+    for (int j = lo; j < hi; ++j) {
+        if (step[j] & 0x80u) {
+            page = a.pool_state[top - ord];  // stack entry top - 1 - ord sits at word top - ord
+            t.page_list[2 + held + ord] = page;
+            ++ord;
+            page_s = S[j];
+        }
+        const uint32_t at = ord ? page * P + (S[j] - page_s) : newest * P + fill0 + S[j];
+        index2[2 * j] = at;
+        index2[2 * j + 1] = at + (S[j + 1] - S[j]);
+    }
+    if (tid == T - 1) {
+        uint32_t l = max(last_inc, start_j);  // the last page start of all
+        for (int k = 0; k < T / 64; ++k) l = max(l, wave_b[half][k]);
+        t.page_list[0] = held + ord;
+        t.page_list[1] = l ? S[n] - S[l - 1] : fill0 + S[n];
+    }
+}
+
 // Pool of n free pages: the stack holds n - 1 down to 0, so page 0 is handed out first.
 __global__ void pool_init_kernel(uint32_t *state, int64_t n_pages) {
     const int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
@@ -1092,6 +1229,48 @@ __global__ void init_kernel(uint32_t *status, uint32_t *k_index, uint32_t *v_ind
         v_index[0] = 0;
         if (k_pages) k_pages[0] = k_pages[1] = v_pages[0] = v_pages[1] = 0;
     }
+}
+
+// V-median repacking, step 1, codes below 16 (packs of 16): a wave per token quantizes with the packs' fixed-point
+// rule and counts every code with ballots; the lower median is the first code whose running count
+// passes the middle.  (A workgroup per token with per-thread counters and 1e-3 wide guards, which
+// sent most waves to the divide: 28.6 us for 12032 tokens of 1024 values.)
+__global__ __launch_bounds__(256) void v_median16_key_kernel(const __half *__restrict__ src, int64_t batch_stride,
+                                                             int64_t token_stride, int row_elems, int qmax,
+                                                             const uint32_t *__restrict__ meta, int64_t meta_stride,
+                                                             int64_t first_token, int n_tokens,
+                                                             uint8_t *__restrict__ keys, bool bf16) {
+    const int lane = threadIdx.x & 63, t = blockIdx.x * 4 + (threadIdx.x >> 6), b = blockIdx.y;
+    if (t >= n_tokens) return;
+    const __half *row = src + b * batch_stride + t * token_stride;
+    const float4 tq = token_quant(meta[b * meta_stride + first_token + t]);
+    int count[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) count[v] = 0;
+    for (int i = 0; i < row_elems; i += 512) {
+        uint32_t pair[4] = {0, 0, 0, 0};  // no code where the row has ended
+        if (i + 8 * lane < row_elems) quantize_token8(load8_as_fp16(row + i + 8 * lane, bf16), tq, uint32_t(qmax), pair);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            if (v < qmax) {  // the last code's count is what is left
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    count[v] += __popcll(__builtin_amdgcn_ballot_w64((pair[k] & 0xFFFFu) == 0x4300u + v));
+                    count[v] += __popcll(__builtin_amdgcn_ballot_w64((pair[k] >> 16) == 0x4300u + v));
+                }
+            }
+        }
+    }
+    const int rank = (row_elems - 1) / 2;
+    int seen = 0, key = qmax;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        if (v < qmax) {
+            seen += count[v];
+            if (seen > rank && key == qmax) key = v;
+        }
+    }
+    if (lane == 0) keys[b * meta_stride + first_token + t] = uint8_t(key);
 }
 
 // V-median repacking, step 1 (Sec. III-B.3): the lower median of the H*128 quantized V codes of
@@ -1231,7 +1410,10 @@ int launch_token_params(const kv_cache *c, const CompressJob &kjob, const Compre
     a.first_token = kjob.first_token;
     a.row_elems = H * D;
     a.bf16 = kjob.bf16;
-    hipLaunchKernelGGL(token_params_kernel, dim3(n_tokens, B, 2), dim3(256), 0, s, a);
+    if (a.row_elems <= 2048)
+        hipLaunchKernelGGL(token_params_kernel<true>, dim3((n_tokens + 3) / 4, B, 2), dim3(256), 0, s, a, n_tokens);
+    else
+        hipLaunchKernelGGL(token_params_kernel<false>, dim3(n_tokens, B, 2), dim3(256), 0, s, a, n_tokens);
     KV_HIP_CHECK(hipGetLastError());
     return KV_OK;
 }
@@ -1241,9 +1423,14 @@ int launch_v_median_order(const kv_cache *c, const CompressJob &vjob, uint32_t *
     const int B = c->cfg.batch, H = c->cfg.n_kv_heads;
     const int n_tokens = vjob.n_blocks * N;
     if (n_tokens <= 0 || H * D / 2048 + 1 > 31) return KV_ERR_ARG;  // 8-bit per-thread counters
-    hipLaunchKernelGGL(v_median_key_kernel, dim3(n_tokens, B), dim3(256), 0, s, vjob.src,
-                       vjob.batch_stride, vjob.token_stride, H * D, vjob.qmax, vjob.meta,
-                       c->max_tokens, vjob.first_token, order, vjob.bf16);
+    if (vjob.qmax < 16 && c->cfg.pack_size == 16)
+        hipLaunchKernelGGL(v_median16_key_kernel, dim3((n_tokens + 3) / 4, B), dim3(256), 0, s, vjob.src, vjob.batch_stride,
+                           vjob.token_stride, H * D, vjob.qmax, vjob.meta, c->max_tokens, vjob.first_token, n_tokens, order,
+                           vjob.bf16);
+    else
+        hipLaunchKernelGGL(v_median_key_kernel, dim3(n_tokens, B), dim3(256), 0, s, vjob.src,
+                           vjob.batch_stride, vjob.token_stride, H * D, vjob.qmax, vjob.meta,
+                           c->max_tokens, vjob.first_token, order, vjob.bf16);
     hipLaunchKernelGGL(block_order_kernel, dim3(vjob.n_blocks, B), dim3(64), 0, s, order, vjob.qmax,
                        k_meta, vjob.meta, c->max_tokens, vjob.first_token);
     KV_HIP_CHECK(hipGetLastError());
@@ -1336,7 +1523,9 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
                 a.first_tensor = i;
             };
             pass(false);
-            if (c->pool)
+            if (c->pool && n_tensors == 2 && n_chunks <= PLACE_SMALL_CHUNKS)
+                hipLaunchKernelGGL(place_small_kernel, dim3(1), dim3(1024), 0, s, a);
+            else if (c->pool)
                 hipLaunchKernelGGL(place_chunks_kernel, dim3(1), dim3(1024), 0, s, a, n_tensors);
             else
                 hipLaunchKernelGGL(scan_offsets_kernel, dim3(n_tensors), dim3(1024), 0, s, a);
