@@ -190,11 +190,13 @@ __device__ inline void k_tail(const KArgs &a, int bh, int lane) {
 // of a workgroup take every fourth block of its range.  A wave keeps ONE chunk buffer and its
 // tiles: the planes of a chunk are copied to the tiles in the first part of its decode, and the
 // next chunk streams into the buffer during the rest (the products, the score exchange, the
-// stores), so five workgroups fit a compute unit and their waves hide one another's waits.  The
+// stores), so four or five workgroups fit a compute unit and their waves hide one another's waits.  The
 // token metadata of a chunk travels the same way as the chunk (one dword per lane, global memory
 // -> LDS, behind the chunk in its buffer).  Workgroups past the plan's take the raw fp16 tail.
-template <int G>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_planes_kernel(KArgs a, FlatPlan plan) {
+// WAVES: waves per SIMD the kernel is compiled for.  Five (96 registers, a few values of the start of a
+// stream's part in scratch memory) where every wave has many chunks, four (107 registers) where the start counts.
+template <int G, int WAVES>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_planes_kernel(KArgs a, FlatPlan plan) {
     constexpr int SIDE = CHUNK_MAX + LDS_TAIL_PAD;  // metadata row behind the chunk
     constexpr int BUF = SIDE + 256;
     static_assert(BUF % 16 == 0, "buffers are 16-byte aligned");
@@ -353,15 +355,22 @@ int launch_k_matvec(const kv_cache *c, const __half *q, float sm_scale, float *s
         PACKKV_DISPATCH_GROUP(c->group, PACKKV_LAUNCH_K8)
     } else {
         FlatPlan plan = FlatPlan::make(a.n_blocks, a.B, a.H);
-        // one round of resident workgroups, never less than one block per wave
-#define PACKKV_LAUNCH_KP(g)                                                                                   \
+        // one round of resident workgroups, never less than one block per wave; five waves per SIMD from eight
+        // chunks per wave on (four / five waves, one head: 15008 chunks 16.2 / 17.3 us, 32000: 27.8 / 28.6,
+        // 64000: 49.7 / 49.3, 208000: 146 / 142; four heads: 16384 chunks 20.3 / 21.5, 100032: 87.4 / 85.3)
+#define PACKKV_LAUNCH_KPW(g, w)                                                                               \
     {                                                                                                         \
-        static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(k_planes_kernel<g>));    \
+        static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(k_planes_kernel<g, w>)); \
         if (plan.total > 0) plan.split(plan_groups_for(a.n_blocks, streams, per_cu, int64_t(1) << 30));       \
-        hipLaunchKernelGGL(k_planes_kernel<g>, dim3(plan.n_groups + tail_groups), dim3(256), 0, s, a, plan); \
+        hipLaunchKernelGGL((k_planes_kernel<g, w>), dim3(plan.n_groups + tail_groups), dim3(256), 0, s, a, plan); \
     }
+        const bool many = plan.total >= int64_t(8) * 4 * flat_groups_for(int64_t(1) << 40, 5, int64_t(1) << 30);
+#define PACKKV_LAUNCH_KP(g)             \
+    if (many) PACKKV_LAUNCH_KPW(g, 5)   \
+    else PACKKV_LAUNCH_KPW(g, 4)
         PACKKV_DISPATCH_GROUP4(c->group, PACKKV_LAUNCH_KP)
 #undef PACKKV_LAUNCH_KP
+#undef PACKKV_LAUNCH_KPW
     }
 #undef PACKKV_LAUNCH_KW
 #undef PACKKV_LAUNCH_K8
