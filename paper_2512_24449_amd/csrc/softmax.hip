@@ -39,21 +39,26 @@ __device__ inline float finite_max(float mx) { return mx == -INFINITY ? 0.0f : m
 __device__ inline float safe_inverse(float sum) { return sum > 0.0f ? 1.0f / sum : 0.0f; }
 
 // NREG == 0: rows of any length, three passes over memory.
+// (32 elements per thread: 64 registers, so that two rows share a compute unit; 416 rows of 32001 tokens
+// took two rounds of one row per unit, the second two thirds full.)
 template <int NREG>
-__global__ __launch_bounds__(SMX_THREADS) void softmax_kernel(float *__restrict__ s, int64_t ld,
+__global__ __launch_bounds__(SMX_THREADS) __attribute__((amdgpu_waves_per_eu(NREG <= 32 ? 8 : 4))) void softmax_kernel(float *__restrict__ s, int64_t ld,
                                                               int64_t tokens) {
     __shared__ float lds[SMX_THREADS / 64];
     float *row = s + int64_t(blockIdx.x) * ld;
     constexpr float LOG2E = 1.4426950408889634f;
     if constexpr (NREG > 0) {
+        // 32-bit indices behind a scalar base per step: no address registers per element
+        const uint32_t tid = threadIdx.x, n = uint32_t(tokens);
         float x[NREG];
         float mx = -INFINITY;
 #pragma unroll
         for (int k = 0; k < NREG; ++k) {
-            const int64_t i = int64_t(k) * SMX_THREADS + threadIdx.x;
-            x[k] = i < tokens ? row[i] : -INFINITY;
-            mx = fmaxf(mx, x[k]);
+            const float *src = row + k * SMX_THREADS;
+            x[k] = tid + uint32_t(k) * SMX_THREADS < n ? src[tid] : -INFINITY;
         }
+#pragma unroll
+        for (int k = 0; k < NREG; ++k) mx = fmaxf(mx, x[k]);
         mx = finite_max(block_reduce(mx, true, lds));
         float sum = 0.0f;
 #pragma unroll
@@ -65,8 +70,8 @@ __global__ __launch_bounds__(SMX_THREADS) void softmax_kernel(float *__restrict_
         const float inv = safe_inverse(sum);
 #pragma unroll
         for (int k = 0; k < NREG; ++k) {
-            const int64_t i = int64_t(k) * SMX_THREADS + threadIdx.x;
-            if (i < tokens) row[i] = x[k] * inv;
+            float *dst = row + k * SMX_THREADS;
+            if (tid + uint32_t(k) * SMX_THREADS < n) dst[tid] = x[k] * inv;
         }
     } else {
         float mx = -INFINITY;
