@@ -434,8 +434,13 @@ __global__ __launch_bounds__(256) void attn8_kernel(AArgs a) {
 
 // Merges the splits of one (batch, query head) row in a fixed order and adds the raw fp16
 // tail tokens (Sec. III-B.1 buffer), whose scores are plain dot products.
+// FLAT: the rows lie as a flat plan wrote them.  A form of its own: reading the plan in front of the first
+// address cost every launch without one 0.2-0.3 us (whole fused attention, 1 x 32 streams of 4096 tokens, tail of
+// 0 / 24 / 62 tokens: 14.4 / 15.3 / 15.9 -> 14.1 / 15.0 / 15.6 us).  The reductions over the lanes below have a fixed
+// cost: walked element by element the same rows took 13.7 / 14.9 / 16.4, less where the tail is short.
+template <bool FLAT>
 __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restrict__ partial,
-                                                           int n_splits, FlatPlan plan,
+                                                           int n_splits, int n_rows, FlatPlan plan,
                                                            const __half *__restrict__ q,
                                                            const __half *__restrict__ k_tail,
                                                            const __half *__restrict__ v_tail,
@@ -451,22 +456,21 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
     // every global load of the kernel is issued before the first result is needed
     SplitRows rows;
     TailRows trows;
-    // the row sets of stream r / Gk are those of the workgroups that hold one of its blocks
     // the row sets of the row's stream: one per split, or with a flat plan (one head per kv-head: row =
     // stream) those of the workgroups that hold one of its blocks
-    int64_t first_row = r, row_stride = gridDim.x;
-    if (plan.n_groups > 0) {
+    int first_row = r, row_stride = n_rows;
+    if constexpr (FLAT) {
         const int w_lo = plan.group_of(int64_t(r) * plan.n_blocks);
         const int w_hi = plan.group_of(int64_t(r + 1) * plan.n_blocks - 1);
         n_splits = w_hi - w_lo + 1;
         first_row = w_lo + r;
         row_stride = 1;
     }
-    partial += first_row * V_PART_STRIDE;
+    partial += int64_t(first_row) * V_PART_STRIDE;
     rows.load_strided(partial, n_splits, row_stride);
     trows.load(v_tail + (int64_t(b) * tail_cap * H + h) * D, int64_t(H) * D, n_tail);
     if (int(threadIdx.x) < n_splits)
-        ms[threadIdx.x] = partial[int64_t(threadIdx.x) * row_stride * V_PART_STRIDE + A_M];
+        ms[threadIdx.x] = partial[(int64_t(threadIdx.x) * row_stride) * V_PART_STRIDE + A_M];
     // tail scores: thread (t, seg) takes 32 channels of tail token t, four threads per token
     {
         const int t = threadIdx.x >> 2, seg = threadIdx.x & 3;
@@ -523,6 +527,7 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
     const float sm_log2 = sm_scale * LOG2E;
     FlatPlan plan = FlatPlan::make(n_blocks, B, Hs);
     int n_splits = 0;
+    bool flat = false;
     if (n_blocks > 0) {
         AArgs a;
         a.k_arena = static_cast<const uint8_t *>(c->buf.k_arena);
@@ -556,7 +561,6 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         // shows (1 x 32 streams of 250 blocks: 21.7 / 23.5 us).  With more heads the sums of a second stream's
         // part do not fit the registers next to the loop (4 x 8 streams of 512, four heads: 46 -> 50 us), and
         // packs of 8 gain nothing (30.1 / 30.6 us, wide 35.3 / 35.2).
-        bool flat = false;
 #define PACKKV_LAUNCH_FLAT(...)                                                                        \
     {                                                                                                  \
         static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(__VA_ARGS__));    \
@@ -595,8 +599,8 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
 #undef PACKKV_LAUNCH_AH
 #undef PACKKV_LAUNCH_FLAT
     }
-    hipLaunchKernelGGL(attn_combine_kernel, dim3(B * H * Gq), dim3(256), 0, s, partial, n_splits,
-                       plan, q, static_cast<const __half *>(c->buf.k_tail),
+    hipLaunchKernelGGL(flat ? attn_combine_kernel<true> : attn_combine_kernel<false>, dim3(B * H * Gq), dim3(256), 0, s, partial,
+                       n_splits, B * H * Gq, plan, q, static_cast<const __half *>(c->buf.k_tail),
                        static_cast<const __half *>(c->buf.v_tail), c->tail_tokens,
                        c->cfg.tail_capacity, H, Gq, sm_log2, out);
     KV_HIP_CHECK(hipGetLastError());
