@@ -278,7 +278,7 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
                 float pt[G];
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
-                    pt[g] = __builtin_amdgcn_exp2f(s[g] - m_ref[g]);  // below 2^-126: 0, nothing next to the block's largest
+                    pt[g] = exp2f(s[g] - m_ref[g]);  // subnormals too: they are the output where larger weights meet values of 0
                     l_lane[g] += pt[g];
                 }
                 v_planes_chunk<G, HIGH>(lds_all, vbuf, vtable, vhighs, vb, vmt, pt, st);
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(256) void attn8_kernel(AArgs a) {
                 float pt[G];
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
-                    pt[g] = __builtin_amdgcn_exp2f(s[g] - m_ref[g]);  // below 2^-126: 0, nothing next to the block's largest
+                    pt[g] = exp2f(s[g] - m_ref[g]);  // subnormals too: they are the output where larger weights meet values of 0
                     l_lane[g] += pt[g];
                 }
                 if constexpr (VW)
