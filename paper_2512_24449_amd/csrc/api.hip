@@ -96,7 +96,7 @@ extern "C" int kv_query_sizes(const kv_config_t *cfg, double bits_per_element_bu
         round256(size_t(cfg->batch) * cfg->tail_capacity * cfg->n_kv_heads * D * 2);
     out->workspace = round256(WS_VPART + v_partial_bytes(cfg->batch, cfg->n_q_heads));
     if (cfg->pack_size == 16)  // staging area of the compressor behind the rest
-        out->workspace += round256(size_t(stage_chunks_for(cfg->batch, cfg->n_kv_heads)) * chunk_max_bytes(16));
+        out->workspace += round256(size_t(stage_chunks_for(cfg->batch, cfg->n_kv_heads, max_chunks)) * CHUNK_MAX);
     out->token_order = cfg->repack ? round256(size_t(cfg->batch) * max_tokens) : 0;
     out->k_pages = out->v_pages = 0;
     return KV_OK;
@@ -179,8 +179,19 @@ int create_cache(const kv_config_t *cfg, kv_page_pool *pool, const kv_buffers_t 
     if (sizes->k_index < need.k_index ||
         sizes->v_index < need.v_index || sizes->k_token_meta < need.k_token_meta ||
         sizes->v_token_meta < need.v_token_meta || sizes->k_tail < need.k_tail ||
-        sizes->v_tail < need.v_tail || sizes->workspace < need.workspace)
+        sizes->v_tail < need.v_tail)
         return KV_ERR_ARG;
+    // the staging area takes what the workspace has behind the rest
+    const int64_t max_tokens = (cfg->max_tokens + N - 1) / N * N;
+    const int64_t max_chunks = max_tokens / N * cfg->batch * cfg->n_kv_heads;
+    const size_t stage_offset = round256(WS_VPART + v_partial_bytes(cfg->batch, cfg->n_q_heads));
+    int stage_chunks = 0;
+    if (sizes->workspace < stage_offset) return KV_ERR_ARG;
+    if (cfg->pack_size == 16) {
+        const size_t slots = (sizes->workspace - stage_offset) / CHUNK_MAX;
+        if (slots < size_t(stage_chunks_for(cfg->batch, cfg->n_kv_heads, max_chunks, true))) return KV_ERR_ARG;
+        stage_chunks = int(std::min<size_t>(slots, stage_chunks_for(cfg->batch, cfg->n_kv_heads, max_chunks))) & ~1;
+    }
     if (cfg->repack && (!aligned256(buffers->token_order) || sizes->token_order < need.token_order))
         return KV_ERR_ARG;
     kv_cache *c = new (std::nothrow) kv_cache;
@@ -188,8 +199,8 @@ int create_cache(const kv_config_t *cfg, kv_page_pool *pool, const kv_buffers_t 
     c->cfg = *cfg;
     c->buf = *buffers;
     c->sizes = *sizes;
-    c->max_tokens = (cfg->max_tokens + N - 1) / N * N;
-    c->max_chunks = c->max_tokens / N * cfg->batch * cfg->n_kv_heads;
+    c->max_tokens = max_tokens;
+    c->max_chunks = max_chunks;
     c->head_split = head_split_for(cfg->n_q_heads / cfg->n_kv_heads, cfg->pack_size);
     c->group = cfg->n_q_heads / cfg->n_kv_heads / c->head_split;
     c->qmax_k = int(lround(1.0 / double(cfg->k_rel_scale)));
@@ -199,8 +210,8 @@ int create_cache(const kv_config_t *cfg, kv_page_pool *pool, const kv_buffers_t 
     c->packed_tokens = 0;
     c->tail_tokens = 0;
     c->fill_bound16[0] = c->fill_bound16[1] = 0;
-    c->stage_offset = round256(WS_VPART + v_partial_bytes(cfg->batch, cfg->n_q_heads));
-    c->stage_chunks = stage_chunks_for(cfg->batch, cfg->n_kv_heads);
+    c->stage_offset = stage_offset;
+    c->stage_chunks = stage_chunks;
     c->pool = pool;
     c->index_words = pool ? 2 : 1;
     c->max_pages_k = c->max_pages_v = 0;
