@@ -46,20 +46,32 @@ struct AArgs {
     float sm_log2;                    // sm_scale * log2(e)
 };
 
+// Reductions over the 64 lanes of a wave, the result in every lane: row swaps and DPP only (a shuffle goes
+// through LDS and costs some 100 cycles of latency where the next step waits for it).
 __device__ inline float wave_all_max(float v) {
+    uint32_t a = __float_as_uint(v), b = a;
+    swap_rows32(a, b);
+    v = fmaxf(__uint_as_float(a), __uint_as_float(b));
+    a = b = __float_as_uint(v);
+    swap_rows16(a, b);
+    v = fmaxf(__uint_as_float(a), __uint_as_float(b));
     v = fmaxf(v, dpp_f32<DPP_ROW_ROR8>(v));
-    v = fmaxf(v, __shfl_xor(v, 4));
+    v = fmaxf(v, dpp_f32<DPP_ROW_ROR4>(v));
     v = fmaxf(v, dpp_f32<DPP_QUAD_XOR2>(v));
-    v = fmaxf(v, dpp_f32<DPP_QUAD_XOR1>(v));
-    v = fmaxf(v, __shfl_xor(v, 16));
-    v = fmaxf(v, __shfl_xor(v, 32));
-    return v;
+    return fmaxf(v, dpp_f32<DPP_QUAD_XOR1>(v));
 }
 
 __device__ inline float wave_all_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    uint32_t a = __float_as_uint(v), b = a;
+    swap_rows32(a, b);
+    v = __uint_as_float(a) + __uint_as_float(b);
+    a = b = __float_as_uint(v);
+    swap_rows16(a, b);
+    v = __uint_as_float(a) + __uint_as_float(b);
+    v += dpp_f32<DPP_ROW_ROR8>(v);
+    v += dpp_f32<DPP_ROW_ROR4>(v);
+    v += dpp_f32<DPP_QUAD_XOR2>(v);
+    return v + dpp_f32<DPP_QUAD_XOR1>(v);
 }
 
 // 2^(a - b) with the convention that an empty side (a = -inf) weighs nothing.
@@ -132,8 +144,8 @@ __device__ inline void attn_store_state(const VPlaneState<G> &st, float (*red)[D
 }
 
 // End of a workgroup's part of a stream: merges the four waves' running sums (each with its own
-// softmax reference) and writes the partial rows.  red aliases the chunk buffers, which are free again
-// on return.
+// softmax reference) and writes the partial rows.  red aliases the chunk buffers (a caller that fills them
+// again passes a barrier first).
 template <int G, class State>
 __device__ inline void attn_store_partial(const AArgs &a, const State &st, const float (&l_lane)[G],
                                           const float (&m_ref)[G], float (*red)[G][D + 4], int wave,
@@ -167,7 +179,6 @@ __device__ inline void attn_store_partial(const AArgs &a, const State &st, const
             dst[A_M] = M;
         }
     }
-    __syncthreads();  // red[][][] has been read: the buffers may be filled again
 }
 
 // HIGH: the V codes of the cache may need four bits (a plane H exists).  The blocks of all streams form
@@ -288,6 +299,7 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
             start_batch(first + 4 * 64);
         }
         attn_store_partial<G>(a, st, l_lane, m_ref, red, wave, lane, row_set);
+        if constexpr (FLAT) __syncthreads();  // red[][][] has been read: the buffers may be filled again
     }
 }
 
@@ -435,9 +447,11 @@ __global__ __launch_bounds__(256) void attn8_kernel(AArgs a) {
 // Merges the splits of one (batch, query head) row in a fixed order and adds the raw fp16
 // tail tokens (Sec. III-B.1 buffer), whose scores are plain dot products.
 // FLAT: the rows lie as a flat plan wrote them.  A form of its own: reading the plan in front of the first
-// address cost every launch without one 0.2-0.3 us (whole fused attention, 1 x 32 streams of 4096 tokens, tail of
-// 0 / 24 / 62 tokens: 14.4 / 15.3 / 15.9 -> 14.1 / 15.0 / 15.6 us).  The reductions over the lanes below have a fixed
-// cost: walked element by element the same rows took 13.7 / 14.9 / 16.4, less where the tail is short.
+// address cost every launch without one 0.2-0.3 us.
+// Bound by its chain of latencies.  Whole fused attention, 1 x 32 streams of 4096 tokens and a tail of 0 / 8 / 24 /
+// 62 tokens, replayed: references and weight sums walked element by element from LDS 13.3 / 14.4 / 14.6 / 16.5 us,
+// across the lanes with shuffles 13.6 / 14.7 / 14.5 / 15.6, with row swaps and DPP, a barrier less and the
+// tail's weight sum at the end 13.2 / 14.4 / 14.2 / 15.3.
 template <bool FLAT>
 __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restrict__ partial,
                                                            int n_splits, int n_rows, FlatPlan plan,
@@ -446,8 +460,8 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
                                                            const __half *__restrict__ v_tail,
                                                            int n_tail, int tail_cap, int H, int G,
                                                            float sm_log2, float *__restrict__ out) {
-    __shared__ float st[N];             // tail scores (log2 units), then tail weights
-    __shared__ float ms[V_SPLITS_MAX];  // split references, then split factors
+    __shared__ float st[N], tw[N];                        // tail scores (log2 units), tail weights
+    __shared__ float ms[V_SPLITS_MAX], mf[V_SPLITS_MAX];  // split references, split factors
     __shared__ float red[16][V_PART_STRIDE];
     static_assert(A_L == 128, "the splits' weight sums sit in the column the reduction returns separately");
     const int r = blockIdx.x;           // b*Hq + hq
@@ -493,23 +507,21 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
         if (seg == 0 && t < n_tail) st[t] = sm_log2 * s;
     }
     __syncthreads();
-    // at most 64 splits and 64 tail tokens: one of each per lane; every wave finds the row's reference and the
-    // tail's weight sum by itself (element after element from LDS they took 3 us with 62 tail tokens)
+    // at most 64 splits and 64 tail tokens: one of each per lane; every wave finds the row's reference by itself
+    // (element after element from LDS reference and weight sum took 3 us with 62 tail tokens)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float my_split = lane < n_splits ? ms[lane] : -INFINITY, my_tail = lane < n_tail ? st[lane] : -INFINITY;
     const float M = wave_all_max(fmaxf(my_split, my_tail));
     const float tail_weight = lane < n_tail ? exp2f(my_tail - M) : 0.0f;
-    const float tail_sum = wave_all_sum(tail_weight);
-    __syncthreads();
-    if (wave == 0 && lane < n_splits) ms[lane] = exp2_diff(my_split, M);
-    if (wave == 1 && lane < n_tail) st[lane] = tail_weight;
+    if (wave == 0 && lane < n_splits) mf[lane] = exp2_diff(my_split, M);
+    if (wave == 1 && lane < n_tail) tw[lane] = tail_weight;
     __syncthreads();
     // weighted sum of the split rows (column 128 = the splits' weight sums), then the tail tokens
     float l;
-    float o = rows.sum(n_splits, red, &l, ms);
+    float o = rows.sum(n_splits, red, &l, mf);
     if (n_tail > 0) {
-        o += trows.sum(st, n_tail, red);
-        l += tail_sum;
+        o += trows.sum(tw, n_tail, red);
+        l += wave_all_sum(tail_weight);
     }
     const int d = threadIdx.x;
     if (d < D) out[int64_t(r) * D + d] = l > 0.0f ? o / l : 0.0f;  // every block dropped and no tail: defined output

@@ -318,20 +318,6 @@ __global__ __launch_bounds__(256) void chunk_kernel(PackArgs a) {
 // on the way; the waves meet once for the byte counts of their packs and once when the chunk's
 // bytes are complete in LDS.
 
-// Rows of 16 lanes: of x keep the even rows and take the odd rows from x's odd rows into y's even
-// rows' place and the other way round (odd rows of x <-> even rows of y).
-__device__ inline void swap_rows16(uint32_t &x, uint32_t &y) {
-    const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
-    x = r[0];
-    y = r[1];
-}
-// The upper 32 lanes of x <-> the lower 32 lanes of y.
-__device__ inline void swap_rows32(uint32_t &x, uint32_t &y) {
-    const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
-    x = r[0];
-    y = r[1];
-}
-
 struct PlaneBits {
     uint32_t low, high, top;  // top: in the low 16 bits
     int w, m;

@@ -45,6 +45,20 @@ __device__ inline int dpp_shift0(int v) {
     return __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xF, true);
 }
 
+// Rows of 16 lanes: of x keep the even rows and take the odd rows from x's odd rows into y's even
+// rows' place and the other way round (odd rows of x <-> even rows of y).
+__device__ inline void swap_rows16(uint32_t &x, uint32_t &y) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    x = r[0];
+    y = r[1];
+}
+// The upper 32 lanes of x <-> the lower 32 lanes of y.
+__device__ inline void swap_rows32(uint32_t &x, uint32_t &y) {
+    const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+    x = r[0];
+    y = r[1];
+}
+
 // Inclusive prefix sum over the 64 lanes of a wave (six DPP adds).
 __device__ inline int wave_inclusive_scan(int v) {
     v += dpp_shift0<DPP_ROW_SHR1, 0xF>(v);
