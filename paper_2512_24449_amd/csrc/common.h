@@ -7,6 +7,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "flat_plan.h"
 #include "packkv.h"
 
 namespace packkv {
@@ -55,79 +56,8 @@ inline int64_t target_workgroups(int64_t total_blocks) {
     return w < 512 ? 512 : (w > 4096 ? 4096 : w);
 }
 
-// Work list of the kernels that walk chunks in the plane layout: the chunks of all streams in one
-// sequence (stream-major, n_blocks per stream), cut into n_groups equal ranges, one per workgroup.
-// A workgroup that crosses a stream boundary writes one partial row set per stream it touches:
-// the set of workgroup w for stream s has number w + s (unique, below n_groups + streams).
-// All divisions are multiplications by numbers the host has prepared: a 64-bit division is some 130
-// instructions, and a workgroup needs several before its first load (1 to 2 us at the
-// start of every workgroup).
-struct Divisor {
-    uint64_t d = 1, m = 0;  // m = floor(2^64 / d) + 1; 0 for d = 1
-    static Divisor of(uint64_t d) {
-        Divisor r;
-        r.d = d;
-        r.m = d > 1 ? ~uint64_t(0) / d + 1 : 0;
-        return r;
-    }
-    // x / d for x * d < 2^64 (m * d exceeds 2^64 by at most d; ~0 / d is floor(2^64 / d) but for
-    // powers of two, where m is exactly 2^64 / d)
-    __device__ inline uint64_t divide(uint64_t x) const { return m ? __umul64hi(x, m) : x; }
-};
-struct FlatPlan {
-    int n_blocks;    // packed blocks per stream
-    int n_groups;    // workgroups
-    int64_t total;   // streams * n_blocks
-    Divisor by_groups, by_blocks, by_heads, by_total;  // by_total: m = 0 if the products below do not fit it
-
-    // streams = batch * heads.  n_groups may be set later, by split().
-    static FlatPlan make(int n_blocks, int batch, int heads) {
-        FlatPlan p;
-        p.n_blocks = n_blocks;
-        p.n_groups = 0;
-        p.total = int64_t(n_blocks) * batch * heads;
-        p.by_blocks = Divisor::of(uint64_t(n_blocks > 0 ? n_blocks : 1));
-        p.by_heads = Divisor::of(uint64_t(heads));
-        return p;
-    }
-    void split(int groups) {
-        n_groups = groups;
-        by_groups = Divisor::of(uint64_t(groups));
-        by_total = Divisor::of(uint64_t(total));
-        if (double(total) * double(total) * groups >= 1e19) by_total.m = 0;
-    }
-    // The longer ranges are spread evenly, so that ranges end at stream boundaries wherever the
-    // numbers allow it (a workgroup with parts of two streams pays its start-up and its end twice:
-    // 25 -> 30 us for the V product of 8 streams of 2048 blocks).
-    __device__ inline int64_t begin(int w) const { return int64_t(by_groups.divide(uint64_t(w) * uint64_t(total))); }
-    // workgroup that holds flattened chunk f (for the largest plans an estimate, off by one at most, put right)
-    __device__ inline int group_of(int64_t f) const {
-        if (by_total.m) return int(by_total.divide(uint64_t((f + 1) * n_groups - 1)));
-        int w = int(double(f) * n_groups / double(total));
-        w = w < n_groups ? w : n_groups - 1;
-        while (begin(w) > f) --w;
-        while (begin(w + 1) <= f) ++w;
-        return w;
-    }
-    // The part of one stream at the head of the range [f, range_end).
-    struct Segment {
-        int stream, b, h, blk_begin, blk_end;
-    };
-    __device__ inline Segment segment(int64_t f, int64_t range_end) const {
-        Segment g;
-        // (scalar from here on: everything the loops derive from them stays in scalar registers)
-        g.stream = __builtin_amdgcn_readfirstlane(int(by_blocks.divide(uint64_t(f))));
-        g.b = __builtin_amdgcn_readfirstlane(int(by_heads.divide(uint64_t(g.stream))));
-        g.h = g.stream - g.b * int(by_heads.d);
-        g.blk_begin = int(f - int64_t(g.stream) * n_blocks);
-        const int64_t left = g.blk_begin + (range_end - f);
-        g.blk_end = left < n_blocks ? int(left) : n_blocks;
-        return g;
-    }
-};
-
-// Workgroups of 256 threads of `kernel` that fit one compute unit; workgroups for a flat work
-// list of `total` chunks, at most `most` (v_matvec.hip).
+// Workgroups of 256 threads of `kernel` that fit one compute unit; flat_groups and plan_groups with the room
+// of this GPU, `per_cu` workgroups to a compute unit (v_matvec.hip).
 int resident_workgroups(const void *kernel);
 int flat_groups_for(int64_t total, int per_cu, int64_t most);
 int plan_groups_for(int n_blocks, int streams, int per_cu, int64_t most);

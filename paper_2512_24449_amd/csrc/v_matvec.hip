@@ -326,9 +326,7 @@ int resident_workgroups(const void *kernel) {
     return n;
 }
 
-// Workgroups for the flat work list of `total` chunks: one round of resident workgroups (per_cu
-// of them fit a compute unit), never less than one block per wave, at most `most`.
-int flat_groups_for(int64_t total, int per_cu, int64_t most) {
+static int64_t resident_room(int per_cu) {
     static int n_cu = 0;
     if (n_cu == 0) {
         int dev = 0, v = 0;
@@ -338,36 +336,11 @@ int flat_groups_for(int64_t total, int per_cu, int64_t most) {
         else
             n_cu = 256;
     }
-    int64_t w = int64_t(n_cu) * per_cu;
-    w = std::min<int64_t>(w, (total + 3) / 4);
-    w = std::min<int64_t>(w, most);
-    return int(std::max<int64_t>(w, 1));
+    return int64_t(n_cu) * per_cu;
 }
-
-// Workgroups for a flat plan over `streams` streams of n_blocks chunks, at most `most`.  Either one round
-// of resident workgroups that cut the list as it comes, or a whole number of workgroups per
-// stream: then none has parts of two streams, each of which costs its start-up (query, index, first
-// chunk) and its end (merge, store) -- about the time of PART_COST chunks of a wave.  The cheaper one by the
-// chunks its longest wave walks: 256 streams of 7 blocks run as 512 workgroups of one stream each (fused
-// attention 21 us; 448 that cross the boundaries 29 us), 416 streams of 500 blocks as one round of 768.
+int flat_groups_for(int64_t total, int per_cu, int64_t most) { return int(flat_groups(total, resident_room(per_cu), most)); }
 int plan_groups_for(int n_blocks, int streams, int per_cu, int64_t most) {
-    constexpr int64_t PART_COST = 2;
-    const int64_t total = int64_t(n_blocks) * streams;
-    const int64_t room = flat_groups_for(int64_t(1) << 40, per_cu, int64_t(1) << 30);
-    auto waves = [](int64_t blocks) { return (blocks + 3) / 4; };
-    const int64_t flat = flat_groups_for(total, per_cu, most);
-    int64_t best = flat;
-    int64_t best_cost = waves((total + flat - 1) / flat) * 4 + 4 * PART_COST * (flat + streams - 1) / flat;
-    const int64_t most_per_stream = std::max<int64_t>(1, std::min<int64_t>(waves(n_blocks), most / streams));
-    for (int64_t want : {int64_t(1), room / streams, most_per_stream}) {
-        const int64_t per_stream = std::max<int64_t>(1, std::min<int64_t>(want, most_per_stream));
-        const int64_t groups = per_stream * streams;
-        if (groups > most) continue;
-        const int64_t rounds = (groups + room - 1) / room;
-        const int64_t cost = 4 * rounds * (waves((n_blocks + per_stream - 1) / per_stream) + PART_COST);
-        if (cost < best_cost || (cost == best_cost && best == flat)) best = groups, best_cost = cost;
-    }
-    return int(best);
+    return plan_groups(n_blocks, streams, resident_room(per_cu), most);
 }
 
 // partial: [row sets][V_PART_STRIDE] floats for the split sums; max_split_rows: how many rows
