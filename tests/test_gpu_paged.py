@@ -280,3 +280,105 @@ def test_smallest_chunks_fill_pages_exactly():
     assert_close_vectors(attn.cpu().numpy(), np.zeros((B, Hq, 128)) + V.numpy()[0, 0, 0, 0], "attention over constant V")
     cache.close()
     pool.close()
+
+
+# Calls of more than 8192 chunks per tensor take the placement kernel that works through memory, one tensor after the
+# other; smaller ones the kernel that keeps both tensors in LDS.  416 chunks to a block of tokens.
+MANY_B, MANY_H = 8, 52
+
+
+def _sizes16(B, H, K, V, pack):
+    """Chunk sizes of one call, from the index of a contiguous cache (its bytes are pinned to the oracle elsewhere)."""
+    flat = binding.PackedKVCache(B, H, H, K.shape[1], pack_size=pack)
+    flat.kv_compress_append(K, V)
+    n = K.shape[1] // 64 * B * H
+    out = []
+    for name in ("k", "v"):
+        w = flat.view(name + "_index", torch.int32)[:n + 1].cpu().numpy().view(np.uint32).astype(np.int64)
+        out.append(np.diff(w).tolist())
+    assert flat.kv_cache_stats().overflow == 0
+    flat.close()
+    return out
+
+
+def _device_kv(B, blocks, H, seed, constant):
+    if constant:   # header-only chunks: 128 of them (64 with packs of 8) to a page, the most there can be
+        K = torch.full((B, 64 * blocks, H, 128), 0.5, dtype=torch.float16, device="cuda:0")
+        return K, torch.zeros_like(K)
+    K, V, _ = synth.make_kv(B, 64 * blocks, H, H, seed, device="cuda:0")
+    K[:, :, : H // 3] *= 0.01   # a third of the heads with narrow codes: chunk sizes that differ
+    return K, V
+
+
+def _append_and_place(cache, model, tensors, expected, K, V, pack):
+    """One append, and where the rule puts its chunks; -> which tensors it dropped."""
+    B, L, H, _ = K.shape
+    cache.kv_compress_append(K, V)
+    dropped = []
+    for t, sizes in enumerate(_sizes16(B, H, K, V, pack)):
+        placed = model.place(tensors[t], sizes)
+        dropped.append(placed is None)
+        expected[t].extend(placed if placed is not None else [(0, 0)] * len(sizes))
+    return dropped
+
+
+def _check_placement(cache, model, tensors, expected):
+    torch.cuda.synchronize()
+    for t, name in enumerate(("k", "v")):
+        got = _chunk_pairs(cache, name, len(expected[t]))
+        bad = [i for i in range(len(got)) if got[i] != expected[t][i]]
+        assert not bad, "%s: %d chunks misplaced, first %d: %s vs %s" % (name, len(bad), bad[0], got[bad[0]], expected[t][bad[0]])
+        pages, fill = _page_list(cache, name)
+        # no page yet: the kernel's fill level is not looked at
+        assert pages == tensors[t]["pages"] and (fill == tensors[t]["fill"] or not pages), name
+    assert cache.pool.kv_page_pool_free_pages() == len(model.free)
+
+
+# 20 blocks: 8320 chunks; 79: 32864, the two tensors in calls of their own; 1 and 19: the small kernel in between
+@pytest.mark.parametrize("calls,pack,constant", [([20, 1, 21], 16, False), ([1, 79, 19, 20], 16, False), ([20, 1], 8, False),
+                                                 ([19, 20, 3], 16, True), ([20], 8, True)])
+def test_placement_of_calls_with_many_chunks(calls, pack, constant):
+    B, H = MANY_B, MANY_H
+    n_pages = 2 * sum(calls) * B * H // (12 if pack == 8 else 14) + 8
+    pool, model = binding.PagePool(n_pages), gpu_cases.PagePlacementModel(n_pages)
+    cache = binding.PackedKVCache(B, H, H, 64 * sum(calls), pool=pool, pack_size=pack)
+    tensors, expected = (model.new_tensor(), model.new_tensor()), ([], [])
+    for i, blocks in enumerate(calls):
+        K, V = _device_kv(B, blocks, H, 50 + i, constant)
+        assert _append_and_place(cache, model, tensors, expected, K, V, pack) == [False, False]
+    assert cache.kv_cache_stats().overflow == 0
+    _check_placement(cache, model, tensors, expected)
+    cache.close()
+    pool.close()
+
+
+@pytest.mark.parametrize("blocks", [20, 79])
+@pytest.mark.parametrize("short_of", ["both", "k", "v"])
+def test_exhausted_pool_in_a_call_with_many_chunks(blocks, short_of):
+    """A pool that lacks a page for K, for V, or for either: that tensor's chunks of the call are dropped, the other's are
+    placed, and a later call that fits goes where the rule says."""
+    B, H = MANY_B, MANY_H
+    first, second = _device_kv(B, 1, H, 60, False), _device_kv(B, blocks, H, 61, False)
+    dry = gpu_cases.PagePlacementModel(1 << 19)
+    t = (dry.new_tensor(), dry.new_tensor())
+    need = []
+    for K, V in (first, second):
+        for i, sizes in enumerate(_sizes16(B, H, K, V, 16)):
+            assert dry.place(t[i], sizes) is not None
+            need.append(len(t[i]["pages"]))
+    k1, v1, k2, v2 = need[0], need[1], need[2] - need[0], need[3] - need[1]
+    spare = {"both": min(k2, v2) - 1, "k": k2 - 1, "v": k2 + v2 - 1}[short_of]
+    assert v2 < k2, "codes of K are wider: V still fits where K does not"
+    n_pages = k1 + v1 + spare
+    pool, model = binding.PagePool(n_pages), gpu_cases.PagePlacementModel(n_pages)
+    cache = binding.PackedKVCache(B, H, H, 64 * (blocks + 2), pool=pool)
+    tensors, expected = (model.new_tensor(), model.new_tensor()), ([], [])
+    assert _append_and_place(cache, model, tensors, expected, *first, 16) == [False, False]
+    dropped = _append_and_place(cache, model, tensors, expected, *second, 16)
+    assert dropped == {"both": [True, True], "k": [True, False], "v": [False, True]}[short_of]
+    _append_and_place(cache, model, tensors, expected, *first, 16)
+    assert cache.kv_cache_stats().overflow == 1
+    _check_placement(cache, model, tensors, expected)
+    cache.close()
+    assert pool.kv_page_pool_free_pages() == n_pages
+    pool.close()
