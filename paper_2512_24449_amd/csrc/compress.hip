@@ -41,14 +41,27 @@ __device__ inline uint4 as_fp16(uint4 raw, bool bf16) {
     }
     return raw;
 }
-// (The input is read once per kernel and is larger than the caches: the non-temporal hint keeps it
-// from pushing out what is read again, the staged chunks for one.)
+// A round whose input is larger than the last-level cache (256 MB; both tensors): its kernels read with the non-
+// temporal hint (STREAM), which keeps the input from pushing out what is read again, the staged chunks for one. The
+// input of a smaller round is still in the caches when its second and third kernel read it, which the hint would
+// not make use of.  Without / with the hint: packs of 8, 67 MB 80 / 84 us, 262 MB 243 / 265, 393 MB 389 / 381, 1.7 GB
+// 1648 / 1618; packs of 16, 67 MB 42.8 / 43.8 (repacked 61.5 / 64), 262 MB 165 / 165, 393 MB 244 / 241, a block of
+// 416 streams 18.1 / 18.9.
+inline bool larger_than_caches(int64_t n_chunks) { return n_chunks * 2 * (N * D * 2) > (int64_t(256) << 20); }
+
 __device__ inline uint4 load8_nt(const __half *p) {
     typedef uint32_t u32x4n __attribute__((ext_vector_type(4)));
     const u32x4n v = __builtin_nontemporal_load(reinterpret_cast<const u32x4n *>(p));
     return make_uint4(v.x, v.y, v.z, v.w);
 }
-__device__ inline uint4 load8_as_fp16(const __half *p, bool bf16) { return as_fp16(load8_nt(p), bf16); }
+template <bool STREAM>
+__device__ inline uint4 load8(const __half *p) {
+    return STREAM ? load8_nt(p) : *reinterpret_cast<const uint4 *>(p);
+}
+template <bool STREAM>
+__device__ inline uint4 load8_as_fp16(const __half *p, bool bf16) {
+    return as_fp16(load8<STREAM>(p), bf16);
+}
 
 // A token's metadata word from its smallest and largest value: fp16 scale | fp16 minimum << 16.
 __device__ inline uint32_t token_meta_word(float mn, float mx, float rel) {
@@ -81,7 +94,7 @@ struct ParamArgs {
 
 // A workgroup per token, or (WAVE: rows of up to 2048 values, which would leave lanes of a workgroup
 // idle) a wave per token, four tokens to a workgroup.
-template <bool WAVE>
+template <bool WAVE, bool STREAM>
 __global__ __launch_bounds__(256) void token_params_kernel(ParamArgs a, int n_tokens) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int t = WAVE ? blockIdx.x * 4 + wave : blockIdx.x, b = blockIdx.y;
@@ -91,7 +104,7 @@ __global__ __launch_bounds__(256) void token_params_kernel(ParamArgs a, int n_to
     float mn = INFINITY, mx = -INFINITY;
     constexpr int STEP = (WAVE ? 64 : 256) * 8;
     for (int i = (WAVE ? lane : int(threadIdx.x)) * 8; i < a.row_elems; i += STEP) {
-        uint4 raw = load8_as_fp16(row + i, a.bf16);
+        uint4 raw = load8_as_fp16<STREAM>(row + i, a.bf16);
         const __half *h = reinterpret_cast<const __half *>(&raw);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -235,7 +248,7 @@ struct PackArgs {
 // kernel below): the chunk has 64/PK token groups of 128 packs, thread tau owns packs tau + 256k
 // (token group (tau >> 7) + 2k, channel tau & 127).  A pack takes PK*w/8 payload bytes.  WIDE (codes above 15, packs of 8): the
 // header is a width byte per pack followed by a minimum byte per pack, widths go up to 8.
-template <bool WRITE, int PK, bool WIDE = false>
+template <bool WRITE, int PK, bool WIDE, bool STREAM>
 __global__ __launch_bounds__(256) void chunk_kernel(PackArgs a) {
     static_assert(PK == 8, "contiguous packs are packs of 8 tokens");
     constexpr int NPACKS = N / PK * D;
@@ -270,7 +283,7 @@ __global__ __launch_bounds__(256) void chunk_kernel(PackArgs a) {
         for (int pass = 0; pass < 4; ++pass) {
             const int row = pass * 16 + (tau >> 4), c8 = (tau & 15) * 8;
             const int src_row = ord ? ord[row] : row;
-            *reinterpret_cast<uint4 *>(tile + row * D + c8) = load8_as_fp16(x_blk + src_row * cs.token_stride + c8, cs.bf16);
+            *reinterpret_cast<uint4 *>(tile + row * D + c8) = load8_as_fp16<STREAM>(x_blk + src_row * cs.token_stride + c8, cs.bf16);
         }
     }
     __syncthreads();
@@ -420,8 +433,7 @@ __device__ inline ChunkInput load_chunk_input(const ChunkSource &cs, int cl, con
     ChunkInput in;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        in.raw[i] = STREAM ? load8_nt(x_blk + rows.src_row[i] * cs.token_stride)
-                           : *reinterpret_cast<const uint4 *>(x_blk + rows.src_row[i] * cs.token_stride);  // converted where it is used
+        in.raw[i] = load8<STREAM>(x_blk + rows.src_row[i] * cs.token_stride);  // converted where it is used
     in.mt = meta_blk[16 * (threadIdx.x >> 6) + cg];
     return in;
 }
@@ -642,8 +654,8 @@ __device__ inline void copy_image(const ChunkLds &lds, int slot, int n16, uint8_
 }
 
 // Staged path, packs of 16: the input is quantized once.
-//   stage     one workgroup per chunk: quantize, build the chunk's bytes in LDS, store them in a
-//             slot of CHUNK_MAX bytes of the staging area in the workspace, and the chunk's size
+//   stage     resident workgroups, a chunk at a time each: quantize, build the chunk's bytes in LDS, store them
+//             in a slot of CHUNK_MAX bytes of the staging area in the workspace, and the chunk's size
 //   compact   one wave per chunk: copy the staged bytes to their place in the arena
 // A chunk's place depends on the sizes of all chunks before it, so some second step is needed;
 // this one re-reads the compressed bytes (a fraction of the input, and still in the last-level
@@ -683,9 +695,7 @@ __global__ __launch_bounds__(256) void chunk16_kernel(PackArgs a) {
 // takes 55, the same loads and stores without it 58, the loads alone 43.  377 vector instructions per wave
 // and chunk (500 with a code tile in LDS, a subtraction, a product and a tie test per value).  A
 // workgroup takes every gridDim.x-th item and has the loads of its next one in flight while it
-// works on the current one.  STREAM: the round's input is larger than the caches (last-level cache
-// 256 MB): read with the non-temporal hint, 3.56 -> 3.47 ms for a prompt of 6.8 GB; a smaller
-// input is still there from the token parameter pass, which the hint would not make use of (67 MB: 51 -> 54 us).
+// works on the current one.  (The hint of STREAM here: 3.56 -> 3.47 ms for a prompt of 6.8 GB, 51 -> 54 us for 67 MB.)
 template <bool STREAM>
 __global__ __launch_bounds__(256) void chunk16_stage_kernel(PackArgs a) {
     const int lo = staged_round(a.t[0].round, a.t[0].index) ? 0 : a.n;
@@ -1219,7 +1229,7 @@ __global__ void tail_copy_kernel(const uint4 *__restrict__ ksrc, const uint4 *__
     for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n16;
          i += int64_t(gridDim.x) * blockDim.x)
         dst[b * dst_batch_stride16 + i] =
-            load8_as_fp16(reinterpret_cast<const __half *>(src + b * src_batch_stride16 + i), bf16);
+            load8_as_fp16<true>(reinterpret_cast<const __half *>(src + b * src_batch_stride16 + i), bf16);
 }
 
 __global__ void init_kernel(uint32_t *status, uint32_t *k_index, uint32_t *v_index, uint32_t *k_pages,
@@ -1236,6 +1246,7 @@ __global__ void init_kernel(uint32_t *status, uint32_t *k_index, uint32_t *v_ind
 // rule and counts every code with ballots; the lower median is the first code whose running count
 // passes the middle.  (A workgroup per token with per-thread counters and 1e-3 wide guards, which
 // sent most waves to the divide: 28.6 us for 12032 tokens of 1024 values.)
+template <bool STREAM>
 __global__ __launch_bounds__(256) void v_median16_key_kernel(const __half *__restrict__ src, int64_t batch_stride,
                                                              int64_t token_stride, int row_elems, int qmax,
                                                              const uint32_t *__restrict__ meta, int64_t meta_stride,
@@ -1250,7 +1261,7 @@ __global__ __launch_bounds__(256) void v_median16_key_kernel(const __half *__res
     for (int v = 0; v < 16; ++v) count[v] = 0;
     for (int i = 0; i < row_elems; i += 512) {
         uint32_t pair[4] = {0, 0, 0, 0};  // no code where the row has ended
-        if (i + 8 * lane < row_elems) quantize_token8(load8_as_fp16(row + i + 8 * lane, bf16), tq, uint32_t(qmax), pair);
+        if (i + 8 * lane < row_elems) quantize_token8(load8_as_fp16<STREAM>(row + i + 8 * lane, bf16), tq, uint32_t(qmax), pair);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             if (v < qmax) {  // the last code's count is what is left
@@ -1276,6 +1287,7 @@ __global__ __launch_bounds__(256) void v_median16_key_kernel(const __half *__res
 
 // V-median repacking, step 1 (Sec. III-B.3): the lower median of the H*128 quantized V codes of
 // one token, written as a sort key.  One workgroup per (token, batch).
+template <bool STREAM>
 __global__ __launch_bounds__(256) void v_median_key_kernel(const __half *__restrict__ src,
                                                            int64_t batch_stride, int64_t token_stride,
                                                            int row_elems, int qmax,
@@ -1291,7 +1303,7 @@ __global__ __launch_bounds__(256) void v_median_key_kernel(const __half *__restr
     if (qmax > 15) {
         // codes up to 255: count straight into the LDS histogram
         for (int i = threadIdx.x * 8; i < row_elems; i += 256 * 8) {
-            uint4 raw = load8_as_fp16(row + i, bf16);
+            uint4 raw = load8_as_fp16<STREAM>(row + i, bf16);
             const __half *hv = reinterpret_cast<const __half *>(&raw);
 #pragma unroll
             for (int k = 0; k < 8; ++k) atomicAdd(&hist[quantize_value(__half2float(hv[k]), tsm.x, tsm.y, tsm.z, qmax)], 1);
@@ -1300,7 +1312,7 @@ __global__ __launch_bounds__(256) void v_median_key_kernel(const __half *__restr
         // sixteen 8-bit counters in two words; a thread sees at most 8 * ceil(row_elems / 2048) values
         uint64_t lo = 0, hi = 0;
         for (int i = threadIdx.x * 8; i < row_elems; i += 256 * 8) {
-            uint4 raw = load8_as_fp16(row + i, bf16);
+            uint4 raw = load8_as_fp16<STREAM>(row + i, bf16);
             const __half *hv = reinterpret_cast<const __half *>(&raw);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
@@ -1411,10 +1423,10 @@ int launch_token_params(const kv_cache *c, const CompressJob &kjob, const Compre
     a.first_token = kjob.first_token;
     a.row_elems = H * D;
     a.bf16 = kjob.bf16;
-    if (a.row_elems <= 2048)
-        hipLaunchKernelGGL(token_params_kernel<true>, dim3((n_tokens + 3) / 4, B, 2), dim3(256), 0, s, a, n_tokens);
-    else
-        hipLaunchKernelGGL(token_params_kernel<false>, dim3(n_tokens, B, 2), dim3(256), 0, s, a, n_tokens);
+    const bool wave = a.row_elems <= 2048, stream = larger_than_caches(int64_t(kjob.n_blocks) * B * H);
+    auto kernel = wave ? (stream ? token_params_kernel<true, true> : token_params_kernel<true, false>)
+                       : (stream ? token_params_kernel<false, true> : token_params_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, dim3(wave ? (n_tokens + 3) / 4 : n_tokens, B, 2), dim3(256), 0, s, a, n_tokens);
     KV_HIP_CHECK(hipGetLastError());
     return KV_OK;
 }
@@ -1424,18 +1436,24 @@ int launch_v_median_order(const kv_cache *c, const CompressJob &vjob, uint32_t *
     const int B = c->cfg.batch, H = c->cfg.n_kv_heads;
     const int n_tokens = vjob.n_blocks * N;
     if (n_tokens <= 0 || H * D / 2048 + 1 > 31) return KV_ERR_ARG;  // 8-bit per-thread counters
+    const bool stream = larger_than_caches(int64_t(vjob.n_blocks) * B * H);
     if (vjob.qmax < 16 && c->cfg.pack_size == 16)
-        hipLaunchKernelGGL(v_median16_key_kernel, dim3((n_tokens + 3) / 4, B), dim3(256), 0, s, vjob.src, vjob.batch_stride,
+        hipLaunchKernelGGL(stream ? v_median16_key_kernel<true> : v_median16_key_kernel<false>, dim3((n_tokens + 3) / 4, B), dim3(256), 0, s, vjob.src, vjob.batch_stride,
                            vjob.token_stride, H * D, vjob.qmax, vjob.meta, c->max_tokens, vjob.first_token, n_tokens, order,
                            vjob.bf16);
     else
-        hipLaunchKernelGGL(v_median_key_kernel, dim3(n_tokens, B), dim3(256), 0, s, vjob.src,
+        hipLaunchKernelGGL(stream ? v_median_key_kernel<true> : v_median_key_kernel<false>, dim3(n_tokens, B), dim3(256), 0, s, vjob.src,
                            vjob.batch_stride, vjob.token_stride, H * D, vjob.qmax, vjob.meta,
                            c->max_tokens, vjob.first_token, order, vjob.bf16);
     hipLaunchKernelGGL(block_order_kernel, dim3(vjob.n_blocks, B), dim3(64), 0, s, order, vjob.qmax,
                        k_meta, vjob.meta, c->max_tokens, vjob.first_token);
     KV_HIP_CHECK(hipGetLastError());
     return KV_OK;
+}
+
+template <bool WRITE, bool WIDE>
+static auto chunk8(bool stream) {
+    return stream ? chunk_kernel<WRITE, 8, WIDE, true> : chunk_kernel<WRITE, 8, WIDE, false>;
 }
 
 int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s) {
@@ -1454,6 +1472,7 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
     // 2 x 1504 repacked bf16 chunks); it places whatever the pool covers, so no fill level is tested.
     const bool staged = planes && (!c->pool || n_chunks <= c->stage_chunks / 2);
     bool two_pass = !staged;
+    const bool stream = larger_than_caches(n_chunks);
     PackArgs a;
     for (int i = 0; i < 2; ++i) {
         const CompressJob &job = i ? vjob : kjob;
@@ -1489,7 +1508,6 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
     a.staging = ws + c->stage_offset;
     if (staged) {
         // equal parts that fit the staging area, half of its slots for each tensor
-        const bool stream = int64_t(n_chunks) * 2 * (N * D * 2) > (int64_t(192) << 20);
         const int most = c->stage_chunks / 2;
         const int parts = (n_chunks + most - 1) / most, per_part = (n_chunks + parts - 1) / parts;
         for (int part = 0; part < n_chunks; part += per_part) {
@@ -1522,8 +1540,8 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
                     const dim3 grid(n_chunks, same ? n_tensors : 1);
                     const bool wide = j ? vjob.wide : kjob.wide;
                     auto kernel = planes ? (write ? chunk16_kernel<true> : chunk16_kernel<false>)
-                                  : wide ? (write ? chunk_kernel<true, 8, true> : chunk_kernel<false, 8, true>)
-                                         : (write ? chunk_kernel<true, 8> : chunk_kernel<false, 8>);
+                                  : wide ? (write ? chunk8<true, true>(stream) : chunk8<false, true>(stream))
+                                         : (write ? chunk8<true, false>(stream) : chunk8<false, false>(stream));
                     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a);
                 }
                 a.first_tensor = i;
