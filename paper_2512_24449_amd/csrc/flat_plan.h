@@ -107,8 +107,9 @@ inline int64_t flat_groups(int64_t total, int64_t room, int64_t most) {
 // of resident workgroups that cut the list as it comes, or a whole number of workgroups per
 // stream: then none has parts of two streams, each of which costs its start-up (query, index, first
 // chunk) and its end (merge, store) -- about the time of PART_COST chunks of a wave.  The cheaper one by the
-// chunks its longest wave walks: 256 streams of 7 blocks run as 512 workgroups of one stream each (fused
-// attention 21 us; 448 that cross the boundaries 29 us), 416 streams of 500 blocks as one round of 768.
+// chunks its longest wave walks: 256 streams of 7 blocks run as 512 workgroups of one stream each (K product 5.9 us,
+// V product 8.9; 448 that cross the boundaries 8.1 and 12.3), 120 of 78 as 960 (12.2 and 15.2; 1024 14.5 and 19.1),
+// 416 streams of 500 blocks as one round.
 inline int plan_groups(int n_blocks, int streams, int64_t room, int64_t most) {
     constexpr int64_t PART_COST = 2;
     const int64_t total = int64_t(n_blocks) * streams;
