@@ -118,10 +118,9 @@ def test_incremental_appends_equal_bulk_compression():
 def test_compressor_takes_each_of_its_paths_and_writes_the_same_bytes():
     """Packs of 16, contiguous arena: a round is staged in parts (quantized once) when even its
     largest chunks fit what is left of the arena, else sized and written in two passes; the host
-    skips the two-pass kernels where its own bound already says "fits" (and rounds below 1024
-    chunks always take two passes).  Three appends into an arena sized for 2.85 bits per element
-    meet all three cases, and the state stays the oracle's bit for bit."""
-    B, H, Hq, blocks = 2, 4, 8, [150, 130, 128]   # 1200, 1040, 1024 chunks; the staging area holds 512
+    skips the two-pass kernels where its own bound already says "fits".  Three appends into an arena
+    sized for 2.85 bits per element meet all three cases, and the state stays the oracle's bit for bit."""
+    B, H, Hq, blocks = 2, 4, 8, [150, 130, 128]   # 1200, 1040, 1024 chunks; the staging area holds 512 of each tensor
     L = 64 * sum(blocks)
     K, V, q = synth.make_kv(B, L, H, Hq, 77)
     cache = binding.PackedKVCache(B, H, Hq, L, k_rel_scale=0.2, v_rel_scale=0.2, bits_per_element_budget=2.85)
