@@ -449,8 +449,9 @@ __device__ inline ChunkInput load_chunk_input(const ChunkSource &cs, int cl, con
 // the subtraction and the quotient in the definition: below 1.4 + 2^(e-8).  With g = 3 (+ 2^(e-7) for
 // e >= 8) the quotient can only be on the other side of a rounding tie, or on one, if the fraction
 // field of t is below 2g: then the token's eight values take the divide.  A token whose offset is so
-// large against its scale that g reaches 1/2 always does, and so does every NaN (its low pattern
-// bits are zero) -- infinite inputs end there.  s = 0: r = 0, code 0.
+// large against its scale that g reaches 1/2 always does, infinite offsets and scales among them.  A NaN
+// gets some code in range: its pattern is above the clamp's on the fast path, and the divide's minimum
+// takes qmax.  s = 0: r = 0, code 0.
 struct TokenQuant {
     float r, c;
     uint32_t guard;  // 2g
