@@ -355,19 +355,16 @@ int launch_k_matvec(const kv_cache *c, const __half *q, float sm_scale, float *s
         PACKKV_DISPATCH_GROUP(c->group, PACKKV_LAUNCH_K8)
     } else {
         FlatPlan plan = FlatPlan::make(a.n_blocks, a.B, a.H);
-        // One round of resident workgroups, never less than one block per wave.  Five waves per SIMD from 5.5 chunks per
-        // wave on for one head, 3.7 for two, 2.8 for three and 2.2 for four.  The line lies where whole steps (K, softmax, V) cross,
-        // whose chunks come from memory and find more waves useful earlier than a K product repeated on chunks that
-        // the last-level cache still holds (four / five waves, us a step: one head, 24576 chunks 60.6 / 61.4, 32000
-        // 72.7 / 71.9; two heads, 16384 55.6 / 56.3, 20480 63.4 / 62.3; four heads, 8192 47.3 / 48.0, 12288 57.0 /
-        // 55.3, 16384 64.3 / 62.6, where the repeated K product says 22.2 / 23.4).
+        // one round of resident workgroups, never less than one block per wave; five waves per SIMD from eight
+        // chunks per wave on (four / five waves, one head: 15008 chunks 16.2 / 17.3 us, 32000: 27.8 / 28.6,
+        // 64000: 49.7 / 49.3, 208000: 146 / 142; four heads: 16384 chunks 20.3 / 21.5, 100032: 87.4 / 85.3)
 #define PACKKV_LAUNCH_KPW(g, w)                                                                               \
     {                                                                                                         \
         static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(k_planes_kernel<g, w>)); \
         if (plan.total > 0) plan.split(plan_groups_for(a.n_blocks, streams, per_cu, int64_t(1) << 30));       \
         hipLaunchKernelGGL((k_planes_kernel<g, w>), dim3(plan.n_groups + tail_groups), dim3(256), 0, s, a, plan); \
     }
-        const bool many = plan.total * (c->group + 1) >= int64_t(11) * 4 * flat_groups_for(int64_t(1) << 40, 5, int64_t(1) << 30);
+        const bool many = plan.total >= int64_t(8) * 4 * flat_groups_for(int64_t(1) << 40, 5, int64_t(1) << 30);
 #define PACKKV_LAUNCH_KP(g)             \
     if (many) PACKKV_LAUNCH_KPW(g, 5)   \
     else PACKKV_LAUNCH_KPW(g, 4)
