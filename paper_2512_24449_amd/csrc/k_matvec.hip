@@ -355,9 +355,14 @@ int launch_k_matvec(const kv_cache *c, const __half *q, float sm_scale, float *s
         PACKKV_DISPATCH_GROUP(c->group, PACKKV_LAUNCH_K8)
     } else {
         FlatPlan plan = FlatPlan::make(a.n_blocks, a.B, a.H);
-        // one round of resident workgroups, never less than one block per wave; five waves per SIMD from eight
-        // chunks per wave on (four / five waves, one head: 15008 chunks 16.2 / 17.3 us, 32000: 27.8 / 28.6,
-        // 64000: 49.7 / 49.3, 208000: 146 / 142; four heads: 16384 chunks 20.3 / 21.5, 100032: 87.4 / 85.3)
+        // One round of resident workgroups, never less than one block per wave; five waves per SIMD from eight chunks per
+        // wave on.  Where the line is best depends on what the step leaves in the last-level cache (four / five waves, us
+        // for append, K, softmax and V, sustained, three caches in turn).  Scores in a new buffer while the one before is
+        // still held: one head, 16000 chunks 47.6 / 49.5, 39936 78.4 / 79.0, 48000 87.2 / 88.1, 64896 114.2 / 111.8; four
+        // heads, 16384 62.0 / 63.7, 32000 90.3 / 91.0, 64000 154.1 / 153.4.  One score buffer used again: one head, 16000
+        // 47.8 / 49.9, 39936 81.5 / 79.9; four heads, 12288 57.9 / 56.8, 16384 65.2 / 64.2, 24576 76.6 / 77.5.
+        // The K product's own duration in such a step is 24.9 / 23.5 at 16384 chunks and four heads, repeated on one
+        // cache it is 22.2 / 23.5: neither says what the step gains.
 #define PACKKV_LAUNCH_KPW(g, w)                                                                               \
     {                                                                                                         \
         static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(k_planes_kernel<g, w>)); \
