@@ -16,6 +16,7 @@ read ceiling, and the CPU oracle timed on a bounded sample.
 from __future__ import annotations
 
 import argparse
+import gc
 import json
 import math
 import os
@@ -34,7 +35,7 @@ ROTATE_BYTES = 1.1e9             # working set to rotate over so reads come from
 # kernel takes 20 % longer in the first milliseconds after an idle phase).  Every timed loop below is
 # therefore preceded by an untimed run of the same kernels for this long, before the W warmup steps.
 CLOCK_RAMP_S = 0.5
-DOM_KERNEL = {"k": "k_planes_kernel<1>", "v": "v_matvec_kernel<1, false>"}   # names in the profiles
+DOM_KERNEL = {"k": "k_planes_kernel<1, 5>", "v": "v_matvec_kernel<1, false>"}   # names in the profiles
 
 
 def stored_profile_numbers(workload, dom):
@@ -584,6 +585,10 @@ def main():
         sys.exit(2)
     binding.lib()
     torch.cuda.set_device(0)
+    # what the imports have made stays for good: without this an automatic collection walks all of it, a pause of
+    # 20 to 40 ms that can fall into a timed loop of a few hundred microseconds
+    gc.collect()
+    gc.freeze()
     w = synth.workload(int(args.workload) if args.workload.isdigit() else args.workload)
 
     if w.decode_steps:
