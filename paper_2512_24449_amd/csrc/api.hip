@@ -316,7 +316,7 @@ int compress_blocks(kv_cache *c, const __half *ksrc, const __half *vsrc, int64_t
         kjob.fill_bound16 = c->fill_bound16[0];
         vjob.fill_bound16 = c->fill_bound16[1];
         int rc;
-        if ((rc = launch_token_params(c, kjob, vjob, s))) return rc;
+        if (!finds_params(c, nb * B * H) && (rc = launch_token_params(c, kjob, vjob, s))) return rc;
         if (c->cfg.repack == KV_REPACK_V_MEDIAN) {
             uint8_t *order = static_cast<uint8_t *>(c->buf.token_order);
             if ((rc = launch_v_median_order(c, vjob, kjob.meta, order, s))) return rc;

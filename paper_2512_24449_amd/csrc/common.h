@@ -56,9 +56,9 @@ inline int64_t target_workgroups(int64_t total_blocks) {
     return w < 512 ? 512 : (w > 4096 ? 4096 : w);
 }
 
-// Workgroups of 256 threads of `kernel` that fit one compute unit; flat_groups and plan_groups with the room
+// Workgroups of `kernel` that fit one compute unit; flat_groups and plan_groups with the room
 // of this GPU, `per_cu` workgroups to a compute unit (v_matvec.hip).
-int resident_workgroups(const void *kernel);
+int resident_workgroups(const void *kernel, int threads = 256);
 int flat_groups_for(int64_t total, int per_cu, int64_t most);
 int plan_groups_for(int n_blocks, int streams, int per_cu, int64_t most);
 
@@ -287,7 +287,9 @@ struct CompressJob {
     uint64_t fill_bound16;    // the arena holds at most this much before the round (every chunk so far at its largest)
 };
 
-// Both tensors of a round (they share every launch).
+// Both tensors of a round (they share every launch).  finds_params: launch_pack finds the token parameters of a
+// round of that many chunks by itself.
+bool finds_params(const kv_cache *c, int n_chunks);
 int launch_token_params(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s);
 int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s);
 // V-median order of the job's blocks (job describes V); permutes the token metadata of both

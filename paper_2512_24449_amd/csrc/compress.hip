@@ -1,18 +1,19 @@
 // Append-side compressor: token-wise quantization, bit-packing, appending
 // (PackKV Sec. III-B.1 .. III-B.4).  Cold path: runs once per 64 decode steps.
 //
-//   token_params   a workgroup or a wave per (token, batch): min/max over the token's
-//                  H*128 values -> fp16 scale = rel*(max-min), fp16 min
+// Packs of 16 in a contiguous arena whose free space takes even the largest chunks, or in a
+// paged arena if the staging area takes the whole round (staged path, the input is read and quantized once):
+//   quantize       resident workgroups, 16 tokens of all kv-heads at a time each: min/max over a token's
+//                  H*128 values -> fp16 scale = rel*(max-min), fp16 min; the codes, pack headers and pack bytes per
+//                  token group to a fixed slot per chunk of the staging area
+//   place_small    (paged) chunk positions, from the pack bytes
+//   assemble       one wave per chunk: codes to bit planes at the chunk's place in the arena; contiguous: the
+//                  workgroup adds up the sizes before its chunks and sets their index words
+// with more than 64 kv-heads or V-median repacking the scales come first:
+//   token_params   a workgroup or a wave per (token, batch)
 //   v_median_key, block_order   (V-median repacking only) sort key per token,
 //                  order of the 64 tokens of a block, metadata into storage order
-// then, packs of 16 in a contiguous arena whose free space takes even the largest chunks, or in a
-// paged arena if the staging area takes the whole round (staged path, the input is quantized once):
-//   stage          resident workgroups, a chunk at a time each: quantize, build the chunk's
-//                  bytes in LDS, store them in a fixed slot of the staging area, and its size
-//   place_small    (paged) chunk positions, from the sizes
-//   compact        one wave per chunk: staged bytes to their place in the arena; contiguous: the
-//                  workgroup adds up the sizes before its chunks and sets their index words
-// else (two-pass path: packs of 8, large rounds of paged arenas, a nearly full arena):
+// else (two-pass path: packs of 8, large rounds of paged arenas, a nearly full arena), behind token_params:
 //   chunk_sizes    one workgroup per chunk: quantize, per-pack width -> bytes
 //   scan_offsets / place_small, place_chunks (paged arena) one workgroup: chunk positions -> index;
 //                  paged: inside pages taken from a shared pool, index of (start, end) pairs
@@ -20,6 +21,7 @@
 //                  payload at its final place
 // K and V share every launch.  No atomics in either path: the arena bytes are a pure function of the input.
 #include <algorithm>
+#include <atomic>
 
 #include "unpack.h"
 
@@ -33,9 +35,10 @@ __device__ inline uint4 as_fp16(uint4 raw, bool bf16) {
         uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const __half lo = __float2half_rn(__uint_as_float(w[k] << 16));
-            const __half hi = __float2half_rn(__uint_as_float(w[k] & 0xFFFF0000u));
-            w[k] = uint32_t(__half_as_ushort(lo)) | (uint32_t(__half_as_ushort(hi)) << 16);
+            typedef float f32x2 __attribute__((ext_vector_type(2)));
+            typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+            const f32x2 both = {__uint_as_float(w[k] << 16), __uint_as_float(w[k] & 0xFFFF0000u)};
+            w[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(both, f16x2));   // one instruction, to nearest even
         }
         raw = make_uint4(w[0], w[1], w[2], w[3]);
     }
@@ -65,16 +68,15 @@ __device__ inline uint4 load8_as_fp16(const __half *p, bool bf16) {
 
 // A token's metadata word from its smallest and largest value: fp16 scale | fp16 minimum << 16.
 __device__ inline uint32_t token_meta_word(float mn, float mx, float rel) {
-    mn = mn + 0.0f;  // a zero minimum or maximum is stored as +0
-    mx = mx + 0.0f;
     float range = mx - mn;
     float s = rel * range;
     // The product is rounded to fp32 first and to fp16 second; keep the
     // compiler from fusing both into one mixed-precision FMA (one rounding).
     asm volatile("" : "+v"(s));
-    __half s16 = __float2half_rn(s);
-    __half m16 = __float2half_rn(mn);  // exact: mn is an fp16 value
-    return uint32_t(__half_as_ushort(s16)) | (uint32_t(__half_as_ushort(m16)) << 16);
+    const uint32_t s16 = __half_as_ushort(__float2half_rn(s)) & 0x7FFFu;  // the range of zeros of either sign is +0
+    uint32_t m16 = __half_as_ushort(__float2half_rn(mn));                // exact: mn is an fp16 value
+    m16 = m16 == 0x8000u ? 0u : m16;                                      // a zero minimum is stored as +0
+    return s16 | (m16 << 16);
 }
 
 // ---------------------------------------------------------------------------
@@ -216,7 +218,7 @@ struct ChunkSource {
     int64_t batch_stride, token_stride;
     int B, H, qmax;
     uint64_t magic_h, magic_hb;  // floor(2^32 / H) + 1, floor(2^32 / (H * B)) + 1
-    const uint32_t *meta;
+    uint32_t *meta;
     int64_t meta_stride, first_token;
     const uint8_t *order;
     bool bf16;
@@ -229,7 +231,11 @@ struct PackTensor {
     StagedRound round;
     uint32_t *index;
     uint8_t *arena;
-    uint32_t *sizes16;      // sizes of this part's (two-pass: round's) chunks, 16-byte units
+    uint32_t *sizes16;      // two-pass: sizes of the round's chunks, 16-byte units
+    uint16_t *widths;       // staged: sums of the pack widths of the part's chunks, [chunk][token group] (8-byte aligned)
+    float rel;
+    bool cap_all;           // staged: see QuantRange
+    float small_scale;
     uint64_t arena_cap16;
     uint32_t *status;       // set when the round does not fit
     uint32_t *page_list;    // paged arena
@@ -238,10 +244,14 @@ struct PackTensor {
 struct PackArgs {
     PackTensor t[2];        // K, V
     int part_first, n;      // chunks part_first .. part_first + n - 1 of the round, in both tensors
+    int part_row, rows;     // the same in rows of H chunks (row = blk*B + b)
+    uint64_t magic_b;       // floor(2^32 / B) + 1
     int index_words;
     int first_tensor;       // a launch whose grid covers one tensor: which (else 0)
     uint32_t *pool_state;   // paged arena
-    uint8_t *staging;       // K chunk i of the part in slot i, V chunk i in slot n + i
+    int split;              // workgroups that share an item's quantization (quantize16_kernel)
+    uint8_t *staging;       // K chunk i of the part in slot i, V chunk i in slot n + i: 512 pack headers [group][channel],
+                            // then the codes of the packs (quantize16_kernel)
 };
 
 // One workgroup per new chunk; packs of PK = 8 tokens (Sec. IV-B; packs of 16 have their own
@@ -654,17 +664,18 @@ __device__ inline void copy_image(const ChunkLds &lds, int slot, int n16, uint8_
     if (tau + 256 < n16) dst[tau + 256] = image[tau + 256];
 }
 
-// Staged path, packs of 16: the input is quantized once.
-//   stage     resident workgroups, a chunk at a time each: quantize, build the chunk's bytes in LDS, store them
-//             in a slot of CHUNK_MAX bytes of the staging area in the workspace, and the chunk's size
-//   compact   one wave per chunk: copy the staged bytes to their place in the arena
+// Staged path, packs of 16: the input is read and quantized once.
+//   quantize  a workgroup holds 16 tokens of all kv-heads in registers: their scales and minimums, then
+//             their codes as nibbles, pack headers and bytes per pack list, into the chunk's slot of CHUNK_MAX
+//             bytes of the staging area in the workspace
+//   assemble  one wave per chunk: turns the codes into planes and puts the chunk's bytes at their place in the arena
 // A chunk's place depends on the sizes of all chunks before it, so some second step is needed;
-// this one re-reads the compressed bytes (a fraction of the input, and still in the last-level
-// cache: the staging area is a few tens of MB) instead of the input.  A round is cut into parts
+// this one reads the codes (a quarter of the input, and still in the last-level cache: the staging area is a
+// few tens of MB) instead of the input.  A round is cut into parts
 // that fit the staging area.  The path runs when even the largest chunks fit the arena (worst16 =
 // chunks of the round times the largest chunk, checked on the device, where the fill level is), so
-// no part can overflow and a round keeps or drops its chunks as a whole; otherwise its kernels
-// return at once and the two-pass kernels do the round, and the other way round.
+// no part can overflow and a round keeps or drops its chunks as a whole; otherwise the second kernel
+// returns at once and the two-pass kernels do the round, and the other way round.
 __device__ inline bool staged_round(const StagedRound &r, const uint32_t *index) {
     return r.worst16 != 0 && uint64_t(index[r.first_chunk]) + r.worst16 <= r.arena_cap16;
 }
@@ -691,44 +702,393 @@ __global__ __launch_bounds__(256) void chunk16_kernel(PackArgs a) {
         t.sizes16[cl] = uint32_t(n16);
 }
 
-// The part's chunks of both tensors, item i = K chunk i (i < n) or V chunk i - n, into slot i.  16384 chunks
-// of packs of 16 (268 MB in, 42 MB out) take 71 us: the arithmetic alone (input from a cached block, no stores)
-// takes 55, the same loads and stores without it 58, the loads alone 43.  377 vector instructions per wave
-// and chunk (500 with a code tile in LDS, a subtraction, a product and a tie test per value).  A
-// workgroup takes every gridDim.x-th item and has the loads of its next one in flight while it
-// works on the current one.  (The hint of STREAM here: 3.56 -> 3.47 ms for a prompt of 6.8 GB, 51 -> 54 us for 67 MB.)
-template <bool STREAM>
-__global__ __launch_bounds__(256) void chunk16_stage_kernel(PackArgs a) {
-    const int lo = staged_round(a.t[0].round, a.t[0].index) ? 0 : a.n;
-    const int hi = staged_round(a.t[1].round, a.t[1].index) ? 2 * a.n : a.n;
-    __shared__ ChunkLds lds;
-    const int stride = int(gridDim.x);
-    int item = lo + int(blockIdx.x);
-    if (item >= hi) return;
-    const int last = hi - 1;
-    auto rows_of = [&](int i) {
-        const int v = i >= a.n;
-        return load_chunk_rows(a.t[v].cs, a.part_first + i - (v ? a.n : 0));
+// Smaller halves of two pairs of fp16 values; the larger ones.  (The builtin forms put a canonicalizing instruction
+// in front of every loaded operand.)
+__device__ inline uint32_t pk_min_f16(uint32_t x, uint32_t y) {
+    uint32_t r;
+    asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+    return r;
+}
+__device__ inline uint32_t pk_max_f16(uint32_t x, uint32_t y) {
+    uint32_t r;
+    asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+    return r;
+}
+// Smallest and largest of three pairs of fp16 values that are no NaN.
+__device__ inline uint32_t pk_min3_f16(uint32_t x, uint32_t y, uint32_t z) {
+    uint32_t r;
+    asm("v_pk_minimum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
+    return r;
+}
+__device__ inline uint32_t pk_max3_f16(uint32_t x, uint32_t y, uint32_t z) {
+    uint32_t r;
+    asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
+    return r;
+}
+template <int CTRL>
+__device__ inline uint32_t dpp_u32(uint32_t v) {
+    return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, 0xF, 0xF, true));
+}
+// Lane i <- lane i ^ 4 of its row (two rotations, each written to half of the lanes).
+__device__ inline uint32_t dpp_xor4(uint32_t v) {
+    const int up = __builtin_amdgcn_update_dpp(0, int(v), 0x12C, 0xF, 0x5, true);   // banks 0, 2: from the lane four above
+    return uint32_t(__builtin_amdgcn_update_dpp(up, int(v), DPP_ROW_ROR4, 0xF, 0xA, true));
+}
+
+// Widths of four packs from the ranges of their codes (a byte 0..15 each): bits of the range.
+__device__ inline uint32_t width_bytes(uint32_t range) {
+    const uint32_t half = (range >> 1) & 0x07070707u;
+    const uint32_t w = __builtin_amdgcn_perm(0x04040404u, 0x03030200u, half);   // half = 0: range itself, below
+    const uint32_t low = __builtin_amdgcn_perm(0u, 0x00000001u, half);
+    return w | (range & low);
+}
+
+// Size of a chunk in 16-byte units from the width sums of its four token groups (a pack of width w takes 2 w bytes).
+__device__ inline uint32_t chunk_units(uint2 sums) {
+    const uint32_t w = (sums.x & 0xFFFFu) + (sums.x >> 16) + (sums.y & 0xFFFFu) + (sums.y >> 16);
+    return uint32_t(HEADER / 16) + ((w + 7) >> 3);
+}
+
+// Sixteen words of a lane (v[k], k < 8: minimums of tokens 2k, 2k + 1; v[8 + k]: their negated maximums), smallest
+// over the 16 lanes of a row: lane i of the row returns word i.
+__device__ inline uint32_t row_min_scatter16(const uint32_t (&v)[16]) {
+    const int lane = threadIdx.x & 63;
+    const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2, b0 = lane & 1;
+    uint32_t a[8], b[4], c[2];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a[k] = pk_min_f16(b3 ? v[8 + k] : v[k], dpp_u32<DPP_ROW_ROR8>(b3 ? v[k] : v[8 + k]));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) b[k] = pk_min_f16(b2 ? a[4 + k] : a[k], dpp_xor4(b2 ? a[k] : a[4 + k]));
+#pragma unroll
+    for (int k = 0; k < 2; ++k) c[k] = pk_min_f16(b1 ? b[2 + k] : b[k], dpp_u32<DPP_QUAD_XOR2>(b1 ? b[k] : b[2 + k]));
+    return pk_min_f16(b0 ? c[1] : c[0], dpp_u32<DPP_QUAD_XOR1>(b0 ? c[0] : c[1]));
+}
+// The same over all 64 lanes: lane l returns word 8 (l / 32) + 4 (l / 16 % 2) + l / 4 % 4.
+__device__ inline uint32_t wave_min_scatter16(const uint32_t (&v)[16]) {
+    const int lane = threadIdx.x & 63;
+    const bool b3 = lane & 8, b2 = lane & 4;
+    uint32_t a[8], b[4], c[2];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        uint32_t x = v[k], y = v[8 + k];
+        swap_rows32(x, y);   // the lower half of the wave keeps word k, the upper half word 8 + k
+        a[k] = pk_min_f16(x, y);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        uint32_t x = a[k], y = a[4 + k];
+        swap_rows16(x, y);   // even rows keep a[k], odd rows a[4 + k]
+        b[k] = pk_min_f16(x, y);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) c[k] = pk_min_f16(b3 ? b[2 + k] : b[k], dpp_u32<DPP_ROW_ROR8>(b3 ? b[k] : b[2 + k]));
+    uint32_t r = pk_min_f16(b2 ? c[1] : c[0], dpp_xor4(b2 ? c[0] : c[1]));
+    r = pk_min_f16(r, dpp_u32<DPP_QUAD_XOR2>(r));
+    return pk_min_f16(r, dpp_u32<DPP_QUAD_XOR1>(r));
+}
+
+// token_quant with a closer guard, for quotients below 15.5 (larger ones, over tiny scales, take the divide): the error of
+// t against quotient + 1/2 + g is below 0.5 (its rounding) + 0.5 (c; 2^(e-8) for e >= 8) + 0.12 (r) + 0.13 (the
+// definition's roundings) units, so g = 2 (+ 2^(e-7)) does: a third fewer divides, which matters here, where all waves
+// of a token wait for the slowest.  A token whose scale is so small that codes could pass qmax always divides.
+__device__ inline float4 token_quant_near(uint32_t mt, float small_scale) {
+    const float s = __half2float(__ushort_as_half(uint16_t(mt & 0xFFFFu)));
+    const float mn = __half2float(__ushort_as_half(uint16_t(mt >> 16)));
+    const float r = s != 0.0f ? __builtin_amdgcn_rcpf(s) : 0.0f;
+    const int e = int((__float_as_uint(fmaf(-mn, r, 128.5f)) >> 23) & 0xFFu) - 127;
+    uint32_t g = 2u + (e >= 8 ? 2u << min(e - 8, 14) : 0u);
+    const float c = fmaf(-mn, r, 128.5f + float(g) * (1.0f / 65536.0f));
+    if (s > 0.0f && s < small_scale) g = 1u << 15;
+    return make_float4(r, c, __uint_as_float(2u * g), __uint_as_float(mt));
+}
+
+// Quantizes four tokens (eight channels each): pair[i][k] as quantize_token8 has it for token i.  The tokens that hold a
+// value near a rounding tie take the divide, one after the other (every second wave meets one in 16 tokens).
+// tok: token_quant_near of the four tokens, every second entry.  cap_all: clamp every value (see QuantRange).
+__device__ inline void quantize_quad(const uint4 (&x)[4], const float4 *tok, uint32_t qmax, bool cap_all, uint32_t (&pair)[4][4]) {
+    uint64_t near_lanes[4], any = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t w[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
+        const float4 tq = tok[2 * i];
+        unsigned short near = 0xFFFF;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t t0 = __float_as_uint(half_mul_add<false>(w[k], tq.x, tq.y));
+            const uint32_t t1 = __float_as_uint(half_mul_add<true>(w[k], tq.x, tq.y));
+            near = min(min(near, (unsigned short)t0), (unsigned short)t1);
+            pair[i][k] = __builtin_amdgcn_perm(t1, t0, 0x07060302u);
+        }
+        near_lanes[i] = __builtin_amdgcn_ballot_w64(near < __float_as_uint(tq.z));
+        any |= near_lanes[i];
+    }
+    if (cap_all) {
+        const uint32_t cap = (0x4300u + qmax) * 0x10001u;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) pair[i >> 2][i & 3] = pk_min(pair[i >> 2][i & 3], cap);
+    }
+    if (any == 0) return;
+    uint32_t todo = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) todo |= __builtin_amdgcn_inverse_ballot_w64(near_lanes[i]) ? 1u << i : 0u;
+    while (todo) {
+        const int i = __builtin_ctz(todo);
+        const uint32_t mt = __float_as_uint(tok[2 * i].w);
+        uint32_t w[4] = {x[0].x, x[0].y, x[0].z, x[0].w};
+#pragma unroll
+        for (int j = 1; j < 4; ++j) {
+            if (i == j) w[0] = x[j].x, w[1] = x[j].y, w[2] = x[j].z, w[3] = x[j].w;
+        }
+        const float s = __half2float(__ushort_as_half(uint16_t(mt & 0xFFFFu)));
+        const float mn = __half2float(__ushort_as_half(uint16_t(mt >> 16)));
+        const float top = float(qmax);
+        const uint32_t keep = s != 0.0f ? ~0u : 0x43004300u;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            __builtin_amdgcn_sched_barrier(0);   // two at a time, in few registers
+            const float q0 = (half_lo(w[k]) - mn) / s, q1 = (half_hi(w[k]) - mn) / s;   // IEEE fp32 divide
+            const uint32_t c0 = __builtin_amdgcn_cvt_pk_u8_f32(fminf(q0, top), 0u, 0u), c1 = __builtin_amdgcn_cvt_pk_u8_f32(fminf(q1, top), 0u, 0u);
+            const uint32_t both = (0x43004300u + (c0 | (c1 << 16))) & keep;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pair[j][k] = i == j ? both : pair[j][k];
+        }
+        todo &= todo - 1;
+    }
+}
+
+// Codes above qmax come out of the multiply-add only where the scale's own rounding to fp16 makes the quotient of the
+// largest value pass qmax + 1/2: by less than 2^-11 of it for a scale in fp16's normal range, which reaches there only if
+// 1 / rel is within 2^-11 of qmax + 1/2 already (cap_all: the tensor's values are all clamped), by more for a subnormal
+// scale (below small_scale the divide and its clamp take the token).  The host's part:
+struct QuantRange {
+    bool cap_all;
+    float small_scale;
+};
+inline QuantRange quant_range(float rel, int qmax) {
+    // the largest quotient is below (s + u) / (rel s) (1 + 2^-20), u half a unit of the scale's last place; with the
+    // guard of token_quant_near, its error and the half that rounds it must stay below qmax + 1
+    const double room = (qmax + 0.5 - 4.0 / 65536.0) * double(rel) / (1.0 + 1.0 / (1 << 20)) - 1.0;   // must exceed u / s
+    QuantRange q;
+    q.cap_all = !(room > 1.0 / 2048.0);
+    q.small_scale = q.cap_all ? 0.0f : float(1.0 / (1 << 25) / room * 1.0001);
+    return q;
+}
+
+// Reads and quantizes the input of a part, once.  A workgroup takes 16 tokens of all kv-heads at a time (an item), a
+// wave four heads of them, a lane eight channels (lane % 16) of all 16 tokens: the item's 4 H KB sit in registers while
+// the tokens' minimums and maximums are found across the workgroup, so the input is not read a second time.  A token's
+// registers are loaded with the next item's as soon as its codes are there.
+// HP < 4 (that many kv-heads): the rows of a wave hold 4 / HP token groups.  GIVEN: the token metadata is there
+// already (more than 64 kv-heads, or tokens that are repacked, whose order depends on it): the waves are independent.
+// Eight codes of a pack make a word, token 2 i in the low half of byte i and token 2 i + 1 in the high half; the words
+// of a chunk go out in the order [group][tokens 0..7, 8..15][channel % 8 / 4][channel / 8][channel % 4], which every
+// store instruction covers without gaps.
+// Bound by memory and arithmetic alike: 8192 chunks of 52 heads of each tensor (268 MB in, 75 MB out) 64 us, about 950 vector
+// instructions per wave and item; the token parameters and the quantizer as two kernels that both read the input
+// took 38 + 71.  6.8 GB with the assembly below 3330 -> 2280 us, 67 MB 41.6 -> 28.9 (8 heads, 268 MB: 144 -> 104).  Landing half of the next
+// item in LDS early, which keeps more loads in flight, gained nothing (2280 -> 2315, 104 -> 114).
+// split: few items leave most of the chip idle, and up to 16 waves of one compute unit then share its
+// vector units; with split workgroups per item, each reads it all and quantizes a part of the heads (8 x 52 heads, one block:
+// flush 19.0 us with one workgroup per item, 16.4 with two, 15.5 with four).
+template <int HP, bool GIVEN, bool STREAM>
+__global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_kernel(PackArgs a) {
+    constexpr int MOST_WAVES = HP < 4 ? 1 : GIVEN ? 4 : 16;
+    __shared__ uint32_t red[2][MOST_WAVES][16];
+    __shared__ float4 tok_all[MOST_WAVES][HP < 4 ? 64 : 16];
+    const int lane = threadIdx.x & 63, cg = lane & 15, row4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = int(blockDim.x >> 6);
+    float4 *tok = tok_all[wave];
+    const int H = a.t[0].cs.H, B = a.t[0].cs.B;
+    const int sets = HP == 4 && GIVEN ? (H + 15) / 16 : 1;   // workgroups that share the heads of an item
+    const int per_tensor = a.rows * HP * sets, n_items = 2 * per_tensor;
+    const int token_bytes = int(2 * a.t[0].cs.token_stride);
+
+    struct Item {
+        int v, row, blk, b, g0, set;   // tensor, row of the part, block and batch element, first token group, head set
     };
-    auto input_of = [&](int i, const ChunkRows &rows) {
-        const int v = i >= a.n;
-        return load_chunk_input<STREAM>(a.t[v].cs, a.part_first + i - (v ? a.n : 0), rows);
+    auto locate = [&](int item) {
+        Item m;
+        m.v = item >= per_tensor;
+        int rest = item - (m.v ? per_tensor : 0);
+        m.set = 0;
+        if (sets > 1) {
+            m.set = rest % sets;
+            rest /= sets;
+        }
+        m.row = rest / HP;
+        m.g0 = (rest % HP) * (4 / HP);
+        const uint32_t full = uint32_t(a.part_row + m.row);
+        m.blk = int((uint64_t(full) * a.magic_b) >> 32);
+        m.b = int(full) - m.blk * B;
+        return m;
     };
-    // The loads of the next chunk and the token order of the one after it are always issued (of
-    // the last chunk again where there is no next one): the count of loads in flight is then the
-    // same on every path, and the waits of the current chunk do not wait for them.
-    ChunkInput in = input_of(item, rows_of(item));
-    ChunkRows rows_next = rows_of(min(item + stride, last));
+    const int head_in_set = HP == 4 ? 4 * wave + row4 : HP == 2 ? row4 & 1 : 0;
+    const int group_in_item = HP == 4 ? 0 : HP == 2 ? row4 >> 1 : row4;
+    auto head_of = [&](const Item &m) { return head_in_set + 16 * m.set; };
+    // storage order of the item's tokens, a byte each (GIVEN, repacked)
+    auto order_of = [&](const Item &m) {
+        const ChunkSource &cs = a.t[m.v].cs;
+        return *reinterpret_cast<const uint4 *>(cs.order + m.b * cs.meta_stride + cs.first_token + int64_t(m.blk) * N +
+                                                16 * (m.g0 + group_in_item));
+    };
+    const bool ordered = GIVEN && a.t[0].cs.order != nullptr;
+    auto block_of = [&](const Item &m) {
+        const ChunkSource &cs = a.t[m.v].cs;
+        return cs.src + m.b * cs.batch_stride + int64_t(m.blk) * N * cs.token_stride;
+    };
+    // where the lane finds token t: bytes behind the block's first token, the same for all lanes and the lane's own
+    auto offset_of = [&](const Item &m, const uint4 &order, int t, int &base) {
+        int off = min(head_of(m), H - 1) * (2 * D) + 16 * cg;
+        base = (16 * m.g0 + t) * token_bytes;
+        if (ordered) {
+            const uint32_t w = t < 4 ? order.x : t < 8 ? order.y : t < 12 ? order.z : order.w;
+            off += int((w >> (8 * (t & 3))) & 0xFFu) * token_bytes;
+            base = 0;
+        } else if (HP < 4) {
+            off += 16 * group_in_item * token_bytes;
+        }
+        return off;
+    };
+    // the block's 64 tokens as a buffer (an empty one if there is no such item: its loads touch no memory)
+    auto buffer_of = [&](const Item &m, bool present) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<__half *>(block_of(m)), 0, present ? int(N * token_bytes) : 0, 0x00027000);
+    };
+    auto load_token = [&](const Item &m, __amdgpu_buffer_rsrc_t buffer, const uint4 &order, int t) {
+        int base;
+        const int off = offset_of(m, order, t, base);
+        typedef uint32_t u32x4n __attribute__((ext_vector_type(4)));
+        const u32x4n v = __builtin_amdgcn_raw_buffer_load_b128(buffer, off, base, STREAM ? 2 : 0);   // 2: non-temporal
+        return make_uint4(v.x, v.y, v.z, v.w);
+    };
+    // split > 1: n_items * split workgroups, one item each (those of an item on the same die)
+    const int split = HP == 4 && !GIVEN ? a.split : 1;
+    int item = split > 1 ? int(blockIdx.x) % n_items : int(blockIdx.x);
+    if (item >= n_items) return;
+    Item cur = locate(item);
+    uint4 raw[16];
+    uint4 order = make_uint4(0, 0, 0, 0), order_next = order;   // storage order of the item's tokens, and of the next one's
+    if (ordered) order = order_of(cur), order_next = order_of(locate(min(item + int(gridDim.x), n_items - 1)));
+    {
+        const __amdgpu_buffer_rsrc_t buffer = buffer_of(cur, true);
+#pragma unroll
+        for (int t = 0; t < 16; ++t) raw[t] = load_token(cur, buffer, order, t);
+    }
     for (int slot = 0;; slot ^= 1) {
-        const int next = item + stride;
-        const ChunkInput in_next = input_of(min(next, last), rows_next);
-        rows_next = rows_of(min(next + stride, last));
-        const int v = item >= a.n;
-        const int n16 = build_plane_chunk<true>(a.t[v].cs, in, lds, slot);
-        if (threadIdx.x == 0) a.t[v].sizes16[item - (v ? a.n : 0)] = uint32_t(n16);
-        copy_image(lds, slot, n16, a.staging + size_t(item) * CHUNK_MAX);
-        if (next >= hi) break;
-        in = in_next;
+        const PackTensor &pt = a.t[cur.v];
+        const ChunkSource &cs = pt.cs;
+        const int g = cur.g0 + group_in_item;
+        uint32_t *meta = cs.meta + cur.b * cs.meta_stride + cs.first_token + int64_t(cur.blk) * N + 16 * g;
+        const int next = item + int(gridDim.x);   // (split: past the end)
+        const bool more = next < n_items;
+        const Item nxt = locate(more ? next : item);
+        order = order_next;
+        if (ordered) order_next = order_of(locate(min(next + int(gridDim.x), n_items - 1)));
+        if (cs.bf16) {
+#pragma unroll
+            for (int t = 0; t < 16; ++t) raw[t] = as_fp16(raw[t], true);
+        }
+        if constexpr (GIVEN) {
+            tok[HP < 4 ? lane : cg] = token_quant_near(meta[cg], pt.small_scale);
+        } else {
+            uint32_t v[16];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const uint4 p = raw[2 * k], q = raw[2 * k + 1];
+                const uint32_t p_mn = pk_min_f16(pk_min_f16(p.x, p.y), pk_min_f16(p.z, p.w)), q_mn = pk_min_f16(pk_min_f16(q.x, q.y), pk_min_f16(q.z, q.w));
+                const uint32_t p_mx = pk_max_f16(pk_max_f16(p.x, p.y), pk_max_f16(p.z, p.w)), q_mx = pk_max_f16(pk_max_f16(q.x, q.y), pk_max_f16(q.z, q.w));
+                v[k] = pk_min_f16(__builtin_amdgcn_perm(q_mn, p_mn, 0x05040100u), __builtin_amdgcn_perm(q_mn, p_mn, 0x07060302u));
+                v[8 + k] = pk_max_f16(__builtin_amdgcn_perm(q_mx, p_mx, 0x05040100u), __builtin_amdgcn_perm(q_mx, p_mx, 0x07060302u)) ^ 0x80008000u;
+            }
+            // word cg (of v) over the whole item, in every row
+            uint32_t word;
+            if constexpr (HP == 4) {
+                const uint32_t part = wave_min_scatter16(v);
+                if ((lane & 3) == 0) red[slot][wave][8 * (row4 >> 1) + 4 * (row4 & 1) + (cg >> 2)] = part;
+                if (waves > 1)
+                    __syncthreads();   // one per item: the words of the next item go to the other slot
+                else
+                    wave_lds_fence();
+                word = red[slot][min(row4, waves - 1)][cg];
+                for (int w = row4 + 4; w < waves; w += 4) word = pk_min_f16(word, red[slot][w][cg]);
+                uint32_t x = word, y = word;
+                swap_rows16(x, y);
+                x = y = pk_min_f16(x, y);
+                swap_rows32(x, y);
+                word = pk_min_f16(x, y);
+            } else {
+                word = row_min_scatter16(v);
+                if constexpr (HP == 2) {
+                    uint32_t x = word, y = word;
+                    swap_rows16(x, y);
+                    word = pk_min_f16(x, y);
+                }
+            }
+            // lane i: token 2i (i < 8) or 2 (i - 8) + 1; its minimum and negated maximum in one half of the two words
+            const uint32_t other = dpp_u32<DPP_ROW_ROR8>(word);
+            const uint32_t mnw = cg < 8 ? word : other >> 16, mxw = cg < 8 ? other : word >> 16;
+            const int t = 2 * (cg & 7) + (cg >> 3);
+            const uint32_t mt = token_meta_word(half_lo(mnw), -half_lo(mxw), pt.rel);
+            tok[HP < 4 ? 16 * row4 + t : t] = token_quant_near(mt, pt.small_scale);
+            if (HP == 4 ? threadIdx.x < 16 : head_in_set == 0) meta[t] = mt;
+            if (split > 1 && ((wave >> 2) & (split - 1)) != int(blockIdx.x) / n_items) return;   // another workgroup's heads
+        }
+        wave_lds_fence();
+        const __amdgpu_buffer_rsrc_t next_buffer = buffer_of(nxt, more);
+        const int head = head_of(cur);
+        const bool present = head < H;
+        const uint32_t at = uint32_t((cur.v ? a.n : 0) + cur.row * H + head) * uint32_t(CHUNK_MAX) + uint32_t(16 * cg);
+        uint32_t codes[8], mn2[4], mx2[4];   // codes: channel c, eight tokens as nibbles
+#pragma unroll
+        for (int quad = 0; quad < 4; ++quad) {
+            // tokens first, first + 2, .. first + 6
+            const int first = 8 * (quad >> 1) + (quad & 1);
+            uint4 x[4];
+            uint32_t pair[4][4];
+            __builtin_amdgcn_sched_barrier(0);   // one quad after the other: the registers do not take more
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = raw[first + 2 * i];
+            quantize_quad(x, tok + (HP < 4 ? 16 * row4 : 0) + first, uint32_t(cs.qmax), pt.cap_all, pair);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) raw[first + 2 * i] = load_token(nxt, next_buffer, order, first + 2 * i);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                // (0x4300 + code is an fp16 number between 3.5 and 3.53)
+                const uint32_t lo = pk_min3_f16(pair[0][k], pair[1][k], pair[2][k]), hi = pk_max3_f16(pair[0][k], pair[1][k], pair[2][k]);
+                mn2[k] = quad ? pk_min3_f16(mn2[k], lo, pair[3][k]) : pk_min(lo, pair[3][k]);
+                mx2[k] = quad ? pk_max3_f16(mx2[k], hi, pair[3][k]) : pk_max(hi, pair[3][k]);
+                const uint32_t p01 = __builtin_amdgcn_perm(pair[1][k], pair[0][k], 0x06020400u);  // even ch. tokens 0 1, odd ch. tokens 0 1
+                const uint32_t p23 = __builtin_amdgcn_perm(pair[3][k], pair[2][k], 0x06020400u);
+                const uint32_t e = __builtin_amdgcn_perm(p23, p01, 0x05040100u), o = __builtin_amdgcn_perm(p23, p01, 0x07060302u);
+                if (quad & 1)
+                    codes[2 * k] |= e << 4, codes[2 * k + 1] |= o << 4;
+                else
+                    codes[2 * k] = e, codes[2 * k + 1] = o;
+            }
+            // what the quad leaves is computed here: moved to where it is used, it would keep all pairs in registers
+#pragma unroll
+            for (int k = 0; k < 4; ++k) consume_here(mn2[k]), consume_here(mx2[k]), consume_here(codes[2 * k]), consume_here(codes[2 * k + 1]);
+            if ((quad & 1) && present) {
+                uint8_t *const to = a.staging + (at + uint32_t(HEADER + 1024 * g + 512 * (quad >> 1)));
+                *reinterpret_cast<uint4 *>(to) = make_uint4(codes[0], codes[1], codes[2], codes[3]);
+                *reinterpret_cast<uint4 *>(to + 256) = make_uint4(codes[4], codes[5], codes[6], codes[7]);
+            }
+        }
+        // headers: bytes (width << 4) | minimum of the lane's eight packs
+        // (the masks: a NaN may leave any byte, the header has to be one all the same; widths are at most 4 for any bytes)
+        const uint32_t m_lo = __builtin_amdgcn_perm(mn2[1], mn2[0], 0x06040200u) & 0x0F0F0F0Fu;
+        const uint32_t m_hi = __builtin_amdgcn_perm(mn2[3], mn2[2], 0x06040200u) & 0x0F0F0F0Fu;
+        const uint32_t x_lo = __builtin_amdgcn_perm(mx2[1], mx2[0], 0x06040200u), x_hi = __builtin_amdgcn_perm(mx2[3], mx2[2], 0x06040200u);
+        const uint32_t w_lo = width_bytes(x_lo - m_lo), w_hi = width_bytes(x_hi - m_hi);
+        uint32_t sum = w_lo + w_hi;   // bytes of at most 8
+        sum += sum >> 16;
+        sum = (sum + (sum >> 8)) & 0xFFu;
+        sum = row_inclusive_scan(sum);
+        if (present) {
+            *reinterpret_cast<uint2 *>(a.staging + (at + uint32_t(D * g) - uint32_t(8 * cg))) = make_uint2((w_lo << 4) | m_lo, (w_hi << 4) | m_hi);
+            if (cg == 15) pt.widths[4 * (cur.row * H + head) + g] = uint16_t(sum);
+        }
+        if (!more) break;
+        cur = nxt;
         item = next;
     }
 }
@@ -742,60 +1102,148 @@ __device__ inline uint32_t block_sum(uint32_t v) {
     return wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3];
 }
 
-// Staged bytes of a part to their place, and its index words.  blockIdx.y: tensor; a wave takes
-// one chunk, so a workgroup four.  Every workgroup adds up the sizes of the part's chunks before
-// its own by itself (at most 32 KB, in the L2 cache of its die after the first): no launch of a scan
-// between staging and compaction, which cost a launch gap and 7 us for 16384 chunks.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void chunk16_compact_kernel(PackArgs a) {
+// A lane's part of a staged chunk: channels 2 lane, 2 lane + 1 in all four token groups.
+struct StagedLane {
+    uint2 codes[4][2];   // [group][half]: eight codes of the two channels
+    uint32_t header[4];  // [group]: two header bytes
+    __device__ inline void load(const uint8_t *slot, int lane) {
+        typedef uint32_t u32x2n __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            header[g] = *reinterpret_cast<const uint16_t *>(slot + D * g + 2 * lane);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const u32x2n v = __builtin_nontemporal_load(reinterpret_cast<const u32x2n *>(
+                    slot + HEADER + 1024 * g + 512 * h + 256 * ((lane >> 1) & 1) + 16 * (lane >> 2) + 8 * (lane & 1)));
+                codes[g][h] = make_uint2(v.x, v.y);
+            }
+        }
+    }
+};
+
+// The bytes of one chunk from its staged codes, in the wave's LDS image.  channel_major: the pack list of K chunks.
+// The image is zero from its last byte in use to the next multiple of 16.
+__device__ inline void assemble_chunk(const StagedLane &in, bool channel_major, uint8_t *img) {
+    const int lane = threadIdx.x & 63;
+    // header bytes by channel, group g in byte g
+    const uint32_t h01 = __builtin_amdgcn_perm(in.header[1], in.header[0], 0x05010400u), h23 = __builtin_amdgcn_perm(in.header[3], in.header[2], 0x05010400u);
+    const uint32_t hdr[2] = {__builtin_amdgcn_perm(h23, h01, 0x05040100u), __builtin_amdgcn_perm(h23, h01, 0x07060302u)};
+    // where the planes of the lane's packs go: words of region E, halfwords of region O before them
+    uint32_t e_at[2][4], o_at[2][4], e_words, o_halves;
+    const uint32_t e0 = (hdr[0] >> 5) & 0x03030303u, e1 = (hdr[1] >> 5) & 0x03030303u;
+    const uint32_t o0 = (hdr[0] >> 4) & 0x01010101u, o1 = (hdr[1] >> 4) & 0x01010101u;
+    if (channel_major) {
+        const uint32_t ep0 = byte_prefix_sums(e0), ep1 = byte_prefix_sums(e1), op0 = byte_prefix_sums(o0), op1 = byte_prefix_sums(o1);
+        const uint32_t both = ((ep0 >> 24) + (ep1 >> 24)) | (((op0 >> 24) + (op1 >> 24)) << 16);
+        const uint32_t inc = uint32_t(wave_inclusive_scan(int(both)));
+        const uint32_t total = uint32_t(__builtin_amdgcn_readlane(int(inc), 63)), before = inc - both;
+        e_words = total & 0xFFFFu, o_halves = total >> 16;
+        const uint32_t eb = before & 0xFFFFu, ob = before >> 16;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            e_at[0][g] = eb + (g ? (ep0 >> (8 * (g - 1))) & 0xFFu : 0u);
+            o_at[0][g] = ob + (g ? (op0 >> (8 * (g - 1))) & 0xFFu : 0u);
+            e_at[1][g] = eb + (ep0 >> 24) + (g ? (ep1 >> (8 * (g - 1))) & 0xFFu : 0u);
+            o_at[1][g] = ob + (op0 >> 24) + (g ? (op1 >> (8 * (g - 1))) & 0xFFu : 0u);
+        }
+    } else {
+        const uint32_t es = e0 + e1, os = o0 + o1;
+        uint32_t run = 0;   // words | halfwords << 16 of the groups before
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const uint32_t both = ((es >> (8 * g)) & 0xFFu) | (((os >> (8 * g)) & 0xFFu) << 16);
+            const uint32_t inc = uint32_t(wave_inclusive_scan(int(both))), before = run + inc - both;
+            e_at[0][g] = before & 0xFFFFu, o_at[0][g] = before >> 16;
+            e_at[1][g] = e_at[0][g] + ((e0 >> (8 * g)) & 0xFFu);
+            o_at[1][g] = o_at[0][g] + ((o0 >> (8 * g)) & 0xFFu);
+            run += uint32_t(__builtin_amdgcn_readlane(int(inc), 63));
+        }
+        e_words = run & 0xFFFFu, o_halves = run >> 16;
+    }
+    const int used = HEADER + 4 * int(e_words) + 2 * int(o_halves);
+    if (lane < 8) *reinterpret_cast<uint16_t *>(img + used + 2 * lane) = 0;
+    if (channel_major) {
+        *reinterpret_cast<uint2 *>(img + 8 * lane) = make_uint2(hdr[0], hdr[1]);
+    } else {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) *reinterpret_cast<uint16_t *>(img + D * g + 2 * lane) = uint16_t(in.header[g]);
+    }
+    uint8_t *const e_region = img + HEADER, *const o_region = img + HEADER + 4 * e_words;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const uint32_t hb = (hdr[c] >> (8 * g)) & 0xFFu, w = hb >> 4;
+            uint32_t all = hb & 15u;   // the minimum in every nibble: no nibble borrows
+            all |= all << 4;
+            all = __builtin_amdgcn_perm(0u, all, 0u);
+            const uint32_t n0 = (c ? in.codes[g][0].y : in.codes[g][0].x) - all, n1 = (c ? in.codes[g][1].y : in.codes[g][1].x) - all;
+            uint32_t *e = reinterpret_cast<uint32_t *>(e_region + 4 * e_at[c][g]);
+            if (w >= 2) e[0] = (n0 & 0x33333333u) | ((n1 << 2) & 0xCCCCCCCCu);
+            if (w == 4) e[1] = ((n0 >> 2) & 0x33333333u) | (n1 & 0xCCCCCCCCu);
+            if (w & 1) {
+                // top bit of every code, token i at bit 4 (i % 4) + i / 4
+                const uint32_t z = ((n0 >> (w - 1)) & 0x11111111u) | (((n1 >> (w - 1)) & 0x11111111u) << 2);
+                *reinterpret_cast<uint16_t *>(o_region + 2 * o_at[c][g]) = uint16_t(z | (z >> 15));
+            }
+        }
+    }
+    wave_lds_fence();
+}
+
+// Chunks of a part from their staged codes to their place, and their index words.  blockIdx.y: tensor; a wave
+// takes one chunk, so a workgroup four (waves that walk several, the next one's codes on their way, are slower: 16384 chunks
+// 25 us, two per wave 27, three 31).  Every workgroup adds up the sizes of the part's chunks
+// before its own by itself (at most 64 KB, in the L2 cache of its die after the first): no launch of a scan in between.
+__global__ __launch_bounds__(256) void assemble16_kernel(PackArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t images[4][CHUNK_MAX + 16];
     const PackTensor &t = a.t[blockIdx.y];
-    if (!staged_round(t.round, t.index)) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool paged = a.index_words == 2;  // the placement kernel has set the chunks' index pairs
     const int wg_first = blockIdx.x * 4, cl = wg_first + wave;
     const bool present = cl < a.n;
-    const bool paged = a.index_words == 2;  // the placement kernel has set the chunks' index pairs
-    // the four sizes of the workgroup in one read (the sizes area goes on behind the last one)
-    const uint4 sz = *reinterpret_cast<const uint4 *>(t.sizes16 + wg_first);
-    const uint32_t start0 = paged ? 0u : t.index[t.round.first_chunk + a.part_first];
-    const uint32_t mine = wave == 0 ? sz.x : wave == 1 ? sz.y : wave == 2 ? sz.z : sz.w;
-    const uint32_t own = (wave > 0 ? sz.x : 0u) + (wave > 1 ? sz.y : 0u) + (wave > 2 ? sz.z : 0u);
-    const int n16 = present ? int(mine) : 0;
-    // the chunk's bytes are on their way while its place is found
-    constexpr int STEPS = (CHUNK_MAX / 16 + 63) / 64;
-    // read once and written once: both with the non-temporal hint (6 % of the whole compression)
-    typedef uint32_t u32x4n __attribute__((ext_vector_type(4)));
-    const u32x4n *src = reinterpret_cast<const u32x4n *>(a.staging + size_t(blockIdx.y * a.n + cl) * CHUNK_MAX);
-    u32x4n v[STEPS];
-#pragma unroll
-    for (int i = 0; i < STEPS; ++i)
-        if (lane + 64 * i < n16) v[i] = __builtin_nontemporal_load(src + lane + 64 * i);
+    uint32_t *const index = t.index + (t.round.first_chunk + a.part_first) * a.index_words;
+    const uint2 *widths = reinterpret_cast<const uint2 *>(t.widths);
+    // one memory latency for all that the start needs
+    StagedLane in;
+    if (present) in.load(a.staging + size_t(blockIdx.y * a.n + cl) * CHUNK_MAX, lane);
+    const uint32_t first = t.index[t.round.first_chunk];
+    uint32_t place, units = 0;
     if (paged) {
-        if (!present) return;
-        const int64_t e = 2 * (t.round.first_chunk + cl);
-        const uint32_t o0 = t.index[e], o1 = t.index[e + 1];
-        u32x4n *dst = reinterpret_cast<u32x4n *>(t.arena + size_t(o0) * 16);
-        if (o1 == o0) return;  // dropped: the pool could not cover the call
+        const uint2 pair = *reinterpret_cast<const uint2 *>(index + 2 * min(cl, a.n - 1));
+        place = pair.x;
+        units = present ? pair.y - pair.x : 0;   // 0: dropped, the pool could not cover the call
+    } else {
+        place = index[0];
+        uint32_t before = 0;
+#pragma unroll 4
+        for (int i = 2 * int(threadIdx.x); i < wg_first; i += 512) {
+            const uint4 q = *reinterpret_cast<const uint4 *>(widths + i);
+            before += chunk_units(make_uint2(q.x, q.y)) + chunk_units(make_uint2(q.z, q.w));
+        }
+        // the workgroup's four chunks (the sizes area goes on behind the last one)
 #pragma unroll
-        for (int i = 0; i < STEPS; ++i)
-            if (lane + 64 * i < n16) __builtin_nontemporal_store(v[i], dst + lane + 64 * i);
-        return;
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t u = chunk_units(widths[wg_first + k]);
+            if (k < wave) place += u;
+            if (k == wave) units = u;
+        }
+        place += block_sum(before);
     }
-    uint32_t before = 0;
-#pragma unroll 1
-    for (int i = 4 * tid; i < wg_first; i += 4096) {
-        uint4 q[4];
+    if (t.round.worst16 == 0 || uint64_t(first) + t.round.worst16 > t.round.arena_cap16) return;   // not a staged round
+    if (!present || units == 0) return;
+    if (!paged && lane == 0) index[cl + 1] = place + units;
+    uint8_t *const img = images[wave];
+    assemble_chunk(in, blockIdx.y == 0, img);
+    typedef uint32_t u32x4n __attribute__((ext_vector_type(4)));
+    u32x4n *dst = reinterpret_cast<u32x4n *>(t.arena + size_t(place) * 16);
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            q[k] = i + 1024 * k < wg_first ? *reinterpret_cast<const uint4 *>(t.sizes16 + i + 1024 * k) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) before += q[k].x + q[k].y + q[k].z + q[k].w;
+    for (int i = 0; i < (CHUNK_MAX / 16 + 63) / 64; ++i) {
+        if (lane + 64 * i < int(units)) {
+            const uint4 q = *reinterpret_cast<const uint4 *>(img + 16 * (lane + 64 * i));
+            __builtin_nontemporal_store(u32x4n{q.x, q.y, q.z, q.w}, dst + lane + 64 * i);
+        }
     }
-    const uint32_t start = start0 + block_sum(before) + own;
-    if (!present) return;
-    if (lane == 0) t.index[t.round.first_chunk + a.part_first + cl + 1] = start + mine;
-    u32x4n *dst = reinterpret_cast<u32x4n *>(t.arena + size_t(start) * 16);
-#pragma unroll
-    for (int i = 0; i < STEPS; ++i)
-        if (lane + 64 * i < n16) __builtin_nontemporal_store(v[i], dst + lane + 64 * i);
 }
 
 // Two-pass rounds, one workgroup per tensor (blockIdx.x): index[first+i+1] = index[first] + sum_{j<=i} sizes16[j].
@@ -1083,7 +1531,7 @@ __global__ __launch_bounds__(1024) void place_small_kernel(PackArgs a) {
     const uint32_t held = t.page_list[0], newest_fill = t.page_list[1];
     const uint32_t newest = held ? t.page_list[1 + held] : 0u;
     const uint32_t fill0 = held ? newest_fill : P;  // no page yet: like a full one
-    for (int i = tid; i < n; i += T) S[i] = t.sizes16[i];
+    for (int i = tid; i < n; i += T) S[i] = t.widths ? chunk_units(reinterpret_cast<const uint2 *>(t.widths)[i]) : t.sizes16[i];
     __syncthreads();
     // exclusive prefix sums, S[n] = total
     const int per = (n + T - 1) / T, lo = min(tid * per, n), hi = min(lo + per, n);
@@ -1457,6 +1905,43 @@ static auto chunk8(bool stream) {
     return stream ? chunk_kernel<WRITE, 8, WIDE, true> : chunk_kernel<WRITE, 8, WIDE, false>;
 }
 
+// Whether a round of n_chunks chunks (per tensor) is staged, unless the arena turns out to be too full.
+static bool staged_rounds(const kv_cache *c, int n_chunks) {
+    const int most = c->stage_chunks / 2;
+    return c->cfg.pack_size == 16 && most >= c->cfg.n_kv_heads && (!c->pool || n_chunks <= most);
+}
+
+bool finds_params(const kv_cache *c, int n_chunks) {
+    return staged_rounds(c, n_chunks) && c->cfg.n_kv_heads <= 64 && c->cfg.repack == KV_REPACK_NONE;
+}
+
+template <int HP, bool GIVEN>
+static void launch_quantize16_as(PackArgs &a, int H, bool stream, hipStream_t s) {
+    const int waves = HP < 4 ? 1 : std::min((H + 3) / 4, GIVEN ? 4 : 16);
+    // workgroups of that many waves that fit a compute unit (0: not asked yet)
+    static std::atomic<int> per_cu_of[17];
+    int per_cu = per_cu_of[waves].load(std::memory_order_relaxed);
+    if (!per_cu) {
+        per_cu = resident_workgroups(reinterpret_cast<const void *>(quantize16_kernel<HP, GIVEN, false>), 64 * waves);
+        per_cu_of[waves].store(per_cu, std::memory_order_relaxed);
+    }
+    const int64_t items = int64_t(2) * a.rows * HP * (HP == 4 && GIVEN ? (H + 15) / 16 : 1);
+    int groups = flat_groups_for(items * 4, per_cu, int64_t(1) << 30);   // all resident, at most one per item
+    a.split = 1;
+    if (HP == 4 && !GIVEN) {
+        const int room = flat_groups_for(int64_t(1) << 40, 1, int64_t(1) << 30);
+        while (a.split < 4 && 4 * a.split < waves && items * a.split * 2 <= room) a.split *= 2;
+        groups *= a.split;
+    }
+    hipLaunchKernelGGL((stream ? quantize16_kernel<HP, GIVEN, true> : quantize16_kernel<HP, GIVEN, false>), dim3(groups), dim3(64 * waves), 0, s, a);
+}
+
+static void launch_quantize16(PackArgs &a, int H, bool given, bool stream, hipStream_t s) {
+    if (H == 1) given ? launch_quantize16_as<1, true>(a, H, stream, s) : launch_quantize16_as<1, false>(a, H, stream, s);
+    else if (H == 2) given ? launch_quantize16_as<2, true>(a, H, stream, s) : launch_quantize16_as<2, false>(a, H, stream, s);
+    else given ? launch_quantize16_as<4, true>(a, H, stream, s) : launch_quantize16_as<4, false>(a, H, stream, s);
+}
+
 int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s) {
     const int B = c->cfg.batch, H = c->cfg.n_kv_heads;
     const int n_chunks = kjob.n_blocks * B * H;
@@ -1471,7 +1956,7 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
     // Paged arena: the placement needs the sizes of the whole round, so the staged path takes the
     // rounds that fit the staging area whole (the input is then quantized once, not twice: 33 -> 21 us for
     // 2 x 1504 repacked bf16 chunks); it places whatever the pool covers, so no fill level is tested.
-    const bool staged = planes && (!c->pool || n_chunks <= c->stage_chunks / 2);
+    const bool staged = staged_rounds(c, n_chunks);
     bool two_pass = !staged;
     const bool stream = larger_than_caches(n_chunks);
     PackArgs a;
@@ -1487,6 +1972,11 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
         t.cs.magic_h = (uint64_t(1) << 32) / uint64_t(H) + 1;
         t.cs.magic_hb = (uint64_t(1) << 32) / (uint64_t(H) * uint64_t(B)) + 1;
         t.cs.meta = job.meta;
+        t.rel = job.rel;
+        const QuantRange range = quant_range(job.rel, job.qmax);
+        t.cap_all = range.cap_all;
+        t.small_scale = range.small_scale;
+        t.widths = nullptr;
         t.cs.meta_stride = c->max_tokens;
         t.cs.first_token = job.first_token;
         t.cs.order = job.order;
@@ -1504,30 +1994,33 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
         if (staged && !c->pool && job.fill_bound16 + t.round.worst16 > job.arena_cap16) two_pass = true;
     }
     a.index_words = c->index_words;
+    a.magic_b = (uint64_t(1) << 32) / uint64_t(B) + 1;
     a.first_tensor = 0;
     a.pool_state = c->pool ? c->pool->state : nullptr;
     a.staging = ws + c->stage_offset;
     if (staged) {
-        // equal parts that fit the staging area, half of its slots for each tensor
-        const int most = c->stage_chunks / 2;
-        const int parts = (n_chunks + most - 1) / most, per_part = (n_chunks + parts - 1) / parts;
-        for (int part = 0; part < n_chunks; part += per_part) {
-            a.part_first = part;
-            a.n = std::min(per_part, n_chunks - part);
-            a.t[0].sizes16 = sizes16;
-            a.t[1].sizes16 = sizes16 + ((a.n + 3) & ~3);
-            static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(chunk16_stage_kernel<false>));
-            const int groups = flat_groups_for(int64_t(a.n) * 8, per_cu, 2 * a.n);  // all resident, at most one per chunk
-            hipLaunchKernelGGL(stream ? chunk16_stage_kernel<true> : chunk16_stage_kernel<false>, dim3(groups), dim3(256), 0, s, a);
+        // equal parts of whole rows that fit the staging area, half of its slots for each tensor
+        const int rows = n_chunks / H, most = c->stage_chunks / 2 / H;
+        const int parts = (rows + most - 1) / most, per_part = (rows + parts - 1) / parts;
+        for (int part = 0; part < rows; part += per_part) {
+            a.part_row = part;
+            a.rows = std::min(per_part, rows - part);
+            a.part_first = part * H;
+            a.n = a.rows * H;
+            a.t[0].widths = reinterpret_cast<uint16_t *>(sizes16);
+            a.t[1].widths = a.t[0].widths + 4 * ((a.n + 1) & ~1);
+            launch_quantize16(a, H, !finds_params(c, n_chunks), stream, s);
             static_assert(PLACE_SMALL_CHUNKS >= 16384 / 2, "a staged round of a paged cache fits the placement kernel");
+            static_assert(16384 * 8 + 64 <= WS_SIZES_BYTES, "the width sums of a part fit the sizes area");
             if (c->pool) hipLaunchKernelGGL(place_small_kernel, dim3(1), dim3(1024), 0, s, a);
-            hipLaunchKernelGGL(chunk16_compact_kernel, dim3((a.n + 3) / 4, 2), dim3(256), 0, s, a);
+            hipLaunchKernelGGL(assemble16_kernel, dim3((a.n + 3) / 4, 2), dim3(256), 0, s, a);
         }
     }
     if (two_pass) {
         // both tensors per launch where the sizes area takes both (and, packs of 8, the layouts agree)
         a.part_first = 0;
         a.n = n_chunks;
+        a.t[0].widths = a.t[1].widths = nullptr;
         const bool both = 2 * ((n_chunks + 3) & ~3) <= MAX_NEW_CHUNKS;
         const bool same = planes || kjob.wide == vjob.wide;
         for (int i = 0; i < 2; i += both ? 2 : 1) {

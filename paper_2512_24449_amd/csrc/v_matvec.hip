@@ -318,11 +318,11 @@ int v_splits_for(int n_blocks, int streams) {
 
 // partial: [splits][B * H_q][V_PART_STRIDE] floats for the split sums; max_split_rows: how many
 // such rows it can take (the split count is lowered to fit).
-// Workgroups of 256 threads of `kernel` that fit one compute unit (registers, LDS); 1 if the
+// Workgroups of `kernel` that fit one compute unit (registers, LDS); 1 if the
 // runtime cannot tell.
-int resident_workgroups(const void *kernel) {
+int resident_workgroups(const void *kernel, int threads) {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, 256, 0) != hipSuccess || n < 1) n = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, threads, 0) != hipSuccess || n < 1) n = 1;
     return n;
 }
 

@@ -45,3 +45,32 @@ def test_append_behind_restored_contents_in_a_tight_arena():
     assert (got.overflow, got.k_bytes, got.v_bytes) == (0, want.k_bytes, want.v_bytes)
     for name, n in (("k_arena", want.k_bytes), ("v_arena", want.v_bytes)):
         assert torch.equal(tight.tensors[name][:n], full.tensors[name][:n])
+
+
+# One read of the input, packs of 16: kv-heads per wave (1, 2, 4 rows), waves per workgroup, workgroups that share an
+# item (few items: 1, 2 or 4 per item at 20 heads), more kv-heads than a workgroup holds (token parameters first)
+@pytest.mark.parametrize("B,H,blocks", [(1, 1, 2), (3, 1, 5), (2, 2, 3), (1, 3, 2), (1, 4, 1), (2, 5, 1), (1, 16, 1), (1, 17, 2),
+                                        (1, 20, 7), (2, 20, 9), (1, 33, 1), (1, 64, 1), (1, 65, 1), (1, 81, 2)])
+@pytest.mark.parametrize("repack", [False, True])
+def test_heads_per_wave_and_shared_items(B, H, blocks, repack):
+    if repack and H > 20 and H != 65:
+        pytest.skip("the oracle's order takes long; 17 and 65 heads cover the head sets")
+    gpu_cases.run_case(B, H, H, blocks * 64 + 1, seed=blocks + H, repack=repack)
+
+
+# rel: the largest quotient reaches qmax + 1/2 (every value clamped), and does not
+@pytest.mark.parametrize("rel", [0.0953, 2 / 21, 0.1, 1 / 15])
+@pytest.mark.parametrize("magnitude", [1.0, 2.0 ** -14, 2.0 ** -20, 2.0 ** -22, 2.0 ** -24])
+def test_tiny_scales_and_ties(rel, magnitude):
+    """Ranges down to fp16's smallest steps, where a scale's own rounding lets quotients pass qmax, and values on and next
+    to rounding ties: bytes against the oracle."""
+    import numpy as np
+    from paper_2512_24449_amd import binding
+    rng = np.random.default_rng(3)
+    K = (rng.integers(-12, 13, size=(1, 192, 5, 128)) * magnitude).astype(np.float16)
+    V = (rng.standard_normal((1, 192, 5, 128)) * 4 * magnitude).astype(np.float16)
+    V[0, 64:128] = (rng.integers(0, 22, size=(64, 5, 128)) * 0.5 * magnitude).astype(np.float16)
+    cache = binding.PackedKVCache(1, 5, 5, 192, k_rel_scale=rel, v_rel_scale=rel)
+    cache.kv_compress_append(torch.from_numpy(K).cuda(), torch.from_numpy(V).cuda())
+    n_packed, ck, cv = gpu_cases.oracle_cache(K, V, rel, rel)
+    gpu_cases.check_packed_state(cache, n_packed, ck, cv, 1, 5)
