@@ -46,8 +46,7 @@ struct AArgs {
     float sm_log2;                    // sm_scale * log2(e)
 };
 
-// Reductions over the 64 lanes of a wave, the result in every lane: row swaps and DPP only (a shuffle goes
-// through LDS and costs some 100 cycles of latency where the next step waits for it).
+// Maximum over the 64 lanes of a wave, in every lane (see wave_all_sum).
 __device__ inline float wave_all_max(float v) {
     uint32_t a = __float_as_uint(v), b = a;
     swap_rows32(a, b);
@@ -59,19 +58,6 @@ __device__ inline float wave_all_max(float v) {
     v = fmaxf(v, dpp_f32<DPP_ROW_ROR4>(v));
     v = fmaxf(v, dpp_f32<DPP_QUAD_XOR2>(v));
     return fmaxf(v, dpp_f32<DPP_QUAD_XOR1>(v));
-}
-
-__device__ inline float wave_all_sum(float v) {
-    uint32_t a = __float_as_uint(v), b = a;
-    swap_rows32(a, b);
-    v = __uint_as_float(a) + __uint_as_float(b);
-    a = b = __float_as_uint(v);
-    swap_rows16(a, b);
-    v = __uint_as_float(a) + __uint_as_float(b);
-    v += dpp_f32<DPP_ROW_ROR8>(v);
-    v += dpp_f32<DPP_ROW_ROR4>(v);
-    v += dpp_f32<DPP_QUAD_XOR2>(v);
-    return v + dpp_f32<DPP_QUAD_XOR1>(v);
 }
 
 // 2^(a - b) with the convention that an empty side (a = -inf) weighs nothing.
@@ -163,21 +149,27 @@ __device__ inline void attn_store_partial(const AArgs &a, const State &st, const
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < G * (D + 1); i += 256) {
-        const int g = i / (D + 1), d = i % (D + 1);
+    // four outputs to a thread
+    if (threadIdx.x < G * (D / 4)) {
+        const int g = threadIdx.x / (D / 4), d4 = threadIdx.x % (D / 4);
         const float m0 = red[0][g][D + 2], m1 = red[1][g][D + 2], m2 = red[2][g][D + 2], m3 = red[3][g][D + 2];
         const float M = fmaxf(fmaxf(m0, m1), fmaxf(m2, m3));
-        const float f0 = exp2_diff(m0, M), f1 = exp2_diff(m1, M), f2 = exp2_diff(m2, M), f3 = exp2_diff(m3, M);
-        float *dst = a.partial + (row_set * G + g) * V_PART_STRIDE;
-        if (d < D) {
+        const float f[4] = {exp2_diff(m0, M), exp2_diff(m1, M), exp2_diff(m2, M), exp2_diff(m3, M)};
+        float4 o[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
             // outputs carry the per-head sum p*min term
-            dst[d] = (f0 * (red[0][g][d] + red[0][g][D]) + f1 * (red[1][g][d] + red[1][g][D])) +
-                     (f2 * (red[2][g][d] + red[2][g][D]) + f3 * (red[3][g][d] + red[3][g][D]));
-        } else {
-            dst[A_L] = (f0 * red[0][g][D + 1] + f1 * red[1][g][D + 1]) +
-                       (f2 * red[2][g][D + 1] + f3 * red[3][g][D + 1]);
-            dst[A_M] = M;
+            const float4 x = *reinterpret_cast<const float4 *>(&red[w][g][4 * d4]);
+            const float pmin = red[w][g][D];
+            o[w] = make_float4(f[w] * (x.x + pmin), f[w] * (x.y + pmin), f[w] * (x.z + pmin), f[w] * (x.w + pmin));
         }
+        float *dst = a.partial + (row_set * G + g) * V_PART_STRIDE;
+        *reinterpret_cast<float4 *>(dst + 4 * d4) =
+            make_float4((o[0].x + o[1].x) + (o[2].x + o[3].x), (o[0].y + o[1].y) + (o[2].y + o[3].y),
+                        (o[0].z + o[1].z) + (o[2].z + o[3].z), (o[0].w + o[1].w) + (o[2].w + o[3].w));
+        if (d4 == 0)
+            *reinterpret_cast<float2 *>(dst + A_L) = make_float2((f[0] * red[0][g][D + 1] + f[1] * red[1][g][D + 1]) +
+                                                                 (f[2] * red[2][g][D + 1] + f[3] * red[3][g][D + 1]), M);
     }
 }
 
@@ -189,7 +181,8 @@ template <int G, bool HIGH, bool FLAT>
 __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
     // per wave: buffer 0 holds the K chunk (and then its tiles, k_planes.h), buffer 1 the V chunk of
     // the block in flight; between two streams the same memory holds the cross-wave reduction array
-    // red[4][G][D + 4]
+    // red[4][G][D + 4].  (A second K buffer, the next K chunk on its way while one is decoded: 41.7 -> 42.6 us for
+    // 4 x 8 streams of 512 blocks at four heads, 69.3 -> 75.9 for twice as many: two workgroups per compute unit, not three.)
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * 2 * CHUNK_LDS + LDS_TAIL_PAD];
     constexpr int VB = vb_bytes<G>();
     __shared__ __attribute__((aligned(16))) uint8_t vb_all[4 * VB];  // digit staging of the V phase
@@ -199,16 +192,13 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
     static_assert(sizeof(float) * 4 * G * (D + 4) <= 4 * 2 * CHUNK_LDS, "reduction array must fit");
     static_assert(K_TILES_BYTES <= CHUNK_LDS && CHUNK_LDS % 16 == 0, "the K tiles are built in the K buffer");
     float(*red)[G][D + 4] = reinterpret_cast<float(*)[G][D + 4]>(lds_all);
-    for (int i = threadIdx.x; i < 4 * VB / 4; i += 256) reinterpret_cast<uint32_t *>(vb_all)[i] = 0;
-    build_k_plane_table(ktable);
-    build_plane_table(vtable, vhighs);
-
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = blockIdx.x;
     const int col = lane & 15;
     const int kbuf = wave * 2 * CHUNK_LDS, vbuf = kbuf + CHUNK_LDS;
     uint8_t *vb = vb_all + wave * VB;
+    bool tables = false;
     const int64_t range_end = FLAT ? plan.begin(grp + 1) : 1;
 
     for (int64_t f = FLAT ? plan.begin(grp) : 0; f < range_end;) {
@@ -239,17 +229,35 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
 
         IndexBatch ik, iv;
         uint32_t kmt_next = 0, vmt_next = 0;
-        // index words of up to 64 blocks of this wave, then both chunks of the first of them
-        auto start_batch = [&](int first) {
+        // index words of up to 64 blocks of this wave
+        auto load_index = [&](int first) {
             if (first >= blk_end) return;
             ik.load(a.k_index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
             iv.load(a.v_index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
             const int64_t tok0 = b * a.meta_stride + int64_t(first) * N + lane;
             kmt_next = a.k_meta[tok0], vmt_next = a.v_meta[tok0];
-            chunk_issue_lds<CHUNK_MAX, HEADER, true>(a.k_arena, ik.start16(0), ik.end16(0), lds_all + kbuf, lane);
-            if (FLAT) chunk_issue_lds<CHUNK_MAX, HEADER, true>(a.v_arena, iv.start16(0), iv.end16(0), lds_all + vbuf, lane);
         };
-        start_batch(blk_begin + wave);
+        // the chunks of block `it` of the batch
+        auto issue_k = [&](int it) {
+            chunk_issue_lds<CHUNK_MAX, HEADER, true>(a.k_arena, ik.start16(it), ik.end16(it), lds_all + kbuf, lane);
+        };
+        auto issue_v = [&](int it) {
+            chunk_issue_lds<CHUNK_MAX, HEADER, true>(a.v_arena, iv.start16(it), iv.end16(it), lds_all + vbuf, lane);
+        };
+        auto issue_first = [&](int first) {
+            if (first >= blk_end) return;
+            issue_k(0);
+            issue_v(0);
+        };
+        load_index(blk_begin + wave);
+        if (!tables) {  // while the index words are on their way
+            for (int i = threadIdx.x; i < 4 * VB / 4; i += 256) reinterpret_cast<uint32_t *>(vb_all)[i] = 0;
+            build_k_plane_table<false>(ktable);
+            build_plane_table<false>(vtable, vhighs);
+            __syncthreads();
+            tables = true;
+        }
+        issue_first(blk_begin + wave);
         kq.build(lane);  // while the first chunks are on their way
         for (int first = blk_begin + wave; first < blk_end; first += 4 * 64) {
             const int n_it = min(64, (blk_end - first + 3) / 4);
@@ -260,9 +268,9 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
                 wait_chunk_landed();  // K chunk of this block
                 uint32_t kmt = kmt_next, vmt = vmt_next;
                 consume_here(kmt), consume_here(vmt);
-                if (!FLAT || it > 0) {
+                if (it > 0) {
                     lds_reads_returned();  // the previous V chunk has been read completely
-                    chunk_issue_lds<CHUNK_MAX, HEADER, true>(a.v_arena, iv.start16(it), iv.end16(it), lds_all + vbuf, lane);
+                    issue_v(it);
                 }
                 if (it + 1 < n_it) {
                     const int64_t tok = b * a.meta_stride + int64_t(first + 4 * (it + 1)) * N + lane;
@@ -283,8 +291,7 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
                 }
                 wait_chunk_landed();  // V chunk of this block
                 lds_reads_returned();  // the K tiles have been read completely before the next chunk overwrites them
-                if (it + 1 < n_it)
-                    chunk_issue_lds<CHUNK_MAX, HEADER, true>(a.k_arena, ik.start16(it + 1), ik.end16(it + 1), lds_all + kbuf, lane);
+                if (it + 1 < n_it) issue_k(it + 1);
                 if (!valid) continue;
                 float pt[G];
 #pragma unroll
@@ -296,7 +303,8 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
             }
             wait_chunk_landed();
             lds_reads_returned();  // the last V chunk has been read before the next batch's first overwrites it
-            start_batch(first + 4 * 64);
+            load_index(first + 4 * 64);
+            issue_first(first + 4 * 64);
         }
         attn_store_partial<G>(a, st, l_lane, m_ref, red, wave, lane, row_set);
         if constexpr (FLAT) __syncthreads();  // red[][][] has been read: the buffers may be filled again

@@ -46,12 +46,13 @@ static_assert(4 * N * 4 <= 1024, "the score tile reuses the minimum tile");
 
 // Per-width constants (LDS, entry w = 0..4): x = mask of plane L (whole word or 0), y = mask of
 // plane H, z / w = mask that sends the widened plane T to tile L (width 1) / tile H (width 3).
+template <bool SYNC = true>
 __device__ inline void build_k_plane_table(uint4 *table) {
     const uint32_t w = threadIdx.x;
     if (w < 5)
         table[w] = make_uint4(w >= 2 ? ~0u : 0u, w == 4 ? ~0u : 0u, w == 1 ? 0x55555555u : 0u,
                               w == 3 ? 0x55555555u : 0u);
-    __syncthreads();
+    if (SYNC) __syncthreads();
 }
 
 // The query side of the product for one (batch, kv-head) stream: lane (m = lane % 16, kb =

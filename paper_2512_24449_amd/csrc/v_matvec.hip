@@ -64,12 +64,10 @@ __global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
     static_assert(sizeof(float) * 4 * G * (D + 4) <= 4 * NBUF * BUF, "reduction array must fit");
     static_assert(BUF % 16 == 0, "buffers are 16-byte aligned");
     float(*red)[G][D + 4] = reinterpret_cast<float(*)[G][D + 4]>(lds_all);
-    for (int i = threadIdx.x; i < 4 * VB / 4; i += 256) reinterpret_cast<uint32_t *>(vb_all)[i] = 0;
-    build_plane_table(table, highs);
-
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int buf_base = wave * NBUF * BUF;
+    bool tables = false;
     uint8_t *vb = vb_all + wave * VB;
     const int grp = blockIdx.x;
     const int64_t range_end = plan.begin(grp + 1);
@@ -94,9 +92,17 @@ __global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
             return chunk_issue_lds_counted<CHUNK_BYTES, HEADER, true>(a.arena, ib.start16(it), ib.end16(it), buf, lane);
         };
 
+        IndexBatch ib;
+        auto load_index = [&](int first) {
+            if (first < blk_end) ib.load(a.index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
+        };
+        load_index(blk_begin + wave);
+        if (!tables) {  // while the index words are on their way
+            for (int i = threadIdx.x; i < 4 * VB / 4; i += 256) reinterpret_cast<uint32_t *>(vb_all)[i] = 0;
+            build_plane_table(table, highs);
+            tables = true;
+        }
         for (int first = blk_begin + wave; first < blk_end; first += 4 * 64) {
-            IndexBatch ib;
-            ib.load(a.index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
             const int n_it = min(64, (blk_end - first + 3) / 4);
             wait_chunk_landed();  // the index words (the only loads the compiler sees)
             issue(ib, 0, first, 0);
@@ -127,15 +133,20 @@ __global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
                 v_planes_chunk<G, HIGH>(lds_all, cur, table, highs, vb, mt, pt, st);
             }
             wait_chunk_landed();
+            load_index(first + 4 * 64);
         }
         __syncthreads();  // every wave is done with its chunk buffers: reuse them as red[][][]
 
         v_planes_store<G>(st, red[wave], lane);
         __syncthreads();
         float *dst = a.partial + int64_t(grp + stream) * G * V_PART_STRIDE;
-        for (int i = threadIdx.x; i < G * (D + 1); i += 256) {
-            const int g = i / (D + 1), d = i % (D + 1);
-            dst[g * V_PART_STRIDE + d] = (red[0][g][d] + red[1][g][d]) + (red[2][g][d] + red[3][g][d]);
+        if (threadIdx.x < G * (D / 4)) {
+            const int g = threadIdx.x / (D / 4), d4 = threadIdx.x % (D / 4);
+            const float4 x = *reinterpret_cast<const float4 *>(&red[0][g][4 * d4]), y = *reinterpret_cast<const float4 *>(&red[1][g][4 * d4]);
+            const float4 z = *reinterpret_cast<const float4 *>(&red[2][g][4 * d4]), w = *reinterpret_cast<const float4 *>(&red[3][g][4 * d4]);
+            *reinterpret_cast<float4 *>(dst + g * V_PART_STRIDE + 4 * d4) =
+                make_float4((x.x + y.x) + (z.x + w.x), (x.y + y.y) + (z.y + w.y), (x.z + y.z) + (z.z + w.z), (x.w + y.w) + (z.w + w.w));
+            if (d4 == 0) dst[g * V_PART_STRIDE + D] = (red[0][g][D] + red[1][g][D]) + (red[2][g][D] + red[3][g][D]);
         }
         __syncthreads();  // red[][][] has been read: the buffers may be filled again
     }

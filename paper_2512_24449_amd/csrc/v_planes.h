@@ -34,6 +34,7 @@ constexpr int v_pieces() { return G <= 3 ? 5 : 4; }
 // for width 1, bit 2 for width 3, or 0 without the plane), z, w = right rotations that bring the
 // doubled word of plane T under that mask for tokens 0..7 and 8..15.  highs[w] = mask of plane H.
 constexpr int PLANE_TABLE_ENTRIES = 5;
+template <bool SYNC = true>
 __device__ inline void build_plane_table(uint4 *table, uint32_t *highs) {
     const uint32_t w = threadIdx.x;
     if (w < PLANE_TABLE_ENTRIES) {
@@ -41,7 +42,7 @@ __device__ inline void build_plane_table(uint4 *table, uint32_t *highs) {
                               w == 3 ? 30u : 0u, w == 3 ? 0u : 2u);
         if (highs) highs[w] = w == 4 ? FIELD2_MASK : 0u;
     }
-    __syncthreads();
+    if (SYNC) __syncthreads();
 }
 
 // B operand staging per wave: digit bytes [column][token 0..63] for the columns in use, then a row
@@ -179,56 +180,101 @@ __device__ inline void v_planes_chunk(const uint8_t *lds_all, int cur, const uin
 // and the block scale was taken one above the unit.
 constexpr float V_PLANES_OUT_SCALE = 512.0f;  // 2 * 2^9 / 2
 
-template <int N_SHIFT>
-__device__ inline float row_shl0(float v) {   // lane i <- lane i + N_SHIFT of its row of 16, 0 past the row's end
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x100 + N_SHIFT, 0xF, 0xF, true));
+// Sum over the 64 lanes of a wave, the result in every lane: row swaps and DPP only (a shuffle goes
+// through LDS and costs some 100 cycles of latency where the next step waits for it).
+__device__ inline float wave_all_sum(float v) {
+    uint32_t a = __float_as_uint(v), b = a;
+    swap_rows32(a, b);
+    v = __uint_as_float(a) + __uint_as_float(b);
+    a = b = __float_as_uint(v);
+    swap_rows16(a, b);
+    v = __uint_as_float(a) + __uint_as_float(b);
+    v += dpp_f32<DPP_ROW_ROR8>(v);
+    v += dpp_f32<DPP_ROW_ROR4>(v);
+    v += dpp_f32<DPP_QUAD_XOR2>(v);
+    return v + dpp_f32<DPP_QUAD_XOR1>(v);
+}
+
+// x and y over the lanes 32 (16) apart: the lower half of the wave (even rows) returns the sum of x, the upper half
+// (odd rows) that of y.
+__device__ inline float halves_sum(float x, float y) {
+    uint32_t a = __float_as_uint(x), b = __float_as_uint(y);
+    swap_rows32(a, b);
+    return __uint_as_float(a) + __uint_as_float(b);
+}
+__device__ inline float row_pairs_sum(float x, float y) {
+    uint32_t a = __float_as_uint(x), b = __float_as_uint(y);
+    swap_rows16(a, b);
+    return __uint_as_float(a) + __uint_as_float(b);
 }
 
 // Writes this wave's sums as red[g][0..127] (outputs) and red[g][128] (the token-minimum term).
-// The digits of a head sit in neighbouring columns (lanes of a row): the first of them collects
-// the others in a fixed order.
+// The pack-minimum term goes first: the four token groups are added by row swaps, which hand every row a part of
+// the sums.  The digits of a head sit in neighbouring columns (lanes of a row); they are added in a fixed order.
+// This end of a workgroup's part is one chain of latencies; with shuffles for the minimum term and a column's first lane
+// reading and writing 32 sums one by one it took 2.2 us of a workgroup with one head, 5.4 with four.
 template <int G>
 __device__ inline void v_planes_store(const VPlaneState<G> &st, float (*red)[D + 4], int lane) {
     constexpr int NP = v_pieces<G>();
     const int rg = lane >> 4, col = lane & 15;
-    const int head = col / NP, piece = col % NP;
-    const float place = head < G ? V_PLANES_OUT_SCALE * float(1u << (4 * piece)) : 0.0f;
-    // pack-minimum term first: lanes 0..15 cover every channel of every head
+    float pm[G];
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
+    for (int g = 0; g < G; ++g) pm[g] = wave_all_sum(st.pm[g]);
+    if (lane == 0) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) red[g][D] = pm[g];
+    }
+    if constexpr (G == 4) {
+        // row r: head r, eight channels 8 col ..
+        float m[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            m[j] = row_pairs_sum(halves_sum(st.macc[0][j], st.macc[2][j]), halves_sum(st.macc[1][j], st.macc[3][j]));
+        float4 *to = reinterpret_cast<float4 *>(red[rg] + 8 * col);
+        to[0] = make_float4(m[0], m[1], m[2], m[3]);
+        to[1] = make_float4(m[4], m[5], m[6], m[7]);
+        wave_lds_fence();
+        // four digits of head col / 4: lane col % 4 = p takes the sum of row 4 rg + p of every tile
+        const bool b1 = lane & 2, b0 = lane & 1;
+        const float place = V_PLANES_OUT_SCALE * float(1u << (4 * (col & 3)));
+        float4 *row = reinterpret_cast<float4 *>(red[col >> 2] + 8 * (4 * rg + (col & 3)));
+        const float4 lo = row[0], hi = row[1];
+        float o[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            float v = st.macc[g][j];
-            v += __shfl_xor(v, 16);
-            v += __shfl_xor(v, 32);
-            if (lane < 16) red[g][8 * lane + j] = v;
+            const float v0 = st.acc[j][0] * place, v1 = st.acc[j][1] * place, v2 = st.acc[j][2] * place, v3 = st.acc[j][3] * place;
+            const float a = (b1 ? v2 : v0) + dpp_f32<DPP_QUAD_XOR2>(b1 ? v0 : v2);
+            const float b = (b1 ? v3 : v1) + dpp_f32<DPP_QUAD_XOR2>(b1 ? v1 : v3);
+            o[j] = (b0 ? b : a) + dpp_f32<DPP_QUAD_XOR1>(b0 ? a : b);
         }
-        float s = st.pm[g];
+        row[0] = make_float4(lo.x + o[0], lo.y + o[1], lo.z + o[2], lo.w + o[3]);
+        row[1] = make_float4(hi.x + o[4], hi.y + o[5], hi.z + o[6], hi.w + o[7]);
+    } else {
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-        if (lane == 0) red[g][D] = s;
-    }
-    wave_lds_fence();
-    const bool first = piece == 0 && head < G;
-    float *row = red[first ? head : 0] + 32 * rg;
+        for (int g = 0; g < G; ++g) {
+            // row r: channels 8 col + 2 r, 8 col + 2 r + 1
+            float m[2];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        // four sums at a time keep the register count of the main loop
-        float sum[4], cur[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float v = st.acc[j][r] * place;
-            float t = v + row_shl0<1>(v);
-            t += row_shl0<2>(v);
-            t += row_shl0<3>(v);
-            if constexpr (NP == 5) t += row_shl0<4>(v);
-            sum[r] = t;
+            for (int k = 0; k < 2; ++k)
+                m[k] = row_pairs_sum(halves_sum(st.macc[g][k], st.macc[g][4 + k]), halves_sum(st.macc[g][2 + k], st.macc[g][6 + k]));
+            *reinterpret_cast<float2 *>(red[g] + 8 * col + 4 * (rg >> 1) + 2 * (rg & 1)) = make_float2(m[0], m[1]);
         }
-        if (first) {
+        wave_lds_fence();
+        const int head = col / NP, piece = col % NP;
+        const float place = V_PLANES_OUT_SCALE * float(1u << (4 * piece));
+        // the sums over a head's columns, sixteen at a time: lane `col` of the row takes channel 8 (4 rg + 2 half) + col
 #pragma unroll
-            for (int r = 0; r < 4; ++r) cur[r] = row[8 * r + j];
+        for (int g = 0; g < G; ++g) {
+            const float mine = head == g ? place : 0.0f;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) row[8 * r + j] = cur[r] + sum[r];
+            for (int half = 0; half < 2; ++half) {
+                float *at = red[g] + 32 * rg + 16 * half + col;
+                const float before = *at;
+                float v[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) v[i] = st.acc[i & 7][2 * half + (i >> 3)] * mine;
+                *at = before + row_reduce_scatter16(v, lane);
+            }
         }
     }
 }
