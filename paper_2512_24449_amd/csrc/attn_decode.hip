@@ -20,6 +20,7 @@
 #include <algorithm>
 
 #include "k_planes.h"
+#include "last_group.h"
 #include "pack8.h"
 #include "v_chunk.h"
 #include "v_planes.h"
@@ -44,6 +45,11 @@ struct AArgs {
     int n_blocks;                     // packed blocks per stream
     int blocks_per_split;             // not FLAT: blocks of a workgroup
     float sm_log2;                    // sm_scale * log2(e)
+    // MERGE: the last workgroup of a stream merges its rows (else attn_combine_kernel does)
+    uint32_t *counters;
+    const __half *k_tail, *v_tail;
+    int n_tail, tail_cap;
+    float *out;
 };
 
 // Maximum over the 64 lanes of a wave, in every lane (see wave_all_sum).
@@ -132,7 +138,7 @@ __device__ inline void attn_store_state(const VPlaneState<G> &st, float (*red)[D
 // End of a workgroup's part of a stream: merges the four waves' running sums (each with its own
 // softmax reference) and writes the partial rows.  red aliases the chunk buffers (a caller that fills them
 // again passes a barrier first).
-template <int G, class State>
+template <int G, bool MERGE, class State>
 __device__ inline void attn_store_partial(const AArgs &a, const State &st, const float (&l_lane)[G],
                                           const float (&m_ref)[G], float (*red)[G][D + 4], int wave,
                                           int lane, int64_t row_set,
@@ -164,12 +170,101 @@ __device__ inline void attn_store_partial(const AArgs &a, const State &st, const
             o[w] = make_float4(f[w] * (x.x + pmin), f[w] * (x.y + pmin), f[w] * (x.z + pmin), f[w] * (x.w + pmin));
         }
         float *dst = a.partial + (row_set * G + g) * V_PART_STRIDE;
-        *reinterpret_cast<float4 *>(dst + 4 * d4) =
-            make_float4((o[0].x + o[1].x) + (o[2].x + o[3].x), (o[0].y + o[1].y) + (o[2].y + o[3].y),
-                        (o[0].z + o[1].z) + (o[2].z + o[3].z), (o[0].w + o[1].w) + (o[2].w + o[3].w));
-        if (d4 == 0)
-            *reinterpret_cast<float2 *>(dst + A_L) = make_float2((f[0] * red[0][g][D + 1] + f[1] * red[1][g][D + 1]) +
-                                                                 (f[2] * red[2][g][D + 1] + f[3] * red[3][g][D + 1]), M);
+        const float4 sum = make_float4((o[0].x + o[1].x) + (o[2].x + o[3].x), (o[0].y + o[1].y) + (o[2].y + o[3].y),
+                                       (o[0].z + o[1].z) + (o[2].z + o[3].z), (o[0].w + o[1].w) + (o[2].w + o[3].w));
+        const float l = (f[0] * red[0][g][D + 1] + f[1] * red[1][g][D + 1]) + (f[2] * red[2][g][D + 1] + f[3] * red[3][g][D + 1]);
+        if constexpr (MERGE) {
+            store_shared(dst + 4 * d4, sum.x, sum.y);
+            store_shared(dst + 4 * d4 + 2, sum.z, sum.w);
+            if (d4 == 0) store_shared(dst + A_L, l, M);
+        } else {
+            *reinterpret_cast<float4 *>(dst + 4 * d4) = sum;
+            if (d4 == 0) *reinterpret_cast<float2 *>(dst + A_L) = make_float2(l, M);
+        }
+    }
+}
+
+// The last workgroup of a stream: merges its n_sets row sets and the raw fp16 tail as attn_combine_kernel does, a
+// wave, or with one or two heads several waves, per query head.  flag, scratch: a word and 4 * 256 floats of LDS that
+// nothing else uses any more.
+template <int G>
+__device__ inline void attn_merge_stream(const AArgs &a, int stream, int b, int h, int n_sets, int64_t set_stride, uint32_t *flag,
+                                         float *scratch) {
+    if (!last_group(a.counters + stream, uint32_t(n_sets), flag)) return;
+    constexpr int W = G == 1 ? 4 : G == 2 ? 2 : 1;   // waves per head: each takes every W-th row set and 64 / W tail tokens
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = wave % W;
+    float *const weights = scratch + 256 * wave, *const sums = weights + 64;
+    const int kvh = h / a.dup, Hkv = a.H / a.dup;
+    const int sets = (n_sets - part + W - 1) / W, tail0 = part * (N / W), n_tail = max(0, min(a.n_tail - tail0, N / W));
+    for (int g = wave / W; g < G; g += 4 / W) {
+        const int64_t row = int64_t(stream) * G + g;
+        const int64_t stride = set_stride * G * V_PART_STRIDE;
+        const float *first = a.partial + row * V_PART_STRIDE + part * stride;
+        const int64_t tail_at = ((int64_t(b) * a.tail_cap + tail0) * Hkv + kvh) * D;
+        RowSum rows;
+        TailSum tail;
+        rows.load(first, W * stride, 0, sets, lane);
+        float2 lm = make_float2(0.0f, -INFINITY);
+        if (lane < sets) lm = load_shared(first + lane * W * stride + A_L);
+        if (n_tail > 0) {
+            tail.load(a.v_tail + tail_at, int64_t(Hkv) * D, 0, n_tail, lane);
+            // scores: four lanes per token, 32 channels each, sixteen tokens at a time
+            const __half *q = a.q + row * D + 32 * (lane & 3);
+            uint4 qr[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) qr[c] = *reinterpret_cast<const uint4 *>(q + 8 * c);
+#pragma unroll 1
+            for (int t0 = 0; t0 < n_tail; t0 += 16) {
+                const int t = t0 + (lane >> 2);
+                float s = 0.0f;
+                if (t < n_tail) {
+                    const __half *krow = a.k_tail + tail_at + int64_t(t) * Hkv * D + 32 * (lane & 3);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const uint4 kr = *reinterpret_cast<const uint4 *>(krow + 8 * c);
+                        const __half *kk = reinterpret_cast<const __half *>(&kr), *qq = reinterpret_cast<const __half *>(&qr[c]);
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) s = fmaf(__half2float(kk[e]), __half2float(qq[e]), s);
+                    }
+                }
+                s += dpp_f32<DPP_QUAD_XOR1>(s);
+                s += dpp_f32<DPP_QUAD_XOR2>(s);
+                if ((lane & 3) == 0) weights[t] = a.sm_log2 * s;
+            }
+            wave_lds_fence();
+        }
+        const float my_tail = lane < n_tail ? weights[lane] : -INFINITY;
+        float M = wave_all_max(fmaxf(lm.y, my_tail));
+        if constexpr (W > 1) {   // the waves of a head agree on its reference
+            if (lane == 0) sums[128] = M;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < W; ++w) M = fmaxf(M, scratch[256 * (wave - part + w) + 192]);
+        }
+        const float f = lane < sets ? exp2_diff(lm.y, M) : 0.0f, w = lane < n_tail ? exp2f(my_tail - M) : 0.0f;
+        float l = wave_all_sum(fmaf(f, lm.x, w));
+        float2 o = rows.sum(first, W * stride, sets, f, lane);
+        if (n_tail > 0) {
+            weights[lane] = w;
+            wave_lds_fence();
+            const float2 t = tail.sum(a.v_tail + tail_at, int64_t(Hkv) * D, weights, n_tail, sums, lane);
+            o.x += t.x, o.y += t.y;
+        }
+        if constexpr (W > 1) {
+            *reinterpret_cast<float2 *>(sums + 2 * lane) = o;
+            if (lane == 0) sums[129] = l;
+            __syncthreads();
+            if (part != 0) continue;
+            o = make_float2(0.0f, 0.0f), l = 0.0f;
+#pragma unroll
+            for (int p = 0; p < W; ++p) {
+                const float *theirs = sums + 256 * p;
+                const float2 v = *reinterpret_cast<const float2 *>(theirs + 2 * lane);
+                o.x += v.x, o.y += v.y, l += theirs[129];
+            }
+        }
+        const bool some = l > 0.0f;  // every block dropped and no tail: defined output
+        *reinterpret_cast<float2 *>(a.out + row * D + 2 * lane) = make_float2(some ? o.x / l : 0.0f, some ? o.y / l : 0.0f);
     }
 }
 
@@ -177,7 +272,7 @@ __device__ inline void attn_store_partial(const AArgs &a, const State &st, const
 // one work list cut into equal ranges, one per workgroup and one round of resident workgroups
 // (FlatPlan), so no last round runs nearly empty; a workgroup whose range crosses a stream
 // boundary writes a partial row set per stream.
-template <int G, bool HIGH, bool FLAT>
+template <int G, bool HIGH, bool FLAT, bool MERGE>
 __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
     // per wave: buffer 0 holds the K chunk (and then its tiles, k_planes.h), buffer 1 the V chunk of
     // the block in flight; between two streams the same memory holds the cross-wave reduction array
@@ -306,8 +401,12 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
             load_index(first + 4 * 64);
             issue_first(first + 4 * 64);
         }
-        attn_store_partial<G>(a, st, l_lane, m_ref, red, wave, lane, row_set);
-        if constexpr (FLAT) __syncthreads();  // red[][][] has been read: the buffers may be filled again
+        attn_store_partial<G, MERGE>(a, st, l_lane, m_ref, red, wave, lane, row_set);
+        if constexpr (FLAT)
+            __syncthreads();  // red[][][] has been read: the buffers may be filled again
+        else if constexpr (MERGE)
+            attn_merge_stream<G>(a, stream, b, h, gridDim.x, gridDim.y, reinterpret_cast<uint32_t *>(vhighs),
+                                 reinterpret_cast<float *>(lds_all));
     }
 }
 
@@ -321,7 +420,7 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
 // in ONE buffer, transfers overlap with the unpacking of other waves only, and three workgroups
 // fit.  The transfers carry the non-temporal hint, as those of the plane layout do: with the cache read from memory
 // 29.6 -> 28.4 us (4 x 8 streams of 156 blocks, four heads), 35.1 -> 33.0 (2 x 32 of 127, both tensors wide).
-template <int G, bool KW, bool VW>
+template <int G, bool KW, bool VW, bool MERGE>
 __global__ __launch_bounds__(256) void attn8_kernel(AArgs a) {
     constexpr bool SHARED = KW && VW;
     constexpr int KLDS = KW ? CHUNKW_LDS : CHUNK8_LDS, VLDS = SHARED ? 0 : (VW ? CHUNKW_LDS : CHUNK8_LDS);
@@ -449,7 +548,9 @@ __global__ __launch_bounds__(256) void attn8_kernel(AArgs a) {
         wait_chunk_landed();
     }
     // wide V codes enter the matrix cores as the numbers themselves
-    attn_store_partial<G>(a, st, l_lane, m_ref, red, wave, lane, int64_t(split) * gridDim.y + bh, VW ? 1.0f : CODE_SCALE_LIFTED);
+    attn_store_partial<G, MERGE>(a, st, l_lane, m_ref, red, wave, lane, int64_t(split) * gridDim.y + bh, VW ? 1.0f : CODE_SCALE_LIFTED);
+    if constexpr (MERGE)
+        attn_merge_stream<G>(a, bh, b, h, gridDim.x, gridDim.y, reinterpret_cast<uint32_t *>(table), reinterpret_cast<float *>(lds_all));
 }
 
 // Merges the splits of one (batch, query head) row in a fixed order and adds the raw fp16
@@ -547,7 +648,7 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
     const float sm_log2 = sm_scale * LOG2E;
     FlatPlan plan = FlatPlan::make(n_blocks, B, Hs);
     int n_splits = 0;
-    bool flat = false;
+    bool flat = false, merged = false;
     if (n_blocks > 0) {
         AArgs a;
         a.k_arena = static_cast<const uint8_t *>(c->buf.k_arena);
@@ -568,13 +669,26 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         n_splits = v_splits_for(n_blocks, B * Hs);
         a.blocks_per_split = (n_blocks + n_splits - 1) / n_splits;
         n_splits = (n_blocks + a.blocks_per_split - 1) / a.blocks_per_split;
+        merged = merge_in_kernel(int64_t(n_splits) * B * Hs, int64_t(B) * Hs, c->wide_k || c->wide_v);
+        a.counters = reinterpret_cast<uint32_t *>(ws + WS_STATUS) + ST_COUNTERS;
+        a.k_tail = static_cast<const __half *>(c->buf.k_tail);
+        a.v_tail = static_cast<const __half *>(c->buf.v_tail);
+        a.n_tail = c->tail_tokens;
+        a.tail_cap = c->cfg.tail_capacity;
+        a.out = out;
         const dim3 grid(n_splits, B * Hs);
-#define PACKKV_LAUNCH_A8NN(g) hipLaunchKernelGGL((attn8_kernel<g, false, false>), grid, dim3(256), 0, s, a)
-#define PACKKV_LAUNCH_A8WN(g) hipLaunchKernelGGL((attn8_kernel<g, true, false>), grid, dim3(256), 0, s, a)
-#define PACKKV_LAUNCH_A8NW(g) hipLaunchKernelGGL((attn8_kernel<g, false, true>), grid, dim3(256), 0, s, a)
-#define PACKKV_LAUNCH_A8WW(g) hipLaunchKernelGGL((attn8_kernel<g, true, true>), grid, dim3(256), 0, s, a)
-#define PACKKV_LAUNCH_A(g) hipLaunchKernelGGL((attn_kernel<g, false, false>), grid, dim3(256), 0, s, a, plan)
-#define PACKKV_LAUNCH_AH(g) hipLaunchKernelGGL((attn_kernel<g, true, false>), grid, dim3(256), 0, s, a, plan)
+#define PACKKV_LAUNCH_A8X(g, kw, vw)                                                                         \
+    if (merged) hipLaunchKernelGGL((attn8_kernel<g, kw, vw, true>), grid, dim3(256), 0, s, a);               \
+    else hipLaunchKernelGGL((attn8_kernel<g, kw, vw, false>), grid, dim3(256), 0, s, a)
+#define PACKKV_LAUNCH_A8NN(g) PACKKV_LAUNCH_A8X(g, false, false)
+#define PACKKV_LAUNCH_A8WN(g) PACKKV_LAUNCH_A8X(g, true, false)
+#define PACKKV_LAUNCH_A8NW(g) PACKKV_LAUNCH_A8X(g, false, true)
+#define PACKKV_LAUNCH_A8WW(g) PACKKV_LAUNCH_A8X(g, true, true)
+#define PACKKV_LAUNCH_AX(g, high)                                                                            \
+    if (merged) hipLaunchKernelGGL((attn_kernel<g, high, false, true>), grid, dim3(256), 0, s, a, plan);     \
+    else hipLaunchKernelGGL((attn_kernel<g, high, false, false>), grid, dim3(256), 0, s, a, plan)
+#define PACKKV_LAUNCH_A(g) PACKKV_LAUNCH_AX(g, false)
+#define PACKKV_LAUNCH_AH(g) PACKKV_LAUNCH_AX(g, true)
         // One head per kv-head and at least eight blocks for every wave of one round of resident workgroups:
         // a flat plan (8 x 52 streams of 500 blocks: 4160 workgroups at 768 resident ended in a round that was
         // two fifths full; 258 -> 239 us, 1 x 32 of 1000: 55 -> 49).  Below that the longer start-up of the plan
@@ -592,8 +706,8 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         }                                                                                              \
     }
         if (c->cfg.pack_size == 16 && G == 1) {
-            if (c->qmax_v > 7) PACKKV_LAUNCH_FLAT(attn_kernel<1, true, true>)
-            else PACKKV_LAUNCH_FLAT(attn_kernel<1, false, true>)
+            if (c->qmax_v > 7) PACKKV_LAUNCH_FLAT(attn_kernel<1, true, true, false>)
+            else PACKKV_LAUNCH_FLAT(attn_kernel<1, false, true, false>)
         }
         if (flat) {
         } else if (c->cfg.pack_size == 8) {
@@ -611,6 +725,8 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         } else {
             PACKKV_DISPATCH_GROUP4(G, PACKKV_LAUNCH_A)
         }
+#undef PACKKV_LAUNCH_A8X
+#undef PACKKV_LAUNCH_AX
 #undef PACKKV_LAUNCH_A8NN
 #undef PACKKV_LAUNCH_A8WN
 #undef PACKKV_LAUNCH_A8NW
@@ -619,10 +735,11 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
 #undef PACKKV_LAUNCH_AH
 #undef PACKKV_LAUNCH_FLAT
     }
-    hipLaunchKernelGGL(flat ? attn_combine_kernel<true> : attn_combine_kernel<false>, dim3(B * H * Gq), dim3(256), 0, s, partial,
-                       n_splits, B * H * Gq, plan, q, static_cast<const __half *>(c->buf.k_tail),
-                       static_cast<const __half *>(c->buf.v_tail), c->tail_tokens,
-                       c->cfg.tail_capacity, H, Gq, sm_log2, out);
+    if (flat || !merged)
+        hipLaunchKernelGGL(flat ? attn_combine_kernel<true> : attn_combine_kernel<false>, dim3(B * H * Gq), dim3(256), 0, s, partial,
+                           n_splits, B * H * Gq, plan, q, static_cast<const __half *>(c->buf.k_tail),
+                           static_cast<const __half *>(c->buf.v_tail), c->tail_tokens,
+                           c->cfg.tail_capacity, H, Gq, sm_log2, out);
     KV_HIP_CHECK(hipGetLastError());
     return KV_OK;
 }

@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <mutex>
 
+#include "last_group.h"
 #include "pack8.h"
 #include "v_chunk.h"
 #include "v_planes.h"
@@ -36,7 +37,81 @@ struct VArgs {
     int dup;                // H counts every kv-head dup times (query groups above 8 are split): kv-head = h / dup
     int n_blocks;           // packed blocks per stream
     int blocks_per_split;
+    // MERGE: the last workgroup of a stream merges its rows (else v_reduce_kernel does)
+    uint32_t *counters;
+    const __half *tail;     // [B][tail_cap][kv-heads][128]
+    int64_t packed_tokens;
+    int n_tail, tail_cap;
+    float *out;
 };
+
+// The sums of a workgroup's four waves, red[4][G][..], to the partial rows dst[g].
+template <int G, bool MERGE>
+__device__ inline void v_store_partial(const VArgs &a, const float (*red)[G][D + 4], float *dst) {
+    if (threadIdx.x < G * (D / 4)) {
+        const int g = threadIdx.x / (D / 4), d4 = threadIdx.x % (D / 4);
+        const float4 x = *reinterpret_cast<const float4 *>(&red[0][g][4 * d4]), y = *reinterpret_cast<const float4 *>(&red[1][g][4 * d4]);
+        const float4 z = *reinterpret_cast<const float4 *>(&red[2][g][4 * d4]), w = *reinterpret_cast<const float4 *>(&red[3][g][4 * d4]);
+        const float4 sum = make_float4((x.x + y.x) + (z.x + w.x), (x.y + y.y) + (z.y + w.y), (x.z + y.z) + (z.z + w.z), (x.w + y.w) + (z.w + w.w));
+        const float pmin = (red[0][g][D] + red[1][g][D]) + (red[2][g][D] + red[3][g][D]);
+        float *row = dst + g * V_PART_STRIDE;
+        if constexpr (MERGE) {
+            store_shared(row + 4 * d4, sum.x, sum.y);
+            store_shared(row + 4 * d4 + 2, sum.z, sum.w);
+            if (d4 == 0) store_shared(row + D, pmin, 0.0f);
+        } else {
+            *reinterpret_cast<float4 *>(row + 4 * d4) = sum;
+            if (d4 == 0) row[D] = pmin;
+        }
+    }
+}
+
+// The last workgroup of a stream: adds its n_sets row sets (the first at first_set, set_stride floats apart) and the raw
+// fp16 tail, as v_reduce_kernel does, a wave, or with one or two heads several waves, per query head.
+template <int G>
+__device__ inline void v_merge_stream(const VArgs &a, int stream, int b, int h, const float *first_set, int n_sets, int64_t set_stride,
+                                      uint32_t *flag, float *scratch) {
+    if (!last_group(a.counters + stream, uint32_t(n_sets), flag)) return;
+    constexpr int W = G == 1 ? 4 : G == 2 ? 2 : 1;   // waves per head: each takes every W-th row set and 64 / W tail tokens
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = wave % W;
+    float *const weights = scratch + 256 * wave, *const sums = weights + 64;
+    const int kvh = h / a.dup, Hkv = a.H / a.dup;
+    const int sets = (n_sets - part + W - 1) / W, tail0 = part * (N / W), n_tail = max(0, min(a.n_tail - tail0, N / W));
+    for (int g = wave / W; g < G; g += 4 / W) {
+        const int64_t row = int64_t(stream) * G + g;
+        const float *first = first_set + g * V_PART_STRIDE + part * set_stride;
+        const __half *vrow = a.tail + ((int64_t(b) * a.tail_cap + tail0) * Hkv + kvh) * D;
+        RowSum rows;
+        TailSum tail;
+        rows.load(first, W * set_stride, 0, sets, lane);
+        float pmin = 0.0f;
+        if (lane < sets) pmin = load_shared(first + lane * W * set_stride + D).x;
+        if (n_tail > 0) {
+            tail.load(vrow, int64_t(Hkv) * D, 0, n_tail, lane);
+            weights[lane] = lane < n_tail ? a.p[row * a.ld + a.packed_tokens + tail0 + lane] : 0.0f;
+            wave_lds_fence();
+        }
+        pmin = wave_all_sum(pmin);
+        float2 o = rows.sum(first, W * set_stride, sets, 1.0f, lane);
+        o.x += pmin, o.y += pmin;
+        if (n_tail > 0) {
+            const float2 t = tail.sum(vrow, int64_t(Hkv) * D, weights, n_tail, sums, lane);
+            o.x += t.x, o.y += t.y;
+        }
+        if constexpr (W > 1) {
+            *reinterpret_cast<float2 *>(sums + 2 * lane) = o;
+            __syncthreads();
+            if (part != 0) continue;
+            o = make_float2(0.0f, 0.0f);
+#pragma unroll
+            for (int p = 0; p < W; ++p) {
+                const float2 v = *reinterpret_cast<const float2 *>(sums + 256 * p + 2 * lane);
+                o.x += v.x, o.y += v.y;
+            }
+        }
+        *reinterpret_cast<float2 *>(a.out + row * D + 2 * lane) = o;
+    }
+}
 
 // Packs of 16 tokens, plane layout (v_planes.h).  HIGH: the codes of the cache may need four bits
 // (otherwise a chunk is at most 512 + 512 * 6 bytes).  The chunks of all streams form one work
@@ -47,7 +122,7 @@ struct VArgs {
 // travel the same way (one dword per lane, global memory -> LDS, behind the chunk in its buffer):
 // no vector memory instruction of the loop is visible to the compiler, so the only waits are the
 // counted ones below.
-template <int G, bool HIGH>
+template <int G, bool HIGH, bool MERGE>
 __global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
     constexpr int CHUNK_BYTES = HIGH ? CHUNK_MAX : HEADER + PACKS * 6;
     constexpr int SLICES = (CHUNK_BYTES + 1023) / 1024;
@@ -61,6 +136,7 @@ __global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
     __shared__ __attribute__((aligned(16))) uint8_t vb_all[4 * VB];
     __shared__ uint4 table[PLANE_TABLE_ENTRIES];
     __shared__ uint32_t highs[PLANE_TABLE_ENTRIES];
+    __shared__ uint32_t merge_flag;
     static_assert(sizeof(float) * 4 * G * (D + 4) <= 4 * NBUF * BUF, "reduction array must fit");
     static_assert(BUF % 16 == 0, "buffers are 16-byte aligned");
     float(*red)[G][D + 4] = reinterpret_cast<float(*)[G][D + 4]>(lds_all);
@@ -140,13 +216,11 @@ __global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
         v_planes_store<G>(st, red[wave], lane);
         __syncthreads();
         float *dst = a.partial + int64_t(grp + stream) * G * V_PART_STRIDE;
-        if (threadIdx.x < G * (D / 4)) {
-            const int g = threadIdx.x / (D / 4), d4 = threadIdx.x % (D / 4);
-            const float4 x = *reinterpret_cast<const float4 *>(&red[0][g][4 * d4]), y = *reinterpret_cast<const float4 *>(&red[1][g][4 * d4]);
-            const float4 z = *reinterpret_cast<const float4 *>(&red[2][g][4 * d4]), w = *reinterpret_cast<const float4 *>(&red[3][g][4 * d4]);
-            *reinterpret_cast<float4 *>(dst + g * V_PART_STRIDE + 4 * d4) =
-                make_float4((x.x + y.x) + (z.x + w.x), (x.y + y.y) + (z.y + w.y), (x.z + y.z) + (z.z + w.z), (x.w + y.w) + (z.w + w.w));
-            if (d4 == 0) dst[g * V_PART_STRIDE + D] = (red[0][g][D] + red[1][g][D]) + (red[2][g][D] + red[3][g][D]);
+        v_store_partial<G, MERGE>(a, red, dst);
+        if constexpr (MERGE) {
+            const int w_lo = plan.group_of(int64_t(stream) * plan.n_blocks), w_hi = plan.group_of(int64_t(stream + 1) * plan.n_blocks - 1);
+            v_merge_stream<G>(a, stream, b, h, a.partial + int64_t(w_lo + stream) * G * V_PART_STRIDE, w_hi - w_lo + 1,
+                              int64_t(G) * V_PART_STRIDE, &merge_flag, reinterpret_cast<float *>(lds_all));
         }
         __syncthreads();  // red[][][] has been read: the buffers may be filled again
     }
@@ -155,7 +229,7 @@ __global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
 // The same for chunks with packs of 8 tokens (Sec. IV-B; pack8.h).  Here and for wide chunks the transfers carry the
 // non-temporal hint too (cache read from memory: 15.6 -> 15.1 us for 32 streams of 156 blocks at four heads, wide
 // 23.0 -> 20.4 for 64 of 127; the K products gain less and lose 1 % on large caches, and go without).
-template <int G>
+template <int G, bool MERGE>
 __global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a) {
     // two chunk buffers per wave; after the main loop the same memory holds the
     // cross-wave reduction array red[4][G][D + 4]
@@ -220,16 +294,17 @@ __global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a) {
 
     v_state_store<G>(st, red[wave], lane);
     __syncthreads();
-    for (int i = threadIdx.x; i < G * (D + 1); i += 256) {
-        const int g = i / (D + 1), d = i % (D + 1);
-        const float v = (red[0][g][d] + red[1][g][d]) + (red[2][g][d] + red[3][g][d]);
-        a.partial[(int64_t(split) * a.B * a.H * G + (int64_t(b) * a.H * G + h * G + g)) * V_PART_STRIDE + d] = v;
+    const int64_t set_stride = int64_t(a.B) * a.H * G * V_PART_STRIDE;
+    float *first_set = a.partial + int64_t(bh) * G * V_PART_STRIDE;
+    v_store_partial<G, MERGE>(a, red, first_set + split * set_stride);
+    if constexpr (MERGE) {
+        v_merge_stream<G>(a, bh, b, h, first_set, gridDim.x, set_stride, reinterpret_cast<uint32_t *>(table), reinterpret_cast<float *>(lds_all));
     }
 }
 
 // Wide chunks (codes above 15; pack8.h): one buffer per wave (a chunk is up to 10 KB), so the
 // transfer is waited for before the unpack; the other waves of the compute unit overlap with it.
-template <int G>
+template <int G, bool MERGE>
 __global__ __launch_bounds__(256) void vw_matvec_kernel(VArgs a) {
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * CHUNKW_LDS + LDS_TAIL_PAD];
     __shared__ __attribute__((aligned(16))) uint8_t blds_all[4 * BLds<G>::BYTES];
@@ -274,10 +349,11 @@ __global__ __launch_bounds__(256) void vw_matvec_kernel(VArgs a) {
 
     v_state_store<G>(st, red[wave], lane, 1.0f);  // the wide path feeds the codes as numbers
     __syncthreads();
-    for (int i = threadIdx.x; i < G * (D + 1); i += 256) {
-        const int g = i / (D + 1), d = i % (D + 1);
-        const float v = (red[0][g][d] + red[1][g][d]) + (red[2][g][d] + red[3][g][d]);
-        a.partial[(int64_t(split) * a.B * a.H * G + (int64_t(b) * a.H * G + h * G + g)) * V_PART_STRIDE + d] = v;
+    const int64_t set_stride = int64_t(a.B) * a.H * G * V_PART_STRIDE;
+    float *first_set = a.partial + int64_t(bh) * G * V_PART_STRIDE;
+    v_store_partial<G, MERGE>(a, red, first_set + split * set_stride);
+    if constexpr (MERGE) {
+        v_merge_stream<G>(a, bh, b, h, first_set, gridDim.x, set_stride, reinterpret_cast<uint32_t *>(vtable), reinterpret_cast<float *>(lds_all));
     }
 }
 
@@ -381,6 +457,13 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
     a.dup = c->head_split;
     a.n_blocks = n_blocks;
     a.blocks_per_split = 0;
+    a.tail = static_cast<const __half *>(c->buf.v_tail);
+    a.packed_tokens = c->packed_tokens;
+    a.n_tail = c->tail_tokens;
+    a.tail_cap = c->cfg.tail_capacity;
+    a.out = out;
+    a.counters = static_cast<uint32_t *>(c->buf.workspace) + WS_STATUS / 4 + ST_COUNTERS;
+    bool merged = false;
     if (n_blocks > 0 && planes) {
         // row sets: one per (workgroup, stream it touches), G rows each
         if (max_split_rows / G <= int64_t(B) * Hs) return KV_ERR_CAPACITY;
@@ -389,9 +472,11 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
         const int64_t most_groups = std::min<int64_t>(int64_t(62) * B * Hs, max_split_rows / G - int64_t(B) * Hs);
 #define PACKKV_LAUNCH_VX(g, high)                                                                          \
     {                                                                                                      \
-        static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(v_matvec_kernel<g, high>)); \
+        static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(v_matvec_kernel<g, high, false>)); \
         plan.split(plan_groups_for(n_blocks, B * Hs, per_cu, most_groups));                               \
-        hipLaunchKernelGGL((v_matvec_kernel<g, high>), dim3(plan.n_groups), dim3(256), 0, s, a, plan);      \
+        merged = merge_in_kernel(plan.n_groups, int64_t(B) * Hs);                                 \
+        if (merged) hipLaunchKernelGGL((v_matvec_kernel<g, high, true>), dim3(plan.n_groups), dim3(256), 0, s, a, plan); \
+        else hipLaunchKernelGGL((v_matvec_kernel<g, high, false>), dim3(plan.n_groups), dim3(256), 0, s, a, plan); \
     }
 #define PACKKV_LAUNCH_V(g) PACKKV_LAUNCH_VX(g, false)
 #define PACKKV_LAUNCH_VH(g) PACKKV_LAUNCH_VX(g, true)
@@ -408,8 +493,13 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
         a.blocks_per_split = (n_blocks + n_splits - 1) / n_splits;
         n_splits = (n_blocks + a.blocks_per_split - 1) / a.blocks_per_split;
         dim3 grid(n_splits, B * Hs);
-#define PACKKV_LAUNCH_VW(g) hipLaunchKernelGGL(vw_matvec_kernel<g>, grid, dim3(256), 0, s, a)
-#define PACKKV_LAUNCH_V8(g) hipLaunchKernelGGL(v8_matvec_kernel<g>, grid, dim3(256), 0, s, a)
+        merged = merge_in_kernel(int64_t(n_splits) * B * Hs, int64_t(B) * Hs, c->wide_v);
+#define PACKKV_LAUNCH_VW(g)                                                                     \
+    if (merged) hipLaunchKernelGGL((vw_matvec_kernel<g, true>), grid, dim3(256), 0, s, a);      \
+    else hipLaunchKernelGGL((vw_matvec_kernel<g, false>), grid, dim3(256), 0, s, a)
+#define PACKKV_LAUNCH_V8(g)                                                                     \
+    if (merged) hipLaunchKernelGGL((v8_matvec_kernel<g, true>), grid, dim3(256), 0, s, a);      \
+    else hipLaunchKernelGGL((v8_matvec_kernel<g, false>), grid, dim3(256), 0, s, a)
         if (c->wide_v) {
             PACKKV_DISPATCH_GROUP(G, PACKKV_LAUNCH_VW)
         } else {
@@ -417,6 +507,10 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
         }
 #undef PACKKV_LAUNCH_VW
 #undef PACKKV_LAUNCH_V8
+    }
+    if (merged) {
+        KV_HIP_CHECK(hipGetLastError());
+        return KV_OK;
     }
     hipLaunchKernelGGL(v_reduce_kernel, dim3(B * H * Gq), dim3(256), 0, s, partial, n_splits,
                        B * H * Gq, plan, G, p, ld_p, c->packed_tokens,
