@@ -420,8 +420,9 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
 // in ONE buffer, transfers overlap with the unpacking of other waves only, and three workgroups
 // fit.  The transfers carry the non-temporal hint, as those of the plane layout do: with the cache read from memory
 // 29.6 -> 28.4 us (4 x 8 streams of 156 blocks, four heads), 35.1 -> 33.0 (2 x 32 of 127, both tensors wide).
+// (Three waves per SIMD where the buffers leave room for them.)
 template <int G, bool KW, bool VW, bool MERGE>
-__global__ __launch_bounds__(256) void attn8_kernel(AArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G <= 4 && KW == VW ? 3 : 1))) void attn8_kernel(AArgs a) {
     constexpr bool SHARED = KW && VW;
     constexpr int KLDS = KW ? CHUNKW_LDS : CHUNK8_LDS, VLDS = SHARED ? 0 : (VW ? CHUNKW_LDS : CHUNK8_LDS);
     constexpr int KMAX = KW ? CHUNKW_MAX : CHUNK8_MAX, VMAX = VW ? CHUNKW_MAX : CHUNK8_MAX;
@@ -433,10 +434,6 @@ __global__ __launch_bounds__(256) void attn8_kernel(AArgs a) {
     static_assert(sizeof(float) * 4 * G * (D + 4) <= 4 * (KLDS + VLDS), "reduction array must fit");
     static_assert(WIDE_TABLE_ENTRIES <= 16, "table sizes above");
     float(*red)[G][D + 4] = reinterpret_cast<float(*)[G][D + 4]>(lds_all);
-    if constexpr (!KW) build_pair_table(table);
-    if constexpr (!VW) build_pack_table(vtable, CODE_LIFT, fold_min<G>());
-    if constexpr (KW || VW) build_wide_tables(KW ? table : nullptr, VW ? vtable : nullptr);
-
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int split = blockIdx.x;
@@ -447,6 +444,19 @@ __global__ __launch_bounds__(256) void attn8_kernel(AArgs a) {
     const int64_t head0 = int64_t(b) * a.H * G + h * G;
     const int tok_in_blk = k8_token_of_block_lane(lane);
 
+    const int blk_begin = split * a.blocks_per_split;
+    const int blk_end = min(blk_begin + a.blocks_per_split, a.n_blocks);
+    IndexBatch ik, iv;
+    auto load_index = [&](int first) {
+        if (first >= blk_end) return;
+        ik.load(a.k_index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
+        iv.load(a.v_index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
+    };
+    load_index(blk_begin + wave);
+    // while the index words are on their way
+    if constexpr (!KW) build_pair_table(table);
+    if constexpr (!VW) build_pack_table(vtable, CODE_LIFT, fold_min<G>());
+    if constexpr (KW || VW) build_wide_tables(KW ? table : nullptr, VW ? vtable : nullptr);
     KQuery8<G> kq;
     kq.load(a.q + head0 * D, lane);
     VLane<G> vl;
@@ -458,12 +468,7 @@ __global__ __launch_bounds__(256) void attn8_kernel(AArgs a) {
 #pragma unroll
     for (int g = 0; g < G; ++g) m_ref[g] = -INFINITY, l_lane[g] = 0.0f;
 
-    const int blk_begin = split * a.blocks_per_split;
-    const int blk_end = min(blk_begin + a.blocks_per_split, a.n_blocks);
     for (int first = blk_begin + wave; first < blk_end; first += 4 * 64) {
-        IndexBatch ik, iv;
-        ik.load(a.k_index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
-        iv.load(a.v_index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
         const int n_it = min(64, (blk_end - first + 3) / 4);
         chunk_issue_lds<KMAX, KHDR, true>(a.k_arena, ik.start16(0), ik.end16(0), lds_all + kbuf, lane);
         const int64_t tok0 = b * a.meta_stride + int64_t(first) * N + tok_in_blk;
@@ -546,6 +551,7 @@ __global__ __launch_bounds__(256) void attn8_kernel(AArgs a) {
             }
         }
         wait_chunk_landed();
+        load_index(first + 4 * 64);
     }
     // wide V codes enter the matrix cores as the numbers themselves
     attn_store_partial<G, MERGE>(a, st, l_lane, m_ref, red, wave, lane, int64_t(split) * gridDim.y + bh, VW ? 1.0f : CODE_SCALE_LIFTED);

@@ -361,4 +361,42 @@ __device__ inline float row_all_reduce16(float v) {
     return v;
 }
 
+// Sum over the 64 lanes of a wave, the result in every lane: row swaps and DPP only (a shuffle goes
+// through LDS and costs some 100 cycles of latency where the next step waits for it).
+__device__ inline float wave_all_sum(float v) {
+    uint32_t a = __float_as_uint(v), b = a;
+    swap_rows32(a, b);
+    v = __uint_as_float(a) + __uint_as_float(b);
+    a = b = __float_as_uint(v);
+    swap_rows16(a, b);
+    v = __uint_as_float(a) + __uint_as_float(b);
+    v += dpp_f32<DPP_ROW_ROR8>(v);
+    v += dpp_f32<DPP_ROW_ROR4>(v);
+    v += dpp_f32<DPP_QUAD_XOR2>(v);
+    return v + dpp_f32<DPP_QUAD_XOR1>(v);
+}
+
+// x and y over the lanes 32 (16) apart: the lower half of the wave (even rows) returns the sum of x, the upper half
+// (odd rows) that of y.
+__device__ inline float halves_sum(float x, float y) {
+    uint32_t a = __float_as_uint(x), b = __float_as_uint(y);
+    swap_rows32(a, b);
+    return __uint_as_float(a) + __uint_as_float(b);
+}
+__device__ inline float row_pairs_sum(float x, float y) {
+    uint32_t a = __float_as_uint(x), b = __float_as_uint(y);
+    swap_rows16(a, b);
+    return __uint_as_float(a) + __uint_as_float(b);
+}
+
+// The sums of macc[0 .. 7] over the four rows of a wave (lane = channels 8 (lane % 16) ..): row r's lanes write channels 2 r and
+// 2 r + 1 of their eight to `to` (one head's 128 outputs).
+__device__ inline void store_row_sums8(const float (&macc)[8], float *to, int lane) {
+    const int row = lane >> 4;
+    float m[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) m[k] = row_pairs_sum(halves_sum(macc[k], macc[4 + k]), halves_sum(macc[2 + k], macc[6 + k]));
+    *reinterpret_cast<float2 *>(to + 8 * (lane & 15) + 4 * (row >> 1) + 2 * (row & 1)) = make_float2(m[0], m[1]);
+}
+
 }  // namespace packkv

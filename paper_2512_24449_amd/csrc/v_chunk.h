@@ -70,36 +70,45 @@ struct VState {
 
 // Writes this wave's sums as red[g][0..127] (outputs) and red[g][128] (sum p*min).
 // code_scale: what one unit of the A operand stands for (codes enter as code * 2^-24 * 2^lift).
+// (Lanes that took every output on its own and added the minimum terms by shuffles: see v_planes_store.)
 template <int G>
 __device__ inline void v_state_store(const VState<G> &st, float (*red)[D + 4], int lane,
                                      float code_scale = CODE_SCALE_LIFTED) {
     const int row = lane >> 4, col = lane & 15;
     const int head = col >> 1;
+    float pm[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) pm[g] = wave_all_sum(st.pm[g]);
+    if (lane == 0) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) red[g][D] = pm[g];
+    }
+    // hi column + lo column: the even lane keeps rows 4 row, 4 row + 1 of every tile, the odd lane the two behind
+    const bool odd = lane & 1;
+    const float scale = odd ? code_scale / 2048.0f : code_scale;
+    float o[2][8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            float v = st.acc[j][r] * ((col & 1) ? code_scale / 2048.0f : code_scale);
-            v += dpp_f32<DPP_QUAD_XOR1>(v);  // hi column + lo column
-            if (!(col & 1) && head < G) red[head][8 * (4 * row + r) + j] = v;
-        }
+        const float v0 = st.acc[j][0] * scale, v1 = st.acc[j][1] * scale, v2 = st.acc[j][2] * scale, v3 = st.acc[j][3] * scale;
+        o[0][j] = (odd ? v2 : v0) + dpp_f32<DPP_QUAD_XOR1>(odd ? v0 : v2);
+        o[1][j] = (odd ? v3 : v1) + dpp_f32<DPP_QUAD_XOR1>(odd ? v1 : v3);
     }
-    wave_lds_fence();
+    if constexpr (!fold_min<G>()) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        if constexpr (!fold_min<G>()) {
+        for (int g = 0; g < G; ++g) store_row_sums8(st.macc[g], red[g], lane);
+        wave_lds_fence();
+    }
+    if (head < G) {
+        float4 *to = reinterpret_cast<float4 *>(red[head] + 8 * (4 * row + (odd ? 2 : 0)));
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                float v = st.macc[g][j];
-                v += __shfl_xor(v, 16);
-                v += __shfl_xor(v, 32);
-                if (lane < 16) red[g][8 * lane + j] += v;
+        for (int k = 0; k < 4; ++k) {
+            float4 v = make_float4(o[k >> 1][4 * (k & 1)], o[k >> 1][4 * (k & 1) + 1], o[k >> 1][4 * (k & 1) + 2], o[k >> 1][4 * (k & 1) + 3]);
+            if constexpr (!fold_min<G>()) {
+                const float4 m = to[k];
+                v = make_float4(v.x + m.x, v.y + m.y, v.z + m.z, v.w + m.w);
             }
+            to[k] = v;
         }
-        float s = st.pm[g];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-        if (lane == 0) red[g][D] = s;
     }
 }
 

@@ -238,25 +238,27 @@ __global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a) {
     __shared__ uint4 table[PACK_TABLE_ENTRIES];
     static_assert(sizeof(float) * 4 * G * (D + 4) <= 4 * 2 * CHUNK8_LDS, "reduction array must fit");
     float(*red)[G][D + 4] = reinterpret_cast<float(*)[G][D + 4]>(lds_all);
-    build_pack_table(table, CODE_LIFT, fold_min<G>());
-
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int split = blockIdx.x;
     const int bh = blockIdx.y;
     const int h = bh % a.H, b = bh / a.H;
     const int buf_base = wave * 2 * CHUNK8_LDS;
+    const int blk_begin = split * a.blocks_per_split;
+    const int blk_end = min(blk_begin + a.blocks_per_split, a.n_blocks);
+    IndexBatch ib;
+    auto load_index = [&](int first) {
+        if (first < blk_end) ib.load(a.index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
+    };
+    load_index(blk_begin + wave);
+    build_pack_table(table, CODE_LIFT, fold_min<G>());
     VLane<G> vl;
     vl.init(blds_all + wave * BLds<G>::BYTES, lane);
     vl.bslot = v8_bslot<G>(lane);  // lane l is token l of the block
     VState<G> st;
     st.clear();
 
-    const int blk_begin = split * a.blocks_per_split;
-    const int blk_end = min(blk_begin + a.blocks_per_split, a.n_blocks);
     for (int first = blk_begin + wave; first < blk_end; first += 4 * 64) {
-        IndexBatch ib;
-        ib.load(a.index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
         const int n_it = min(64, (blk_end - first + 3) / 4);
         chunk_issue_lds<CHUNK8_MAX, HEADER8, true>(a.arena, ib.start16(0), ib.end16(0), lds_all + buf_base, lane);
         uint32_t mt_next = a.meta[b * a.meta_stride + int64_t(first) * N + lane];
@@ -289,6 +291,7 @@ __global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a) {
             v8_chunk<G>(lds_all, cur, table, vl, mt, pt, st);
         }
         wait_chunk_landed();
+        load_index(first + 4 * 64);
     }
     __syncthreads();  // every wave is done with its chunk buffers: reuse them as red[][][]
 
@@ -311,25 +314,27 @@ __global__ __launch_bounds__(256) void vw_matvec_kernel(VArgs a) {
     __shared__ uint4 vtable[16];
     static_assert(sizeof(float) * 4 * G * (D + 4) <= 4 * CHUNKW_LDS, "reduction array must fit");
     float(*red)[G][D + 4] = reinterpret_cast<float(*)[G][D + 4]>(lds_all);
-    build_wide_tables(nullptr, vtable);
-
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int split = blockIdx.x;
     const int bh = blockIdx.y;
     const int h = bh % a.H, b = bh / a.H;
     const int buf = wave * CHUNKW_LDS;
+    const int blk_begin = split * a.blocks_per_split;
+    const int blk_end = min(blk_begin + a.blocks_per_split, a.n_blocks);
+    IndexBatch ib;
+    auto load_index = [&](int first) {
+        if (first < blk_end) ib.load(a.index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
+    };
+    load_index(blk_begin + wave);
+    build_wide_tables(nullptr, vtable);
     VLane<G> vl;
     vl.init(blds_all + wave * BLds<G>::BYTES, lane);
     vl.bslot = v8_bslot<G>(lane);  // lane l is token l of the block
     VState<G> st;
     st.clear();
 
-    const int blk_begin = split * a.blocks_per_split;
-    const int blk_end = min(blk_begin + a.blocks_per_split, a.n_blocks);
     for (int first = blk_begin + wave; first < blk_end; first += 4 * 64) {
-        IndexBatch ib;
-        ib.load(a.index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
         const int n_it = min(64, (blk_end - first + 3) / 4);
         for (int it = 0; it < n_it; ++it) {
             const bool valid = ib.end16(it) - ib.start16(it) >= uint32_t(HEADERW / 16);
@@ -344,6 +349,7 @@ __global__ __launch_bounds__(256) void vw_matvec_kernel(VArgs a) {
             if (!valid) continue;  // a block dropped by an arena overflow contributes nothing
             vw_chunk<G>(lds_all, buf, vtable, vl, mt, pt, st);
         }
+        load_index(first + 4 * 64);
     }
     __syncthreads();  // every wave is done with its chunk buffer: reuse the memory as red[][][]
 

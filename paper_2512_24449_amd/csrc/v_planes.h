@@ -180,34 +180,6 @@ __device__ inline void v_planes_chunk(const uint8_t *lds_all, int cur, const uin
 // and the block scale was taken one above the unit.
 constexpr float V_PLANES_OUT_SCALE = 512.0f;  // 2 * 2^9 / 2
 
-// Sum over the 64 lanes of a wave, the result in every lane: row swaps and DPP only (a shuffle goes
-// through LDS and costs some 100 cycles of latency where the next step waits for it).
-__device__ inline float wave_all_sum(float v) {
-    uint32_t a = __float_as_uint(v), b = a;
-    swap_rows32(a, b);
-    v = __uint_as_float(a) + __uint_as_float(b);
-    a = b = __float_as_uint(v);
-    swap_rows16(a, b);
-    v = __uint_as_float(a) + __uint_as_float(b);
-    v += dpp_f32<DPP_ROW_ROR8>(v);
-    v += dpp_f32<DPP_ROW_ROR4>(v);
-    v += dpp_f32<DPP_QUAD_XOR2>(v);
-    return v + dpp_f32<DPP_QUAD_XOR1>(v);
-}
-
-// x and y over the lanes 32 (16) apart: the lower half of the wave (even rows) returns the sum of x, the upper half
-// (odd rows) that of y.
-__device__ inline float halves_sum(float x, float y) {
-    uint32_t a = __float_as_uint(x), b = __float_as_uint(y);
-    swap_rows32(a, b);
-    return __uint_as_float(a) + __uint_as_float(b);
-}
-__device__ inline float row_pairs_sum(float x, float y) {
-    uint32_t a = __float_as_uint(x), b = __float_as_uint(y);
-    swap_rows16(a, b);
-    return __uint_as_float(a) + __uint_as_float(b);
-}
-
 // Writes this wave's sums as red[g][0..127] (outputs) and red[g][128] (the token-minimum term).
 // The pack-minimum term goes first: the four token groups are added by row swaps, which hand every row a part of
 // the sums.  The digits of a head sit in neighbouring columns (lanes of a row); they are added in a fixed order.
@@ -251,14 +223,7 @@ __device__ inline void v_planes_store(const VPlaneState<G> &st, float (*red)[D +
         row[1] = make_float4(hi.x + o[4], hi.y + o[5], hi.z + o[6], hi.w + o[7]);
     } else {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            // row r: channels 8 col + 2 r, 8 col + 2 r + 1
-            float m[2];
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-                m[k] = row_pairs_sum(halves_sum(st.macc[g][k], st.macc[g][4 + k]), halves_sum(st.macc[g][2 + k], st.macc[g][6 + k]));
-            *reinterpret_cast<float2 *>(red[g] + 8 * col + 4 * (rg >> 1) + 2 * (rg & 1)) = make_float2(m[0], m[1]);
-        }
+        for (int g = 0; g < G; ++g) store_row_sums8(st.macc[g], red[g], lane);
         wave_lds_fence();
         const int head = col / NP, piece = col % NP;
         const float place = V_PLANES_OUT_SCALE * float(1u << (4 * piece));
