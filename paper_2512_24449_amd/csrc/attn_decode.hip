@@ -418,14 +418,16 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
 // two buffers per wave would leave room for one workgroup per compute unit only (measured 0.76 ms
 // at the headline shape, slower than the three-step path); the K and the V chunk then take turns
 // in ONE buffer, transfers overlap with the unpacking of other waves only, and three workgroups
-// fit.  The transfers carry the non-temporal hint, as those of the plane layout do: with the cache read from memory
+// fit.  MID: no code above 31 in a wide tensor, so that a chunk fits a smaller buffer and K and V have
+// one each (two workgroups per compute unit).  The transfers carry the non-temporal hint, as those of the plane layout do: with the cache read from memory
 // 29.6 -> 28.4 us (4 x 8 streams of 156 blocks, four heads), 35.1 -> 33.0 (2 x 32 of 127, both tensors wide).
-// (Three waves per SIMD where the buffers leave room for them.)
-template <int G, bool KW, bool VW, bool MERGE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G <= 4 && KW == VW ? 3 : 1))) void attn8_kernel(AArgs a) {
-    constexpr bool SHARED = KW && VW;
-    constexpr int KLDS = KW ? CHUNKW_LDS : CHUNK8_LDS, VLDS = SHARED ? 0 : (VW ? CHUNKW_LDS : CHUNK8_LDS);
-    constexpr int KMAX = KW ? CHUNKW_MAX : CHUNK8_MAX, VMAX = VW ? CHUNKW_MAX : CHUNK8_MAX;
+// (Three waves per SIMD where the buffers leave room for them, two with more heads.)
+template <int G, bool KW, bool VW, bool MID, bool MERGE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G <= 4 && KW == VW && !MID ? 3 : 2))) void attn8_kernel(AArgs a) {
+    constexpr bool SHARED = KW && VW && !MID;
+    constexpr int WLDS = MID ? CHUNKM_LDS : CHUNKW_LDS, WMAX = MID ? CHUNKM_MAX : CHUNKW_MAX;
+    constexpr int KLDS = KW ? WLDS : CHUNK8_LDS, VLDS = SHARED ? 0 : (VW ? WLDS : CHUNK8_LDS);
+    constexpr int KMAX = KW ? WMAX : CHUNK8_MAX, VMAX = VW ? WMAX : CHUNK8_MAX;
     constexpr int KHDR = KW ? HEADERW : HEADER8, VHDR = VW ? HEADERW : HEADER8;
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * (KLDS + VLDS) + LDS_TAIL_PAD];
     __shared__ __attribute__((aligned(16))) uint8_t blds_all[4 * BLds<G>::BYTES];
@@ -494,16 +496,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G <= 4 && K
             if (valid) {
                 float u0[G], u1[G];
                 if constexpr (KW) {
-                    const uint2 w0 = *reinterpret_cast<const uint2 *>(lds_all + kbuf + lane * 8);
-                    const uint2 m0 = *reinterpret_cast<const uint2 *>(lds_all + kbuf + 1024 + lane * 8);
-                    LanePacksW lp0;
-                    lp0.init(w0, m0, kbuf + HEADERW);
-                    kw_half<G>(lds_all, table, lp0, kq, lane, u0);
-                    const uint2 w1 = *reinterpret_cast<const uint2 *>(lds_all + kbuf + 512 + lane * 8);
-                    const uint2 m1 = *reinterpret_cast<const uint2 *>(lds_all + kbuf + 1536 + lane * 8);
-                    LanePacksW lp1;
-                    lp1.init(w1, m1, lp0.end_all);
-                    kw_half<G>(lds_all, table, lp1, kq, lane, u1);
+                    kw_chunk<G>(lds_all, kbuf, table, kq, lane, u0, u1);
                 } else {
                     const uint2 hdr0 = *reinterpret_cast<const uint2 *>(lds_all + kbuf + lane * 8);
                     LanePacks8 lp0;
@@ -683,13 +676,17 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         a.tail_cap = c->cfg.tail_capacity;
         a.out = out;
         const dim3 grid(n_splits, B * Hs);
-#define PACKKV_LAUNCH_A8X(g, kw, vw)                                                                         \
-    if (merged) hipLaunchKernelGGL((attn8_kernel<g, kw, vw, true>), grid, dim3(256), 0, s, a);               \
-    else hipLaunchKernelGGL((attn8_kernel<g, kw, vw, false>), grid, dim3(256), 0, s, a)
-#define PACKKV_LAUNCH_A8NN(g) PACKKV_LAUNCH_A8X(g, false, false)
-#define PACKKV_LAUNCH_A8WN(g) PACKKV_LAUNCH_A8X(g, true, false)
-#define PACKKV_LAUNCH_A8NW(g) PACKKV_LAUNCH_A8X(g, false, true)
-#define PACKKV_LAUNCH_A8WW(g) PACKKV_LAUNCH_A8X(g, true, true)
+        const bool mid = (!c->wide_k || c->qmax_k <= MID_QMAX) && (!c->wide_v || c->qmax_v <= MID_QMAX);
+#define PACKKV_LAUNCH_A8X(g, kw, vw, mid)                                                                    \
+    if (merged) hipLaunchKernelGGL((attn8_kernel<g, kw, vw, mid, true>), grid, dim3(256), 0, s, a);          \
+    else hipLaunchKernelGGL((attn8_kernel<g, kw, vw, mid, false>), grid, dim3(256), 0, s, a)
+#define PACKKV_LAUNCH_A8W(g, kw, vw)              \
+    if (mid) { PACKKV_LAUNCH_A8X(g, kw, vw, true); } \
+    else { PACKKV_LAUNCH_A8X(g, kw, vw, false); }
+#define PACKKV_LAUNCH_A8NN(g) PACKKV_LAUNCH_A8X(g, false, false, false)
+#define PACKKV_LAUNCH_A8WN(g) PACKKV_LAUNCH_A8W(g, true, false)
+#define PACKKV_LAUNCH_A8NW(g) PACKKV_LAUNCH_A8W(g, false, true)
+#define PACKKV_LAUNCH_A8WW(g) PACKKV_LAUNCH_A8W(g, true, true)
 #define PACKKV_LAUNCH_AX(g, high)                                                                            \
     if (merged) hipLaunchKernelGGL((attn_kernel<g, high, false, true>), grid, dim3(256), 0, s, a, plan);     \
     else hipLaunchKernelGGL((attn_kernel<g, high, false, false>), grid, dim3(256), 0, s, a, plan)
@@ -732,6 +729,7 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
             PACKKV_DISPATCH_GROUP4(G, PACKKV_LAUNCH_A)
         }
 #undef PACKKV_LAUNCH_A8X
+#undef PACKKV_LAUNCH_A8W
 #undef PACKKV_LAUNCH_AX
 #undef PACKKV_LAUNCH_A8NN
 #undef PACKKV_LAUNCH_A8WN

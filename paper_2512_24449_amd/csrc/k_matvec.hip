@@ -43,9 +43,11 @@ struct KArgs {
 // Packs of 8 tokens (Sec. IV-B), any group size: every chunk is decoded as two halves of 32
 // tokens (pack8.h).  After the two reductions lane (r, i) holds token 32 (i & 1) + 8 r + (i >> 1)
 // of the block, for every head; one 256-byte store per head.
-template <int G>
+// MID: wide chunks without codes above 31, of which two buffers fit as well (pack8.h).
+template <int G, bool MID>
 __device__ inline void k8_stream(const KArgs &a, int bh, int blk_begin, int blk_end, int wave, int lane,
                                  uint8_t *lds0, int buf_base, const uint2 *table) {
+    constexpr int LDS = MID ? CHUNKM_LDS : CHUNK8_LDS, MAXB = MID ? CHUNKM_MAX : CHUNK8_MAX, HDR = MID ? HEADERW : HEADER8;
     const int h = bh % a.H, b = bh / a.H;
     const int64_t head0 = int64_t(b) * a.H * G + h * G;
     KQuery8<G> kq;
@@ -58,14 +60,14 @@ __device__ inline void k8_stream(const KArgs &a, int bh, int blk_begin, int blk_
         ib.load(a.index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
         const int n_it = min(64, (blk_end - first + 3) / 4);
         vmem_order_fence();
-        chunk_issue_lds<CHUNK8_MAX, HEADER8>(a.arena, ib.start16(0), ib.end16(0), lds0 + buf_base, lane);
+        chunk_issue_lds<MAXB, HDR>(a.arena, ib.start16(0), ib.end16(0), lds0 + buf_base, lane);
         vmem_order_fence();
         const uint32_t *meta = a.meta + b * a.meta_stride + tok_in_blk;
         uint32_t mt_next = meta[int64_t(first) * N];
         for (int it = 0; it < n_it; ++it) {
-            const int cur = buf_base + (it & 1) * CHUNK8_LDS;
+            const int cur = buf_base + (it & 1) * LDS;
             const int64_t tok = int64_t(first + 4 * it) * N + tok_in_blk;
-            const bool valid = ib.end16(it) - ib.start16(it) >= uint32_t(HEADER8 / 16);
+            const bool valid = ib.end16(it) - ib.start16(it) >= uint32_t(HDR / 16);
             // issued after this chunk's transfers, and allowed to stay in flight: the metadata
             // load and, from the second iteration on, the previous iteration's G score stores
             if (it == 0)
@@ -75,8 +77,8 @@ __device__ inline void k8_stream(const KArgs &a, int bh, int blk_begin, int blk_
             uint32_t mt = mt_next;
             consume_here(mt);
             if (it + 1 < n_it) {
-                chunk_issue_lds<CHUNK8_MAX, HEADER8>(a.arena, ib.start16(it + 1), ib.end16(it + 1),
-                                                     lds0 + buf_base + ((it + 1) & 1) * CHUNK8_LDS, lane);
+                chunk_issue_lds<MAXB, HDR>(a.arena, ib.start16(it + 1), ib.end16(it + 1),
+                                                     lds0 + buf_base + ((it + 1) & 1) * LDS, lane);
                 vmem_order_fence();
                 mt_next = meta[int64_t(first + 4 * (it + 1)) * N];
             }
@@ -87,14 +89,18 @@ __device__ inline void k8_stream(const KArgs &a, int bh, int blk_begin, int blk_
                 continue;
             }
             float u0[G], u1[G];
-            const uint2 hdr0 = *reinterpret_cast<const uint2 *>(lds0 + cur + lane * 8);
-            LanePacks8 lp0;
-            lp0.init(hdr0.x, hdr0.y, cur + HEADER8);
-            k8_half<G>(lds0, table, lp0, kq, lane, u0);
-            const uint2 hdr1 = *reinterpret_cast<const uint2 *>(lds0 + cur + 512 + lane * 8);
-            LanePacks8 lp1;
-            lp1.init(hdr1.x, hdr1.y, lp0.end_all);
-            k8_half<G>(lds0, table, lp1, kq, lane, u1);
+            if constexpr (MID) {
+                kw_chunk<G>(lds0, cur, table, kq, lane, u0, u1);
+            } else {
+                const uint2 hdr0 = *reinterpret_cast<const uint2 *>(lds0 + cur + lane * 8);
+                LanePacks8 lp0;
+                lp0.init(hdr0.x, hdr0.y, cur + HEADER8);
+                k8_half<G>(lds0, table, lp0, kq, lane, u0);
+                const uint2 hdr1 = *reinterpret_cast<const uint2 *>(lds0 + cur + 512 + lane * 8);
+                LanePacks8 lp1;
+                lp1.init(hdr1.x, hdr1.y, lp0.end_all);
+                k8_half<G>(lds0, table, lp1, kq, lane, u1);
+            }
             const float scale = __half2float(__ushort_as_half(uint16_t(mt & 0xFFFFu)));
             const float mn = __half2float(__ushort_as_half(uint16_t(mt >> 16)));
 #pragma unroll
@@ -135,16 +141,7 @@ __device__ inline void kw_stream(const KArgs &a, int bh, int blk_begin, int blk_
                 continue;
             }
             float u0[G], u1[G];
-            const uint2 w0 = *reinterpret_cast<const uint2 *>(lds0 + buf + lane * 8);
-            const uint2 m0 = *reinterpret_cast<const uint2 *>(lds0 + buf + 1024 + lane * 8);
-            LanePacksW lp0;
-            lp0.init(w0, m0, buf + HEADERW);
-            kw_half<G>(lds0, ktable, lp0, kq, lane, u0);
-            const uint2 w1 = *reinterpret_cast<const uint2 *>(lds0 + buf + 512 + lane * 8);
-            const uint2 m1 = *reinterpret_cast<const uint2 *>(lds0 + buf + 1536 + lane * 8);
-            LanePacksW lp1;
-            lp1.init(w1, m1, lp0.end_all);
-            kw_half<G>(lds0, ktable, lp1, kq, lane, u1);
+            kw_chunk<G>(lds0, buf, ktable, kq, lane, u0, u1);
             const float scale = __half2float(__ushort_as_half(uint16_t(mt & 0xFFFFu)));
             const float mn = __half2float(__ushort_as_half(uint16_t(mt >> 16)));
 #pragma unroll
@@ -275,11 +272,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES))) vo
     }
 }
 
-template <int G>
+template <int G, bool MID>
 __global__ __launch_bounds__(256) void k8_matvec_kernel(KArgs a) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * 2 * CHUNK8_LDS + LDS_TAIL_PAD];
-    __shared__ uint2 table[PACK_TABLE_ENTRIES];
-    build_pair_table(table);
+    constexpr int LDS = MID ? CHUNKM_LDS : CHUNK8_LDS;
+    __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * 2 * LDS + LDS_TAIL_PAD];
+    __shared__ uint2 table[MID ? 16 : PACK_TABLE_ENTRIES];
+    if constexpr (MID) build_wide_tables(table, nullptr);
+    else build_pair_table(table);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = blockIdx.x;
@@ -288,7 +287,7 @@ __global__ __launch_bounds__(256) void k8_matvec_kernel(KArgs a) {
         const int part = grp % a.groups_per_stream;
         const int blk_begin = part * a.blocks_per_group;
         const int blk_end = min(blk_begin + a.blocks_per_group, a.n_blocks);
-        k8_stream<G>(a, bh, blk_begin, blk_end, wave, lane, lds_all, wave * 2 * CHUNK8_LDS, table);
+        k8_stream<G, MID>(a, bh, blk_begin, blk_end, wave, lane, lds_all, wave * 2 * LDS, table);
     } else {
         const int bh = (grp - a.n_stream_groups) * 4 + wave;
         if (bh < a.B * a.H) k_tail<G>(a, bh, lane);
@@ -348,8 +347,11 @@ int launch_k_matvec(const kv_cache *c, const __half *q, float sm_scale, float *s
     const int grid = a.n_stream_groups + tail_groups;
     if (grid == 0) return KV_OK;
 #define PACKKV_LAUNCH_KW(g) hipLaunchKernelGGL(kw_matvec_kernel<g>, dim3(grid), dim3(256), 0, s, a)
-#define PACKKV_LAUNCH_K8(g) hipLaunchKernelGGL(k8_matvec_kernel<g>, dim3(grid), dim3(256), 0, s, a)
-    if (c->wide_k) {
+#define PACKKV_LAUNCH_K8(g) hipLaunchKernelGGL((k8_matvec_kernel<g, false>), dim3(grid), dim3(256), 0, s, a)
+#define PACKKV_LAUNCH_KM(g) hipLaunchKernelGGL((k8_matvec_kernel<g, true>), dim3(grid), dim3(256), 0, s, a)
+    if (c->wide_k && c->qmax_k <= MID_QMAX) {
+        PACKKV_DISPATCH_GROUP(c->group, PACKKV_LAUNCH_KM)
+    } else if (c->wide_k) {
         PACKKV_DISPATCH_GROUP(c->group, PACKKV_LAUNCH_KW)
     } else if (c->cfg.pack_size == 8) {
         PACKKV_DISPATCH_GROUP(c->group, PACKKV_LAUNCH_K8)
@@ -379,6 +381,7 @@ int launch_k_matvec(const kv_cache *c, const __half *q, float sm_scale, float *s
     }
 #undef PACKKV_LAUNCH_KW
 #undef PACKKV_LAUNCH_K8
+#undef PACKKV_LAUNCH_KM
     KV_HIP_CHECK(hipGetLastError());
     return KV_OK;
 }

@@ -274,6 +274,10 @@ __device__ inline void v8_chunk(const uint8_t *lds_all, int cur, const uint4 *ta
 // pair into the normal numbers `code` instead, exactly: OR in the bit pattern of 1024.0, then
 // subtract 1024.0 in packed fp16 -- two instructions per word.
 constexpr int CHUNKW_LDS = CHUNKW_MAX;
+// Codes of up to 31 (relative scales down to 1/31): widths of at most 5 bits, and a buffer two thirds as large, of which a wave
+// gets two where it gets one of the others.
+constexpr int MID_QMAX = 31;
+constexpr int CHUNKM_MAX = HEADERW + N / 8 * D * 5, CHUNKM_LDS = CHUNKM_MAX;
 constexpr int WIDE_TABLE_ENTRIES = 9;   // widths 0..8
 typedef _Float16 vhalf2 __attribute__((ext_vector_type(2)));
 
@@ -368,6 +372,22 @@ __device__ inline void kw_half(const uint8_t *lds0, const uint2 *ktable, const L
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) u[g] = row_reduce_scatter8(acc[g], lane) * CODE_SCALE;
+}
+
+// Both halves of the wide chunk at byte offset `cur`.
+template <int G>
+__device__ inline void kw_chunk(const uint8_t *lds0, int cur, const uint2 *ktable, const KQuery8<G> &kq, int lane, float (&u0)[G],
+                                float (&u1)[G]) {
+    const uint2 w0 = *reinterpret_cast<const uint2 *>(lds0 + cur + lane * 8);
+    const uint2 m0 = *reinterpret_cast<const uint2 *>(lds0 + cur + 1024 + lane * 8);
+    LanePacksW lp0;
+    lp0.init(w0, m0, cur + HEADERW);
+    kw_half<G>(lds0, ktable, lp0, kq, lane, u0);
+    const uint2 w1 = *reinterpret_cast<const uint2 *>(lds0 + cur + 512 + lane * 8);
+    const uint2 m1 = *reinterpret_cast<const uint2 *>(lds0 + cur + 1536 + lane * 8);
+    LanePacksW lp1;
+    lp1.init(w1, m1, lp0.end_all);
+    kw_half<G>(lds0, ktable, lp1, kq, lane, u1);
 }
 
 // V, one wide chunk (both halves); the lane's token as in v8_chunk (K8_ORDER).  vtable:

@@ -229,21 +229,24 @@ __global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
 // The same for chunks with packs of 8 tokens (Sec. IV-B; pack8.h).  Here and for wide chunks the transfers carry the
 // non-temporal hint too (cache read from memory: 15.6 -> 15.1 us for 32 streams of 156 blocks at four heads, wide
 // 23.0 -> 20.4 for 64 of 127; the K products gain less and lose 1 % on large caches, and go without).
-template <int G, bool MERGE>
+// MID: wide chunks without codes above 31, of which two fit as well (pack8.h; with one buffer, as below, 64 streams of 127
+// blocks took 22.6 us).
+template <int G, bool MID, bool MERGE>
 __global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a) {
+    constexpr int LDS = MID ? CHUNKM_LDS : CHUNK8_LDS, MAXB = MID ? CHUNKM_MAX : CHUNK8_MAX, HDR = MID ? HEADERW : HEADER8;
     // two chunk buffers per wave; after the main loop the same memory holds the
     // cross-wave reduction array red[4][G][D + 4]
-    __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * 2 * CHUNK8_LDS + LDS_TAIL_PAD];
+    __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * 2 * LDS + LDS_TAIL_PAD];
     __shared__ __attribute__((aligned(16))) uint8_t blds_all[4 * BLds<G>::BYTES];
-    __shared__ uint4 table[PACK_TABLE_ENTRIES];
-    static_assert(sizeof(float) * 4 * G * (D + 4) <= 4 * 2 * CHUNK8_LDS, "reduction array must fit");
+    __shared__ uint4 table[MID ? 16 : PACK_TABLE_ENTRIES];
+    static_assert(sizeof(float) * 4 * G * (D + 4) <= 4 * 2 * LDS, "reduction array must fit");
     float(*red)[G][D + 4] = reinterpret_cast<float(*)[G][D + 4]>(lds_all);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int split = blockIdx.x;
     const int bh = blockIdx.y;
     const int h = bh % a.H, b = bh / a.H;
-    const int buf_base = wave * 2 * CHUNK8_LDS;
+    const int buf_base = wave * 2 * LDS;
     const int blk_begin = split * a.blocks_per_split;
     const int blk_end = min(blk_begin + a.blocks_per_split, a.n_blocks);
     IndexBatch ib;
@@ -251,7 +254,8 @@ __global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a) {
         if (first < blk_end) ib.load(a.index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
     };
     load_index(blk_begin + wave);
-    build_pack_table(table, CODE_LIFT, fold_min<G>());
+    if constexpr (MID) build_wide_tables(nullptr, table);
+    else build_pack_table(table, CODE_LIFT, fold_min<G>());
     VLane<G> vl;
     vl.init(blds_all + wave * BLds<G>::BYTES, lane);
     vl.bslot = v8_bslot<G>(lane);  // lane l is token l of the block
@@ -260,15 +264,15 @@ __global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a) {
 
     for (int first = blk_begin + wave; first < blk_end; first += 4 * 64) {
         const int n_it = min(64, (blk_end - first + 3) / 4);
-        chunk_issue_lds<CHUNK8_MAX, HEADER8, true>(a.arena, ib.start16(0), ib.end16(0), lds_all + buf_base, lane);
+        chunk_issue_lds<MAXB, HDR, true>(a.arena, ib.start16(0), ib.end16(0), lds_all + buf_base, lane);
         uint32_t mt_next = a.meta[b * a.meta_stride + int64_t(first) * N + lane];
         float p_next[G];
 #pragma unroll
         for (int g = 0; g < G; ++g)
             p_next[g] = a.p[(int64_t(b) * a.H * G + h * G + g) * a.ld + int64_t(first) * N + lane];
         for (int it = 0; it < n_it; ++it) {
-            const int cur = buf_base + (it & 1) * CHUNK8_LDS;
-            const bool valid = ib.end16(it) - ib.start16(it) >= uint32_t(HEADER8 / 16);
+            const int cur = buf_base + (it & 1) * LDS;
+            const bool valid = ib.end16(it) - ib.start16(it) >= uint32_t(HDR / 16);
             wait_chunk_landed();
             uint32_t mt = mt_next;
             consume_here(mt);
@@ -280,22 +284,23 @@ __global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a) {
             }
             // the next chunk streams into the other buffer while this one is unpacked
             if (it + 1 < n_it) {
-                chunk_issue_lds<CHUNK8_MAX, HEADER8, true>(a.arena, ib.start16(it + 1), ib.end16(it + 1),
-                                lds_all + buf_base + ((it + 1) & 1) * CHUNK8_LDS, lane);
+                chunk_issue_lds<MAXB, HDR, true>(a.arena, ib.start16(it + 1), ib.end16(it + 1),
+                                lds_all + buf_base + ((it + 1) & 1) * LDS, lane);
                 const int64_t tok = int64_t(first + 4 * (it + 1)) * N + lane;
                 mt_next = a.meta[b * a.meta_stride + tok];
 #pragma unroll
                 for (int g = 0; g < G; ++g) p_next[g] = a.p[(int64_t(b) * a.H * G + h * G + g) * a.ld + tok];
             }
             if (!valid) continue;  // a block dropped by an arena overflow contributes nothing
-            v8_chunk<G>(lds_all, cur, table, vl, mt, pt, st);
+            if constexpr (MID) vw_chunk<G>(lds_all, cur, table, vl, mt, pt, st);
+            else v8_chunk<G>(lds_all, cur, table, vl, mt, pt, st);
         }
         wait_chunk_landed();
         load_index(first + 4 * 64);
     }
     __syncthreads();  // every wave is done with its chunk buffers: reuse them as red[][][]
 
-    v_state_store<G>(st, red[wave], lane);
+    v_state_store<G>(st, red[wave], lane, MID ? 1.0f : CODE_SCALE_LIFTED);  // the wide path feeds the codes as numbers
     __syncthreads();
     const int64_t set_stride = int64_t(a.B) * a.H * G * V_PART_STRIDE;
     float *first_set = a.partial + int64_t(bh) * G * V_PART_STRIDE;
@@ -503,16 +508,22 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
 #define PACKKV_LAUNCH_VW(g)                                                                     \
     if (merged) hipLaunchKernelGGL((vw_matvec_kernel<g, true>), grid, dim3(256), 0, s, a);      \
     else hipLaunchKernelGGL((vw_matvec_kernel<g, false>), grid, dim3(256), 0, s, a)
-#define PACKKV_LAUNCH_V8(g)                                                                     \
-    if (merged) hipLaunchKernelGGL((v8_matvec_kernel<g, true>), grid, dim3(256), 0, s, a);      \
-    else hipLaunchKernelGGL((v8_matvec_kernel<g, false>), grid, dim3(256), 0, s, a)
-        if (c->wide_v) {
+#define PACKKV_LAUNCH_V8X(g, mid)                                                               \
+    if (merged) hipLaunchKernelGGL((v8_matvec_kernel<g, mid, true>), grid, dim3(256), 0, s, a); \
+    else hipLaunchKernelGGL((v8_matvec_kernel<g, mid, false>), grid, dim3(256), 0, s, a)
+#define PACKKV_LAUNCH_V8(g) PACKKV_LAUNCH_V8X(g, false)
+#define PACKKV_LAUNCH_VM(g) PACKKV_LAUNCH_V8X(g, true)
+        if (c->wide_v && c->qmax_v <= MID_QMAX) {
+            PACKKV_DISPATCH_GROUP(G, PACKKV_LAUNCH_VM)
+        } else if (c->wide_v) {
             PACKKV_DISPATCH_GROUP(G, PACKKV_LAUNCH_VW)
         } else {
             PACKKV_DISPATCH_GROUP(G, PACKKV_LAUNCH_V8)
         }
 #undef PACKKV_LAUNCH_VW
 #undef PACKKV_LAUNCH_V8
+#undef PACKKV_LAUNCH_VM
+#undef PACKKV_LAUNCH_V8X
     }
     if (merged) {
         KV_HIP_CHECK(hipGetLastError());
