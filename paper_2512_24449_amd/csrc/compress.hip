@@ -967,6 +967,13 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
     Item cur = locate(item);
     uint4 raw[16];
     uint4 order = make_uint4(0, 0, 0, 0), order_next = order;   // storage order of the item's tokens, and of the next one's
+    // token metadata (GIVEN) of the lane's token cg, of the item and of the next one: ahead of what waits for the order
+    auto meta_of = [&](const Item &m) {
+        const ChunkSource &cs = a.t[m.v].cs;
+        return cs.meta + m.b * cs.meta_stride + cs.first_token + int64_t(m.blk) * N + 16 * (m.g0 + group_in_item);
+    };
+    uint32_t given = 0;
+    if constexpr (GIVEN) given = meta_of(cur)[cg];
     if (ordered) order = order_of(cur), order_next = order_of(locate(min(item + int(gridDim.x), n_items - 1)));
     {
         const __amdgpu_buffer_rsrc_t buffer = buffer_of(cur, true);
@@ -977,7 +984,6 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
         const PackTensor &pt = a.t[cur.v];
         const ChunkSource &cs = pt.cs;
         const int g = cur.g0 + group_in_item;
-        uint32_t *meta = cs.meta + cur.b * cs.meta_stride + cs.first_token + int64_t(cur.blk) * N + 16 * g;
         const int next = item + int(gridDim.x);   // (split: past the end)
         const bool more = next < n_items;
         const Item nxt = locate(more ? next : item);
@@ -988,7 +994,9 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
             for (int t = 0; t < 16; ++t) raw[t] = as_fp16(raw[t], true);
         }
         if constexpr (GIVEN) {
-            tok[HP < 4 ? lane : cg] = token_quant_near(meta[cg], pt.small_scale);
+            const uint32_t now = given;
+            given = meta_of(nxt)[cg];
+            tok[HP < 4 ? lane : cg] = token_quant_near(now, pt.small_scale);
         } else {
             uint32_t v[16];
 #pragma unroll
@@ -1029,7 +1037,7 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
             const int t = 2 * (cg & 7) + (cg >> 3);
             const uint32_t mt = token_meta_word(half_lo(mnw), -half_lo(mxw), pt.rel);
             tok[HP < 4 ? 16 * row4 + t : t] = token_quant_near(mt, pt.small_scale);
-            if (HP == 4 ? threadIdx.x < 16 : head_in_set == 0) meta[t] = mt;
+            if (HP == 4 ? threadIdx.x < 16 : head_in_set == 0) meta_of(cur)[t] = mt;
             if (split > 1 && ((wave >> 2) & (split - 1)) != int(blockIdx.x) / n_items) return;   // another workgroup's heads
         }
         wave_lds_fence();
@@ -1731,38 +1739,81 @@ __global__ void init_kernel(uint32_t *status, uint32_t *k_index, uint32_t *v_ind
     }
 }
 
-// V-median repacking, step 1, codes below 16 (packs of 16): a wave per token quantizes with the packs' fixed-point
-// rule and counts every code with ballots; the lower median is the first code whose running count
-// passes the middle.  (A workgroup per token with per-thread counters and 1e-3 wide guards, which
-// sent most waves to the divide: 28.6 us for 12032 tokens of 1024 values.)
-template <bool STREAM>
-__global__ __launch_bounds__(256) void v_median16_key_kernel(const __half *__restrict__ src, int64_t batch_stride,
-                                                             int64_t token_stride, int row_elems, int qmax,
-                                                             const uint32_t *__restrict__ meta, int64_t meta_stride,
-                                                             int64_t first_token, int n_tokens,
-                                                             uint8_t *__restrict__ keys, bool bf16) {
+// Token parameters of both tensors (blockIdx.z) and V-median repacking, step 1, in one, codes below 16 (packs of 16): a
+// wave holds a token's row of up to NREG * 512 values in registers, finds its scale and minimum, and of V
+// quantizes it with the packs' fixed-point rule and counts every code with ballots; the lower median is the first code
+// whose running count passes the middle.  NREG = 0, longer rows: read again for the codes.
+// Bound by the counts, 120 ballots for 512 values.  One kernel instead of two that both read V: 12032 tokens of 1024
+// values 12 + 15.5 -> 17.6 us, 7936 tokens of 6656 values 31 + 39 -> 63 (those all in registers: 140, the unrolled
+// counts overflow the instruction cache; 4096 values read twice: 40.0 instead of 35.5).
+template <int NREG, bool STREAM>
+__global__ __launch_bounds__(256) void token_params_keys_kernel(ParamArgs a, int n_tokens, int qmax, uint8_t *__restrict__ keys) {
     const int lane = threadIdx.x & 63, t = blockIdx.x * 4 + (threadIdx.x >> 6), b = blockIdx.y;
     if (t >= n_tokens) return;
-    const __half *row = src + b * batch_stride + t * token_stride;
-    const float4 tq = token_quant(meta[b * meta_stride + first_token + t]);
+    const ParamTensor &pt = a.t[blockIdx.z];
+    const __half *row = pt.src + b * a.batch_stride + t * a.token_stride;
+    uint4 x[NREG ? NREG : 1];
+    uint32_t mn = 0x7C007C00u, mx = 0xFC00FC00u;
+    auto widen = [&](const uint4 &v) {
+        mn = pk_min_f16(mn, pk_min_f16(pk_min_f16(v.x, v.y), pk_min_f16(v.z, v.w)));
+        mx = pk_max_f16(mx, pk_max_f16(pk_max_f16(v.x, v.y), pk_max_f16(v.z, v.w)));
+    };
+    if constexpr (NREG == 0) {
+        for (int e = 8 * lane; e < a.row_elems; e += 512) widen(as_fp16(load8<STREAM>(row + e), a.bf16));
+    }
+#pragma unroll
+    for (int k = 0; k < NREG; ++k)
+        if (512 * k + 8 * lane < a.row_elems) x[k] = load8<STREAM>(row + 512 * k + 8 * lane);
+#pragma unroll
+    for (int k = 0; k < NREG; ++k)
+        if (512 * k + 8 * lane < a.row_elems) widen(x[k] = as_fp16(x[k], a.bf16));
+    mx ^= 0x80008000u;
+    // minimum in the low half, negated maximum in the high half
+    uint32_t w = pk_min_f16(__builtin_amdgcn_perm(mx, mn, 0x05040100u), __builtin_amdgcn_perm(mx, mn, 0x07060302u)), y = w;
+    swap_rows32(w, y);
+    y = w = pk_min_f16(w, y);
+    swap_rows16(w, y);
+    w = pk_min_f16(w, y);
+    w = pk_min_f16(w, dpp_u32<DPP_ROW_ROR8>(w));
+    w = pk_min_f16(w, dpp_u32<DPP_ROW_ROR4>(w));
+    w = pk_min_f16(w, dpp_u32<DPP_QUAD_XOR2>(w));
+    w = pk_min_f16(w, dpp_u32<DPP_QUAD_XOR1>(w));
+    const uint32_t mt = token_meta_word(half_lo(w), -half_hi(w), pt.rel);
+    const int64_t at = b * a.meta_stride + a.first_token + t;
+    if (lane == 0) pt.meta[at] = mt;
+    if (blockIdx.z == 0) return;
+    const float4 tq = token_quant(mt);
     int count[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) count[v] = 0;
-    for (int i = 0; i < row_elems; i += 512) {
+    auto tally = [&](const uint4 &v, bool present) {
         uint32_t pair[4] = {0, 0, 0, 0};  // no code where the row has ended
-        if (i + 8 * lane < row_elems) quantize_token8(load8_as_fp16<STREAM>(row + i + 8 * lane, bf16), tq, uint32_t(qmax), pair);
+        if (present) quantize_token8(v, tq, uint32_t(qmax), pair);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            if (v < qmax) {  // the last code's count is what is left
+        for (int c = 0; c < 16; ++c) {
+            if (c < qmax) {  // the last code's count is what is left
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    count[v] += __popcll(__builtin_amdgcn_ballot_w64((pair[k] & 0xFFFFu) == 0x4300u + v));
-                    count[v] += __popcll(__builtin_amdgcn_ballot_w64((pair[k] >> 16) == 0x4300u + v));
+                for (int i = 0; i < 4; ++i) {
+                    count[c] += __popcll(__builtin_amdgcn_ballot_w64((pair[i] & 0xFFFFu) == 0x4300u + c));
+                    count[c] += __popcll(__builtin_amdgcn_ballot_w64((pair[i] >> 16) == 0x4300u + c));
                 }
             }
         }
+    };
+    if constexpr (NREG == 0) {
+        for (int e0 = 0; e0 < a.row_elems; e0 += 512) {
+            const int e = e0 + 8 * lane;
+            x[0] = make_uint4(0, 0, 0, 0);
+            if (e < a.row_elems) x[0] = as_fp16(load8<STREAM>(row + e), a.bf16);
+            tally(x[0], e < a.row_elems);
+        }
     }
-    const int rank = (row_elems - 1) / 2;
+#pragma unroll
+    for (int k = 0; k < NREG; ++k) {
+        if (512 * k >= a.row_elems) break;
+        tally(x[k], 512 * k + 8 * lane < a.row_elems);
+    }
+    const int rank = (a.row_elems - 1) / 2;
     int seen = 0, key = qmax;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
@@ -1771,7 +1822,7 @@ __global__ __launch_bounds__(256) void v_median16_key_kernel(const __half *__res
             if (seen > rank && key == qmax) key = v;
         }
     }
-    if (lane == 0) keys[b * meta_stride + first_token + t] = uint8_t(key);
+    if (lane == 0) keys[at] = uint8_t(key);
 }
 
 // V-median repacking, step 1 (Sec. III-B.3): the lower median of the H*128 quantized V codes of
@@ -1899,6 +1950,11 @@ int launch_tail_copy(const kv_cache *c, const __half *ksrc, const __half *vsrc, 
     return KV_OK;
 }
 
+// The V-median keys come with the token parameters (codes of the fixed-point rule).
+static bool keys_with_params(const kv_cache *c) {
+    return c->cfg.repack == KV_REPACK_V_MEDIAN && c->cfg.pack_size == 16 && c->qmax_v < 16;
+}
+
 int launch_token_params(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s) {
     const int B = c->cfg.batch, H = c->cfg.n_kv_heads;
     const int n_tokens = kjob.n_blocks * N;
@@ -1913,6 +1969,20 @@ int launch_token_params(const kv_cache *c, const CompressJob &kjob, const Compre
     a.row_elems = H * D;
     a.bf16 = kjob.bf16;
     const bool wave = a.row_elems <= 2048, stream = larger_than_caches(int64_t(kjob.n_blocks) * B * H);
+    if (keys_with_params(c)) {
+        uint8_t *keys = static_cast<uint8_t *>(c->buf.token_order);
+        const dim3 grid((n_tokens + 3) / 4, B, 2);
+#define PACKKV_LAUNCH_KEYS(nreg)                                                                                                   \
+    hipLaunchKernelGGL((stream ? token_params_keys_kernel<nreg, true> : token_params_keys_kernel<nreg, false>), grid, dim3(256), 0, s, a, \
+                       n_tokens, vjob.qmax, keys)
+        if (a.row_elems <= 1024) PACKKV_LAUNCH_KEYS(2);
+        else if (a.row_elems <= 2048) PACKKV_LAUNCH_KEYS(4);
+        else if (a.row_elems <= 4096) PACKKV_LAUNCH_KEYS(8);
+        else PACKKV_LAUNCH_KEYS(0);
+#undef PACKKV_LAUNCH_KEYS
+        KV_HIP_CHECK(hipGetLastError());
+        return KV_OK;
+    }
     auto kernel = wave ? (stream ? token_params_kernel<true, true> : token_params_kernel<true, false>)
                        : (stream ? token_params_kernel<false, true> : token_params_kernel<false, false>);
     hipLaunchKernelGGL(kernel, dim3(wave ? (n_tokens + 3) / 4 : n_tokens, B, 2), dim3(256), 0, s, a, n_tokens);
@@ -1926,11 +1996,7 @@ int launch_v_median_order(const kv_cache *c, const CompressJob &vjob, uint32_t *
     const int n_tokens = vjob.n_blocks * N;
     if (n_tokens <= 0 || H * D / 2048 + 1 > 31) return KV_ERR_ARG;  // 8-bit per-thread counters
     const bool stream = larger_than_caches(int64_t(vjob.n_blocks) * B * H);
-    if (vjob.qmax < 16 && c->cfg.pack_size == 16)
-        hipLaunchKernelGGL(stream ? v_median16_key_kernel<true> : v_median16_key_kernel<false>, dim3((n_tokens + 3) / 4, B), dim3(256), 0, s, vjob.src, vjob.batch_stride,
-                           vjob.token_stride, H * D, vjob.qmax, vjob.meta, c->max_tokens, vjob.first_token, n_tokens, order,
-                           vjob.bf16);
-    else
+    if (!keys_with_params(c))
         hipLaunchKernelGGL(stream ? v_median_key_kernel<true> : v_median_key_kernel<false>, dim3(n_tokens, B), dim3(256), 0, s, vjob.src,
                            vjob.batch_stride, vjob.token_stride, H * D, vjob.qmax, vjob.meta,
                            c->max_tokens, vjob.first_token, order, vjob.bf16);

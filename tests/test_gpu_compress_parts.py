@@ -74,3 +74,10 @@ def test_tiny_scales_and_ties(rel, magnitude):
     cache.kv_compress_append(torch.from_numpy(K).cuda(), torch.from_numpy(V).cuda())
     n_packed, ck, cv = gpu_cases.oracle_cache(K, V, rel, rel)
     gpu_cases.check_packed_state(cache, n_packed, ck, cv, 1, 5)
+
+
+# Token parameters and V-median keys in one kernel: rows of up to 1024, 2048 and 4096 values in registers, longer ones
+# read twice; a last piece of 512 values that is not full
+@pytest.mark.parametrize("H", [8, 9, 31, 32, 33, 66])
+def test_rows_of_keys_and_token_parameters(H):
+    gpu_cases.run_case(1, H, H, 64, seed=H, repack=True)
