@@ -35,7 +35,7 @@ ROTATE_BYTES = 1.1e9             # working set to rotate over so reads come from
 # kernel takes 20 % longer in the first milliseconds after an idle phase).  Every timed loop below is
 # therefore preceded by an untimed run of the same kernels for this long, before the W warmup steps.
 CLOCK_RAMP_S = 0.5
-DOM_KERNEL = {"k": "k_planes_kernel<1, 5>", "v": "v_matvec_kernel<1, false>"}   # names in the profiles
+DOM_KERNEL = {"k": "k_planes_kernel<1, 5>", "v": "v_matvec_kernel<1, false, false>"}   # names in the profiles
 
 
 def stored_profile_numbers(workload, dom):
@@ -473,10 +473,10 @@ def run_compress(w, K, V, torch, binding):
     return {"prompt_ms": round(ms, 3), "fp16_input_gbps": round(in_bytes / (ms * 1e-3) / 1e9, 1),
             "pct_hbm_peak_on_input": round(100.0 * in_bytes / (ms * 1e-3) / 8e12, 2),
             "tail_flush_ms": round(flush_ms, 4),
-            "hbm_bytes_per_input_byte": "about 2.5 (stored: profiles/hbm_traffic_llama2_30b_32k_b8.txt): the input is "
-                                        "read twice (token minimum and maximum, then quantization), the packed bytes "
-                                        "are written to a staging slot, read back and written to their place",
-            "note": "staged path, every value quantized once; bound by HBM traffic"}
+            "hbm_bytes_per_input_byte": "about 1.7 (stored: profiles/hbm_traffic_llama2_30b_32k_b8.txt): the input is "
+                                        "read once, its codes are written to a staging slot as nibbles, read back and "
+                                        "written to their place as planes",
+            "note": "staged path, every value read and quantized once; bound by the quantizer's arithmetic next to its traffic"}
 
 
 def run_repack(w, torch, binding, synth):
