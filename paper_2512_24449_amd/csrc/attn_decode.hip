@@ -676,7 +676,14 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         a.tail_cap = c->cfg.tail_capacity;
         a.out = out;
         const dim3 grid(n_splits, B * Hs);
-        const bool mid = (!c->wide_k || c->qmax_k <= MID_QMAX) && (!c->wide_v || c->qmax_v <= MID_QMAX);
+        // MID with both tensors wide: while all its workgroups, two to a compute unit, run at once; beyond, three with one
+        // buffer that K and V share do as well or better (with MID / without: 16000 chunks 45.0 / 51.1 us, four
+        // heads 59.6 / 67.8, 20000 65.6 / 62.0, 24000 66.2 / 62.7, 40000 99.6 / 97.8, 208000 466 / 451; only two full rounds,
+        // 32000, 80.8 / 86.3).  With one wide
+        // tensor two workgroups fit either way, and MID is faster at all sizes (208000 chunks 351 / 406, 382 / 432).
+        const bool both = c->wide_k && c->wide_v;
+        const bool mid = (!c->wide_k || c->qmax_k <= MID_QMAX) && (!c->wide_v || c->qmax_v <= MID_QMAX) &&
+                         (!both || n_splits * B * Hs <= mid_room());
 #define PACKKV_LAUNCH_A8X(g, kw, vw, mid)                                                                    \
     if (merged) hipLaunchKernelGGL((attn8_kernel<g, kw, vw, mid, true>), grid, dim3(256), 0, s, a);          \
     else hipLaunchKernelGGL((attn8_kernel<g, kw, vw, mid, false>), grid, dim3(256), 0, s, a)

@@ -63,13 +63,15 @@ inline int64_t target_workgroups(int64_t total_blocks) {
 int resident_workgroups(const void *kernel, int threads = 256);
 int flat_groups_for(int64_t total, int per_cu, int64_t most);
 int plan_groups_for(int n_blocks, int streams, int per_cu, int64_t most);
+// Workgroups of the kernels for wide chunks with two smaller buffers to a wave (pack8.h) that run at once.
+inline int mid_room() { return flat_groups_for(int64_t(1) << 40, 2, int64_t(1) << 30); }
 
 // Staging area of the compressor (packs of 16): chunks it holds, half of them for each tensor, each in
 // a slot of the largest chunk's size.  64 blocks of both tensors at a time, within 512 .. 16384 chunks
 // (2.4 .. 75 MB) and no more than the cache can hold: large enough to fill the chip, small enough to
 // stay in the last-level cache until it is read back.  A cache also works with half of that (least =
-// true), in twice as many parts: 4096 tokens of 32 streams take 42.8 us in one part and 50.0 in two, with 18.9
-// and 9.4 MB of staging; 16384 tokens of 8 streams 72 and 105, with 4.7 and 2.4 MB.
+// true), in twice as many parts: 4096 tokens of 32 streams take 28.9 us in one part and 40.2 in two, with 18.9
+// and 9.4 MB of staging; 16384 tokens of 8 streams 60.8 and 98.5, with 4.7 and 2.4 MB.
 inline int stage_chunks_for(int batch, int n_kv_heads, int64_t max_chunks, bool least = false) {
     const int64_t want = int64_t(batch) * n_kv_heads * (least ? 64 : 128);
     const int64_t some = want < (least ? 256 : 512) ? (least ? 256 : 512) : want > 16384 ? 16384 : want;

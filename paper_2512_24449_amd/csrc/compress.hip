@@ -46,10 +46,10 @@ __device__ inline uint4 as_fp16(uint4 raw, bool bf16) {
 }
 // A round whose input is larger than the last-level cache (256 MB; both tensors): its kernels read with the non-
 // temporal hint (STREAM), which keeps the input from pushing out what is read again, the staged chunks for one. The
-// input of a smaller round is still in the caches when its second and third kernel read it, which the hint would
-// not make use of.  Without / with the hint: packs of 8, 67 MB 80 / 84 us, 262 MB 243 / 265, 393 MB 389 / 381, 1.7 GB
-// 1648 / 1618; packs of 16, 67 MB 42.8 / 43.8 (repacked 61.5 / 64), 262 MB 165 / 165, 393 MB 244 / 241, a block of
-// 416 streams 18.1 / 18.9.
+// input of a smaller round may still be in the caches from what wrote it or is read again from them (packs of 8, repacked
+// tokens), which the hint would not make use of.  Without / with the hint: packs of 8, 67 MB 80 / 84 us, 262 MB 243 / 265, 393 MB 389 / 381, 1.7 GB
+// 1648 / 1618; packs of 16, 67 MB 28.9 / 29.5 (repacked 53.0 / 54.5), 255 MB 116.8 / 116.0, 788 MB 277 / 267, a block of
+// 416 streams 16.1 / 17.4.
 inline bool larger_than_caches(int64_t n_chunks) { return n_chunks * 2 * (N * D * 2) > (int64_t(256) << 20); }
 
 __device__ inline uint4 load8_nt(const __half *p) {

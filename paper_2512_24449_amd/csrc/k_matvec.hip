@@ -349,7 +349,11 @@ int launch_k_matvec(const kv_cache *c, const __half *q, float sm_scale, float *s
 #define PACKKV_LAUNCH_KW(g) hipLaunchKernelGGL(kw_matvec_kernel<g>, dim3(grid), dim3(256), 0, s, a)
 #define PACKKV_LAUNCH_K8(g) hipLaunchKernelGGL((k8_matvec_kernel<g, false>), dim3(grid), dim3(256), 0, s, a)
 #define PACKKV_LAUNCH_KM(g) hipLaunchKernelGGL((k8_matvec_kernel<g, true>), dim3(grid), dim3(256), 0, s, a)
-    if (c->wide_k && c->qmax_k <= MID_QMAX) {
+    // MID while all its workgroups, two to a compute unit, run at once: beyond, the kernel with one larger buffer and more
+    // workgroups is the faster one, a second round that is partly full counting most (append, K, softmax, V with MID / without:
+    // 16000 chunks 55.7 / 60.4 us, four heads 76.4 / 79.5, 20000 in 640 workgroups 83.6 / 77.1, 25000 95.1 / 92.4, 52000 159 /
+    // 158, 208000 536 / 520; 32000 in 1024 workgroups 106 / 114 or, in more and shorter streams, 106 / 103).
+    if (c->wide_k && c->qmax_k <= MID_QMAX && a.n_stream_groups <= mid_room()) {
         PACKKV_DISPATCH_GROUP(c->group, PACKKV_LAUNCH_KM)
     } else if (c->wide_k) {
         PACKKV_DISPATCH_GROUP(c->group, PACKKV_LAUNCH_KW)

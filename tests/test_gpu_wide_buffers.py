@@ -45,3 +45,24 @@ def test_largest_chunks(levels, Hq):
 @pytest.mark.parametrize("H,Hq,L", [(2, 2, 9 * 64 + 1), (1, 5, 4 * 64), (3, 24, 6 * 64 + 63)])
 def test_mixed_layouts(k_rel, v_rel, H, Hq, L):
     gpu_cases.run_case(1, H, Hq, L, seed=Hq, pack_size=8, k_rel=k_rel, v_rel=v_rel)
+
+
+# More workgroups than the kernels with two smaller buffers run at once: the other kernels take codes of up to 31 as well.
+# Both batch elements have the same contents, and a cache of one of them stays on the near side of the line (all its
+# results depend on its own tokens only): about 480 and 960 workgroups on either side of a line at 512.
+@pytest.mark.parametrize("Hq", [40, 120])
+def test_both_sides_of_the_line_between_buffers(Hq):
+    B, H, L = 2, 40, 400 * 64 + 5
+    g = torch.Generator(device="cuda:0").manual_seed(Hq)
+    K, V = (torch.randn((1, L, H, 128), generator=g, device="cuda:0").to(torch.float16) for _ in range(2))
+    q = torch.randn((1, Hq, 128), generator=g, device="cuda:0").to(torch.float16)
+    got = []
+    for batch in (1, B):
+        cache = binding.PackedKVCache(batch, H, Hq, L, k_rel_scale=1 / 31, v_rel_scale=1 / 31, pack_size=8)
+        cache.kv_compress_append(K.expand(batch, -1, -1, -1).contiguous(), V.expand(batch, -1, -1, -1).contiguous())
+        qb = q.expand(batch, -1, -1).contiguous()
+        got.append((cache.kv_k_matvec(qb, 0.05)[:, :, :L].cpu().numpy(), cache.kv_decode_attention(qb, 0.05).cpu().numpy()))
+        assert cache.kv_cache_stats().overflow == 0
+    for b in range(B):
+        gpu_cases.assert_close_vectors(got[1][0][b], got[0][0][0], "K", tol=1e-5)
+        gpu_cases.assert_close_vectors(got[1][1][b], got[0][1][0], "fused", tol=1e-5)
