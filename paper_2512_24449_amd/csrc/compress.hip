@@ -725,6 +725,9 @@ __device__ inline uint32_t pk_max3_f16(uint32_t x, uint32_t y, uint32_t z) {
     asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
     return r;
 }
+// The two above take the other operand where one is a NaN.  With the mode register's IEEE bit (9) set, as kernels start, a
+// signalling NaN would come out as a quiet one instead, and the other operand be lost.
+__device__ inline void ieee_mode_off() { __builtin_amdgcn_s_setreg(1 | (9 << 6), 0); }
 template <int CTRL>
 __device__ inline uint32_t dpp_u32(uint32_t v) {
     return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, 0xF, 0xF, true));
@@ -791,6 +794,7 @@ __device__ inline uint32_t wave_min_scatter16(const uint32_t (&v)[16]) {
 // t against quotient + 1/2 + g is below 0.5 (its rounding) + 0.5 (c; 2^(e-8) for e >= 8) + 0.12 (r) + 0.13 (the
 // definition's roundings) units, so g = 2 (+ 2^(e-7)) does: a third fewer divides, which matters here, where all waves
 // of a token wait for the slowest.  A token whose scale is so small that codes could pass qmax always divides.
+// r and c come divided by 256 (exactly: they are powers of two away from underflow), for half_mul_add_unit.
 __device__ inline float4 token_quant_near(uint32_t mt, float small_scale) {
     const float s = __half2float(__ushort_as_half(uint16_t(mt & 0xFFFFu)));
     const float mn = __half2float(__ushort_as_half(uint16_t(mt >> 16)));
@@ -799,10 +803,23 @@ __device__ inline float4 token_quant_near(uint32_t mt, float small_scale) {
     uint32_t g = 2u + (e >= 8 ? 2u << min(e - 8, 14) : 0u);
     const float c = fmaf(-mn, r, 128.5f + float(g) * (1.0f / 65536.0f));
     if (s > 0.0f && s < small_scale) g = 1u << 15;
-    return make_float4(r, c, __uint_as_float(2u * g), __uint_as_float(mt));
+    return make_float4(r * (1.0f / 256.0f), c * (1.0f / 256.0f), __uint_as_float(2u * g), __uint_as_float(mt));
 }
 
-// Quantizes four tokens (eight channels each): pair[i][k] as quantize_token8 has it for token i.  The tokens that hold a
+// half_mul_add clamped to 0 .. 1: with the operands of token_quant_near t / 256, in [1/2, 1), whose bits 16.. are 0x3F00 + code.
+// A NaN becomes 0 and what is too large 1: their low 16 bits are 0, so both take the divide, whose minimum gives them a code
+// in range, and no other token's code sees them.
+template <bool HI>
+__device__ inline float half_mul_add_unit(uint32_t two_halves, float r, float c) {
+    float t;
+    if (HI)
+        asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0] clamp" : "=v"(t) : "v"(two_halves), "v"(r), "v"(c));
+    else
+        asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[1,0,0] clamp" : "=v"(t) : "v"(two_halves), "v"(r), "v"(c));
+    return t;
+}
+
+// Quantizes four tokens (eight channels each): pair[i][k] = 0x3F00 + code of values 2k (low half) and 2k + 1 of token i.  The tokens that hold a
 // value near a rounding tie take the divide, one after the other (every second wave meets one in 16 tokens).
 // tok: token_quant_near of the four tokens, every second entry.  cap_all: clamp every value (see QuantRange).
 __device__ inline void quantize_quad(const uint4 (&x)[4], const float4 *tok, uint32_t qmax, bool cap_all, uint32_t (&pair)[4][4]) {
@@ -814,8 +831,8 @@ __device__ inline void quantize_quad(const uint4 (&x)[4], const float4 *tok, uin
         unsigned short near = 0xFFFF;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const uint32_t t0 = __float_as_uint(half_mul_add<false>(w[k], tq.x, tq.y));
-            const uint32_t t1 = __float_as_uint(half_mul_add<true>(w[k], tq.x, tq.y));
+            const uint32_t t0 = __float_as_uint(half_mul_add_unit<false>(w[k], tq.x, tq.y));
+            const uint32_t t1 = __float_as_uint(half_mul_add_unit<true>(w[k], tq.x, tq.y));
             near = min(min(near, (unsigned short)t0), (unsigned short)t1);
             pair[i][k] = __builtin_amdgcn_perm(t1, t0, 0x07060302u);
         }
@@ -823,7 +840,7 @@ __device__ inline void quantize_quad(const uint4 (&x)[4], const float4 *tok, uin
         any |= near_lanes[i];
     }
     if (cap_all) {
-        const uint32_t cap = (0x4300u + qmax) * 0x10001u;
+        const uint32_t cap = (0x3F00u + qmax) * 0x10001u;
 #pragma unroll
         for (int i = 0; i < 16; ++i) pair[i >> 2][i & 3] = pk_min(pair[i >> 2][i & 3], cap);
     }
@@ -842,13 +859,13 @@ __device__ inline void quantize_quad(const uint4 (&x)[4], const float4 *tok, uin
         const float s = __half2float(__ushort_as_half(uint16_t(mt & 0xFFFFu)));
         const float mn = __half2float(__ushort_as_half(uint16_t(mt >> 16)));
         const float top = float(qmax);
-        const uint32_t keep = s != 0.0f ? ~0u : 0x43004300u;
+        const uint32_t keep = s != 0.0f ? ~0u : 0x3F003F00u;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             __builtin_amdgcn_sched_barrier(0);   // two at a time, in few registers
             const float q0 = (half_lo(w[k]) - mn) / s, q1 = (half_hi(w[k]) - mn) / s;   // IEEE fp32 divide
             const uint32_t c0 = __builtin_amdgcn_cvt_pk_u8_f32(fminf(q0, top), 0u, 0u), c1 = __builtin_amdgcn_cvt_pk_u8_f32(fminf(q1, top), 0u, 0u);
-            const uint32_t both = (0x43004300u + (c0 | (c1 << 16))) & keep;
+            const uint32_t both = (0x3F003F00u + (c0 | (c1 << 16))) & keep;
 #pragma unroll
             for (int j = 0; j < 4; ++j) pair[j][k] = i == j ? both : pair[j][k];
         }
@@ -893,6 +910,7 @@ inline QuantRange quant_range(float rel, int qmax) {
 template <int HP, bool GIVEN, bool STREAM>
 __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_kernel(PackArgs a) {
     constexpr int MOST_WAVES = HP < 4 ? 1 : GIVEN ? 4 : 16;
+    ieee_mode_off();
     __shared__ uint32_t red[2][MOST_WAVES][16];
     __shared__ float4 tok_all[MOST_WAVES][HP < 4 ? 64 : 16];
     const int lane = threadIdx.x & 63, cg = lane & 15, row4 = lane >> 4;
@@ -1060,7 +1078,7 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
             for (int i = 0; i < 4; ++i) raw[first + 2 * i] = load_token(nxt, next_buffer, order, first + 2 * i);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                // (0x4300 + code is an fp16 number between 3.5 and 3.53)
+                // (0x3F00 + code is an fp16 number between 1.75 and 1.77)
                 const uint32_t lo = pk_min3_f16(pair[0][k], pair[1][k], pair[2][k]), hi = pk_max3_f16(pair[0][k], pair[1][k], pair[2][k]);
                 mn2[k] = quad ? pk_min3_f16(mn2[k], lo, pair[3][k]) : pk_min(lo, pair[3][k]);
                 mx2[k] = quad ? pk_max3_f16(mx2[k], hi, pair[3][k]) : pk_max(hi, pair[3][k]);
@@ -1082,7 +1100,7 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
             }
         }
         // headers: bytes (width << 4) | minimum of the lane's eight packs
-        // (the masks: a NaN may leave any byte, the header has to be one all the same; widths are at most 4 for any bytes)
+        // (codes are at most 15; the masks keep the header one for any bytes, of which width_bytes makes at most 4)
         const uint32_t m_lo = __builtin_amdgcn_perm(mn2[1], mn2[0], 0x06040200u) & 0x0F0F0F0Fu;
         const uint32_t m_hi = __builtin_amdgcn_perm(mn2[3], mn2[2], 0x06040200u) & 0x0F0F0F0Fu;
         const uint32_t x_lo = __builtin_amdgcn_perm(mx2[1], mx2[0], 0x06040200u), x_hi = __builtin_amdgcn_perm(mx2[3], mx2[2], 0x06040200u);
@@ -1750,6 +1768,7 @@ template <int NREG, bool STREAM>
 __global__ __launch_bounds__(256) void token_params_keys_kernel(ParamArgs a, int n_tokens, int qmax, uint8_t *__restrict__ keys) {
     const int lane = threadIdx.x & 63, t = blockIdx.x * 4 + (threadIdx.x >> 6), b = blockIdx.y;
     if (t >= n_tokens) return;
+    ieee_mode_off();
     const ParamTensor &pt = a.t[blockIdx.z];
     const __half *row = pt.src + b * a.batch_stride + t * a.token_stride;
     uint4 x[NREG ? NREG : 1];
