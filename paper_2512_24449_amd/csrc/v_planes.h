@@ -120,7 +120,9 @@ __device__ inline void v_planes_chunk(const uint8_t *lds_all, int cur, const uin
         const float w = pt[g] * scale;
         // the chunk's unit: with E the biased exponent of the largest weight, weights are counted
         // in steps of 2^(E - 126 - BITS), so every count stays below 2^BITS
-        const int E = int(wave_max_bits(w) >> 23);
+        // (at most 255: a block whose weights all carry a sign, NaNs for one, adds less than 2^116 to a column's sums all the
+        // same; v_planes_store weights them with 0 for the other heads, which an infinite sum would turn into a NaN)
+        const int E = min(255, int(wave_max_bits(w) >> 23));
         const int mul_field = min(254, 253 + BITS - E);     // 2^(BITS + 126 - E), capped
         const int unit_field = max(0, E + 1 - BITS);        // 2^(E - 126 - BITS), or 0 below the float range
         const float y = fmaf(w, __int_as_float(mul_field << 23), MAGIC);  // round to nearest even
