@@ -245,6 +245,7 @@ struct PackArgs {
     PackTensor t[2];        // K, V
     int part_first, n;      // chunks part_first .. part_first + n - 1 of the round, in both tensors
     int part_row, rows;     // the same in rows of H chunks (row = blk*B + b)
+    int round_rows;         // rows of the whole round
     uint64_t magic_b;       // floor(2^32 / B) + 1
     int index_words;
     int first_tensor;       // a launch whose grid covers one tensor: which (else 0)
@@ -674,8 +675,9 @@ __device__ inline void copy_image(const ChunkLds &lds, int slot, int n16, uint8_
 // few tens of MB) instead of the input.  A round is cut into parts
 // that fit the staging area.  The path runs when even the largest chunks fit the arena (worst16 =
 // chunks of the round times the largest chunk, checked on the device, where the fill level is), so
-// no part can overflow and a round keeps or drops its chunks as a whole; otherwise the second kernel
-// returns at once and the two-pass kernels do the round, and the other way round.
+// no part can overflow and a round keeps or drops its chunks as a whole; otherwise the first kernel finds the token
+// metadata only (nothing where it is given), the second returns at once and the two-pass kernels do the round, and the
+// other way round.
 __device__ inline bool staged_round(const StagedRound &r, const uint32_t *index) {
     return r.worst16 != 0 && uint64_t(index[r.first_chunk]) + r.worst16 <= r.arena_cap16;
 }
@@ -907,7 +909,10 @@ inline QuantRange quant_range(float rel, int qmax) {
 // split: few items leave most of the chip idle, and up to 16 waves of one compute unit then share its
 // vector units; with split workgroups per item, each reads it all and quantizes a part of the heads (8 x 52 heads, one block:
 // flush 19.0 us with one workgroup per item, 16.4 with two, 15.5 with four).
-template <int HP, bool GIVEN, bool STREAM>
+// UNSURE: the round may not be staged, and the kernel finds out first (at run time the question alone cost sure rounds 1 %, a
+// block of 8 x 52 heads 16.0 -> 16.4 us).  Not staged, 8000 tokens of 8 x 52 heads take 1025 us, 4096 of 32 55; quantized
+// all the same, and thrown away, 1305 and 67.
+template <int HP, bool GIVEN, bool STREAM, bool UNSURE>
 __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_kernel(PackArgs a) {
     constexpr int MOST_WAVES = HP < 4 ? 1 : GIVEN ? 4 : 16;
     ieee_mode_off();
@@ -918,7 +923,10 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
     float4 *tok = tok_all[wave];
     const int H = a.t[0].cs.H, B = a.t[0].cs.B;
     const int sets = HP == 4 && GIVEN ? (H + 15) / 16 : 1;   // workgroups that share the heads of an item
-    const int per_tensor = a.rows * HP * sets, n_items = 2 * per_tensor;
+    // of a tensor whose round is not staged the first part takes the token metadata of the whole round, if it is not given
+    const bool skip_k = UNSURE && !staged_round(a.t[0].round, a.t[0].index), skip_v = UNSURE && !staged_round(a.t[1].round, a.t[1].index);
+    const int skip_rows = GIVEN || a.part_row ? 0 : a.round_rows;
+    const int items_k = (skip_k ? skip_rows : a.rows) * HP * sets, n_items = items_k + (skip_v ? skip_rows : a.rows) * HP * sets;
     const int token_bytes = int(2 * a.t[0].cs.token_stride);
 
     struct Item {
@@ -926,8 +934,8 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
     };
     auto locate = [&](int item) {
         Item m;
-        m.v = item >= per_tensor;
-        int rest = item - (m.v ? per_tensor : 0);
+        m.v = item >= items_k;
+        int rest = item - (m.v ? items_k : 0);
         m.set = 0;
         if (sets > 1) {
             m.set = rest % sets;
@@ -979,7 +987,7 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
         return make_uint4(v.x, v.y, v.z, v.w);
     };
     // split > 1: n_items * split workgroups, one item each (those of an item on the same die)
-    const int split = HP == 4 && !GIVEN ? a.split : 1;
+    const int split = HP == 4 && !GIVEN && !skip_k && !skip_v ? a.split : 1;
     int item = split > 1 ? int(blockIdx.x) % n_items : int(blockIdx.x);
     if (item >= n_items) return;
     Item cur = locate(item);
@@ -1025,6 +1033,12 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
                 v[k] = pk_min_f16(__builtin_amdgcn_perm(q_mn, p_mn, 0x05040100u), __builtin_amdgcn_perm(q_mn, p_mn, 0x07060302u));
                 v[8 + k] = pk_max_f16(__builtin_amdgcn_perm(q_mx, p_mx, 0x05040100u), __builtin_amdgcn_perm(q_mx, p_mx, 0x07060302u)) ^ 0x80008000u;
             }
+            const bool skip = cur.v ? skip_v : skip_k;
+            if (skip) {
+                const __amdgpu_buffer_rsrc_t buffer = buffer_of(nxt, more);
+#pragma unroll
+                for (int t = 0; t < 16; ++t) raw[t] = load_token(nxt, buffer, order, t);
+            }
             // word cg (of v) over the whole item, in every row
             uint32_t word;
             if constexpr (HP == 4) {
@@ -1056,6 +1070,12 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
             const uint32_t mt = token_meta_word(half_lo(mnw), -half_lo(mxw), pt.rel);
             tok[HP < 4 ? 16 * row4 + t : t] = token_quant_near(mt, pt.small_scale);
             if (HP == 4 ? threadIdx.x < 16 : head_in_set == 0) meta_of(cur)[t] = mt;
+            if (skip) {
+                if (!more) break;
+                cur = nxt;
+                item = next;
+                continue;
+            }
             if (split > 1 && ((wave >> 2) & (split - 1)) != int(blockIdx.x) / n_items) return;   // another workgroup's heads
         }
         wave_lds_fence();
@@ -1221,9 +1241,11 @@ __device__ inline void assemble_chunk(const StagedLane &in, bool channel_major, 
 // takes one chunk, so a workgroup four (waves that walk several, the next one's codes on their way, are slower: 16384 chunks
 // 25 us, two per wave 27, three 31).  Every workgroup adds up the sizes of the part's chunks
 // before its own by itself (at most 64 KB, in the L2 cache of its die after the first): no launch of a scan in between.
+template <bool UNSURE>
 __global__ __launch_bounds__(256) void assemble16_kernel(PackArgs a) {
     __shared__ __attribute__((aligned(16))) uint8_t images[4][CHUNK_MAX + 16];
     const PackTensor &t = a.t[blockIdx.y];
+    if (UNSURE && !staged_round(t.round, t.index)) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool paged = a.index_words == 2;  // the placement kernel has set the chunks' index pairs
     const int wg_first = blockIdx.x * 4, cl = wg_first + wave;
@@ -2041,13 +2063,13 @@ bool finds_params(const kv_cache *c, int n_chunks) {
 }
 
 template <int HP, bool GIVEN>
-static void launch_quantize16_as(PackArgs &a, int H, bool stream, hipStream_t s) {
+static void launch_quantize16_as(PackArgs &a, int H, bool stream, bool unsure, hipStream_t s) {
     const int waves = HP < 4 ? 1 : std::min((H + 3) / 4, GIVEN ? 4 : 16);
     // workgroups of that many waves that fit a compute unit (0: not asked yet)
     static std::atomic<int> per_cu_of[17];
     int per_cu = per_cu_of[waves].load(std::memory_order_relaxed);
     if (!per_cu) {
-        per_cu = resident_workgroups(reinterpret_cast<const void *>(quantize16_kernel<HP, GIVEN, false>), 64 * waves);
+        per_cu = resident_workgroups(reinterpret_cast<const void *>(quantize16_kernel<HP, GIVEN, false, false>), 64 * waves);
         per_cu_of[waves].store(per_cu, std::memory_order_relaxed);
     }
     const int64_t items = int64_t(2) * a.rows * HP * (HP == 4 && GIVEN ? (H + 15) / 16 : 1);
@@ -2058,13 +2080,15 @@ static void launch_quantize16_as(PackArgs &a, int H, bool stream, hipStream_t s)
         while (a.split < 4 && 4 * a.split < waves && items * a.split * 2 <= room) a.split *= 2;
         groups *= a.split;
     }
-    hipLaunchKernelGGL((stream ? quantize16_kernel<HP, GIVEN, true> : quantize16_kernel<HP, GIVEN, false>), dim3(groups), dim3(64 * waves), 0, s, a);
+    auto kernel = unsure ? (stream ? quantize16_kernel<HP, GIVEN, true, true> : quantize16_kernel<HP, GIVEN, false, true>)
+                         : (stream ? quantize16_kernel<HP, GIVEN, true, false> : quantize16_kernel<HP, GIVEN, false, false>);
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(64 * waves), 0, s, a);
 }
 
-static void launch_quantize16(PackArgs &a, int H, bool given, bool stream, hipStream_t s) {
-    if (H == 1) given ? launch_quantize16_as<1, true>(a, H, stream, s) : launch_quantize16_as<1, false>(a, H, stream, s);
-    else if (H == 2) given ? launch_quantize16_as<2, true>(a, H, stream, s) : launch_quantize16_as<2, false>(a, H, stream, s);
-    else given ? launch_quantize16_as<4, true>(a, H, stream, s) : launch_quantize16_as<4, false>(a, H, stream, s);
+static void launch_quantize16(PackArgs &a, int H, bool given, bool stream, bool unsure, hipStream_t s) {
+    if (H == 1) given ? launch_quantize16_as<1, true>(a, H, stream, unsure, s) : launch_quantize16_as<1, false>(a, H, stream, unsure, s);
+    else if (H == 2) given ? launch_quantize16_as<2, true>(a, H, stream, unsure, s) : launch_quantize16_as<2, false>(a, H, stream, unsure, s);
+    else given ? launch_quantize16_as<4, true>(a, H, stream, unsure, s) : launch_quantize16_as<4, false>(a, H, stream, unsure, s);
 }
 
 int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s) {
@@ -2075,7 +2099,8 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
     uint32_t *sizes16 = reinterpret_cast<uint32_t *>(ws + WS_SIZES);
     const bool planes = c->cfg.pack_size == 16;
     // packs of 16, contiguous arena: the staged path when even the largest chunks fit (decided on
-    // the device, where the fill level is); the kernels of the other path return at once.  The
+    // the device, where the fill level is); the kernels of the other path return at once, but for the token
+    // metadata, which the first kernel of the staged path finds either way.  The
     // host knows an upper bound of the fill level: where that already says "fits", the two-pass
     // kernels are not launched at all.
     // Paged arena: the placement needs the sizes of the whole round, so the staged path takes the
@@ -2118,6 +2143,7 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
         t.max_pages = job.max_pages;
         if (staged && !c->pool && job.fill_bound16 + t.round.worst16 > job.arena_cap16) two_pass = true;
     }
+    const bool unsure = two_pass;   // the device decides (staged_round)
     a.index_words = c->index_words;
     a.magic_b = (uint64_t(1) << 32) / uint64_t(B) + 1;
     a.first_tensor = 0;
@@ -2127,6 +2153,7 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
         // equal parts of whole rows that fit the staging area, half of its slots for each tensor
         const int rows = n_chunks / H, most = c->stage_chunks / 2 / H;
         const int parts = (rows + most - 1) / most, per_part = (rows + parts - 1) / parts;
+        a.round_rows = rows;
         for (int part = 0; part < rows; part += per_part) {
             a.part_row = part;
             a.rows = std::min(per_part, rows - part);
@@ -2134,11 +2161,11 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
             a.n = a.rows * H;
             a.t[0].widths = reinterpret_cast<uint16_t *>(sizes16);
             a.t[1].widths = a.t[0].widths + 4 * ((a.n + 1) & ~1);
-            launch_quantize16(a, H, !finds_params(c, n_chunks), stream, s);
+            launch_quantize16(a, H, !finds_params(c, n_chunks), stream, unsure, s);
             static_assert(PLACE_SMALL_CHUNKS >= 16384 / 2, "a staged round of a paged cache fits the placement kernel");
             static_assert(16384 * 8 + 64 <= WS_SIZES_BYTES, "the width sums of a part fit the sizes area");
             if (c->pool) hipLaunchKernelGGL(place_small_kernel, dim3(1), dim3(1024), 0, s, a);
-            hipLaunchKernelGGL(assemble16_kernel, dim3((a.n + 3) / 4, 2), dim3(256), 0, s, a);
+            hipLaunchKernelGGL(unsure ? assemble16_kernel<true> : assemble16_kernel<false>, dim3((a.n + 3) / 4, 2), dim3(256), 0, s, a);
         }
     }
     if (two_pass) {
