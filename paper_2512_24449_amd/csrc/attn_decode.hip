@@ -668,7 +668,7 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         n_splits = v_splits_for(n_blocks, B * Hs);
         a.blocks_per_split = (n_blocks + n_splits - 1) / n_splits;
         n_splits = (n_blocks + a.blocks_per_split - 1) / a.blocks_per_split;
-        merged = merge_in_kernel(int64_t(n_splits) * B * Hs, int64_t(B) * Hs, c->wide_k || c->wide_v);
+        merged = merge_in_kernel(int64_t(n_splits) * B * Hs, int64_t(B) * Hs, G, c->wide_k || c->wide_v);
         a.counters = reinterpret_cast<uint32_t *>(ws + WS_STATUS) + ST_COUNTERS;
         a.k_tail = static_cast<const __half *>(c->buf.k_tail);
         a.v_tail = static_cast<const __half *>(c->buf.v_tail);
@@ -685,7 +685,7 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         const bool mid = (!c->wide_k || c->qmax_k <= MID_QMAX) && (!c->wide_v || c->qmax_v <= MID_QMAX) &&
                          (!both || n_splits * B * Hs <= mid_room());
 #define PACKKV_LAUNCH_A8X(g, kw, vw, mid)                                                                    \
-    if (merged) hipLaunchKernelGGL((attn8_kernel<g, kw, vw, mid, true>), grid, dim3(256), 0, s, a);          \
+    if (merged) hipLaunchKernelGGL((attn8_kernel<g, kw, vw, mid, (g <= MERGED_HEADS)>), grid, dim3(256), 0, s, a); \
     else hipLaunchKernelGGL((attn8_kernel<g, kw, vw, mid, false>), grid, dim3(256), 0, s, a)
 #define PACKKV_LAUNCH_A8W(g, kw, vw)              \
     if (mid) { PACKKV_LAUNCH_A8X(g, kw, vw, true); } \

@@ -16,8 +16,13 @@ namespace packkv {
 // kernel of its own: fused attention, 1 stream in 4 workgroups 12.7 / 11.5 and 16.2 / 12.2 us, 32 in 128 13.0 / 12.3 and 16.2 /
 // 13.0, 8 of four heads in 128 14.7 / 14.3 and 16.4 / 14.5, 32 in 512 16.1 / 16.0 and 16.0 / 15.4; three steps, 1 in 4 23.2 /
 // 15.8 and 26.4 / 16.7.  Wide chunks, whose kernels run longer than the host takes: 16 in 128 17.0 / 17.1 and 16.6 / 16.4.
-inline bool merge_in_kernel(int64_t groups, int64_t streams, bool wide = false) {
-    return streams <= COUNTED_STREAMS && groups <= (wide ? 64 : 128);
+// A wave merges a head, so more than four heads take it a second turn, and with seven and eight the merge held registers in scratch:
+// 2 streams of packs of 8 in 16 workgroups, merged here and by a kernel of its own, fused attention at five heads 13.5 / 11.7 us,
+// six 14.4 / 12.3, seven 15.1 / 12.9, eight 19.9 / 13.4, V product 8.3 / 7.5, 8.4 / 7.6, 8.6 / 7.6, 8.7 / 7.7 (four heads 10.6 /
+// 11.2 and 6.9 / 7.4).
+constexpr int MERGED_HEADS = 4;
+inline bool merge_in_kernel(int64_t groups, int64_t streams, int heads, bool wide = false) {
+    return heads <= MERGED_HEADS && streams <= COUNTED_STREAMS && groups <= (wide ? 64 : 128);
 }
 
 __device__ inline void store_shared(float *to, float x, float y) {

@@ -485,7 +485,7 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
     {                                                                                                      \
         static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(v_matvec_kernel<g, high, false>)); \
         plan.split(plan_groups_for(n_blocks, B * Hs, per_cu, most_groups));                               \
-        merged = merge_in_kernel(plan.n_groups, int64_t(B) * Hs);                                 \
+        merged = merge_in_kernel(plan.n_groups, int64_t(B) * Hs, G);                              \
         if (merged) hipLaunchKernelGGL((v_matvec_kernel<g, high, true>), dim3(plan.n_groups), dim3(256), 0, s, a, plan); \
         else hipLaunchKernelGGL((v_matvec_kernel<g, high, false>), dim3(plan.n_groups), dim3(256), 0, s, a, plan); \
     }
@@ -504,12 +504,12 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
         a.blocks_per_split = (n_blocks + n_splits - 1) / n_splits;
         n_splits = (n_blocks + a.blocks_per_split - 1) / a.blocks_per_split;
         dim3 grid(n_splits, B * Hs);
-        merged = merge_in_kernel(int64_t(n_splits) * B * Hs, int64_t(B) * Hs, c->wide_v);
+        merged = merge_in_kernel(int64_t(n_splits) * B * Hs, int64_t(B) * Hs, G, c->wide_v);
 #define PACKKV_LAUNCH_VW(g)                                                                     \
-    if (merged) hipLaunchKernelGGL((vw_matvec_kernel<g, true>), grid, dim3(256), 0, s, a);      \
+    if (merged) hipLaunchKernelGGL((vw_matvec_kernel<g, (g <= MERGED_HEADS)>), grid, dim3(256), 0, s, a);      \
     else hipLaunchKernelGGL((vw_matvec_kernel<g, false>), grid, dim3(256), 0, s, a)
 #define PACKKV_LAUNCH_V8X(g, mid)                                                               \
-    if (merged) hipLaunchKernelGGL((v8_matvec_kernel<g, mid, true>), grid, dim3(256), 0, s, a); \
+    if (merged) hipLaunchKernelGGL((v8_matvec_kernel<g, mid, (g <= MERGED_HEADS)>), grid, dim3(256), 0, s, a); \
     else hipLaunchKernelGGL((v8_matvec_kernel<g, mid, false>), grid, dim3(256), 0, s, a)
 #define PACKKV_LAUNCH_V8(g) PACKKV_LAUNCH_V8X(g, false)
 #define PACKKV_LAUNCH_VM(g) PACKKV_LAUNCH_V8X(g, true)

@@ -1,5 +1,5 @@
 """Short contexts of few streams: the last workgroup of a stream merges the partial rows inside the V product and the
-fused attention (csrc/last_group.h; up to 32 streams and 128 workgroups, 64 with wide chunks).  Against the oracle on both sides
+fused attention (csrc/last_group.h; up to 32 streams and 128 workgroups, 64 with wide chunks, up to four heads).  Against the oracle on both sides
 of that line, with tails that end in every wave's part of it, and replayed from a graph."""
 import pytest
 import torch
