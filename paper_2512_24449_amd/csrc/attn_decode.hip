@@ -184,8 +184,8 @@ __device__ inline void attn_store_partial(const AArgs &a, const State &st, const
     }
 }
 
-// The last workgroup of a stream: merges its n_sets row sets and the raw fp16 tail as attn_combine_kernel does, a
-// wave, or with one or two heads several waves, per query head.  flag, scratch: a word and 4 * 256 floats of LDS that
+// The last workgroup of a stream: merges its n_sets row sets and the raw fp16 tail, by attn_combine_kernel's formulas in an
+// order of its own, a wave, or with one or two heads several waves, per query head.  flag, scratch: a word and 4 * 256 floats of LDS that
 // nothing else uses any more.
 template <int G>
 __device__ inline void attn_merge_stream(const AArgs &a, int stream, int b, int h, int n_sets, int64_t set_stride, uint32_t *flag,

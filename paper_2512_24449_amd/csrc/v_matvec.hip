@@ -67,7 +67,7 @@ __device__ inline void v_store_partial(const VArgs &a, const float (*red)[G][D +
 }
 
 // The last workgroup of a stream: adds its n_sets row sets (the first at first_set, set_stride floats apart) and the raw
-// fp16 tail, as v_reduce_kernel does, a wave, or with one or two heads several waves, per query head.
+// fp16 tail, in an order of its own, a wave, or with one or two heads several waves, per query head.
 template <int G>
 __device__ inline void v_merge_stream(const VArgs &a, int stream, int b, int h, const float *first_set, int n_sets, int64_t set_stride,
                                       uint32_t *flag, float *scratch) {
