@@ -245,7 +245,8 @@ int kv_v_matvec(kv_cache_t *cache, const float *p, int64_t ld_p, float *out, voi
  * (bitwise, as long as the split count is not lowered, see below); the per-split
  * partial sums go to a fixed array inside the library (KV_NOALLOC_MAX_SPLIT_ROWS
  * rows of 132 floats, about 4.3 MB, held by every GPU the library runs on until
- * the process ends) instead of the cache's workspace.  The call allocates and
+ * the process ends) instead of the cache's workspace, of which only counters of
+ * this entry point's own are used (short contexts).  The call allocates and
  * frees nothing.  The context axis is split over at most
  * KV_NOALLOC_MAX_SPLIT_ROWS / (batch * n_q_heads) workgroups per stream;
  * KV_ERR_CAPACITY if batch * n_q_heads exceeds KV_NOALLOC_MAX_SPLIT_ROWS.

@@ -46,7 +46,7 @@ struct AArgs {
     int blocks_per_split;             // not FLAT: blocks of a workgroup
     float sm_log2;                    // sm_scale * log2(e)
     // MERGE: the last workgroup of a stream merges its rows (else attn_combine_kernel does)
-    uint32_t *counters;
+    uint8_t *counters;      // of stream 0, a word per stream
     const __half *k_tail, *v_tail;
     int n_tail, tail_cap;
     float *out;
@@ -190,7 +190,7 @@ __device__ inline void attn_store_partial(const AArgs &a, const State &st, const
 template <int G>
 __device__ inline void attn_merge_stream(const AArgs &a, int stream, int b, int h, int n_sets, int64_t set_stride, uint32_t *flag,
                                          float *scratch) {
-    if (!last_group(a.counters + stream, uint32_t(n_sets), flag)) return;
+    if (!last_group(a.counters + 4 * stream, uint32_t(n_sets), flag)) return;
     constexpr int W = G == 1 ? 4 : G == 2 ? 2 : 1;   // waves per head: each takes every W-th row set and 64 / W tail tokens
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = wave % W;
     float *const weights = scratch + 256 * wave, *const sums = weights + 64;
@@ -669,7 +669,7 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         a.blocks_per_split = (n_blocks + n_splits - 1) / n_splits;
         n_splits = (n_blocks + a.blocks_per_split - 1) / a.blocks_per_split;
         merged = merge_in_kernel(int64_t(n_splits) * B * Hs, int64_t(B) * Hs, G, c->wide_k || c->wide_v);
-        a.counters = reinterpret_cast<uint32_t *>(ws + WS_STATUS) + ST_COUNTERS;
+        a.counters = ws + WS_STATUS + 4 * ST_COUNTERS + COUNT_ATTENTION;
         a.k_tail = static_cast<const __half *>(c->buf.k_tail);
         a.v_tail = static_cast<const __half *>(c->buf.v_tail);
         a.n_tail = c->tail_tokens;

@@ -45,7 +45,7 @@ constexpr int V_PART_STRIDE = 132;              // floats: 128 outputs, [128] = 
 constexpr int PAGE16 = KV_PAGE_BYTES / 16;      // 16-byte units per page of a paged arena
 
 enum { ST_OVERFLOW_K = 0, ST_OVERFLOW_V = 1, ST_COUNTERS = 32 };
-// Streams whose split context the splitting kernel can merge itself: one status word each (last_group.h).
+// Streams whose split context the splitting kernel can merge itself: one status word of counters each (last_group.h).
 constexpr int COUNTED_STREAMS = 32;
 
 // Workgroups (of four waves, one chunk per wave at a time) to spread `total_blocks` chunks

@@ -4,7 +4,9 @@
 //
 // The partial rows go out with agent-scope stores and are read with agent-scope loads: the dies' L2 caches are not
 // coherent with each other for ordinary accesses inside a kernel.  Nothing waits: a workgroup that is not the
-// last one ends.  The counters are zero between calls (calls on one cache do not overlap).
+// last one ends.  The counters are zero between calls (calls on one cache do not overlap).  A stream has one for each
+// of the calls that merge, a byte of one word each: calls that overlap all the same, which kv_v_matvec_noalloc may with those
+// that use the workspace, do not count for one another, and two of one kind and size leave zero behind.
 #pragma once
 
 #include "unpack.h"
@@ -34,15 +36,20 @@ __device__ inline float2 load_shared(const float *from) {
     return make_float2(__uint_as_float(uint32_t(v)), __uint_as_float(uint32_t(v >> 32)));
 }
 
-// Whether this workgroup is the last of `expected` at `counter` (which it then sets back).  All threads call, with
-// their agent-scope stores issued; flag: a word of LDS.  Contains two workgroup barriers.
-__device__ inline bool last_group(uint32_t *counter, uint32_t expected, uint32_t *flag) {
+enum { COUNT_ATTENTION = 0, COUNT_V = 1, COUNT_V_NOALLOC = 2 };  // byte of the word
+
+// Whether this workgroup is the last of `expected` (at most 64) at the counter, a byte (which it then sets back).  All
+// threads call, with their agent-scope stores issued; flag: a word of LDS.  Contains two workgroup barriers.
+__device__ inline bool last_group(uint8_t *counter, uint32_t expected, uint32_t *flag) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores are where the others will read
     __syncthreads();
     if (threadIdx.x == 0) {
-        const uint32_t before = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const bool last = before + 1 == expected;
-        if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int byte = int(reinterpret_cast<uintptr_t>(counter) & 3u), shift = 8 * byte;
+        uint32_t *word = reinterpret_cast<uint32_t *>(counter - byte);
+        const uint32_t before = __hip_atomic_fetch_add(word, 1u << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t mine = ((before >> shift) & 255u) + 1;
+        const bool last = mine == expected || mine == 2 * expected;   // (2: of two calls that overlap)
+        if (last) __hip_atomic_fetch_sub(word, expected << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *flag = last;
     }
     __syncthreads();

@@ -38,7 +38,7 @@ struct VArgs {
     int n_blocks;           // packed blocks per stream
     int blocks_per_split;
     // MERGE: the last workgroup of a stream merges its rows (else v_reduce_kernel does)
-    uint32_t *counters;
+    uint8_t *counters;      // of stream 0, a word per stream
     const __half *tail;     // [B][tail_cap][kv-heads][128]
     int64_t packed_tokens;
     int n_tail, tail_cap;
@@ -71,7 +71,7 @@ __device__ inline void v_store_partial(const VArgs &a, const float (*red)[G][D +
 template <int G>
 __device__ inline void v_merge_stream(const VArgs &a, int stream, int b, int h, const float *first_set, int n_sets, int64_t set_stride,
                                       uint32_t *flag, float *scratch) {
-    if (!last_group(a.counters + stream, uint32_t(n_sets), flag)) return;
+    if (!last_group(a.counters + 4 * stream, uint32_t(n_sets), flag)) return;
     constexpr int W = G == 1 ? 4 : G == 2 ? 2 : 1;   // waves per head: each takes every W-th row set and 64 / W tail tokens
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = wave % W;
     float *const weights = scratch + 256 * wave, *const sums = weights + 64;
@@ -442,9 +442,9 @@ int plan_groups_for(int n_blocks, int streams, int per_cu, int64_t most) {
 }
 
 // partial: [row sets][V_PART_STRIDE] floats for the split sums; max_split_rows: how many rows
-// (one per query head and split or row set) it can take.
+// (one per query head and split or row set) it can take; counter: COUNT_V or COUNT_V_NOALLOC.
 static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p, float *out, float *partial,
-                                int64_t max_split_rows, hipStream_t s) {
+                                int64_t max_split_rows, int counter, hipStream_t s) {
     // Hs: kv-heads as the stream kernels count them (each dup times, see head_split); the combine
     // kernel works per query head and sees the real kv-head count and the whole group
     const int B = c->cfg.batch, H = c->cfg.n_kv_heads, G = c->group, Hs = H * c->head_split, Gq = G * c->head_split;
@@ -473,7 +473,7 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
     a.n_tail = c->tail_tokens;
     a.tail_cap = c->cfg.tail_capacity;
     a.out = out;
-    a.counters = static_cast<uint32_t *>(c->buf.workspace) + WS_STATUS / 4 + ST_COUNTERS;
+    a.counters = static_cast<uint8_t *>(c->buf.workspace) + WS_STATUS + 4 * ST_COUNTERS + counter;
     bool merged = false;
     if (n_blocks > 0 && planes) {
         // row sets: one per (workgroup, stream it touches), G rows each
@@ -540,7 +540,7 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
 int launch_v_matvec(const kv_cache *c, const float *p, int64_t ld_p, float *out, hipStream_t s) {
     uint8_t *ws = static_cast<uint8_t *>(c->buf.workspace);
     return launch_v_matvec_into(c, p, ld_p, out, reinterpret_cast<float *>(ws + WS_VPART),
-                                int64_t(V_SPLITS_MAX) * c->cfg.batch * c->cfg.n_q_heads, s);
+                                int64_t(V_SPLITS_MAX) * c->cfg.batch * c->cfg.n_q_heads, COUNT_V, s);
 }
 
 // ---- the V product for callers that cannot allocate ------------------------------------------
@@ -573,7 +573,7 @@ int launch_v_matvec_noalloc(const kv_cache *c, const float *p, int64_t ld_p, flo
     if (rc != KV_OK) return rc;
     // every split row that the combine kernel reads is written in full by the stream kernel of
     // the same call: nothing in the array has to start at zero
-    return launch_v_matvec_into(c, p, ld_p, out, partial, KV_NOALLOC_MAX_SPLIT_ROWS, s);
+    return launch_v_matvec_into(c, p, ld_p, out, partial, KV_NOALLOC_MAX_SPLIT_ROWS, COUNT_V_NOALLOC, s);
 }
 
 }  // namespace packkv

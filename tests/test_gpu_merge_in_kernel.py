@@ -54,3 +54,29 @@ def test_replays_of_a_captured_step():
         step()
         torch.cuda.synchronize()
         assert torch.equal(out, want) and torch.equal(out_v, want_v)
+
+
+@pytest.mark.parametrize("G,pack_size", [(1, 16), (4, 16), (2, 8)])
+def test_calls_count_for_themselves(G, pack_size):
+    """Each of the three entry points that merge has counters of its own: another call on the cache that has counted some
+    of its workgroups and not ended (its counts are put there by the host) changes neither their results nor its counts."""
+    from paper_2512_24449_amd import binding, synth
+    H, L = 2, 20 * 64 + 5
+    K, V, q = synth.make_kv(1, L, H, H * G, 9, device="cuda:0")
+    cache = binding.PackedKVCache(1, H, H * G, L, pack_size=pack_size)
+    cache.kv_compress_append(K, V)
+    p = torch.softmax(torch.randn(1, H * G, L, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(3)), -1)
+
+    def calls():
+        out = torch.empty(1, H * G, 128, device="cuda:0")
+        return [lambda: cache.kv_decode_attention(q, 0.09), lambda: cache.kv_v_matvec(p), lambda: cache.kv_v_matvec_noalloc(p, out)]
+
+    want = [f().clone() for f in calls()]
+    words = cache.tensors["workspace"][:256].view(torch.int32)[32:32 + H]
+    assert bool((words == 0).all()), "the counters are zero between calls"
+    for which in range(3):
+        others = sum(3 << (8 * i) for i in range(3) if i != which)
+        words.fill_(others)
+        got = calls()[which]()
+        assert torch.equal(got, want[which]) and bool((words == others).all())
+        words.zero_()
