@@ -384,11 +384,11 @@ struct ChunkInput {
     uint32_t mt;
 };
 
-// LDS of a workgroup that builds chunks; the image of one chunk is copied out while the next is built.
+// LDS of a workgroup that builds a chunk.
 struct ChunkLds {
     float4 tok[N];              // token_quant of the block's tokens
-    uint32_t counts[2][4][64];  // per wave: byte counts of the packs (see build_plane_chunk)
-    __attribute__((aligned(16))) uint8_t image[2][CHUNK_MAX];
+    __attribute__((aligned(16))) uint32_t counts[4][64];  // per wave: byte counts of the packs (see build_plane_chunk)
+    __attribute__((aligned(16))) uint8_t image[CHUNK_MAX];
 };
 
 // Chunk cl of the round is (blk*B + b)*H + h.  cl is the same for the whole workgroup, so the
@@ -408,44 +408,28 @@ __device__ inline ChunkCoord chunk_coord(const ChunkSource &cs, int cl) {
     return k;
 }
 
-// Where chunk cl of the round ((blk*B + b)*H + h) finds the lane's four tokens: rows row0 + 2i of
-// the block in storage order, at the source positions the token order gives.
-struct ChunkRows {
-    int src_row[4];
-};
-__device__ inline int chunk_row0() {
-    const int q = threadIdx.x >> 4;  // 4 * wave + q
-    return 16 * (q >> 2) + 8 * ((q >> 1) & 1) + (q & 1);
-}
-__device__ inline ChunkRows load_chunk_rows(const ChunkSource &cs, int cl) {
-    const ChunkCoord k = chunk_coord(cs, cl);
-    const int b = k.b, blk = k.blk;
-    const int row0 = chunk_row0();
-    ChunkRows r;
-    if (cs.order) {
-        const uint8_t *ord = cs.order + b * cs.meta_stride + cs.first_token + int64_t(blk) * N;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r.src_row[i] = ord[row0 + 2 * i];
-    } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r.src_row[i] = row0 + 2 * i;
-    }
-    return r;
-}
-
-// Issues the loads of chunk cl.  STREAM: with the non-temporal hint.
-template <bool STREAM>
-__device__ inline ChunkInput load_chunk_input(const ChunkSource &cs, int cl, const ChunkRows &rows) {
+// Loads chunk cl of the round, (blk*B + b)*H + h: the lane's four tokens are rows row0 + 2i of the block in storage order,
+// at the source positions the token order gives.
+__device__ inline ChunkInput load_chunk_input(const ChunkSource &cs, int cl) {
     const ChunkCoord k = chunk_coord(cs, cl);
     const int h = k.h, b = k.b, blk = k.blk;
-    const int cg = threadIdx.x & 15;
+    const int cg = threadIdx.x & 15, q = threadIdx.x >> 4;  // q: 4 * wave + lane / 16
+    const int row0 = 16 * (q >> 2) + 8 * ((q >> 1) & 1) + (q & 1);
     const __half *x_blk = cs.src + b * cs.batch_stride + int64_t(blk) * N * cs.token_stride + h * D + cg * 8;
-    const uint32_t *meta_blk = cs.meta + b * cs.meta_stride + cs.first_token + int64_t(blk) * N;
+    const int64_t tok0 = b * cs.meta_stride + cs.first_token + int64_t(blk) * N;
+    int row[4];
+    if (cs.order) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) row[i] = cs.order[tok0 + row0 + 2 * i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) row[i] = row0 + 2 * i;
+    }
     ChunkInput in;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        in.raw[i] = load8<STREAM>(x_blk + rows.src_row[i] * cs.token_stride);  // converted where it is used
-    in.mt = meta_blk[16 * (threadIdx.x >> 6) + cg];
+        in.raw[i] = *reinterpret_cast<const uint4 *>(x_blk + row[i] * cs.token_stride);  // converted where it is used
+    in.mt = cs.meta[tok0 + 16 * (threadIdx.x >> 6) + cg];
     return in;
 }
 
@@ -542,15 +526,14 @@ __device__ inline uint32_t row_inclusive_scan(uint32_t x) {
     return uint32_t(v);
 }
 
-// Quantizes a chunk and, if WRITE, puts its bytes together in lds.image[slot] (complete in every
+// Quantizes a chunk and, if WRITE, puts its bytes together in lds.image (complete in every
 // thread's view on return).  Returns the chunk's size in 16-byte units.  All 256 threads call;
-// contains workgroup barriers (one without WRITE).  Consecutive calls alternate `slot`: the bytes
-// of the call before may still be read while this one runs.
+// contains workgroup barriers (one without WRITE).
 //
-// Bound by vector instructions next to memory (the input is read once here): per value one fused
+// Bound by vector instructions next to memory (both passes read the input): per value one fused
 // multiply-add, half a byte permute, half a clamp, a third of a minimum for the tie test.
 template <bool WRITE>
-__device__ inline int build_plane_chunk(const ChunkSource &cs, const ChunkInput &in, ChunkLds &lds, int slot) {
+__device__ inline int build_plane_chunk(const ChunkSource &cs, const ChunkInput &in, ChunkLds &lds) {
     const int tau = threadIdx.x, lane = tau & 63, cg = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tau >> 6);
     if (lane < 16) lds.tok[16 * wave + lane] = token_quant(in.mt);
@@ -606,18 +589,18 @@ __device__ inline int build_plane_chunk(const ChunkSource &cs, const ChunkInput 
         uint32_t before, four;
         rows4_sum(mine, before, four);
         const uint32_t inc = row_inclusive_scan(four);
-        if (lane == 15) lds.counts[slot][0][wave] = inc;
+        if (lane == 15) lds.counts[0][wave] = inc;
         __syncthreads();
-        const uint4 t = *reinterpret_cast<const uint4 *>(&lds.counts[slot][0][0]);
+        const uint4 t = *reinterpret_cast<const uint4 *>(&lds.counts[0][0]);
         total = (t.x + t.y) + (t.z + t.w);
         off0 = inc - four + before + (wave > 0 ? t.x : 0u) + (wave > 1 ? t.y : 0u) + (wave > 2 ? t.z : 0u);
         off1 = off0 + (e0 | (o0 << 16));
     } else {
         // channel-major (K): for every channel the four groups, i.e. the four waves
-        lds.counts[slot][wave][lane] = e0 | (o0 << 8) | (e1 << 16) | (o1 << 24);  // sums of four stay below 256
+        lds.counts[wave][lane] = e0 | (o0 << 8) | (e1 << 16) | (o1 << 24);  // sums of four stay below 256
         __syncthreads();
-        const uint32_t n0 = lds.counts[slot][0][lane], n1 = lds.counts[slot][1][lane];
-        const uint32_t n2 = lds.counts[slot][2][lane], n3 = lds.counts[slot][3][lane];
+        const uint32_t n0 = lds.counts[0][lane], n1 = lds.counts[1][lane];
+        const uint32_t n2 = lds.counts[2][lane], n3 = lds.counts[3][lane];
         const uint32_t all = (n0 + n1) + (n2 + n3);
         const uint32_t earlier = (wave > 0 ? n0 : 0u) + (wave > 1 ? n1 : 0u) + (wave > 2 ? n2 : 0u);
         const uint32_t all0 = (all & 0xFFu) | ((all & 0xFF00u) << 8), all1 = ((all >> 16) & 0xFFu) | ((all >> 8) & 0xFF0000u);
@@ -632,7 +615,7 @@ __device__ inline int build_plane_chunk(const ChunkSource &cs, const ChunkInput 
     const int e_bytes = int(total & 0xFFFFu), used = HEADER + e_bytes + int(total >> 16);
     const int padded = (used + 15) & ~15;
     if constexpr (WRITE) {
-        uint8_t *img = lds.image[slot];
+        uint8_t *img = lds.image;
         const int d = 8 * cg + 2 * q;
         const uint32_t h0 = uint32_t((w0 << 4) | pb[0].m), h1 = uint32_t((w1 << 4) | pb[1].m);
         if (cs.pack_order == 0) {
@@ -656,10 +639,10 @@ __device__ inline int build_plane_chunk(const ChunkSource &cs, const ChunkInput 
 }
 
 // The finished bytes of a chunk to global memory.
-__device__ inline void copy_image(const ChunkLds &lds, int slot, int n16, uint8_t *__restrict__ to) {
+__device__ inline void copy_image(const ChunkLds &lds, int n16, uint8_t *__restrict__ to) {
     static_assert(CHUNK_MAX <= 2 * 256 * 16, "two 16-byte units per thread move a chunk");
     const int tau = threadIdx.x;
-    const uint4 *image = reinterpret_cast<const uint4 *>(lds.image[slot]);
+    const uint4 *image = reinterpret_cast<const uint4 *>(lds.image);
     uint4 *dst = reinterpret_cast<uint4 *>(to);
     if (tau < n16) dst[tau] = image[tau];
     if (tau + 256 < n16) dst[tau + 256] = image[tau + 256];
@@ -697,9 +680,9 @@ __global__ __launch_bounds__(256) void chunk16_kernel(PackArgs a) {
         dst = t.arena + size_t(o0) * 16;
     }
     __shared__ ChunkLds lds;
-    const int n16 = build_plane_chunk<WRITE>(t.cs, load_chunk_input<false>(t.cs, cl, load_chunk_rows(t.cs, cl)), lds, 0);
+    const int n16 = build_plane_chunk<WRITE>(t.cs, load_chunk_input(t.cs, cl), lds);
     if (WRITE)
-        copy_image(lds, 0, n16, dst);
+        copy_image(lds, n16, dst);
     else if (threadIdx.x == 0)
         t.sizes16[cl] = uint32_t(n16);
 }
