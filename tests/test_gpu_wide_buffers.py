@@ -47,22 +47,41 @@ def test_mixed_layouts(k_rel, v_rel, H, Hq, L):
     gpu_cases.run_case(1, H, Hq, L, seed=Hq, pack_size=8, k_rel=k_rel, v_rel=v_rel)
 
 
-# More workgroups than the kernels with two smaller buffers run at once: the other kernels take codes of up to 31 as well.
-# Both batch elements have the same contents, and a cache of one of them stays on the near side of the line (all its
-# results depend on its own tokens only): about 480 and 960 workgroups on either side of a line at 512.
-@pytest.mark.parametrize("Hq", [40, 120])
+def _workgroups(streams, n_blocks):
+    """Workgroups of the K product and of the fused attention (target_workgroups and the splits of csrc)."""
+    target = min(max(streams * n_blocks // 32, 512), 4096)
+    per_group = max(4, -(-(-(-n_blocks // max(1, target // streams))) // 4) * 4)
+    splits = min(-(-target // streams), -(-n_blocks // 4), 64)
+    return streams * -(-n_blocks // per_group), streams * -(-n_blocks // -(-n_blocks // splits))
+
+
+# More workgroups than the kernels with two smaller buffers run at once, two to a compute unit: the other kernels take codes
+# of up to 31 as well.  Both batch elements have the same contents, and a cache of one of them stays on the near side of the
+# line (all its results depend on its own tokens only).  Heads repeat two base heads, so that the oracle has little to do.
+@pytest.mark.parametrize("Hq", [32, 96])
 def test_both_sides_of_the_line_between_buffers(Hq):
-    B, H, L = 2, 40, 400 * 64 + 5
+    B, H, blocks = 2, 32, 400
+    L, G = blocks * 64 + 5, Hq // H
+    room = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    assert max(_workgroups(H, blocks)) <= room < min(_workgroups(B * H, blocks)), "one kernel on both sides"
     g = torch.Generator(device="cuda:0").manual_seed(Hq)
-    K, V = (torch.randn((1, L, H, 128), generator=g, device="cuda:0").to(torch.float16) for _ in range(2))
+    K, V = (torch.randn((1, L, 2, 128), generator=g, device="cuda:0").to(torch.float16) for _ in range(2))
     q = torch.randn((1, Hq, 128), generator=g, device="cuda:0").to(torch.float16)
     got = []
     for batch in (1, B):
         cache = binding.PackedKVCache(batch, H, Hq, L, k_rel_scale=1 / 31, v_rel_scale=1 / 31, pack_size=8)
-        cache.kv_compress_append(K.expand(batch, -1, -1, -1).contiguous(), V.expand(batch, -1, -1, -1).contiguous())
+        cache.kv_compress_append(K.repeat(batch, 1, H // 2, 1), V.repeat(batch, 1, H // 2, 1))
         qb = q.expand(batch, -1, -1).contiguous()
         got.append((cache.kv_k_matvec(qb, 0.05)[:, :, :L].cpu().numpy(), cache.kv_decode_attention(qb, 0.05).cpu().numpy()))
         assert cache.kv_cache_stats().overflow == 0
     for b in range(B):
         gpu_cases.assert_close_vectors(got[1][0][b], got[0][0][0], "K", tol=1e-5)
         gpu_cases.assert_close_vectors(got[1][1][b], got[0][1][0], "fused", tol=1e-5)
+    K, V = K.cpu().numpy(), V.cpu().numpy()
+    n_packed, ck, cv = gpu_cases.oracle_cache(K, V, 1 / 31, 1 / 31, 8)
+    (kcodes, kmeta), (vcodes, vmeta) = gpu_cases.full_codes(ck, K.shape, n_packed), gpu_cases.full_codes(cv, V.shape, n_packed)
+    by_base = sorted(range(Hq), key=lambda i: i // G % 2)
+    qn = q.cpu().numpy()[:, by_base]
+    gpu_cases.assert_close_vectors(got[0][0][:, by_base], oracle.k_scores(kcodes, K, kmeta, n_packed, qn, 0.05), "K against the oracle")
+    gpu_cases.assert_close_vectors(got[0][1][:, by_base], oracle.attention(kcodes, K, kmeta, vcodes, V, vmeta, n_packed, qn, 0.05),
+                                   "fused against the oracle")
