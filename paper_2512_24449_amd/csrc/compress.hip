@@ -1766,7 +1766,7 @@ __global__ void init_kernel(uint32_t *status, uint32_t *k_index, uint32_t *v_ind
 // wave holds a token's row of up to NREG * 512 values in registers, finds its scale and minimum, and of V
 // quantizes it with the packs' fixed-point rule and counts every code with ballots; the lower median is the first code
 // whose running count passes the middle.  NREG = 0, longer rows: read again for the codes.
-// Bound by the counts, 120 ballots for 512 values.  One kernel instead of two that both read V: 12032 tokens of 1024
+// Bound by the counts, eight ballots for 512 values and each code but the last (five levels 40, fifteen 120).  One kernel instead of two that both read V: 12032 tokens of 1024
 // values 12 + 15.5 -> 17.6 us, 7936 tokens of 6656 values 31 + 39 -> 63 (those all in registers: 140, the unrolled
 // counts overflow the instruction cache; 4096 values read twice: 40.0 instead of 35.5).
 template <int NREG, bool STREAM>
