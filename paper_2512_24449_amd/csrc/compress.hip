@@ -792,7 +792,7 @@ __device__ inline float4 token_quant_near(uint32_t mt, float small_scale) {
 }
 
 // half_mul_add clamped to 0 .. 1: with the operands of token_quant_near t / 256, in [1/2, 1), whose bits 16.. are 0x3F00 + code.
-// A NaN becomes 0 and what is too large 1: their low 16 bits are 0, so both take the divide, whose minimum gives them a code
+// A NaN becomes 0 (the mode register's DX10_CLAMP bit, set as kernels start) and what is too large 1: their low 16 bits are 0, so both take the divide, whose minimum gives them a code
 // in range, and no other token's code sees them.
 template <bool HI>
 __device__ inline float half_mul_add_unit(uint32_t two_halves, float r, float c) {

@@ -2,7 +2,8 @@
 numpy for fp16 tokens as the kernel meets them.  t = fl(x * r + c) with r = 1 / s up to an ulp and c = fl(128.5 +
 g * 2^-16 - min * r); the code is the integer part of t - 128, unless the 16 fraction bits of t are below 2g or the
 token's scale is below the tensor's small_scale, where the IEEE divide decides; values are clamped on the fast path only
-where the tensor's relative scale asks for it.  The result is the code of clamp(rint(fl((x - min) / scale)), 0, qmax)
+where the tensor's relative scale asks for it.  (The kernel holds t / 256, clamped to 0 .. 1; for numbers that changes the
+exponent only.)  The result is the code of clamp(rint(fl((x - min) / scale)), 0, qmax)
 (PackKV Sec. III-B.2)."""
 import numpy as np
 import pytest
