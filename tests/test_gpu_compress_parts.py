@@ -1,5 +1,5 @@
 """The compressor of packs of 16 at the edges of its split: the staging area holds half of its slots
-per tensor, a compaction workgroup takes four chunks and adds up the sizes before them; both tensors share
+per tensor, an assembling workgroup takes four chunks and adds up the sizes before them; both tensors share
 every launch.  Bytes, index and metadata against the oracle, bit for bit."""
 import pytest
 import torch
