@@ -248,9 +248,9 @@ extern "C" int kv_cache_create_paged(const kv_config_t *cfg, kv_page_pool_t *poo
 extern "C" int kv_cache_release(kv_cache_t *c, void *hip_stream) {
     if (!c) return KV_ERR_ARG;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    int rc;
-    if (c->pool && (rc = launch_release_pages(c, s))) return rc;
-    if ((rc = launch_init(c, s))) return rc;  // status words, index[0]; the page lists are empty already
+    // status words, index[0]; paged: the pages as well
+    const int rc = c->pool ? launch_release_pages(c, s) : launch_init(c, s);
+    if (rc) return rc;
     c->packed_tokens = 0;
     c->tail_tokens = 0;
     c->fill_bound16[0] = c->fill_bound16[1] = 0;

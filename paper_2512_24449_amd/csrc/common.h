@@ -304,7 +304,7 @@ int launch_tail_copy(const kv_cache *c, const __half *ksrc, const __half *vsrc, 
                      int n, int tail_pos, bool bf16, hipStream_t s);
 int launch_init(const kv_cache *c, hipStream_t s);
 int launch_pool_init(const kv_page_pool *pool, hipStream_t s);
-// Gives the pages of both tensors back to the pool and empties the page lists.
+// Gives the pages of both tensors back to the pool and empties the page lists; launch_init's work as well.
 int launch_release_pages(const kv_cache *c, hipStream_t s);
 int launch_k_matvec(const kv_cache *c, const __half *q, float sm_scale, float *scores,
                     int64_t ld_scores, hipStream_t s);

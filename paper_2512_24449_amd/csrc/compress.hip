@@ -1719,12 +1719,19 @@ __global__ void pool_init_kernel(uint32_t *state, int64_t n_pages) {
     if (i < n_pages) state[1 + i] = uint32_t(n_pages - 1 - i);
 }
 
+// What a new or released cache starts from.
+__device__ inline void init_words(uint32_t *status, uint32_t *k_index, uint32_t *v_index) {
+    if (threadIdx.x < 64) status[threadIdx.x] = 0;
+    if (threadIdx.x == 0) k_index[0] = v_index[0] = 0;
+}
+
 // Pushes the pages of both tensors back onto the pool's stack (the newest page of a list first,
 // so a cache that refills an otherwise idle pool gets its pages in the same order again) and
-// empties the lists.  One wave.
-__global__ __launch_bounds__(64) void release_pages_kernel(uint32_t *k_list, uint32_t *v_list,
-                                                           uint32_t *pool_state, int64_t n_pages) {
+// empties the lists; status and index start anew with it.  One wave.
+__global__ __launch_bounds__(64) void release_pages_kernel(uint32_t *k_list, uint32_t *v_list, uint32_t *pool_state,
+                                                           int64_t n_pages, uint32_t *status, uint32_t *k_index, uint32_t *v_index) {
     const int lane = threadIdx.x;
+    init_words(status, k_index, v_index);
     for (int t = 0; t < 2; ++t) {
         uint32_t *list = t ? v_list : k_list;
         const uint32_t cnt = list[0];
@@ -1754,12 +1761,8 @@ __global__ void tail_copy_kernel(const uint4 *__restrict__ ksrc, const uint4 *__
 
 __global__ void init_kernel(uint32_t *status, uint32_t *k_index, uint32_t *v_index, uint32_t *k_pages,
                             uint32_t *v_pages) {
-    if (threadIdx.x < 64) status[threadIdx.x] = 0;
-    if (threadIdx.x == 0) {
-        k_index[0] = 0;
-        v_index[0] = 0;
-        if (k_pages) k_pages[0] = k_pages[1] = v_pages[0] = v_pages[1] = 0;
-    }
+    init_words(status, k_index, v_index);
+    if (threadIdx.x == 0 && k_pages) k_pages[0] = k_pages[1] = v_pages[0] = v_pages[1] = 0;
 }
 
 // Token parameters of both tensors (blockIdx.z) and V-median repacking, step 1, in one, codes below 16 (packs of 16): a
@@ -1952,7 +1955,8 @@ int launch_release_pages(const kv_cache *c, hipStream_t s) {
     if (!c->pool) return KV_ERR_ARG;
     hipLaunchKernelGGL(release_pages_kernel, dim3(1), dim3(64), 0, s,
                        static_cast<uint32_t *>(c->buf.k_pages), static_cast<uint32_t *>(c->buf.v_pages),
-                       c->pool->state, c->pool->n_pages);
+                       c->pool->state, c->pool->n_pages, reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(c->buf.workspace) + WS_STATUS),
+                       static_cast<uint32_t *>(c->buf.k_index), static_cast<uint32_t *>(c->buf.v_index));
     KV_HIP_CHECK(hipGetLastError());
     return KV_OK;
 }
