@@ -26,12 +26,6 @@ int head_split_for(int g, int pack_size) {
     return 0;
 }
 
-// Capacity of an arena in the 16-byte units of the 32-bit index words: what lies beyond the last
-// addressable unit of a larger buffer stays unused.
-uint32_t arena_units(size_t bytes) {
-    return uint32_t(std::min<size_t>(bytes / 16, 0xFFFFFFFFu));
-}
-
 int check_config(const kv_config_t *c) {
     if (!c) return KV_ERR_ARG;
     if (c->batch < 1 || c->n_kv_heads < 1 || c->n_q_heads < 1 || c->max_tokens < 1) return KV_ERR_ARG;
@@ -270,9 +264,10 @@ extern "C" int kv_cache_destroy(kv_cache_t *cache) {
 
 namespace {
 
-// Compress `n_blocks` full blocks whose tokens start at `src` (batch 0).
+// Compress `n_blocks` full blocks whose tokens start at `src` (batch 0).  held > 0: one block, whose first `held` tokens
+// are in the tail.  rest: new tokens for the tail behind the blocks (its tokens become 0 if they have been copied).
 int compress_blocks(kv_cache *c, const __half *ksrc, const __half *vsrc, int64_t batch_stride,
-                    int n_blocks, bool bf16, hipStream_t s) {
+                    int n_blocks, bool bf16, int held, TailRest *rest, hipStream_t s) {
     const int B = c->cfg.batch, H = c->cfg.n_kv_heads;
     const int per_round = std::max(1, MAX_NEW_CHUNKS / (B * H));
     uint8_t *ws = static_cast<uint8_t *>(c->buf.workspace);
@@ -289,6 +284,7 @@ int compress_blocks(kv_cache *c, const __half *ksrc, const __half *vsrc, int64_t
         job.order = nullptr;
         job.pack_order = 0;
         job.bf16 = bf16;
+        job.held = held;
         CompressJob kjob = job, vjob = job;
         kjob.src = ksrc + int64_t(done) * N * job.token_stride;
         kjob.rel = c->cfg.k_rel_scale;
@@ -313,8 +309,6 @@ int compress_blocks(kv_cache *c, const __half *ksrc, const __half *vsrc, int64_t
         vjob.status = status + ST_OVERFLOW_V;
         vjob.page_list = static_cast<uint32_t *>(c->buf.v_pages);
         vjob.max_pages = c->max_pages_v;
-        kjob.fill_bound16 = c->fill_bound16[0];
-        vjob.fill_bound16 = c->fill_bound16[1];
         int rc;
         if (!finds_params(c, nb * B * H) && (rc = launch_token_params(c, kjob, vjob, s))) return rc;
         if (c->cfg.repack == KV_REPACK_V_MEDIAN) {
@@ -322,7 +316,7 @@ int compress_blocks(kv_cache *c, const __half *ksrc, const __half *vsrc, int64_t
             if ((rc = launch_v_median_order(c, vjob, kjob.meta, order, s))) return rc;
             kjob.order = vjob.order = order;
         }
-        if ((rc = launch_pack(c, kjob, vjob, s))) return rc;
+        if ((rc = launch_pack(c, kjob, vjob, done + nb == n_blocks ? rest : nullptr, s))) return rc;
         c->fill_bound16[0] += uint64_t(nb) * B * H * (chunk_max_bytes(c->cfg.pack_size, c->wide_k) / 16);
         c->fill_bound16[1] += uint64_t(nb) * B * H * (chunk_max_bytes(c->cfg.pack_size, c->wide_v) / 16);
         c->packed_tokens += int64_t(nb) * N;
@@ -355,22 +349,37 @@ int append_tokens(kv_cache_t *c, const void *k_new, const void *v_new, int32_t n
     int64_t pos = 0, remaining = n_new;
     int rc;
 
+    TailRest rest;
+    auto compress = [&](const __half *k, const __half *v, int64_t batch_stride, int n_blocks, bool as_bf16, int held, int64_t behind) {
+        rest = TailRest{{ksrc + behind * row, vsrc + behind * row}, src_batch_stride, int(n_new - behind) % N, bf16};
+        const int tokens = rest.tokens;
+        const int err = compress_blocks(c, k, v, batch_stride, n_blocks, as_bf16, held, &rest, s);
+        if (err) return err;
+        const bool copied = rest.tokens == 0;
+        c->tail_tokens = copied ? tokens : 0;
+        if (copied) remaining -= tokens;
+        return KV_OK;
+    };
     if (c->tail_tokens > 0 || remaining < N) {
-        const int take = int(std::min<int64_t>(remaining, N - c->tail_tokens));
-        if ((rc = launch_tail_copy(c, ksrc, vsrc, src_batch_stride, take, c->tail_tokens, bf16, s))) return rc;
-        c->tail_tokens += take;
+        const int take = int(std::min<int64_t>(remaining, N - c->tail_tokens)), held = c->tail_tokens;
+        const bool full_tail = held + take == N, in_place = full_tail && held > 0 && completes_in_place(c);
+        if (!in_place && (rc = launch_tail_copy(c, ksrc, vsrc, src_batch_stride, take, held, bf16, s))) return rc;
+        if (!in_place) c->tail_tokens += take;
         pos += take;
         remaining -= take;
-        if (c->tail_tokens == N) {
-            if ((rc = compress_blocks(c, ktail, vtail, int64_t(c->cfg.tail_capacity) * row, 1, false, s))) return rc;
-            c->tail_tokens = 0;
+        if (full_tail) {
+            const int64_t behind = remaining < N ? pos : n_new;   // more blocks follow: they take the rest
+            rc = in_place ? compress(ksrc, vsrc, src_batch_stride, 1, bf16, held, behind)
+                          : compress(ktail, vtail, int64_t(c->cfg.tail_capacity) * row, 1, false, 0, behind);
+            if (rc) return rc;
         }
     }
     const int full = int(remaining / N);
     if (full > 0) {
-        if ((rc = compress_blocks(c, ksrc + pos * row, vsrc + pos * row, src_batch_stride, full, bf16, s))) return rc;
+        const int64_t at = pos;
         pos += int64_t(full) * N;
         remaining -= int64_t(full) * N;
+        if ((rc = compress(ksrc + at * row, vsrc + at * row, src_batch_stride, full, bf16, 0, pos))) return rc;
     }
     if (remaining > 0) {
         if ((rc = launch_tail_copy(c, ksrc + pos * row, vsrc + pos * row, src_batch_stride, int(remaining), 0, bf16, s)))

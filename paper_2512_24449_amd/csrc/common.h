@@ -288,14 +288,26 @@ struct CompressJob {
     int64_t max_pages;        // page numbers the list has room for
     const uint8_t *order;     // [B][max_tokens] source position of each storage slot inside its block, or null
     int pack_order;           // packs of 16 (plane layout): 0 group-major pack list (V), 1 channel-major (K)
-    uint64_t fill_bound16;    // the arena holds at most this much before the round (every chunk so far at its largest)
+    int held;                 // > 0: the job is one block whose first `held` tokens are in the raw tail; src: the others
 };
+// New tokens behind a round's last block that go to the start of the raw tails; launch_pack sets tokens to 0 if its kernels copy them.
+struct TailRest {
+    const __half *src[2];     // K, V
+    int64_t batch_stride;     // elements
+    int tokens;
+    bool bf16;
+};
+// Capacity of an arena in the 16-byte units of the 32-bit index words: what lies beyond the last
+// addressable unit of a larger buffer stays unused.
+inline uint32_t arena_units(size_t bytes) { return uint32_t(bytes / 16 < 0xFFFFFFFFu ? bytes / 16 : 0xFFFFFFFFu); }
 
 // Both tensors of a round (they share every launch).  finds_params: launch_pack finds the token parameters of a
 // round of that many chunks by itself.
 bool finds_params(const kv_cache *c, int n_chunks);
 int launch_token_params(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s);
-int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s);
+// A block that new tokens complete is compressed from the tail and the new tokens where they are (CompressJob::held).
+bool completes_in_place(const kv_cache *c);
+int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, TailRest *rest, hipStream_t s);
 // V-median order of the job's blocks (job describes V); permutes the token metadata of both
 // tensors into storage order and fills `order`.
 int launch_v_median_order(const kv_cache *c, const CompressJob &vjob, uint32_t *k_meta, uint8_t *order,

@@ -240,6 +240,8 @@ struct PackTensor {
     uint32_t *status;       // set when the round does not fit
     uint32_t *page_list;    // paged arena
     int64_t max_pages;
+    __half *tail;           // raw tail, and what of the new tokens the round's last kernel copies to its start
+    const __half *rest;
 };
 struct PackArgs {
     PackTensor t[2];        // K, V
@@ -251,6 +253,10 @@ struct PackArgs {
     int first_tensor;       // a launch whose grid covers one tensor: which (else 0)
     uint32_t *pool_state;   // paged arena
     int split;              // workgroups that share an item's quantization (quantize16_kernel)
+    int held;               // quantize16_kernel<.. MIXED>: tokens of the block that the tail holds
+    int rest_units;         // 16-byte units of a batch element that the tail takes behind the round, 0: none
+    int64_t rest_stride;    // elements between the batch elements of `rest`
+    bool rest_bf16;
     uint8_t *staging;       // K chunk i of the part in slot i, V chunk i in slot n + i: 512 pack headers [group][channel],
                             // then the codes of the packs (quantize16_kernel)
 };
@@ -892,11 +898,15 @@ inline QuantRange quant_range(float rel, int qmax) {
 // split: few items leave most of the chip idle, and up to 16 waves of one compute unit then share its
 // vector units; with split workgroups per item, each reads it all and quantizes a part of the heads (8 x 52 heads, one block:
 // flush 19.0 us with one workgroup per item, 16.4 with two, 15.5 with four).
+// MIXED: the round is the block that the new tokens complete: its first `held` tokens are read from the tail, the others
+// where the caller has them, and those are left in the tail as well, so that no copy has to run first (the appends that
+// complete a block of 8 x 52 heads 16.1 -> 14.6 us, of 4 x 1 heads 15.4 -> 11.6).  One item to a workgroup.
 // UNSURE: the round may not be staged, and the kernel finds out first (at run time the question alone cost sure rounds 1 %, a
 // block of 8 x 52 heads 16.0 -> 16.4 us).  Not staged, 8000 tokens of 8 x 52 heads take 1025 us, 4096 of 32 55; quantized
 // all the same, and thrown away, 1305 and 67.
-template <int HP, bool GIVEN, bool STREAM, bool UNSURE>
+template <int HP, bool GIVEN, bool STREAM, bool UNSURE, bool MIXED>
 __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_kernel(PackArgs a) {
+    static_assert(!MIXED || (!GIVEN && !UNSURE), "the block of the tail: rounds that are staged for sure and find their parameters");
     constexpr int MOST_WAVES = HP < 4 ? 1 : GIVEN ? 4 : 16;
     ieee_mode_off();
     __shared__ uint32_t red[2][MOST_WAVES][16];
@@ -984,7 +994,20 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
     uint32_t given = 0;
     if constexpr (GIVEN) given = meta_of(cur)[cg];
     if (ordered) order = order_of(cur), order_next = order_of(locate(min(item + int(gridDim.x), n_items - 1)));
-    {
+    // MIXED: token t of the lane's group is in the tail already; the lane's place in the tail's token 0
+    auto from_tail = [&](int t) { return 16 * (cur.g0 + group_in_item) + t < a.held; };
+    auto tail_of = [&](int b, int head) { return a.t[cur.v].tail + (int64_t(b) * N * H + head) * D + 8 * cg; };
+    if constexpr (MIXED) {
+        const ChunkSource &cs = a.t[cur.v].cs;
+        const int head = min(head_of(cur), H - 1);
+        const __half *const old = tail_of(cur.b, head);
+        const __half *const fresh = cs.src + cur.b * cs.batch_stride + head * D + 8 * cg;   // the first new token
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            const int token = 16 * (cur.g0 + group_in_item) + t;
+            raw[t] = load8<STREAM>((from_tail(t) ? old + token * cs.token_stride : fresh + (token - a.held) * cs.token_stride));
+        }
+    } else {
         const __amdgpu_buffer_rsrc_t buffer = buffer_of(cur, true);
 #pragma unroll
         for (int t = 0; t < 16; ++t) raw[t] = load_token(cur, buffer, order, t);
@@ -994,13 +1017,13 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
         const ChunkSource &cs = pt.cs;
         const int g = cur.g0 + group_in_item;
         const int next = item + int(gridDim.x);   // (split: past the end)
-        const bool more = next < n_items;
+        const bool more = !MIXED && next < n_items;
         const Item nxt = locate(more ? next : item);
         order = order_next;
         if (ordered) order_next = order_of(locate(min(next + int(gridDim.x), n_items - 1)));
         if (cs.bf16) {
 #pragma unroll
-            for (int t = 0; t < 16; ++t) raw[t] = as_fp16(raw[t], true);
+            for (int t = 0; t < 16; ++t) raw[t] = as_fp16(raw[t], !MIXED || !from_tail(t));
         }
         if constexpr (GIVEN) {
             const uint32_t now = given;
@@ -1065,6 +1088,12 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
         const __amdgpu_buffer_rsrc_t next_buffer = buffer_of(nxt, more);
         const int head = head_of(cur);
         const bool present = head < H;
+        if constexpr (MIXED) {
+            __half *const to = tail_of(cur.b, head) + 16 * g * cs.token_stride;
+#pragma unroll
+            for (int t = 0; t < 16; ++t)
+                if (present && !from_tail(t)) *reinterpret_cast<uint4 *>(to + t * cs.token_stride) = raw[t];
+        }
         const uint32_t at = uint32_t((cur.v ? a.n : 0) + cur.row * H + head) * uint32_t(CHUNK_MAX) + uint32_t(16 * cg);
         uint32_t codes[8], mn2[4], mx2[4];   // codes: channel c, eight tokens as nibbles
 #pragma unroll
@@ -1078,7 +1107,8 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
             for (int i = 0; i < 4; ++i) x[i] = raw[first + 2 * i];
             quantize_quad(x, tok + (HP < 4 ? 16 * row4 : 0) + first, uint32_t(cs.qmax), pt.cap_all, pair);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) raw[first + 2 * i] = load_token(nxt, next_buffer, order, first + 2 * i);
+            for (int i = 0; i < 4; ++i)
+                if (!MIXED) raw[first + 2 * i] = load_token(nxt, next_buffer, order, first + 2 * i);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 // (0x3F00 + code is an fp16 number between 1.75 and 1.77)
@@ -1220,6 +1250,18 @@ __device__ inline void assemble_chunk(const StagedLane &in, bool channel_major, 
     wave_lds_fence();
 }
 
+// New tokens behind the last full block to the start of the raw tail, by the workgroups behind those of the chunks, REST_UNITS
+// 16-byte units of a batch element each (a launch less: 4 x 3522 tokens of one head 19.4 -> 15.8 us).
+constexpr int REST_UNITS = 512;
+__device__ inline void copy_rest(const PackArgs &a, const PackTensor &t, int wg) {
+    const int B = t.cs.B, slice = wg / B, b = wg - slice * B;
+    const uint4 *src = reinterpret_cast<const uint4 *>(t.rest + b * a.rest_stride);
+    uint4 *dst = reinterpret_cast<uint4 *>(t.tail + int64_t(b) * N * t.cs.H * D);
+    const int end = min((slice + 1) * REST_UNITS, a.rest_units);
+    for (int i = slice * REST_UNITS + int(threadIdx.x); i < end; i += 256)
+        dst[i] = load8_as_fp16<true>(reinterpret_cast<const __half *>(src + i), a.rest_bf16);
+}
+
 // Chunks of a part from their staged codes to their place, and their index words.  blockIdx.y: tensor; a wave
 // takes one chunk, so a workgroup four (waves that walk several, the next one's codes on their way, are slower: 16384 chunks
 // 25 us, two per wave 27, three 31).  Every workgroup adds up the sizes of the part's chunks
@@ -1228,6 +1270,10 @@ template <bool UNSURE>
 __global__ __launch_bounds__(256) void assemble16_kernel(PackArgs a) {
     __shared__ __attribute__((aligned(16))) uint8_t images[4][CHUNK_MAX + 16];
     const PackTensor &t = a.t[blockIdx.y];
+    if (!UNSURE && int(blockIdx.x) >= (a.n + 3) / 4) {
+        copy_rest(a, t, int(blockIdx.x) - (a.n + 3) / 4);
+        return;
+    }
     if (UNSURE && !staged_round(t.round, t.index)) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool paged = a.index_words == 2;  // the placement kernel has set the chunks' index pairs
@@ -2050,35 +2096,51 @@ bool finds_params(const kv_cache *c, int n_chunks) {
 }
 
 template <int HP, bool GIVEN>
-static void launch_quantize16_as(PackArgs &a, int H, bool stream, bool unsure, hipStream_t s) {
+static void launch_quantize16_as(PackArgs &a, int H, bool stream, bool unsure, bool mixed, hipStream_t s) {
     const int waves = HP < 4 ? 1 : std::min((H + 3) / 4, GIVEN ? 4 : 16);
     // workgroups of that many waves that fit a compute unit (0: not asked yet)
     static std::atomic<int> per_cu_of[17];
     int per_cu = per_cu_of[waves].load(std::memory_order_relaxed);
     if (!per_cu) {
-        per_cu = resident_workgroups(reinterpret_cast<const void *>(quantize16_kernel<HP, GIVEN, false, false>), 64 * waves);
+        per_cu = resident_workgroups(reinterpret_cast<const void *>(quantize16_kernel<HP, GIVEN, false, false, false>), 64 * waves);
         per_cu_of[waves].store(per_cu, std::memory_order_relaxed);
     }
     const int64_t items = int64_t(2) * a.rows * HP * (HP == 4 && GIVEN ? (H + 15) / 16 : 1);
-    int groups = flat_groups_for(items * 4, per_cu, int64_t(1) << 30);   // all resident, at most one per item
+    int groups = mixed ? int(items) : flat_groups_for(items * 4, per_cu, int64_t(1) << 30);   // all resident, at most one per item
     a.split = 1;
     if (HP == 4 && !GIVEN) {
         const int room = flat_groups_for(int64_t(1) << 40, 1, int64_t(1) << 30);
         while (a.split < 4 && 4 * a.split < waves && items * a.split * 2 <= room) a.split *= 2;
         groups *= a.split;
     }
-    auto kernel = unsure ? (stream ? quantize16_kernel<HP, GIVEN, true, true> : quantize16_kernel<HP, GIVEN, false, true>)
-                         : (stream ? quantize16_kernel<HP, GIVEN, true, false> : quantize16_kernel<HP, GIVEN, false, false>);
+    auto kernel = unsure ? (stream ? quantize16_kernel<HP, GIVEN, true, true, false> : quantize16_kernel<HP, GIVEN, false, true, false>)
+                         : (stream ? quantize16_kernel<HP, GIVEN, true, false, false> : quantize16_kernel<HP, GIVEN, false, false, false>);
+    if constexpr (!GIVEN)
+        if (mixed) kernel = quantize16_kernel<HP, false, false, false, true>;
     hipLaunchKernelGGL(kernel, dim3(groups), dim3(64 * waves), 0, s, a);
 }
 
-static void launch_quantize16(PackArgs &a, int H, bool given, bool stream, bool unsure, hipStream_t s) {
-    if (H == 1) given ? launch_quantize16_as<1, true>(a, H, stream, unsure, s) : launch_quantize16_as<1, false>(a, H, stream, unsure, s);
-    else if (H == 2) given ? launch_quantize16_as<2, true>(a, H, stream, unsure, s) : launch_quantize16_as<2, false>(a, H, stream, unsure, s);
-    else given ? launch_quantize16_as<4, true>(a, H, stream, unsure, s) : launch_quantize16_as<4, false>(a, H, stream, unsure, s);
+static void launch_quantize16(PackArgs &a, int H, bool given, bool stream, bool unsure, bool mixed, hipStream_t s) {
+#define PACKKV_LAUNCH_QUANTIZE(hp) \
+    given ? launch_quantize16_as<hp, true>(a, H, stream, unsure, false, s) : launch_quantize16_as<hp, false>(a, H, stream, unsure, mixed, s)
+    if (H == 1) PACKKV_LAUNCH_QUANTIZE(1);
+    else if (H == 2) PACKKV_LAUNCH_QUANTIZE(2);
+    else PACKKV_LAUNCH_QUANTIZE(4);
+#undef PACKKV_LAUNCH_QUANTIZE
 }
 
-int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s) {
+// Whether the arenas take the next n_chunks chunks of each tensor at their largest, by the host's bound of the fill level.
+static bool fits_for_sure(const kv_cache *c, int n_chunks) {
+    const uint64_t worst16 = uint64_t(n_chunks) * (CHUNK_MAX / 16);
+    return c->pool || (c->fill_bound16[0] + worst16 <= arena_units(c->sizes.k_arena) && c->fill_bound16[1] + worst16 <= arena_units(c->sizes.v_arena));
+}
+
+bool completes_in_place(const kv_cache *c) {
+    const int n_chunks = c->cfg.batch * c->cfg.n_kv_heads;
+    return finds_params(c, n_chunks) && fits_for_sure(c, n_chunks) && !larger_than_caches(n_chunks);
+}
+
+int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, TailRest *rest, hipStream_t s) {
     const int B = c->cfg.batch, H = c->cfg.n_kv_heads;
     const int n_chunks = kjob.n_blocks * B * H;
     if (n_chunks <= 0 || n_chunks > MAX_NEW_CHUNKS) return KV_ERR_ARG;
@@ -2094,7 +2156,7 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
     // rounds that fit the staging area whole (the input is then quantized once, not twice: 33 -> 21 us for
     // 2 x 1504 repacked bf16 chunks); it places whatever the pool covers, so no fill level is tested.
     const bool staged = staged_rounds(c, n_chunks);
-    bool two_pass = !staged;
+    bool two_pass = !staged || !fits_for_sure(c, n_chunks);
     const bool stream = larger_than_caches(n_chunks);
     PackArgs a;
     for (int i = 0; i < 2; ++i) {
@@ -2128,7 +2190,8 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
         t.status = job.status;
         t.page_list = job.page_list;
         t.max_pages = job.max_pages;
-        if (staged && !c->pool && job.fill_bound16 + t.round.worst16 > job.arena_cap16) two_pass = true;
+        t.tail = static_cast<__half *>(i ? c->buf.v_tail : c->buf.k_tail);
+        t.rest = rest ? rest->src[i] : nullptr;
     }
     const bool unsure = two_pass;   // the device decides (staged_round)
     a.index_words = c->index_words;
@@ -2136,6 +2199,8 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
     a.first_tensor = 0;
     a.pool_state = c->pool ? c->pool->state : nullptr;
     a.staging = ws + c->stage_offset;
+    a.held = kjob.held;
+    a.rest_units = 0;
     if (staged) {
         // equal parts of whole rows that fit the staging area, half of its slots for each tensor
         const int rows = n_chunks / H, most = c->stage_chunks / 2 / H;
@@ -2148,11 +2213,19 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
             a.n = a.rows * H;
             a.t[0].widths = reinterpret_cast<uint16_t *>(sizes16);
             a.t[1].widths = a.t[0].widths + 4 * ((a.n + 1) & ~1);
-            launch_quantize16(a, H, !finds_params(c, n_chunks), stream, unsure, s);
+            launch_quantize16(a, H, !finds_params(c, n_chunks), stream, unsure, kjob.held > 0, s);
             static_assert(PLACE_SMALL_CHUNKS >= 16384 / 2, "a staged round of a paged cache fits the placement kernel");
             static_assert(16384 * 8 + 64 <= WS_SIZES_BYTES, "the width sums of a part fit the sizes area");
             if (c->pool) hipLaunchKernelGGL(place_small_kernel, dim3(1), dim3(1024), 0, s, a);
-            hipLaunchKernelGGL(unsure ? assemble16_kernel<true> : assemble16_kernel<false>, dim3((a.n + 3) / 4, 2), dim3(256), 0, s, a);
+            int groups = (a.n + 3) / 4;
+            if (rest && rest->tokens > 0 && !two_pass && part + per_part >= rows) {   // behind the last read of the tail
+                a.rest_units = rest->tokens * (H * D / 8);
+                a.rest_stride = rest->batch_stride;
+                a.rest_bf16 = rest->bf16;
+                groups += (a.rest_units + REST_UNITS - 1) / REST_UNITS * B;
+                rest->tokens = 0;
+            }
+            hipLaunchKernelGGL(unsure ? assemble16_kernel<true> : assemble16_kernel<false>, dim3(groups, 2), dim3(256), 0, s, a);
         }
     }
     if (two_pass) {
