@@ -115,11 +115,12 @@ typedef struct {
     size_t k_index, v_index;           /* uint32 [max_chunks + 1]                 */
     size_t k_token_meta, v_token_meta; /* uint32 [B][max_tokens]                  */
     size_t k_tail, v_tail;             /* fp16 [B][tail_capacity][H_kv][128]      */
-    size_t workspace;                  /* status words, chunk sizes, V partials, and (packs of
-                                          16) the compressor's staging area: at most 75 MB, and
-                                          at most what the cache's chunks can take; with half
-                                          of that area a cache works too, its large appends
-                                          in twice as many parts */
+    size_t workspace;                  /* status words, chunk sizes, V partials, and the
+                                          compressor's staging area: at most 75 MB (packs of
+                                          8: 84 MB), and at most what the cache's chunks can
+                                          take; with half of that area a cache works too, its
+                                          large appends in twice as many parts (packs of 8:
+                                          with any part of it, or none and slower appends) */
     size_t token_order;                /* uint8 [B][max_tokens]; 0 without repacking */
     size_t k_pages, v_pages;           /* paged caches only: uint32 page lists; else 0 */
 } kv_sizes_t;

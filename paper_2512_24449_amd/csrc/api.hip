@@ -89,8 +89,9 @@ extern "C" int kv_query_sizes(const kv_config_t *cfg, double bits_per_element_bu
     out->k_tail = out->v_tail =
         round256(size_t(cfg->batch) * cfg->tail_capacity * cfg->n_kv_heads * D * 2);
     out->workspace = round256(WS_VPART + v_partial_bytes(cfg->batch, cfg->n_q_heads));
-    if (cfg->pack_size == 16)  // staging area of the compressor behind the rest
-        out->workspace += round256(size_t(stage_chunks_for(cfg->batch, cfg->n_kv_heads, max_chunks)) * CHUNK_MAX);
+    // staging area of the compressor behind the rest
+    const size_t pair = stage_pair_bytes(cfg->pack_size, wide_codes(cfg->k_rel_scale), wide_codes(cfg->v_rel_scale));
+    out->workspace += round256(size_t(stage_chunks_for(cfg->batch, cfg->n_kv_heads, max_chunks, pair)) / 2 * pair);
     out->token_order = cfg->repack ? round256(size_t(cfg->batch) * max_tokens) : 0;
     out->k_pages = out->v_pages = 0;
     return KV_OK;
@@ -181,10 +182,12 @@ int create_cache(const kv_config_t *cfg, kv_page_pool *pool, const kv_buffers_t 
     const size_t stage_offset = round256(WS_VPART + v_partial_bytes(cfg->batch, cfg->n_q_heads));
     int stage_chunks = 0;
     if (sizes->workspace < stage_offset) return KV_ERR_ARG;
-    if (cfg->pack_size == 16) {
-        const size_t slots = (sizes->workspace - stage_offset) / CHUNK_MAX;
-        if (slots < size_t(stage_chunks_for(cfg->batch, cfg->n_kv_heads, max_chunks, true))) return KV_ERR_ARG;
-        stage_chunks = int(std::min<size_t>(slots, stage_chunks_for(cfg->batch, cfg->n_kv_heads, max_chunks))) & ~1;
+    {
+        const size_t pair = stage_pair_bytes(cfg->pack_size, wide_codes(cfg->k_rel_scale), wide_codes(cfg->v_rel_scale));
+        const size_t slots = (sizes->workspace - stage_offset) / pair * 2;
+        // (packs of 8 work without the staging area, in two passes over the input)
+        if (cfg->pack_size == 16 && slots < size_t(stage_chunks_for(cfg->batch, cfg->n_kv_heads, max_chunks, pair, true))) return KV_ERR_ARG;
+        stage_chunks = int(std::min<size_t>(slots, stage_chunks_for(cfg->batch, cfg->n_kv_heads, max_chunks, pair)));
     }
     if (cfg->repack && (!aligned256(buffers->token_order) || sizes->token_order < need.token_order))
         return KV_ERR_ARG;

@@ -66,15 +66,22 @@ int plan_groups_for(int n_blocks, int streams, int per_cu, int64_t most);
 // Workgroups of the kernels for wide chunks with two smaller buffers to a wave (pack8.h) that run at once.
 inline int mid_room() { return flat_groups_for(int64_t(1) << 40, 2, int64_t(1) << 30); }
 
-// Staging area of the compressor (packs of 16): chunks it holds, half of them for each tensor, each in
+// Codes that the staged path of the compressor takes (seven bits; finer scales take the two-pass path).
+constexpr int MOST_STAGED_CODE = 127;
+
+// Staging area of the compressor: chunks it holds, half of them for each tensor, each in
 // a slot of the largest chunk's size.  64 blocks of both tensors at a time, within 512 .. 16384 chunks
-// (2.4 .. 75 MB) and no more than the cache can hold: large enough to fill the chip, small enough to
+// (2.4 .. 75 MB; packs of 8 up to 84 MB, wide chunks included) and no more than the cache can hold: large enough to fill the chip, small enough to
 // stay in the last-level cache until it is read back.  A cache also works with half of that (least =
 // true), in twice as many parts: 4096 tokens of 32 streams take 28.9 us in one part and 40.2 in two, with 18.9
-// and 9.4 MB of staging; 16384 tokens of 8 streams 60.8 and 98.5, with 4.7 and 2.4 MB.
-inline int stage_chunks_for(int batch, int n_kv_heads, int64_t max_chunks, bool least = false) {
-    const int64_t want = int64_t(batch) * n_kv_heads * (least ? 64 : 128);
-    const int64_t some = want < (least ? 256 : 512) ? (least ? 256 : 512) : want > 16384 ? 16384 : want;
+// and 9.4 MB of staging; 16384 tokens of 8 streams 60.8 and 98.5, with 4.7 and 2.4 MB.  (Packs of 8 also work without.)
+inline size_t stage_pair_bytes(int pack_size, bool wide_k, bool wide_v) {   // a slot of each tensor
+    return size_t(chunk_max_bytes(pack_size, wide_k)) + size_t(chunk_max_bytes(pack_size, wide_v));
+}
+inline int stage_chunks_for(int batch, int n_kv_heads, int64_t max_chunks, size_t pair_bytes, bool least = false) {
+    const int64_t most = int64_t(size_t(16384) * CHUNK8_MAX / pair_bytes) * 2;
+    const int64_t want = int64_t(batch) * n_kv_heads * (least ? 64 : 128), cap = most < 16384 ? most : 16384;
+    const int64_t some = want < (least ? 256 : 512) ? (least ? 256 : 512) : want > cap ? cap : want;
     return int(some < 2 * max_chunks ? some : 2 * max_chunks);
 }
 
@@ -205,7 +212,7 @@ struct kv_page_pool {
     int64_t n_pages;
 };
 
-// Staged compression of packs of 16 (compress.hip).  A round whose chunks fit the arena even at
+// Staged compression (compress.hip).  A round whose chunks fit the arena even at
 // their largest takes the staged path; the test runs on the device, where the fill level is.
 struct StagedRound {
     int64_t first_chunk;   // first chunk of the whole round
@@ -225,7 +232,7 @@ struct kv_cache {
     bool wide_k, wide_v;    // codes above 15: wide chunk layout for that tensor
     int64_t packed_tokens;  // per batch element
     int32_t tail_tokens;
-    size_t stage_offset;    // staging area of the compressor inside the workspace (packs of 16; else unused)
+    size_t stage_offset;    // staging area of the compressor inside the workspace
     int stage_chunks;       // chunks it holds
     uint64_t fill_bound16[2];  // K, V: upper bound of the arena's fill level, every chunk so far at its largest
     // paged arena: both tensors live in the pool's pages (buf.k_arena = buf.v_arena = pool->pages),

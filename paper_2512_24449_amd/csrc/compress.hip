@@ -1,19 +1,19 @@
 // Append-side compressor: token-wise quantization, bit-packing, appending
 // (PackKV Sec. III-B.1 .. III-B.4).  Cold path: runs once per 64 decode steps.
 //
-// Packs of 16 in a contiguous arena whose free space takes even the largest chunks, or in a
-// paged arena if the staging area takes the whole round (staged path, the input is read and quantized once):
+// In a contiguous arena whose free space takes even the largest chunks, or in a
+// paged arena if the staging area takes the whole round (staged path, the input is read and quantized once; codes up to 127):
 //   quantize       resident workgroups, 16 tokens of all kv-heads at a time each: min/max over a token's
 //                  H*128 values -> fp16 scale = rel*(max-min), fp16 min; the codes, pack headers and pack bytes per
 //                  token group to a fixed slot per chunk of the staging area
 //   place_small    (paged) chunk positions, from the pack bytes
-//   assemble       one wave per chunk: codes to bit planes at the chunk's place in the arena; contiguous: the
+//   assemble       one wave per chunk: codes to bit planes (packs of 8: consecutive bits) at the chunk's place in the arena; contiguous: the
 //                  workgroup adds up the sizes before its chunks and sets their index words
 // with more than 64 kv-heads or V-median repacking the scales come first:
 //   token_params   a workgroup or a wave per (token, batch)
 //   v_median_key, block_order   (V-median repacking only) sort key per token,
 //                  order of the 64 tokens of a block, metadata into storage order
-// else (two-pass path: packs of 8, large rounds of paged arenas, a nearly full arena), behind token_params:
+// else (two-pass path: large rounds of paged arenas, a nearly full arena, codes above 127), behind token_params:
 //   chunk_sizes    one workgroup per chunk: quantize, per-pack width -> bytes
 //   scan_offsets / place_small, place_chunks (paged arena) one workgroup: chunk positions -> index;
 //                  paged: inside pages taken from a shared pool, index of (start, end) pairs
@@ -236,6 +236,9 @@ struct PackTensor {
     float rel;
     bool cap_all;           // staged: see QuantRange
     float small_scale;
+    bool wide;              // packs of 8: wide chunk layout
+    uint32_t stage_at, slot;  // staged: where the tensor's slots start in the staging area, bytes of a slot
+    uint32_t header16, unit_shift;  // size of a chunk from its width sums: chunk_units
     uint64_t arena_cap16;
     uint32_t *status;       // set when the round does not fit
     uint32_t *page_list;    // paged arena
@@ -257,12 +260,11 @@ struct PackArgs {
     int rest_units;         // 16-byte units of a batch element that the tail takes behind the round, 0: none
     int64_t rest_stride;    // elements between the batch elements of `rest`
     bool rest_bf16;
-    uint8_t *staging;       // K chunk i of the part in slot i, V chunk i in slot n + i: 512 pack headers [group][channel],
-                            // then the codes of the packs (quantize16_kernel)
+    uint8_t *staging;       // chunk i of the part in the tensor's slot i: the pack headers [group][channel], then the codes
+                            // of the packs (quantize16_kernel)
 };
 
-// One workgroup per new chunk; packs of PK = 8 tokens (Sec. IV-B; packs of 16 have their own
-// kernel below): the chunk has 64/PK token groups of 128 packs, thread tau owns packs tau + 256k
+// Two-pass path, packs of 8 (Sec. IV-B; packs of 16 have their own kernel below).  One workgroup per new chunk: the chunk has 64/PK token groups of 128 packs, thread tau owns packs tau + 256k
 // (token group (tau >> 7) + 2k, channel tau & 127).  A pack takes PK*w/8 payload bytes.  WIDE (codes above 15, packs of 8): the
 // header is a width byte per pack followed by a minimum byte per pack, widths go up to 8.
 template <bool WRITE, int PK, bool WIDE, bool STREAM>
@@ -654,10 +656,10 @@ __device__ inline void copy_image(const ChunkLds &lds, int n16, uint8_t *__restr
     if (tau + 256 < n16) dst[tau + 256] = image[tau + 256];
 }
 
-// Staged path, packs of 16: the input is read and quantized once.
+// Staged path: the input is read and quantized once.
 //   quantize  a workgroup holds 16 tokens of all kv-heads in registers: their scales and minimums, then
-//             their codes as nibbles, pack headers and bytes per pack list, into the chunk's slot of CHUNK_MAX
-//             bytes of the staging area in the workspace
+//             their codes as nibbles (wide chunks: bytes), pack headers and bytes per pack list, into the chunk's slot
+//             (the largest chunk's bytes) of the staging area in the workspace
 //   assemble  one wave per chunk: turns the codes into planes and puts the chunk's bytes at their place in the arena
 // A chunk's place depends on the sizes of all chunks before it, so some second step is needed;
 // this one reads the codes (a quarter of the input, and still in the last-level cache: the staging area is a
@@ -737,10 +739,19 @@ __device__ inline uint32_t width_bytes(uint32_t range) {
     return w | (range & low);
 }
 
-// Size of a chunk in 16-byte units from the width sums of its four token groups (a pack of width w takes 2 w bytes).
-__device__ inline uint32_t chunk_units(uint2 sums) {
+// Widths of codes up to 127.
+__device__ inline uint32_t width_bytes7(uint32_t range) {
+    const uint32_t low = width_bytes(range & 0x0F0F0F0Fu), high = width_bytes((range >> 4) & 0x07070707u);
+    const uint32_t any = ((high + 0x7F7F7F7Fu) & 0x80808080u) >> 7, mask = (any << 8) - any;   // bytes whose upper half is not 0
+    return (low & ~mask) | ((high + 0x04040404u) & mask);
+}
+
+// Size of a chunk in 16-byte units from the width sums of its four groups of 16 tokens: a pack of width w takes 2 w bytes
+// (w bytes with packs of 8).
+constexpr uint32_t UNIT_SHIFT16 = 3, UNIT_SHIFT8 = 4;
+__device__ inline uint32_t chunk_units(uint2 sums, uint32_t header16 = HEADER / 16, uint32_t unit_shift = UNIT_SHIFT16) {
     const uint32_t w = (sums.x & 0xFFFFu) + (sums.x >> 16) + (sums.y & 0xFFFFu) + (sums.y >> 16);
-    return uint32_t(HEADER / 16) + ((w + 7) >> 3);
+    return header16 + ((w + (1u << unit_shift) - 1) >> unit_shift);
 }
 
 // Sixteen words of a lane (v[k], k < 8: minimums of tokens 2k, 2k + 1; v[8 + k]: their negated maximums), smallest
@@ -785,13 +796,15 @@ __device__ inline uint32_t wave_min_scatter16(const uint32_t (&v)[16]) {
 // t against quotient + 1/2 + g is below 0.5 (its rounding) + 0.5 (c; 2^(e-8) for e >= 8) + 0.12 (r) + 0.13 (the
 // definition's roundings) units, so g = 2 (+ 2^(e-7)) does: a third fewer divides, which matters here, where all waves
 // of a token wait for the slowest.  A token whose scale is so small that codes could pass qmax always divides.
+// For quotients up to 127.5 (WIDE) r contributes up to 1 unit and the definition's roundings 1: g = 4 (+ 2^(e-7)).
 // r and c come divided by 256 (exactly: they are powers of two away from underflow), for half_mul_add_unit.
+template <bool WIDE = false>
 __device__ inline float4 token_quant_near(uint32_t mt, float small_scale) {
     const float s = __half2float(__ushort_as_half(uint16_t(mt & 0xFFFFu)));
     const float mn = __half2float(__ushort_as_half(uint16_t(mt >> 16)));
     const float r = s != 0.0f ? __builtin_amdgcn_rcpf(s) : 0.0f;
     const int e = int((__float_as_uint(fmaf(-mn, r, 128.5f)) >> 23) & 0xFFu) - 127;
-    uint32_t g = 2u + (e >= 8 ? 2u << min(e - 8, 14) : 0u);
+    uint32_t g = (WIDE ? 4u : 2u) + (e >= 8 ? 2u << min(e - 8, 14) : 0u);
     const float c = fmaf(-mn, r, 128.5f + float(g) * (1.0f / 65536.0f));
     if (s > 0.0f && s < small_scale) g = 1u << 15;
     return make_float4(r * (1.0f / 256.0f), c * (1.0f / 256.0f), __uint_as_float(2u * g), __uint_as_float(mt));
@@ -875,7 +888,7 @@ struct QuantRange {
 inline QuantRange quant_range(float rel, int qmax) {
     // the largest quotient is below (s + u) / (rel s) (1 + 2^-20), u half a unit of the scale's last place; with the
     // guard of token_quant_near, its error and the half that rounds it must stay below qmax + 1
-    const double room = (qmax + 0.5 - 4.0 / 65536.0) * double(rel) / (1.0 + 1.0 / (1 << 20)) - 1.0;   // must exceed u / s
+    const double room = (qmax + 0.5 - (qmax > 15 ? 8.0 : 4.0) / 65536.0) * double(rel) / (1.0 + 1.0 / (1 << 20)) - 1.0;   // must exceed u / s
     QuantRange q;
     q.cap_all = !(room > 1.0 / 2048.0);
     q.small_scale = q.cap_all ? 0.0f : float(1.0 / (1 << 25) / room * 1.0001);
@@ -901,16 +914,23 @@ inline QuantRange quant_range(float rel, int qmax) {
 // MIXED: the round is the block that the new tokens complete: its first `held` tokens are read from the tail, the others
 // where the caller has them, and those are left in the tail as well, so that no copy has to run first (the appends that
 // complete a block of 8 x 52 heads 16.1 -> 14.6 us, of 4 x 1 heads 15.4 -> 11.6).  One item to a workgroup.
+// PACK8: a channel's 16 tokens are two packs, whose minimum and maximum are complete after every second quad.  Wide chunks
+// (codes up to MOST_STAGED_CODE) keep their codes in bytes, [group][quad][channel % 8 / 4][channel / 8][channel % 4],
+// and two header bytes to a pack.  One read of the input instead of three (parameters, sizes, bytes): 8 x 52 heads
+// of 8000 tokens 1603 -> 653 us, wide 1670 -> 947; 4 x 8 heads 134 -> 61; a block of 2 x 40 heads, V wide, 44.7 -> 16.1 (eight
+// launches before, two now).
 // UNSURE: the round may not be staged, and the kernel finds out first (at run time the question alone cost sure rounds 1 %, a
 // block of 8 x 52 heads 16.0 -> 16.4 us).  Not staged, 8000 tokens of 8 x 52 heads take 1025 us, 4096 of 32 55; quantized
 // all the same, and thrown away, 1305 and 67.
-template <int HP, bool GIVEN, bool STREAM, bool UNSURE, bool MIXED>
+template <int HP, bool GIVEN, bool STREAM, bool UNSURE, bool MIXED, bool PACK8>
 __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_kernel(PackArgs a) {
+    static_assert(!PACK8 || !UNSURE, "packs of 8 are staged in rounds that fit for sure");
     static_assert(!MIXED || (!GIVEN && !UNSURE), "the block of the tail: rounds that are staged for sure and find their parameters");
     constexpr int MOST_WAVES = HP < 4 ? 1 : GIVEN ? 4 : 16;
     ieee_mode_off();
     __shared__ uint32_t red[2][MOST_WAVES][16];
     __shared__ float4 tok_all[MOST_WAVES][HP < 4 ? 64 : 16];
+    __shared__ uint32_t first_sums[PACK8 ? MOST_WAVES : 1][64];
     const int lane = threadIdx.x & 63, cg = lane & 15, row4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = int(blockDim.x >> 6);
     float4 *tok = tok_all[wave];
@@ -1028,7 +1048,7 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
         if constexpr (GIVEN) {
             const uint32_t now = given;
             given = meta_of(nxt)[cg];
-            tok[HP < 4 ? lane : cg] = token_quant_near(now, pt.small_scale);
+            tok[HP < 4 ? lane : cg] = PACK8 && pt.wide ? token_quant_near<true>(now, pt.small_scale) : token_quant_near(now, pt.small_scale);
         } else {
             uint32_t v[16];
 #pragma unroll
@@ -1074,7 +1094,7 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
             const uint32_t mnw = cg < 8 ? word : other >> 16, mxw = cg < 8 ? other : word >> 16;
             const int t = 2 * (cg & 7) + (cg >> 3);
             const uint32_t mt = token_meta_word(half_lo(mnw), -half_lo(mxw), pt.rel);
-            tok[HP < 4 ? 16 * row4 + t : t] = token_quant_near(mt, pt.small_scale);
+            tok[HP < 4 ? 16 * row4 + t : t] = PACK8 && pt.wide ? token_quant_near<true>(mt, pt.small_scale) : token_quant_near(mt, pt.small_scale);
             if (HP == 4 ? threadIdx.x < 16 : head_in_set == 0) meta_of(cur)[t] = mt;
             if (skip) {
                 if (!more) break;
@@ -1094,8 +1114,27 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
             for (int t = 0; t < 16; ++t)
                 if (present && !from_tail(t)) *reinterpret_cast<uint4 *>(to + t * cs.token_stride) = raw[t];
         }
-        const uint32_t at = uint32_t((cur.v ? a.n : 0) + cur.row * H + head) * uint32_t(CHUNK_MAX) + uint32_t(16 * cg);
-        uint32_t codes[8], mn2[4], mx2[4];   // codes: channel c, eight tokens as nibbles
+        const bool wide = PACK8 && pt.wide;
+        const uint32_t at = pt.stage_at + uint32_t(cur.row * H + head) * pt.slot + uint32_t(16 * cg);
+        uint32_t codes[8], mn2[4], mx2[4];   // codes: channel c, eight tokens as nibbles (wide: four as bytes)
+        uint32_t width_sum = 0;              // in bytes: at most 28 each
+        // header bytes of the lane's eight packs of group `group`: (width << 4) | minimum, or (wide) the widths and the minimums
+        // (codes are at most 15 or 127; the masks keep the header one for any bytes, of which width_bytes makes at most 4)
+        auto headers = [&](int group) {
+            uint8_t *const to = a.staging + (at + uint32_t(D * group) - uint32_t(8 * cg));
+            const uint32_t m_lo = __builtin_amdgcn_perm(mn2[1], mn2[0], 0x06040200u), m_hi = __builtin_amdgcn_perm(mn2[3], mn2[2], 0x06040200u);
+            const uint32_t x_lo = __builtin_amdgcn_perm(mx2[1], mx2[0], 0x06040200u), x_hi = __builtin_amdgcn_perm(mx2[3], mx2[2], 0x06040200u);
+            if (wide) {
+                const uint32_t m0 = m_lo & 0x7F7F7F7Fu, m1 = m_hi & 0x7F7F7F7Fu, w0 = width_bytes7(x_lo - m0), w1 = width_bytes7(x_hi - m1);
+                width_sum += w0 + w1;
+                if (present) *reinterpret_cast<uint2 *>(to) = make_uint2(w0, w1);
+                if (present) *reinterpret_cast<uint2 *>(to + HEADERW / 2) = make_uint2(m0, m1);
+            } else {
+                const uint32_t m0 = m_lo & 0x0F0F0F0Fu, m1 = m_hi & 0x0F0F0F0Fu, w0 = width_bytes(x_lo - m0), w1 = width_bytes(x_hi - m1);
+                width_sum += w0 + w1;
+                if (present) *reinterpret_cast<uint2 *>(to) = make_uint2((w0 << 4) | m0, (w1 << 4) | m1);
+            }
+        };
 #pragma unroll
         for (int quad = 0; quad < 4; ++quad) {
             // tokens first, first + 2, .. first + 6
@@ -1113,12 +1152,13 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
             for (int k = 0; k < 4; ++k) {
                 // (0x3F00 + code is an fp16 number between 1.75 and 1.77)
                 const uint32_t lo = pk_min3_f16(pair[0][k], pair[1][k], pair[2][k]), hi = pk_max3_f16(pair[0][k], pair[1][k], pair[2][k]);
-                mn2[k] = quad ? pk_min3_f16(mn2[k], lo, pair[3][k]) : pk_min(lo, pair[3][k]);
-                mx2[k] = quad ? pk_max3_f16(mx2[k], hi, pair[3][k]) : pk_max(hi, pair[3][k]);
+                const bool first_quad = PACK8 ? quad % 2 == 0 : quad == 0;
+                mn2[k] = first_quad ? pk_min(lo, pair[3][k]) : pk_min3_f16(mn2[k], lo, pair[3][k]);
+                mx2[k] = first_quad ? pk_max(hi, pair[3][k]) : pk_max3_f16(mx2[k], hi, pair[3][k]);
                 const uint32_t p01 = __builtin_amdgcn_perm(pair[1][k], pair[0][k], 0x06020400u);  // even ch. tokens 0 1, odd ch. tokens 0 1
                 const uint32_t p23 = __builtin_amdgcn_perm(pair[3][k], pair[2][k], 0x06020400u);
                 const uint32_t e = __builtin_amdgcn_perm(p23, p01, 0x05040100u), o = __builtin_amdgcn_perm(p23, p01, 0x07060302u);
-                if (quad & 1)
+                if ((quad & 1) && !wide)
                     codes[2 * k] |= e << 4, codes[2 * k + 1] |= o << 4;
                 else
                     codes[2 * k] = e, codes[2 * k + 1] = o;
@@ -1126,26 +1166,25 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
             // what the quad leaves is computed here: moved to where it is used, it would keep all pairs in registers
 #pragma unroll
             for (int k = 0; k < 4; ++k) consume_here(mn2[k]), consume_here(mx2[k]), consume_here(codes[2 * k]), consume_here(codes[2 * k + 1]);
-            if ((quad & 1) && present) {
-                uint8_t *const to = a.staging + (at + uint32_t(HEADER + 1024 * g + 512 * (quad >> 1)));
+            if (((quad & 1) || wide) && present) {
+                const uint32_t place = wide ? HEADERW + 2048 * g + 512 * quad : (PACK8 ? HEADER8 : HEADER) + 1024 * g + 512 * (quad >> 1);
+                uint8_t *const to = a.staging + (at + place);
                 *reinterpret_cast<uint4 *>(to) = make_uint4(codes[0], codes[1], codes[2], codes[3]);
                 *reinterpret_cast<uint4 *>(to + 256) = make_uint4(codes[4], codes[5], codes[6], codes[7]);
             }
+            if constexpr (PACK8) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (quad & 1) headers(2 * g + (quad >> 1));
+                if (quad == 1) first_sums[wave][lane] = width_sum, width_sum = 0;   // (not in a register: one too many)
+            }
         }
-        // headers: bytes (width << 4) | minimum of the lane's eight packs
-        // (codes are at most 15; the masks keep the header one for any bytes, of which width_bytes makes at most 4)
-        const uint32_t m_lo = __builtin_amdgcn_perm(mn2[1], mn2[0], 0x06040200u) & 0x0F0F0F0Fu;
-        const uint32_t m_hi = __builtin_amdgcn_perm(mn2[3], mn2[2], 0x06040200u) & 0x0F0F0F0Fu;
-        const uint32_t x_lo = __builtin_amdgcn_perm(mx2[1], mx2[0], 0x06040200u), x_hi = __builtin_amdgcn_perm(mx2[3], mx2[2], 0x06040200u);
-        const uint32_t w_lo = width_bytes(x_lo - m_lo), w_hi = width_bytes(x_hi - m_hi);
-        uint32_t sum = w_lo + w_hi;   // bytes of at most 8
+        if constexpr (!PACK8) headers(g);
+        uint32_t sum = width_sum;
+        if (PACK8) sum += first_sums[wave][lane];
         sum += sum >> 16;
         sum = (sum + (sum >> 8)) & 0xFFu;
         sum = row_inclusive_scan(sum);
-        if (present) {
-            *reinterpret_cast<uint2 *>(a.staging + (at + uint32_t(D * g) - uint32_t(8 * cg))) = make_uint2((w_lo << 4) | m_lo, (w_hi << 4) | m_hi);
-            if (cg == 15) pt.widths[4 * (cur.row * H + head) + g] = uint16_t(sum);
-        }
+        if (present && cg == 15) pt.widths[4 * (cur.row * H + head) + g] = uint16_t(sum);
         if (!more) break;
         cur = nxt;
         item = next;
@@ -1283,7 +1322,7 @@ __global__ __launch_bounds__(256) void assemble16_kernel(PackArgs a) {
     const uint2 *widths = reinterpret_cast<const uint2 *>(t.widths);
     // one memory latency for all that the start needs
     StagedLane in;
-    if (present) in.load(a.staging + size_t(blockIdx.y * a.n + cl) * CHUNK_MAX, lane);
+    if (present) in.load(a.staging + (t.stage_at + uint32_t(cl) * uint32_t(CHUNK_MAX)), lane);
     const uint32_t first = t.index[t.round.first_chunk];
     uint32_t place, units = 0;
     if (paged) {
@@ -1320,6 +1359,166 @@ __global__ __launch_bounds__(256) void assemble16_kernel(PackArgs a) {
             const uint4 q = *reinterpret_cast<const uint4 *>(img + 16 * (lane + 64 * i));
             __builtin_nontemporal_store(u32x4n{q.x, q.y, q.z, q.w}, dst + lane + 64 * i);
         }
+    }
+}
+
+// The same for packs of 8 tokens, narrow or wide: consecutive codes of w bits, w bytes to a pack, packs in [group][channel]
+// order.  A lane's part: channels 2 lane, 2 lane + 1 in all eight token groups, two packs next to each other in each.
+template <bool WIDE>
+struct StagedLane8 {
+    uint2 codes[8][WIDE ? 2 : 1];   // [group][quad: tokens 0 2 4 6, 1 3 5 7]: bytes; narrow: eight nibbles
+    uint32_t width[8], least[8];    // [group]: two header bytes (narrow: both in `width`)
+    __device__ inline void load(const uint8_t *slot, int lane) {
+        typedef uint32_t u32x2n __attribute__((ext_vector_type(2)));
+        const int at = 256 * ((lane >> 1) & 1) + 16 * (lane >> 2) + 8 * (lane & 1);
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {
+            width[g] = *reinterpret_cast<const uint16_t *>(slot + D * g + 2 * lane);
+            if (WIDE) least[g] = *reinterpret_cast<const uint16_t *>(slot + HEADERW / 2 + D * g + 2 * lane);
+#pragma unroll
+            for (int q = 0; q < (WIDE ? 2 : 1); ++q) {
+                const u32x2n v = __builtin_nontemporal_load(reinterpret_cast<const u32x2n *>(
+                    slot + (WIDE ? HEADERW + 1024 * g + 512 * q : HEADER8 + 512 * g) + at));
+                codes[g][q] = make_uint2(v.x, v.y);
+            }
+        }
+    }
+};
+
+// Bits `from` .. of the image's payload |= value.  (The image is zero there before; the packs of neighbouring lanes share words.)
+__device__ inline void or_bits(uint32_t *payload, uint32_t byte, uint64_t value, int bytes) {
+    uint32_t *const at = payload + (byte >> 2);
+    const uint32_t shift = 8 * (byte & 3);
+    const uint64_t low = value << shift;
+    if (bytes > 0) atomicOr(at, uint32_t(low));
+    if (int(byte & 3) + bytes > 4) atomicOr(at + 1, uint32_t(low >> 32));
+    if (int(byte & 3) + bytes > 8) atomicOr(at + 2, uint32_t((value >> 32) >> (32 - shift)));   // (shift > 0 here)
+}
+
+// The bytes of a chunk of packs of 8 from its staged codes, in the wave's LDS image of `units` 16-byte units.
+template <bool WIDE>
+__device__ inline void assemble_chunk8(const StagedLane8<WIDE> &in, uint32_t units, uint8_t *img) {
+    constexpr int HDR = WIDE ? HEADERW : HEADER8;
+    const int lane = threadIdx.x & 63;
+    uint4 *const words = reinterpret_cast<uint4 *>(img);
+    for (uint32_t i = HDR / 16 + lane; i < units; i += 64) words[i] = make_uint4(0, 0, 0, 0);
+    wave_lds_fence();
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+        *reinterpret_cast<uint16_t *>(img + D * g + 2 * lane) = uint16_t(in.width[g]);
+        if (WIDE) *reinterpret_cast<uint16_t *>(img + HEADERW / 2 + D * g + 2 * lane) = uint16_t(in.least[g]);
+    }
+    uint32_t *const payload = reinterpret_cast<uint32_t *>(img + HDR);
+    uint32_t run = 0;   // bytes of the groups before
+#pragma unroll
+    for (int g2 = 0; g2 < 4; ++g2) {
+        // the widths of two groups in the halves of a word: at most 1024 bytes each
+        uint32_t w[2][2], both = 0;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t h = in.width[2 * g2 + i];
+            w[i][0] = WIDE ? h & 0xFFu : (h >> 4) & 0xFu, w[i][1] = WIDE ? h >> 8 : h >> 12;
+            both |= (w[i][0] + w[i][1]) << (16 * i);
+        }
+        const uint32_t inc = uint32_t(wave_inclusive_scan(int(both))), before = inc - both;
+        const uint32_t total = uint32_t(__builtin_amdgcn_readlane(int(inc), 63));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int g = 2 * g2 + i;
+            const uint32_t at = run + (i ? (total & 0xFFFFu) + (before >> 16) : before & 0xFFFFu);
+            uint64_t bits[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const uint32_t wc = w[i][c];
+                uint32_t p0, p1;   // halfwords: codes 2 j and 2 j + 1 of the pack, j = 0, 1 and 2, 3
+                if constexpr (WIDE) {
+                    uint32_t all = (in.least[g] >> (8 * c)) & 0xFFu;
+                    all = __builtin_amdgcn_perm(0u, all, 0u);   // the minimum in every byte: no byte borrows
+                    const uint32_t e = (c ? in.codes[g][0].y : in.codes[g][0].x) - all, o = (c ? in.codes[g][WIDE].y : in.codes[g][WIDE].x) - all;
+                    // (codes of up to 7 bits: a pair stays in its halfword)
+                    p0 = __builtin_amdgcn_perm(0u, e, 0x0C010C00u) | (__builtin_amdgcn_perm(0u, o, 0x0C010C00u) << wc);
+                    p1 = __builtin_amdgcn_perm(0u, e, 0x0C030C02u) | (__builtin_amdgcn_perm(0u, o, 0x0C030C02u) << wc);
+                    const uint32_t h0 = (p0 & 0xFFFFu) | ((p0 >> 16) << (2 * wc)), h1 = (p1 & 0xFFFFu) | ((p1 >> 16) << (2 * wc));
+                    bits[c] = uint64_t(h0) | (uint64_t(h1) << (4 * wc));
+                } else {
+                    uint32_t all = (in.width[g] >> (8 * c)) & 0xFu;
+                    all |= all << 4;
+                    all = __builtin_amdgcn_perm(0u, all, 0u);
+                    const uint32_t n = (c ? in.codes[g][0].y : in.codes[g][0].x) - all;
+                    p0 = (n & 0x0F0F0F0Fu) | (((n >> 4) & 0x0F0F0F0Fu) << wc);           // bytes of 2 w bits
+                    p1 = (p0 & 0x00FF00FFu) | (((p0 >> 8) & 0x00FF00FFu) << (2 * wc));   // halfwords of 4 w bits
+                    bits[c] = (p1 & 0xFFFFu) | ((p1 >> 16) << (4 * wc));
+                }
+            }
+            if constexpr (WIDE) {
+                or_bits(payload, at, bits[0], int(w[i][0]));
+                or_bits(payload, at + w[i][0], bits[1], int(w[i][1]));
+            } else {
+                or_bits(payload, at, bits[0] | (bits[1] << (8 * w[i][0])), int(w[i][0] + w[i][1]));
+            }
+        }
+        run += (total & 0xFFFFu) + (total >> 16);
+    }
+    wave_lds_fence();
+}
+
+// assemble16_kernel for packs of 8.  LDS: an image of a slot's size to each wave.
+__global__ __launch_bounds__(256) void assemble8_kernel(PackArgs a) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t images8[];
+    const PackTensor &t = a.t[blockIdx.y];
+    if (int(blockIdx.x) >= (a.n + 3) / 4) {
+        copy_rest(a, t, int(blockIdx.x) - (a.n + 3) / 4);
+        return;
+    }
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wg_first = blockIdx.x * 4, cl = wg_first + wave;
+    const bool present = cl < a.n;
+    const uint8_t *const slot = a.staging + (t.stage_at + uint32_t(min(cl, a.n - 1)) * t.slot);
+    uint32_t place = 0, units = 0;
+    auto find_place = [&]() {
+        uint32_t *const index = t.index + (t.round.first_chunk + a.part_first) * a.index_words;
+        const uint2 *widths = reinterpret_cast<const uint2 *>(t.widths);
+        if (a.index_words == 2) {   // paged: the placement kernel has set the chunks' index pairs
+            const uint2 pair = *reinterpret_cast<const uint2 *>(index + 2 * min(cl, a.n - 1));
+            place = pair.x;
+            units = present ? pair.y - pair.x : 0;   // 0: dropped, the pool could not cover the call
+            return;
+        }
+        place = index[0];
+        uint32_t before = 0;
+#pragma unroll 4
+        for (int i = 2 * int(threadIdx.x); i < wg_first; i += 512) {
+            const uint4 q = *reinterpret_cast<const uint4 *>(widths + i);
+            before += chunk_units(make_uint2(q.x, q.y), t.header16, UNIT_SHIFT8) + chunk_units(make_uint2(q.z, q.w), t.header16, UNIT_SHIFT8);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t u = chunk_units(widths[wg_first + k], t.header16, UNIT_SHIFT8);
+            if (k < wave) place += u;
+            if (k == wave) units = present ? u : 0;
+        }
+        place += block_sum(before);
+        if (present && lane == 0) index[cl + 1] = place + units;
+    };
+    uint8_t *const img = images8 + wave * t.slot;
+    if (t.wide) {
+        StagedLane8<true> in;
+        in.load(slot, lane);
+        find_place();
+        if (units == 0) return;
+        assemble_chunk8<true>(in, units, img);
+    } else {
+        StagedLane8<false> in;
+        in.load(slot, lane);
+        find_place();
+        if (units == 0) return;
+        assemble_chunk8<false>(in, units, img);
+    }
+    typedef uint32_t u32x4n __attribute__((ext_vector_type(4)));
+    u32x4n *dst = reinterpret_cast<u32x4n *>(t.arena + size_t(place) * 16);
+    for (uint32_t i = lane; i < units; i += 64) {
+        const uint4 q = *reinterpret_cast<const uint4 *>(img + 16 * i);
+        __builtin_nontemporal_store(u32x4n{q.x, q.y, q.z, q.w}, dst + i);
     }
 }
 
@@ -1619,7 +1818,7 @@ __global__ __launch_bounds__(1024) void place_small_kernel(PackArgs a) {
     }
 #pragma unroll 4
     for (int i = tid; i < n; i += T) {
-        S[i] = t.widths ? chunk_units(reinterpret_cast<const uint2 *>(t.widths)[i]) : t.sizes16[i];
+        S[i] = t.widths ? chunk_units(reinterpret_cast<const uint2 *>(t.widths)[i], t.header16, t.unit_shift) : t.sizes16[i];
         mark[i] = 0;
     }
     const uint32_t newest = held ? t.page_list[1 + held] : 0u;
@@ -2085,24 +2284,33 @@ static auto chunk8(bool stream) {
     return stream ? chunk_kernel<WRITE, 8, WIDE, true> : chunk_kernel<WRITE, 8, WIDE, false>;
 }
 
-// Whether a round of n_chunks chunks (per tensor) is staged, unless the arena turns out to be too full.
+// Whether the arenas take the next n_chunks chunks of each tensor at their largest, by the host's bound of the fill level.
+static bool fits_for_sure(const kv_cache *c, int n_chunks) {
+    if (c->pool) return true;
+    auto worst16 = [&](bool wide) { return uint64_t(n_chunks) * uint64_t(chunk_max_bytes(c->cfg.pack_size, wide) / 16); };
+    return c->fill_bound16[0] + worst16(c->wide_k) <= arena_units(c->sizes.k_arena) && c->fill_bound16[1] + worst16(c->wide_v) <= arena_units(c->sizes.v_arena);
+}
+
+// Whether a round of n_chunks chunks (per tensor) is staged, unless (packs of 16) the arena turns out to be too full.
+// Packs of 8: only where no arena can be too full, and for codes the fixed-point quantizer takes.
 static bool staged_rounds(const kv_cache *c, int n_chunks) {
     const int most = c->stage_chunks / 2;
-    return c->cfg.pack_size == 16 && most >= c->cfg.n_kv_heads && (!c->pool || n_chunks <= most);
+    if (most < c->cfg.n_kv_heads || (c->pool && n_chunks > most)) return false;
+    return c->cfg.pack_size == 16 || (std::max(c->qmax_k, c->qmax_v) <= MOST_STAGED_CODE && fits_for_sure(c, n_chunks));
 }
 
 bool finds_params(const kv_cache *c, int n_chunks) {
     return staged_rounds(c, n_chunks) && c->cfg.n_kv_heads <= 64 && c->cfg.repack == KV_REPACK_NONE;
 }
 
-template <int HP, bool GIVEN>
+template <int HP, bool GIVEN, bool PACK8>
 static void launch_quantize16_as(PackArgs &a, int H, bool stream, bool unsure, bool mixed, hipStream_t s) {
     const int waves = HP < 4 ? 1 : std::min((H + 3) / 4, GIVEN ? 4 : 16);
     // workgroups of that many waves that fit a compute unit (0: not asked yet)
     static std::atomic<int> per_cu_of[17];
     int per_cu = per_cu_of[waves].load(std::memory_order_relaxed);
     if (!per_cu) {
-        per_cu = resident_workgroups(reinterpret_cast<const void *>(quantize16_kernel<HP, GIVEN, false, false, false>), 64 * waves);
+        per_cu = resident_workgroups(reinterpret_cast<const void *>(quantize16_kernel<HP, GIVEN, false, false, false, PACK8>), 64 * waves);
         per_cu_of[waves].store(per_cu, std::memory_order_relaxed);
     }
     const int64_t items = int64_t(2) * a.rows * HP * (HP == 4 && GIVEN ? (H + 15) / 16 : 1);
@@ -2113,26 +2321,23 @@ static void launch_quantize16_as(PackArgs &a, int H, bool stream, bool unsure, b
         while (a.split < 4 && 4 * a.split < waves && items * a.split * 2 <= room) a.split *= 2;
         groups *= a.split;
     }
-    auto kernel = unsure ? (stream ? quantize16_kernel<HP, GIVEN, true, true, false> : quantize16_kernel<HP, GIVEN, false, true, false>)
-                         : (stream ? quantize16_kernel<HP, GIVEN, true, false, false> : quantize16_kernel<HP, GIVEN, false, false, false>);
+    auto kernel = stream ? quantize16_kernel<HP, GIVEN, true, false, false, PACK8> : quantize16_kernel<HP, GIVEN, false, false, false, PACK8>;
+    if constexpr (!PACK8)
+        if (unsure) kernel = stream ? quantize16_kernel<HP, GIVEN, true, true, false, false> : quantize16_kernel<HP, GIVEN, false, true, false, false>;
     if constexpr (!GIVEN)
-        if (mixed) kernel = quantize16_kernel<HP, false, false, false, true>;
+        if (mixed) kernel = quantize16_kernel<HP, false, false, false, true, PACK8>;
     hipLaunchKernelGGL(kernel, dim3(groups), dim3(64 * waves), 0, s, a);
 }
 
+template <bool PACK8>
 static void launch_quantize16(PackArgs &a, int H, bool given, bool stream, bool unsure, bool mixed, hipStream_t s) {
-#define PACKKV_LAUNCH_QUANTIZE(hp) \
-    given ? launch_quantize16_as<hp, true>(a, H, stream, unsure, false, s) : launch_quantize16_as<hp, false>(a, H, stream, unsure, mixed, s)
+#define PACKKV_LAUNCH_QUANTIZE(hp)                                        \
+    given ? launch_quantize16_as<hp, true, PACK8>(a, H, stream, unsure, false, s) \
+          : launch_quantize16_as<hp, false, PACK8>(a, H, stream, unsure, mixed, s)
     if (H == 1) PACKKV_LAUNCH_QUANTIZE(1);
     else if (H == 2) PACKKV_LAUNCH_QUANTIZE(2);
     else PACKKV_LAUNCH_QUANTIZE(4);
 #undef PACKKV_LAUNCH_QUANTIZE
-}
-
-// Whether the arenas take the next n_chunks chunks of each tensor at their largest, by the host's bound of the fill level.
-static bool fits_for_sure(const kv_cache *c, int n_chunks) {
-    const uint64_t worst16 = uint64_t(n_chunks) * (CHUNK_MAX / 16);
-    return c->pool || (c->fill_bound16[0] + worst16 <= arena_units(c->sizes.k_arena) && c->fill_bound16[1] + worst16 <= arena_units(c->sizes.v_arena));
 }
 
 bool completes_in_place(const kv_cache *c) {
@@ -2182,7 +2387,11 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
         t.cs.bf16 = job.bf16;
         t.cs.pack_order = job.pack_order;
         t.round.first_chunk = job.first_chunk;
-        t.round.worst16 = staged ? uint32_t(n_chunks) * uint32_t(CHUNK_MAX / 16) : 0;
+        t.wide = job.wide;
+        t.slot = uint32_t(chunk_max_bytes(c->cfg.pack_size, job.wide));
+        t.header16 = uint32_t(chunk_header_bytes(c->cfg.pack_size, job.wide) / 16);
+        t.unit_shift = planes ? UNIT_SHIFT16 : UNIT_SHIFT8;
+        t.round.worst16 = staged ? uint32_t(n_chunks) * (t.slot / 16) : 0;
         t.round.arena_cap16 = c->pool ? ~uint64_t(0) : job.arena_cap16;
         t.index = job.index;
         t.arena = job.arena;
@@ -2213,7 +2422,9 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
             a.n = a.rows * H;
             a.t[0].widths = reinterpret_cast<uint16_t *>(sizes16);
             a.t[1].widths = a.t[0].widths + 4 * ((a.n + 1) & ~1);
-            launch_quantize16(a, H, !finds_params(c, n_chunks), stream, unsure, kjob.held > 0, s);
+            a.t[0].stage_at = 0;
+            a.t[1].stage_at = uint32_t(a.n) * a.t[0].slot;
+            (planes ? launch_quantize16<false> : launch_quantize16<true>)(a, H, !finds_params(c, n_chunks), stream, unsure, kjob.held > 0, s);
             static_assert(PLACE_SMALL_CHUNKS >= 16384 / 2, "a staged round of a paged cache fits the placement kernel");
             static_assert(16384 * 8 + 64 <= WS_SIZES_BYTES, "the width sums of a part fit the sizes area");
             if (c->pool) hipLaunchKernelGGL(place_small_kernel, dim3(1), dim3(1024), 0, s, a);
@@ -2225,7 +2436,10 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
                 groups += (a.rest_units + REST_UNITS - 1) / REST_UNITS * B;
                 rest->tokens = 0;
             }
-            hipLaunchKernelGGL(unsure ? assemble16_kernel<true> : assemble16_kernel<false>, dim3(groups, 2), dim3(256), 0, s, a);
+            if (planes)
+                hipLaunchKernelGGL(unsure ? assemble16_kernel<true> : assemble16_kernel<false>, dim3(groups, 2), dim3(256), 0, s, a);
+            else
+                hipLaunchKernelGGL(assemble8_kernel, dim3(groups, 2), dim3(256), 4 * std::max(a.t[0].slot, a.t[1].slot), s, a);
         }
     }
     if (two_pass) {
