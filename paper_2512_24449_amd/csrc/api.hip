@@ -313,8 +313,9 @@ int compress_blocks(kv_cache *c, const __half *ksrc, const __half *vsrc, int64_t
         vjob.page_list = static_cast<uint32_t *>(c->buf.v_pages);
         vjob.max_pages = c->max_pages_v;
         int rc;
-        if (!finds_params(c, nb * B * H) && (rc = launch_token_params(c, kjob, vjob, s))) return rc;
-        if (c->cfg.repack == KV_REPACK_V_MEDIAN) {
+        const bool moved = moves_codes(c, nb * B * H);
+        if (!moved && !finds_params(c, nb * B * H) && (rc = launch_token_params(c, kjob, vjob, s))) return rc;
+        if (c->cfg.repack == KV_REPACK_V_MEDIAN && !moved) {
             uint8_t *order = static_cast<uint8_t *>(c->buf.token_order);
             if ((rc = launch_v_median_order(c, vjob, kjob.meta, order, s))) return rc;
             kjob.order = vjob.order = order;

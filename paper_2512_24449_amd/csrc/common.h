@@ -309,8 +309,9 @@ struct TailRest {
 inline uint32_t arena_units(size_t bytes) { return uint32_t(bytes / 16 < 0xFFFFFFFFu ? bytes / 16 : 0xFFFFFFFFu); }
 
 // Both tensors of a round (they share every launch).  finds_params: launch_pack finds the token parameters of a
-// round of that many chunks by itself.
+// round of that many chunks by itself.  moves_codes: it finds those and the token order.
 bool finds_params(const kv_cache *c, int n_chunks);
+bool moves_codes(const kv_cache *c, int n_chunks);
 int launch_token_params(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s);
 // A block that new tokens complete is compressed from the tail and the new tokens where they are (CompressJob::held).
 bool completes_in_place(const kv_cache *c);

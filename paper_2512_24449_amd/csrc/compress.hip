@@ -256,7 +256,8 @@ struct PackArgs {
     int first_tensor;       // a launch whose grid covers one tensor: which (else 0)
     uint32_t *pool_state;   // paged arena
     int split;              // workgroups that share an item's quantization (quantize16_kernel)
-    int held;               // quantize16_kernel<.. MIXED>: tokens of the block that the tail holds
+    int held;               // > 0: the round is one block, and its first `held` tokens are in the tail
+    uint8_t *keys;          // codes moved into storage order (move_codes_kernel): the tokens' sort keys, later their order
     int rest_units;         // 16-byte units of a batch element that the tail takes behind the round, 0: none
     int64_t rest_stride;    // elements between the batch elements of `rest`
     bool rest_bf16;
@@ -1301,6 +1302,35 @@ __device__ inline void copy_rest(const PackArgs &a, const PackTensor &t, int wg)
         dst[i] = load8_as_fp16<true>(reinterpret_cast<const __half *>(src + i), a.rest_bf16);
 }
 
+// Storage rank of token `lane` of a block among its 64 sort keys: ascending, equal keys in arrival order.
+__device__ inline int storage_rank(int key, int qmax) {
+    const int lane = threadIdx.x & 63;
+    int rank = 0, base = 0;
+    for (int v = 0; v <= qmax; ++v) {
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(key == v);
+        if (key == v) rank = base + __popcll(mask & ((1ull << lane) - 1ull));
+        base += __popcll(mask);
+    }
+    return rank;
+}
+
+// The block's sort keys become its order, and the token metadata of both tensors goes into storage order: one wave, behind the
+// last reader of the keys.  scratch: 64 bytes of LDS.
+__device__ inline void reorder_block(const PackArgs &a, const ChunkCoord &k, uint8_t *scratch) {
+    const int lane = threadIdx.x & 63;
+    const ChunkSource &cs = a.t[1].cs;
+    const int64_t pos = k.b * cs.meta_stride + cs.first_token + int64_t(k.blk) * N;
+    const int key = a.keys[pos + lane];
+    const uint32_t km = a.t[0].cs.meta[pos + lane], vm = cs.meta[pos + lane];
+    const int rank = storage_rank(key, cs.qmax);
+    a.t[0].cs.meta[pos + rank] = km;
+    cs.meta[pos + rank] = vm;
+    scratch[rank] = uint8_t(lane);
+    wave_lds_fence();
+    a.keys[pos + lane] = scratch[lane];
+    wave_lds_fence();
+}
+
 // Chunks of a part from their staged codes to their place, and their index words.  blockIdx.y: tensor; a wave
 // takes one chunk, so a workgroup four (waves that walk several, the next one's codes on their way, are slower: 16384 chunks
 // 25 us, two per wave 27, three 31).  Every workgroup adds up the sizes of the part's chunks
@@ -1347,6 +1377,10 @@ __global__ __launch_bounds__(256) void assemble16_kernel(PackArgs a) {
         place += block_sum(before);
     }
     if (t.round.worst16 == 0 || uint64_t(first) + t.round.worst16 > t.round.arena_cap16) return;   // not a staged round
+    if (!UNSURE && a.keys && blockIdx.y == 1 && present) {
+        const ChunkCoord k = chunk_coord(t.cs, a.part_first + cl);
+        if (k.h == 0) reorder_block(a, k, images[wave]);
+    }
     if (!present || units == 0) return;
     if (!paged && lane == 0) index[cl + 1] = place + units;
     uint8_t *const img = images[wave];
@@ -1501,6 +1535,10 @@ __global__ __launch_bounds__(256) void assemble8_kernel(PackArgs a) {
         if (present && lane == 0) index[cl + 1] = place + units;
     };
     uint8_t *const img = images8 + wave * t.slot;
+    if (a.keys && blockIdx.y == 1 && present) {
+        const ChunkCoord k = chunk_coord(t.cs, a.part_first + cl);
+        if (k.h == 0) reorder_block(a, k, img);
+    }
     if (t.wide) {
         StagedLane8<true> in;
         in.load(slot, lane);
@@ -2010,6 +2048,21 @@ __global__ void init_kernel(uint32_t *status, uint32_t *k_index, uint32_t *v_ind
     if (threadIdx.x == 0 && k_pages) k_pages[0] = k_pages[1] = v_pages[0] = v_pages[1] = 0;
 }
 
+// Minimum (low half) and negated maximum (high half) of a wave's values; mn, mx: two of each to a lane.
+__device__ inline uint32_t wave_extremes(uint32_t mn, uint32_t mx) {
+    mx ^= 0x80008000u;
+    uint32_t w = pk_min_f16(__builtin_amdgcn_perm(mx, mn, 0x05040100u), __builtin_amdgcn_perm(mx, mn, 0x07060302u)), y = w;
+    swap_rows32(w, y);
+    y = w = pk_min_f16(w, y);
+    swap_rows16(w, y);
+    w = pk_min_f16(w, y);
+    w = pk_min_f16(w, dpp_u32<DPP_ROW_ROR8>(w));
+    w = pk_min_f16(w, dpp_u32<DPP_ROW_ROR4>(w));
+    w = pk_min_f16(w, dpp_u32<DPP_QUAD_XOR2>(w));
+    w = pk_min_f16(w, dpp_u32<DPP_QUAD_XOR1>(w));
+    return w;
+}
+
 // Token parameters of both tensors (blockIdx.z) and V-median repacking, step 1, in one, codes below 16 (packs of 16): a
 // wave holds a token's row of up to NREG * 512 values in registers, finds its scale and minimum, and of V
 // quantizes it with the packs' fixed-point rule and counts every code with ballots; the lower median is the first code
@@ -2039,17 +2092,7 @@ __global__ __launch_bounds__(256) void token_params_keys_kernel(ParamArgs a, int
 #pragma unroll
     for (int k = 0; k < NREG; ++k)
         if (512 * k + 8 * lane < a.row_elems) widen(x[k] = as_fp16(x[k], a.bf16));
-    mx ^= 0x80008000u;
-    // minimum in the low half, negated maximum in the high half
-    uint32_t w = pk_min_f16(__builtin_amdgcn_perm(mx, mn, 0x05040100u), __builtin_amdgcn_perm(mx, mn, 0x07060302u)), y = w;
-    swap_rows32(w, y);
-    y = w = pk_min_f16(w, y);
-    swap_rows16(w, y);
-    w = pk_min_f16(w, y);
-    w = pk_min_f16(w, dpp_u32<DPP_ROW_ROR8>(w));
-    w = pk_min_f16(w, dpp_u32<DPP_ROW_ROR4>(w));
-    w = pk_min_f16(w, dpp_u32<DPP_QUAD_XOR2>(w));
-    w = pk_min_f16(w, dpp_u32<DPP_QUAD_XOR1>(w));
+    const uint32_t w = wave_extremes(mn, mx);
     const uint32_t mt = token_meta_word(half_lo(w), -half_hi(w), pt.rel);
     const int64_t at = b * a.meta_stride + a.first_token + t;
     if (lane == 0) pt.meta[at] = mt;
@@ -2095,6 +2138,180 @@ __global__ __launch_bounds__(256) void token_params_keys_kernel(ParamArgs a, int
         }
     }
     if (lane == 0) keys[at] = uint8_t(key);
+}
+
+// Repacked tokens, staged rounds of codes up to 15 and at most 64 kv-heads: the tokens are quantized in arrival order, their
+// codes moved into storage order afterwards, so the input is read once (before: by the kernel above and again, in storage
+// order, by quantize16_kernel).  This kernel is the one above plus the codes of both tensors, eight nibbles to a word, to the
+// chunk's slot as [token][channel]; the tail's tokens of a block that is being completed are handled as in quantize16_kernel.
+// A wave (WAVES = 1: rows of up to 2048 values) or four waves take a token, NREG 16-byte registers to a lane.  The key is found
+// by bisection: the codes up to a bound are counted with ballots, three times for five levels (every code counted: 40 ballots
+// for 512 values instead of 24).  Bound by latency: waves that take several tokens, the next one's values on their way, are
+// slower (12032 tokens of 8 heads, whole append 45.9 us with a token to a wave, 49.2 with four).
+// Appends of repacked tokens, input read twice -> once: 8 x 52 heads of 32 000 tokens 4043 -> 2782 us, 8 x 32 of 8000 552 -> 462,
+// 4 x 8 of 3001 bf16 tokens in pages 62.5 -> 46.1 (of which this kernel 18, 49 MB in), packs of 8, 32 heads of 4000 102 -> 39.
+template <int NREG, int WAVES, bool STREAM>
+__global__ __launch_bounds__(256) void quantize_tokens_kernel(PackArgs a) {
+    ieee_mode_off();
+    __shared__ __attribute__((aligned(16))) uint32_t extremes[4];
+    __shared__ __attribute__((aligned(16))) int counts[2][4];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const PackTensor &pt = a.t[blockIdx.y];
+    const ChunkSource &cs = pt.cs;
+    const int i = WAVES == 1 ? int(blockIdx.x) * 4 + wave : int(blockIdx.x), token = i & (N - 1), row = i / N;   // row of the part
+    const uint32_t full = uint32_t(a.part_row + row), cap = uint32_t(cs.qmax);
+    const int blk = int((uint64_t(full) * a.magic_b) >> 32), b = int(full) - blk * cs.B;
+    const int row_elems = cs.H * D;
+    const int wave_first = WAVES == 1 ? 0 : wave * NREG * 512, first = wave_first + 8 * lane;   // the lane's value of register k: + 512 k
+    const bool old = token < a.held;   // (held is 0 but in a block that is being completed)
+    __half *const tail = pt.tail + (int64_t(b) * N + token) * row_elems;
+    const __half *const src = old ? tail : cs.src + b * cs.batch_stride + (int64_t(blk) * N + token - a.held) * cs.token_stride;
+    uint4 x[NREG];
+#pragma unroll
+    for (int k = 0; k < NREG; ++k)
+        if (first + 512 * k < row_elems) x[k] = load8<STREAM>(src + first + 512 * k);
+    uint32_t mn = 0x7C007C00u, mx = 0xFC00FC00u;
+#pragma unroll
+    for (int k = 0; k < NREG; ++k) {
+        if (first + 512 * k < row_elems) {
+            const uint4 v = x[k] = as_fp16(x[k], cs.bf16 && !old);
+            mn = pk_min_f16(mn, pk_min_f16(pk_min_f16(v.x, v.y), pk_min_f16(v.z, v.w)));
+            mx = pk_max_f16(mx, pk_max_f16(pk_max_f16(v.x, v.y), pk_max_f16(v.z, v.w)));
+        }
+    }
+    uint32_t w = wave_extremes(mn, mx);
+    if constexpr (WAVES > 1) {
+        if (lane == 0) extremes[wave] = w;
+        __syncthreads();
+        const uint4 all = *reinterpret_cast<const uint4 *>(extremes);
+        w = pk_min_f16(pk_min_f16(all.x, all.y), pk_min_f16(all.z, all.w));
+    }
+    const uint32_t mt = token_meta_word(half_lo(w), -half_hi(w), pt.rel);
+    const int64_t at = b * cs.meta_stride + cs.first_token + int64_t(blk) * N + token;
+    if (lane == 0 && (WAVES == 1 || wave == 0)) cs.meta[at] = mt;
+    const float4 tq = token_quant(mt);
+    const uint32_t codes_at = pt.stage_at + uint32_t(row * cs.H) * pt.slot + pt.header16 * 16 + uint32_t(token * (D / 2)) + 4 * (lane & 15);
+    uint32_t low[NREG][4], high[NREG][4];   // 0x4300 + code of the even and odd channels; past the row's end above all codes
+#pragma unroll
+    for (int k = 0; k < NREG; ++k) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) low[k][j] = high[k][j] = 0xFFFFu;
+        const int e = first + 512 * k;
+        if (e < row_elems) {
+            uint32_t pair[4];
+            quantize_token8(x[k], tq, cap, pair);
+            const uint32_t p01 = __builtin_amdgcn_perm(pair[1], pair[0], 0x06020400u), p23 = __builtin_amdgcn_perm(pair[3], pair[2], 0x06020400u);
+            const uint32_t even = __builtin_amdgcn_perm(p23, p01, 0x05040100u), odd = __builtin_amdgcn_perm(p23, p01, 0x07060302u);
+            *reinterpret_cast<uint32_t *>(a.staging + (codes_at + uint32_t(e / D) * pt.slot)) = even | (odd << 4);
+            if (!old && a.held) *reinterpret_cast<uint4 *>(tail + e) = x[k];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) low[k][j] = pair[j] & 0xFFFFu, high[k][j] = pair[j] >> 16;
+        }
+    }
+    if (blockIdx.y == 0) return;
+    // lower median: the smallest code with more than `rank` codes up to it
+    const int rank = (row_elems - 1) / 2;
+    uint32_t below = 0, above = cap;   // it is one of below .. above
+    for (int flip = 0; below < above; flip ^= 1) {
+        const uint32_t mid = (below + above) >> 1, bound = 0x4300u + mid;
+        int n = 0;
+#pragma unroll
+        for (int k = 0; k < NREG; ++k) {
+            if (wave_first + 512 * k >= row_elems) break;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                n += __popcll(__builtin_amdgcn_ballot_w64(low[k][j] <= bound)) + __popcll(__builtin_amdgcn_ballot_w64(high[k][j] <= bound));
+        }
+        if constexpr (WAVES > 1) {
+            if (lane == 0) counts[flip][wave] = n;
+            __syncthreads();   // (one a step: the next step's counts go to the other row)
+            const int4 all = *reinterpret_cast<const int4 *>(counts[flip]);
+            n = __builtin_amdgcn_readfirstlane((all.x + all.y) + (all.z + all.w));
+        }
+        if (n > rank) above = mid; else below = mid + 1;
+    }
+    if (lane == 0 && (WAVES == 1 || wave == 0)) a.keys[at] = uint8_t(below);
+}
+
+// Codes of a chunk from arrival order [token][channel] to packs in storage order, in place in the chunk's slot, with the pack
+// headers and width sums that quantize16_kernel leaves.  A wave to a chunk; lane (row g, cg): the sixteen tokens of group g,
+// channels 8 cg .. 8 cg + 7, two 8 x 8 transpositions of nibbles.  2 x 1504 chunks 6.8 us
+// (12 MB in and out; the quantizer that read the input again 18.4, and the order's kernel 4).
+template <bool PACK8>
+__global__ __launch_bounds__(256) void move_codes_kernel(PackArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t orders[4][N];
+    const PackTensor &pt = a.t[blockIdx.y];
+    const int lane = threadIdx.x & 63, cg = lane & 15, g = lane >> 4, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int cl = int(blockIdx.x) * 4 + wave;
+    if (cl >= a.n) return;
+    const ChunkCoord k = chunk_coord(pt.cs, a.part_first + cl);
+    const int key = a.keys[k.b * pt.cs.meta_stride + pt.cs.first_token + int64_t(k.blk) * N + lane];
+    orders[wave][storage_rank(key, a.t[1].cs.qmax)] = uint8_t(lane);
+    wave_lds_fence();
+    const uint4 order = *reinterpret_cast<const uint4 *>(&orders[wave][16 * g]);
+    uint8_t *const slot = a.staging + (pt.stage_at + uint32_t(cl) * pt.slot);
+    uint8_t *const codes = slot + (PACK8 ? HEADER8 : HEADER);
+    uint32_t x[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+        const uint32_t o = t < 4 ? order.x : t < 8 ? order.y : t < 12 ? order.z : order.w;
+        x[t] = *reinterpret_cast<const uint32_t *>(codes + ((o >> (8 * (t & 3))) & 0xFFu) * (D / 2) + 4 * cg);
+    }
+    uint32_t mn[4], mx[4], sum = 0;   // halves: channels j and j + 4
+    auto headers = [&](int group) {
+        const uint32_t m01 = __builtin_amdgcn_perm(mn[1], mn[0], 0x06020400u), m23 = __builtin_amdgcn_perm(mn[3], mn[2], 0x06020400u);
+        const uint32_t x01 = __builtin_amdgcn_perm(mx[1], mx[0], 0x06020400u), x23 = __builtin_amdgcn_perm(mx[3], mx[2], 0x06020400u);
+        const uint32_t m_lo = __builtin_amdgcn_perm(m23, m01, 0x05040100u), m_hi = __builtin_amdgcn_perm(m23, m01, 0x07060302u);
+        const uint32_t w_lo = width_bytes(__builtin_amdgcn_perm(x23, x01, 0x05040100u) - m_lo);
+        const uint32_t w_hi = width_bytes(__builtin_amdgcn_perm(x23, x01, 0x07060302u) - m_hi);
+        sum += w_lo + w_hi;
+        *reinterpret_cast<uint2 *>(slot + D * group + 8 * cg) = make_uint2((w_lo << 4) | m_lo, (w_hi << 4) | m_hi);
+    };
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+        for (int t = 8 * half; t < 8 * half + 8; t += 2) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                // (codes are fp16 subnormals)
+                const uint32_t p = (x[t] >> (4 * j)) & 0x000F000Fu, q = (x[t + 1] >> (4 * j)) & 0x000F000Fu;
+                const bool first = t == (PACK8 ? 8 * half : 0);
+                mn[j] = first ? pk_min(p, q) : pk_min3_f16(mn[j], p, q);
+                mx[j] = first ? pk_max(p, q) : pk_max3_f16(mx[j], p, q);
+            }
+        }
+        if (PACK8) headers(2 * g + half);
+    }
+    if (!PACK8) headers(g);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        uint32_t y[8];
+#pragma unroll
+        for (int t = 0; t < 8; t += 2) {
+            const uint32_t p = x[8 * half + t], q = x[8 * half + t + 1];
+            y[t] = (p & 0x0F0F0F0Fu) | ((q << 4) & 0xF0F0F0F0u);
+            y[t + 1] = ((p >> 4) & 0x0F0F0F0Fu) | (q & 0xF0F0F0F0u);
+        }
+#pragma unroll
+        for (int t = 0; t < 8; t = t % 4 == 1 ? t + 3 : t + 1) {   // 0 1 4 5
+            const uint32_t p = y[t], q = y[t + 2];
+            y[t] = __builtin_amdgcn_perm(q, p, 0x06020400u);
+            y[t + 2] = __builtin_amdgcn_perm(q, p, 0x07030501u);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint32_t p = y[t], q = y[t + 4];
+            y[t] = __builtin_amdgcn_perm(q, p, 0x05040100u);
+            y[t + 4] = __builtin_amdgcn_perm(q, p, 0x07060302u);
+        }
+        uint8_t *const to = codes + 1024 * g + 512 * half + 16 * cg;
+        *reinterpret_cast<uint4 *>(to) = make_uint4(y[0], y[1], y[2], y[3]);
+        *reinterpret_cast<uint4 *>(to + 256) = make_uint4(y[4], y[5], y[6], y[7]);
+    }
+    sum += sum >> 16;
+    sum = (sum + (sum >> 8)) & 0xFFu;
+    sum = row_inclusive_scan(sum);
+    if (cg == 15) pt.widths[4 * cl + g] = uint16_t(sum);
 }
 
 // V-median repacking, step 1 (Sec. III-B.3): the lower median of the H*128 quantized V codes of
@@ -2163,12 +2380,7 @@ __global__ __launch_bounds__(64) void block_order_kernel(uint8_t *__restrict__ o
     const int64_t pos = blockIdx.y * meta_stride + first_token + int64_t(blockIdx.x) * N;
     const int key = order[pos + lane];
     const uint32_t km = k_meta[pos + lane], vm = v_meta[pos + lane];
-    int rank = 0, base = 0;
-    for (int v = 0; v <= qmax; ++v) {
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(key == v);
-        if (key == v) rank = base + __popcll(mask & ((1ull << lane) - 1ull));
-        base += __popcll(mask);
-    }
+    const int rank = storage_rank(key, qmax);
     ord[rank] = uint8_t(lane);
     k_meta[pos + rank] = km;
     v_meta[pos + rank] = vm;
@@ -2303,6 +2515,25 @@ bool finds_params(const kv_cache *c, int n_chunks) {
     return staged_rounds(c, n_chunks) && c->cfg.n_kv_heads <= 64 && c->cfg.repack == KV_REPACK_NONE;
 }
 
+// A round of many small parts is left to the token parameters of the whole round and two kernels to a part, instead of three
+// (40 000 tokens of 1, 2, 4, 8 streams, 256 and, of eight, 512 chunks to a part: 68, 94, 164, 201 us; moved 75, 101, 175, 197).
+bool moves_codes(const kv_cache *c, int n_chunks) {
+    const int most = c->stage_chunks / 2;
+    return c->cfg.repack == KV_REPACK_V_MEDIAN && staged_rounds(c, n_chunks) && fits_for_sure(c, n_chunks) && c->cfg.n_kv_heads <= 64 &&
+           std::max(c->qmax_k, c->qmax_v) <= 15 && (n_chunks <= most || most >= 512);
+}
+
+static void launch_quantize_tokens(const PackArgs &a, int H, bool stream, hipStream_t s) {
+    const dim3 grid(a.rows * (H <= 16 ? N / 4 : N), 2);
+#define PACKKV_LAUNCH_TOKENS(nreg, waves) \
+    hipLaunchKernelGGL((stream ? quantize_tokens_kernel<nreg, waves, true> : quantize_tokens_kernel<nreg, waves, false>), grid, dim3(256), 0, s, a)
+    if (H <= 8) PACKKV_LAUNCH_TOKENS(2, 1);
+    else if (H <= 16) PACKKV_LAUNCH_TOKENS(4, 1);
+    else if (H <= 32) PACKKV_LAUNCH_TOKENS(2, 4);
+    else PACKKV_LAUNCH_TOKENS(4, 4);
+#undef PACKKV_LAUNCH_TOKENS
+}
+
 template <int HP, bool GIVEN, bool PACK8>
 static void launch_quantize16_as(PackArgs &a, int H, bool stream, bool unsure, bool mixed, hipStream_t s) {
     const int waves = HP < 4 ? 1 : std::min((H + 3) / 4, GIVEN ? 4 : 16);
@@ -2342,7 +2573,7 @@ static void launch_quantize16(PackArgs &a, int H, bool given, bool stream, bool 
 
 bool completes_in_place(const kv_cache *c) {
     const int n_chunks = c->cfg.batch * c->cfg.n_kv_heads;
-    return finds_params(c, n_chunks) && fits_for_sure(c, n_chunks) && !larger_than_caches(n_chunks);
+    return ((finds_params(c, n_chunks) && fits_for_sure(c, n_chunks)) || moves_codes(c, n_chunks)) && !larger_than_caches(n_chunks);
 }
 
 int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, TailRest *rest, hipStream_t s) {
@@ -2409,6 +2640,7 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
     a.pool_state = c->pool ? c->pool->state : nullptr;
     a.staging = ws + c->stage_offset;
     a.held = kjob.held;
+    a.keys = staged && moves_codes(c, n_chunks) ? static_cast<uint8_t *>(c->buf.token_order) : nullptr;
     a.rest_units = 0;
     if (staged) {
         // equal parts of whole rows that fit the staging area, half of its slots for each tensor
@@ -2424,7 +2656,11 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
             a.t[1].widths = a.t[0].widths + 4 * ((a.n + 1) & ~1);
             a.t[0].stage_at = 0;
             a.t[1].stage_at = uint32_t(a.n) * a.t[0].slot;
-            (planes ? launch_quantize16<false> : launch_quantize16<true>)(a, H, !finds_params(c, n_chunks), stream, unsure, kjob.held > 0, s);
+            if (a.keys) {
+                launch_quantize_tokens(a, H, stream, s);
+                hipLaunchKernelGGL(planes ? move_codes_kernel<false> : move_codes_kernel<true>, dim3((a.n + 3) / 4, 2), dim3(256), 0, s, a);
+            } else
+                (planes ? launch_quantize16<false> : launch_quantize16<true>)(a, H, !finds_params(c, n_chunks), stream, unsure, kjob.held > 0, s);
             static_assert(PLACE_SMALL_CHUNKS >= 16384 / 2, "a staged round of a paged cache fits the placement kernel");
             static_assert(16384 * 8 + 64 <= WS_SIZES_BYTES, "the width sums of a part fit the sizes area");
             if (c->pool) hipLaunchKernelGGL(place_small_kernel, dim3(1), dim3(1024), 0, s, a);

@@ -11,8 +11,8 @@ from tests import gpu_cases
 pytestmark = pytest.mark.gpu
 
 
-# kv-heads per wave 1, 2, 4; one, two and four workgroups to an item; 65 heads take the copy first, as do repacked tokens
-# and an arena that is nearly full
+# kv-heads per wave 1, 2, 4; one, two and four workgroups to an item; 65 heads take the copy first, as does
+# an arena that is nearly full
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("pieces", [[1, 63], [63, 1], [37, 27 + 63], [37, 27 + 64 * 2 + 5], [16, 48 + 1], [64 + 15, 49 + 16, 48 + 2]])
 @pytest.mark.parametrize("B,H,kind", [(1, 1, ""), (3, 1, ""), (2, 2, ""), (1, 3, ""), (2, 5, "paged"), (2, 20, ""), (8, 52, ""), (1, 64, ""),
