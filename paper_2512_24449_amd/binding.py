@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libpackkv.so -- argument marshalling only.
+"""Thin binding of libpackkv.so -- argument marshalling only: ctypes, and for the calls of a decode step and of an append
+a native module (csrc/binding_native.cpp) that is tried first and leaves every argument it does not expect to the code here.
 
 Function names follow the C ABI (include/packkv.h).  PyTorch is used for
 device memory and streams; every step of the path runs in the HIP kernels.
@@ -56,8 +57,12 @@ EXPORTS = ("kv_query_sizes", "kv_cache_create", "kv_cache_destroy", "kv_compress
            "kv_strerror", "kv_fp16_k_matvec", "kv_fp16_v_matvec", "kv_fp16_v_workspace_bytes",
            "kv_stream_read", "kv_page_pool_state_bytes", "kv_page_pool_create", "kv_page_pool_destroy",
            "kv_page_pool_free_pages", "kv_query_sizes_paged", "kv_cache_create_paged", "kv_cache_release")
+# entry points the native module calls, in its order
+_NATIVE_CALLS = ("kv_compress_append", "kv_compress_append_bf16", "kv_k_matvec", "kv_softmax", "kv_v_matvec",
+                 "kv_decode_attention", "kv_cache_restore", "kv_cache_release", "kv_cache_tokens")
 
 _lib = None
+_native = None
 
 
 def library_path() -> str:
@@ -65,11 +70,13 @@ def library_path() -> str:
 
 
 def lib():
-    """Load libpackkv.so; build it first only if no built library exists."""
-    global _lib
+    """Load libpackkv.so and the native module; build them first only if they do not exist."""
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(_build.LIB):
             _build.build()
+        if not os.path.exists(_build.NATIVE):
+            _build.build_native()
         L = C.CDLL(_build.LIB)
         vp, i32, i64, f32 = C.c_void_p, C.c_int32, C.c_int64, C.c_float
         L.kv_query_sizes.argtypes = [C.POINTER(kv_config_t), C.c_double, C.POINTER(kv_sizes_t)]
@@ -107,7 +114,10 @@ def lib():
             if name not in ("kv_cache_tokens", "kv_strerror", "kv_fp16_v_workspace_bytes",
                             "kv_page_pool_state_bytes"):
                 getattr(L, name).restype = C.c_int
-        _lib = L
+        from . import _native as native
+        native.bind(tuple(C.cast(getattr(L, name), vp).value for name in _NATIVE_CALLS), _check,
+                    _current_device, _current_raw_stream, getattr(torch._C, "_cuda_isInBadFork", None))
+        _lib, _native = L, native
     return _lib
 
 
@@ -221,6 +231,7 @@ class PackedKVCache:
             else:
                 _check(lib().kv_cache_create(C.byref(self.cfg), C.byref(bufs), C.byref(self.sizes),
                                              C.byref(handle)), "kv_cache_create")
+        self._calls = _native.Calls(batch, n_kv_heads, n_q_heads, str(self.device))
         self.handle = handle
         self.batch, self.n_kv_heads, self.n_q_heads = batch, n_kv_heads, n_q_heads
         self._q_shape, self._row_shape = (batch, n_q_heads, HEAD_DIM), (batch, n_q_heads)
@@ -241,11 +252,25 @@ class PackedKVCache:
             pass
 
     @property
+    def handle(self):
+        """The kv_cache_t of the library (ctypes.c_void_p), None once closed."""
+        return self._handle
+
+    @handle.setter
+    def handle(self, value):
+        self._handle = value
+        calls = getattr(self, "_calls", None)
+        if calls is not None:
+            calls.set_handle((value.value if isinstance(value, C.c_void_p) else value) or 0)
+
+    @property
     def tokens(self) -> int:
         return _lib.kv_cache_tokens(self.handle)
 
     def kv_compress_append(self, k_new: torch.Tensor, v_new: torch.Tensor, stream=None):
         """k_new, v_new: fp16 (or both bf16: kv_compress_append_bf16) [B, n, H_kv, 128] contiguous device tensors."""
+        if self._calls.append(k_new, v_new, stream) is not NotImplemented:
+            return
         dtype, shape = k_new.dtype, k_new.shape
         assert dtype == v_new.dtype and dtype in (torch.float16, torch.bfloat16)
         assert k_new.is_contiguous() and v_new.is_contiguous() and shape == v_new.shape
@@ -262,6 +287,9 @@ class PackedKVCache:
 
     def kv_k_matvec(self, q: torch.Tensor, sm_scale: float, scores: torch.Tensor = None, stream=None):
         """q: fp16 [B, Hq, 128] -> scores fp32 [B, Hq, ld] (ld >= tokens)."""
+        done = self._calls.k_matvec(q, sm_scale, scores, stream)
+        if done is not NotImplemented:
+            return done
         assert q.dtype == torch.float16 and q.is_contiguous()
         assert q.shape == self._q_shape
         if scores is None:
@@ -277,6 +305,10 @@ class PackedKVCache:
 
     def kv_v_matvec(self, p: torch.Tensor, out: torch.Tensor = None, stream=None):
         """p: fp32 [B, Hq, ld] -> out fp32 [B, Hq, 128]."""
+        if out is None:
+            done = self._calls.v_matvec(p, stream)
+            if done is not NotImplemented:
+                return done
         assert p.dtype == torch.float32 and p.is_contiguous()
         assert p.shape[:2] == self._row_shape
         if out is None:
@@ -298,6 +330,9 @@ class PackedKVCache:
 
     def kv_softmax(self, scores: torch.Tensor, stream=None):
         """In-place softmax over the cached tokens of scores fp32 [B, Hq, ld]; returns scores."""
+        done = self._calls.softmax(scores, stream)
+        if done is not NotImplemented:
+            return done
         assert scores.dtype == torch.float32 and scores.is_contiguous()
         assert scores.shape[:2] == self._row_shape
         rc = _lib.kv_softmax(self.handle, scores.data_ptr(), scores.shape[2], _stream_ptr(stream))
@@ -307,6 +342,10 @@ class PackedKVCache:
 
     def kv_decode_attention(self, q: torch.Tensor, sm_scale: float, out: torch.Tensor = None, stream=None):
         """q: fp16 [B, Hq, 128] -> out fp32 [B, Hq, 128] = softmax(sm_scale * q K^T) V over the whole cache."""
+        if out is None:
+            done = self._calls.attention(q, sm_scale, stream)
+            if done is not NotImplemented:
+                return done
         assert q.dtype == torch.float16 and q.is_contiguous()
         assert q.shape == self._q_shape
         if out is None:
@@ -322,11 +361,15 @@ class PackedKVCache:
         return st
 
     def kv_cache_release(self, stream=None):
+        if self._calls.release(stream) is not NotImplemented:
+            return
         rc = _lib.kv_cache_release(self.handle, _stream_ptr(stream))
         if rc != KV_OK:
             _check(rc, "kv_cache_release")
 
     def kv_cache_restore(self, tokens: int):
+        if self._calls.restore(tokens) is not NotImplemented:
+            return
         rc = _lib.kv_cache_restore(self.handle, tokens)
         if rc != KV_OK:
             _check(rc, "kv_cache_restore")

@@ -1,4 +1,4 @@
-"""Builds libpackkv.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Builds libpackkv.so (HIP, gfx950 only) in-tree with hipcc, and the binding's native part with g++."""
 from __future__ import annotations
 
 import glob
@@ -9,6 +9,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpackkv.so")
+NATIVE_SOURCE = os.path.join(CSRC, "binding_native.cpp")
+NATIVE = os.path.join(HERE, "_native.so")
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
@@ -24,9 +26,26 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def build_native(verbose: bool = False) -> str:
+    """Compile the module that marshals the binding's frequent calls (against torch's headers)."""
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    tmp = NATIVE + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-isystem", os.path.join(base, "include"), "-I", sysconfig.get_paths()["include"], "-o", tmp, NATIVE_SOURCE,
+           "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.check_call(cmd)
+    os.replace(tmp, NATIVE)
+    return NATIVE
+
+
 def build(verbose: bool = False) -> str:
     """Compile every HIP source (one hipcc process per file, in parallel) and link them into one
-    shared library; always recompiles."""
+    shared library, and the native module beside it; always recompiles."""
     import concurrent.futures
     import shutil
     import tempfile
@@ -44,7 +63,9 @@ def build(verbose: bool = False) -> str:
             return obj
         jobs = max(1, min(len(sources()), int(os.environ.get("MAX_JOBS", "0")) or os.cpu_count() or 1, 8))
         with concurrent.futures.ThreadPoolExecutor(jobs) as pool:
+            native = pool.submit(build_native, verbose)
             objs = list(pool.map(compile_one, sources()))
+            native.result()
         tmp = LIB + ".tmp%d" % os.getpid()
         cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs
         if verbose:
@@ -57,10 +78,10 @@ def build(verbose: bool = False) -> str:
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB):
+    if not (os.path.exists(LIB) and os.path.exists(NATIVE)):
         return True
-    t = os.path.getmtime(LIB)
-    deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + [os.path.join(ROOT, "include", "packkv.h")]
+    t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
+    deps = sources() + [NATIVE_SOURCE] + glob.glob(os.path.join(CSRC, "*.h")) + [os.path.join(ROOT, "include", "packkv.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
 
