@@ -1335,11 +1335,13 @@ __device__ inline void reorder_block(const PackArgs &a, const ChunkCoord &k, uin
 // takes one chunk, so a workgroup four (waves that walk several, the next one's codes on their way, are slower: 16384 chunks
 // 25 us, two per wave 27, three 31).  Every workgroup adds up the sizes of the part's chunks
 // before its own by itself (at most 64 KB, in the L2 cache of its die after the first): no launch of a scan in between.
-template <bool UNSURE>
+// EXTRAS: there is a rest to copy or a block order to finish (the question alone cost the others 2 %).
+template <bool UNSURE, bool EXTRAS>
 __global__ __launch_bounds__(256) void assemble16_kernel(PackArgs a) {
+    static_assert(!(UNSURE && EXTRAS), "rounds that may not be staged leave both to other kernels");
     __shared__ __attribute__((aligned(16))) uint8_t images[4][CHUNK_MAX + 16];
     const PackTensor &t = a.t[blockIdx.y];
-    if (!UNSURE && int(blockIdx.x) >= (a.n + 3) / 4) {
+    if (EXTRAS && int(blockIdx.x) >= (a.n + 3) / 4) {
         copy_rest(a, t, int(blockIdx.x) - (a.n + 3) / 4);
         return;
     }
@@ -1377,7 +1379,7 @@ __global__ __launch_bounds__(256) void assemble16_kernel(PackArgs a) {
         place += block_sum(before);
     }
     if (t.round.worst16 == 0 || uint64_t(first) + t.round.worst16 > t.round.arena_cap16) return;   // not a staged round
-    if (!UNSURE && a.keys && blockIdx.y == 1 && present) {
+    if (EXTRAS && a.keys && blockIdx.y == 1 && present) {
         const ChunkCoord k = chunk_coord(t.cs, a.part_first + cl);
         if (k.h == 0) reorder_block(a, k, images[wave]);
     }
@@ -2672,8 +2674,11 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
                 groups += (a.rest_units + REST_UNITS - 1) / REST_UNITS * B;
                 rest->tokens = 0;
             }
-            if (planes)
-                hipLaunchKernelGGL(unsure ? assemble16_kernel<true> : assemble16_kernel<false>, dim3(groups, 2), dim3(256), 0, s, a);
+            if (planes) {
+                auto assemble = a.keys || a.rest_units ? assemble16_kernel<false, true> : assemble16_kernel<false, false>;
+                if (unsure) assemble = assemble16_kernel<true, false>;
+                hipLaunchKernelGGL(assemble, dim3(groups, 2), dim3(256), 0, s, a);
+            }
             else
                 hipLaunchKernelGGL(assemble8_kernel, dim3(groups, 2), dim3(256), 4 * std::max(a.t[0].slot, a.t[1].slot), s, a);
         }
