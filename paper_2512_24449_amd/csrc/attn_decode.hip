@@ -635,8 +635,6 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
     if (d < D) out[int64_t(r) * D + d] = l > 0.0f ? o / l : 0.0f;  // every block dropped and no tail: defined output
 }
 
-int v_splits_for(int n_blocks, int streams);
-
 int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, float *out, hipStream_t s) {
     // Hs: kv-heads as the stream kernels count them (each dup times, see head_split); the combine
     // kernel works per query head and sees the real kv-head count and the whole group
@@ -665,7 +663,35 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         a.dup = c->head_split;
         a.n_blocks = n_blocks;
         a.sm_log2 = sm_log2;
-        n_splits = v_splits_for(n_blocks, B * Hs);
+        // MID with both tensors wide: where it is cheaper with all its workgroups, two to a compute unit, at once; else three with
+        // one buffer that K and V share do as well or better (with MID / without: 16000 chunks 45.0 / 51.1 us, four
+        // heads 59.6 / 67.8, 25600 in 512 workgroups 64.1 / 73.1, 166400 in 416 426 / 369).  With one wide
+        // tensor two workgroups fit either way, and MID is faster at all sizes (208000 chunks 351 / 406, 382 / 432).
+        const bool both = c->wide_k && c->wide_v;
+        bool mid = (c->wide_k || c->wide_v) && (!c->wide_k || c->qmax_k <= MID_QMAX) && (!c->wide_v || c->qmax_v <= MID_QMAX);
+        int per_cu = 1;
+#define PACKKV_ROOM(...) { static const int n = resident_workgroups(reinterpret_cast<const void *>(__VA_ARGS__)); per_cu = n; }
+#define PACKKV_ROOM_8(g) \
+    if (both) PACKKV_ROOM(attn8_kernel<g, true, true, false, false>) \
+    else if (c->wide_k) { if (mid) PACKKV_ROOM(attn8_kernel<g, true, false, true, false>) else PACKKV_ROOM(attn8_kernel<g, true, false, false, false>) } \
+    else if (c->wide_v) { if (mid) PACKKV_ROOM(attn8_kernel<g, false, true, true, false>) else PACKKV_ROOM(attn8_kernel<g, false, true, false, false>) } \
+    else PACKKV_ROOM(attn8_kernel<g, false, false, false, false>)
+#define PACKKV_ROOM_16(g) if (c->qmax_v > 7) PACKKV_ROOM(attn_kernel<g, true, false, false>) else PACKKV_ROOM(attn_kernel<g, false, false, false>)
+        if (c->cfg.pack_size == 8) {
+            PACKKV_DISPATCH_GROUP(G, PACKKV_ROOM_8)
+        } else {
+            PACKKV_DISPATCH_GROUP4(G, PACKKV_ROOM_16)
+        }
+#undef PACKKV_ROOM_8
+#undef PACKKV_ROOM_16
+#undef PACKKV_ROOM
+        StreamSplits splits = splits_for(n_blocks, B * Hs, per_cu);
+        if (both && mid) {
+            const StreamSplits with_mid = splits_for(n_blocks, B * Hs, 2);
+            mid = with_mid.n * B * Hs <= mid_room() && with_mid.cost <= splits.cost;
+            if (mid) splits = with_mid;
+        }
+        n_splits = splits.n;
         a.blocks_per_split = (n_blocks + n_splits - 1) / n_splits;
         n_splits = (n_blocks + a.blocks_per_split - 1) / a.blocks_per_split;
         merged = merge_in_kernel(int64_t(n_splits) * B * Hs, int64_t(B) * Hs, G, c->wide_k || c->wide_v);
@@ -676,14 +702,6 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         a.tail_cap = c->cfg.tail_capacity;
         a.out = out;
         const dim3 grid(n_splits, B * Hs);
-        // MID with both tensors wide: while all its workgroups, two to a compute unit, run at once; beyond, three with one
-        // buffer that K and V share do as well or better (with MID / without: 16000 chunks 45.0 / 51.1 us, four
-        // heads 59.6 / 67.8, 20000 65.6 / 62.0, 24000 66.2 / 62.7, 40000 99.6 / 97.8, 208000 466 / 451; only two full rounds,
-        // 32000, 80.8 / 86.3).  With one wide
-        // tensor two workgroups fit either way, and MID is faster at all sizes (208000 chunks 351 / 406, 382 / 432).
-        const bool both = c->wide_k && c->wide_v;
-        const bool mid = (!c->wide_k || c->qmax_k <= MID_QMAX) && (!c->wide_v || c->qmax_v <= MID_QMAX) &&
-                         (!both || n_splits * B * Hs <= mid_room());
 #define PACKKV_LAUNCH_A8X(g, kw, vw, mid)                                                                    \
     if (merged) hipLaunchKernelGGL((attn8_kernel<g, kw, vw, mid, (g <= MERGED_HEADS)>), grid, dim3(256), 0, s, a); \
     else hipLaunchKernelGGL((attn8_kernel<g, kw, vw, mid, false>), grid, dim3(256), 0, s, a)

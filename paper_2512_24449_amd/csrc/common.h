@@ -63,6 +63,7 @@ inline int64_t target_workgroups(int64_t total_blocks) {
 int resident_workgroups(const void *kernel, int threads = 256);
 int flat_groups_for(int64_t total, int per_cu, int64_t most);
 int plan_groups_for(int n_blocks, int streams, int per_cu, int64_t most);
+StreamSplits splits_for(int n_blocks, int streams, int per_cu, int most = 64);
 // Workgroups of the kernels for wide chunks with two smaller buffers to a wave (pack8.h) that run at once.
 inline int mid_room() { return flat_groups_for(int64_t(1) << 40, 2, int64_t(1) << 30); }
 

@@ -129,4 +129,35 @@ inline int plan_groups(int n_blocks, int streams, int64_t room, int64_t most) {
     return int(best);
 }
 
+// Workgroups per stream where every stream is split alike, for kernels of which `per_cu` workgroups of four waves fit one of
+// `cus` compute units; at least one block per wave, at most `most`; and what that costs by the rule.
+// The starting point: about eight blocks to a wave, within two workgroups to a compute unit and 4096 in all.  But the more waves
+// a SIMD unit shares, the longer each block takes: with one, two and three workgroups to a compute unit 2.6, 3.4 and 4.2 us
+// behind 6, 7 and 9 us of start and end (fused attention, 32 streams of 128 to 1000 blocks, four heads), in units of 2.6 / 16 us below; what is over
+// a round of resident workgroups costs its share, and half a workgroup's time at the end.  Where the most workgroups for one, two, .. to a
+// compute unit are at least 8 % cheaper they are taken: 32 streams of 1000 blocks 1024 -> 768 workgroups, 66.0 -> 60.8 us; 64 of 300 (three
+// heads) 640 -> 768, 45.5 -> 41.1; 40 of 160 (one head) 520 -> 480, 23.7 -> 21.3; 416 of 500 stay.
+struct StreamSplits {
+    int n;
+    int64_t cost;
+    bool usual;   // the starting point
+};
+inline StreamSplits stream_splits(int n_blocks, int streams, int cus, int per_cu, int most) {
+    const int64_t most_here = std::max<int64_t>(1, std::min<int64_t>(most, (n_blocks + 3) / 4)), room = int64_t(cus) * per_cu;
+    auto with = [&](int64_t want) {
+        const int64_t n = std::max<int64_t>(1, std::min(want, most_here)), groups = n * streams, blocks = ((n_blocks + n - 1) / n + 3) / 4;
+        const int64_t sharing = std::min<int64_t>((groups + cus - 1) / cus, per_cu), block = 16 + 5 * (sharing - 1), ends = 37 + 9 * (sharing - 1);
+        return StreamSplits{int(n), groups <= room ? blocks * block + ends : groups * blocks * block / room + ends + blocks * 8, false};
+    };
+    const int64_t usual = std::min<int64_t>(std::max<int64_t>(int64_t(n_blocks) * streams / 32, 2 * cus), 16 * cus);
+    StreamSplits start = with((usual + streams - 1) / streams);
+    start.usual = true;
+    StreamSplits best = start;
+    for (int64_t sharing = 1; sharing <= per_cu; ++sharing) {
+        const StreamSplits s = with(sharing * cus / streams);
+        if (s.cost < best.cost) best = s;
+    }
+    return best.cost * 100 <= start.cost * 92 ? best : start;
+}
+
 }  // namespace packkv

@@ -332,28 +332,52 @@ int launch_k_matvec(const kv_cache *c, const __half *q, float sm_scale, float *s
     a.H = c->cfg.n_kv_heads * c->head_split;
     a.n_blocks = int(c->packed_tokens / N);
     const int streams = a.B * a.H;
-    // never less than one block per wave
-    const int64_t want_groups =
-        std::max<int64_t>(1, target_workgroups(int64_t(a.n_blocks) * streams) / streams);
-    int bpg = int((a.n_blocks + want_groups - 1) / want_groups);
-    bpg = std::max(4, (bpg + 3) / 4 * 4);
-    a.blocks_per_group = bpg;
-    a.groups_per_stream = a.n_blocks > 0 ? (a.n_blocks + bpg - 1) / bpg : 0;
-    a.n_stream_groups = a.groups_per_stream * streams;
+    // packs of 8: never less than one block per wave (packs of 16 have a plan, below)
+    bool mid = c->wide_k && c->qmax_k <= MID_QMAX;
+    auto split = [&](int per_cu) {
+        const StreamSplits splits = splits_for(std::max(a.n_blocks, 1), streams, per_cu, 1 << 20);
+        // (rounded down from the usual number: 128 streams of 1000 blocks 112.1 us with 3584 workgroups, 114.7 with 4096)
+        const int64_t n = splits.usual ? std::max<int64_t>(1, target_workgroups(int64_t(a.n_blocks) * streams) / streams) : splits.n;
+        const int bpg = std::max(4, int((a.n_blocks + n - 1) / n + 3) / 4 * 4);
+        a.blocks_per_group = bpg;
+        a.groups_per_stream = (a.n_blocks + bpg - 1) / bpg;
+        a.n_stream_groups = a.groups_per_stream * streams;
+        return splits.cost;
+    };
+    a.n_stream_groups = 0;
+    if (c->cfg.pack_size == 8) {
+        int per_cu = 1;
+#define PACKKV_ROOM(kernel) { static const int n = resident_workgroups(reinterpret_cast<const void *>(kernel)); per_cu = n; }
+#define PACKKV_ROOM_W(g) PACKKV_ROOM(kw_matvec_kernel<g>)
+#define PACKKV_ROOM_8(g) PACKKV_ROOM((k8_matvec_kernel<g, false>))
+        if (c->wide_k) {
+            PACKKV_DISPATCH_GROUP(c->group, PACKKV_ROOM_W)
+        } else {
+            PACKKV_DISPATCH_GROUP(c->group, PACKKV_ROOM_8)
+        }
+#undef PACKKV_ROOM_8
+#undef PACKKV_ROOM_W
+#undef PACKKV_ROOM
+        const int64_t cost = split(per_cu);
+        if (mid) {
+            mid = split(2) <= cost && a.n_stream_groups <= mid_room();
+            if (!mid) split(per_cu);
+        }
+    }
     a.n_tail = c->tail_tokens;
     a.tail_cap = c->cfg.tail_capacity;
     a.sm_scale = sm_scale;
     const int tail_groups = a.n_tail > 0 ? (streams + 3) / 4 : 0;
-    const int grid = a.n_stream_groups + tail_groups;
-    if (grid == 0) return KV_OK;
+    const int grid = a.n_stream_groups + tail_groups;   // (packs of 16: the plan's workgroups and those)
+    if (a.n_blocks == 0 && tail_groups == 0) return KV_OK;
 #define PACKKV_LAUNCH_KW(g) hipLaunchKernelGGL(kw_matvec_kernel<g>, dim3(grid), dim3(256), 0, s, a)
 #define PACKKV_LAUNCH_K8(g) hipLaunchKernelGGL((k8_matvec_kernel<g, false>), dim3(grid), dim3(256), 0, s, a)
 #define PACKKV_LAUNCH_KM(g) hipLaunchKernelGGL((k8_matvec_kernel<g, true>), dim3(grid), dim3(256), 0, s, a)
-    // MID while all its workgroups, two to a compute unit, run at once: beyond, the kernel with one larger buffer and more
+    // MID where all its workgroups, two to a compute unit, run at once and that is no dearer: else the kernel with one larger buffer and more
     // workgroups is the faster one, a second round that is partly full counting most (append, K, softmax, V with MID / without:
-    // 16000 chunks 55.7 / 60.4 us, four heads 76.4 / 79.5, 20000 in 640 workgroups 83.6 / 77.1, 25000 95.1 / 92.4, 52000 159 /
-    // 158, 208000 536 / 520; 32000 in 1024 workgroups 106 / 114 or, in more and shorter streams, 106 / 103).
-    if (c->wide_k && c->qmax_k <= MID_QMAX && a.n_stream_groups <= mid_room()) {
+    // 16000 chunks 55.7 / 60.4 us, four heads 76.4 / 79.5, 20000 in 640 workgroups 83.6 / 77.1, 52000 159 /
+    // 158, 208000 536 / 520; 25600 of 256 streams, this product alone, 32.8 in 512 workgroups / 30.9 in 768).
+    if (mid) {
         PACKKV_DISPATCH_GROUP(c->group, PACKKV_LAUNCH_KM)
     } else if (c->wide_k) {
         PACKKV_DISPATCH_GROUP(c->group, PACKKV_LAUNCH_KW)

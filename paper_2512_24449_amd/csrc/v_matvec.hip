@@ -405,15 +405,6 @@ __global__ __launch_bounds__(256) void v_reduce_kernel(const float *__restrict__
     if (d < D) out[int64_t(r) * D + d] = acc;
 }
 
-int v_splits_for(int n_blocks, int streams) {
-    const int64_t want = (target_workgroups(int64_t(n_blocks) * streams) + streams - 1) / streams;
-    const int by_blocks = (n_blocks + 3) / 4;  // at least one block per wave
-    int64_t s = want < by_blocks ? want : by_blocks;
-    if (s > V_SPLITS_MAX) s = V_SPLITS_MAX;
-    if (s < 1) s = 1;
-    return int(s);
-}
-
 // partial: [splits][B * H_q][V_PART_STRIDE] floats for the split sums; max_split_rows: how many
 // such rows it can take (the split count is lowered to fit).
 // Workgroups of `kernel` that fit one compute unit (registers, LDS); 1 if the
@@ -439,6 +430,9 @@ static int64_t resident_room(int per_cu) {
 int flat_groups_for(int64_t total, int per_cu, int64_t most) { return int(flat_groups(total, resident_room(per_cu), most)); }
 int plan_groups_for(int n_blocks, int streams, int per_cu, int64_t most) {
     return plan_groups(n_blocks, streams, resident_room(per_cu), most);
+}
+StreamSplits splits_for(int n_blocks, int streams, int per_cu, int most) {
+    return stream_splits(n_blocks, streams, int(resident_room(1)), per_cu, most);
 }
 
 // partial: [row sets][V_PART_STRIDE] floats for the split sums; max_split_rows: how many rows
@@ -500,7 +494,24 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
 #undef PACKKV_LAUNCH_V
 #undef PACKKV_LAUNCH_VX
     } else if (n_blocks > 0) {
-        n_splits = int(std::min<int64_t>(v_splits_for(n_blocks, B * Hs), max_split_rows / rows));
+        const bool mid = c->wide_v && c->qmax_v <= MID_QMAX;
+        int per_cu = 1;
+#define PACKKV_ROOM(kernel) { static const int n = resident_workgroups(reinterpret_cast<const void *>(kernel)); per_cu = n; }
+#define PACKKV_ROOM_VM(g) PACKKV_ROOM((v8_matvec_kernel<g, true, false>))
+#define PACKKV_ROOM_VW(g) PACKKV_ROOM((vw_matvec_kernel<g, false>))
+#define PACKKV_ROOM_V8(g) PACKKV_ROOM((v8_matvec_kernel<g, false, false>))
+        if (mid) {
+            PACKKV_DISPATCH_GROUP(G, PACKKV_ROOM_VM)
+        } else if (c->wide_v) {
+            PACKKV_DISPATCH_GROUP(G, PACKKV_ROOM_VW)
+        } else {
+            PACKKV_DISPATCH_GROUP(G, PACKKV_ROOM_V8)
+        }
+#undef PACKKV_ROOM_VM
+#undef PACKKV_ROOM_VW
+#undef PACKKV_ROOM_V8
+#undef PACKKV_ROOM
+        n_splits = int(std::min<int64_t>(splits_for(n_blocks, B * Hs, per_cu).n, max_split_rows / rows));
         a.blocks_per_split = (n_blocks + n_splits - 1) / n_splits;
         n_splits = (n_blocks + a.blocks_per_split - 1) / a.blocks_per_split;
         dim3 grid(n_splits, B * Hs);
@@ -513,7 +524,7 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
     else hipLaunchKernelGGL((v8_matvec_kernel<g, mid, false>), grid, dim3(256), 0, s, a)
 #define PACKKV_LAUNCH_V8(g) PACKKV_LAUNCH_V8X(g, false)
 #define PACKKV_LAUNCH_VM(g) PACKKV_LAUNCH_V8X(g, true)
-        if (c->wide_v && c->qmax_v <= MID_QMAX) {
+        if (mid) {
             PACKKV_DISPATCH_GROUP(G, PACKKV_LAUNCH_VM)
         } else if (c->wide_v) {
             PACKKV_DISPATCH_GROUP(G, PACKKV_LAUNCH_VW)
