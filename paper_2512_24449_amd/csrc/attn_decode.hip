@@ -268,23 +268,128 @@ __device__ inline void attn_merge_stream(const AArgs &a, int stream, int b, int 
     }
 }
 
+// SOLO: a workgroup has its stream to itself, tail included.  Wave w of WAVES takes the tail's tokens 64 / WAVES * w ..; their K and V values
+// are loaded ahead of the first chunks and stay in registers.
+template <int G, int WAVES>
+struct SoloTail {
+    static constexpr int PER = N / WAVES, SEGS = 64 / PER, CH = D / SEGS;   // tokens to a wave; K: lanes to a token, channels to a lane
+    uint4 k[CH / 8], v[PER / 4];                                            // V: token lane / 16 + 4 i, channels 8 (lane % 16) ..
+    __device__ inline void load(const AArgs &a, int b, int h, int wave, int lane) {
+        const int Hkv = a.H / a.dup;
+        const int64_t at = ((int64_t(b) * a.tail_cap + PER * wave) * Hkv + h / a.dup) * D, step = int64_t(Hkv) * D;
+        const int left = a.n_tail - PER * wave;
+        const __half *krow = a.k_tail + at + (lane / SEGS) * step + CH * (lane % SEGS);
+        const __half *vrow = a.v_tail + at + (lane >> 4) * step + 8 * (lane & 15);
+#pragma unroll
+        for (int c = 0; c < CH / 8; ++c) {
+            k[c] = make_uint4(0, 0, 0, 0);
+            if (lane / SEGS < left) k[c] = *reinterpret_cast<const uint4 *>(krow + 8 * c);
+        }
+#pragma unroll
+        for (int i = 0; i < PER / 4; ++i) {
+            v[i] = make_uint4(0, 0, 0, 0);
+            if ((lane >> 4) + 4 * i < left) v[i] = *reinterpret_cast<const uint4 *>(vrow + 4 * i * step);
+        }
+    }
+    __device__ inline void consume() {
+#pragma unroll
+        for (int c = 0; c < CH / 8; ++c) consume_here(k[c].x), consume_here(k[c].y), consume_here(k[c].z), consume_here(k[c].w);
+#pragma unroll
+        for (int i = 0; i < PER / 4; ++i) consume_here(v[i].x), consume_here(v[i].y), consume_here(v[i].z), consume_here(v[i].w);
+    }
+    // Adds the wave's tail tokens to its rows red[g] (outputs), l[g], m[g] of every head; q: the G heads' queries, in LDS;
+    // weights: 64 floats of LDS.
+    __device__ inline void add(const AArgs &a, const __half *q, float (*red)[D + 4], const float (&l_lane)[G], const float (&m_ref)[G],
+                               float *weights, int wave, int lane) {
+        const int left = a.n_tail - PER * wave;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            float l = wave_all_sum(l_lane[g]), m = m_ref[g];
+            float2 *const row = row_sums8_place(red[g], lane);
+            if (left > 0) {
+                float s = 0.0f;
+#pragma unroll
+                for (int c = 0; c < CH / 8; ++c) {
+                    const uint4 qv = *reinterpret_cast<const uint4 *>(q + g * D + CH * (lane % SEGS) + 8 * c);
+                    const __half *kk = reinterpret_cast<const __half *>(&k[c]), *qq = reinterpret_cast<const __half *>(&qv);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) s = fmaf(__half2float(kk[e]), __half2float(qq[e]), s);
+                }
+                s += dpp_f32<DPP_QUAD_XOR1>(s);
+                s += dpp_f32<DPP_QUAD_XOR2>(s);
+                if constexpr (SEGS == 8) s += dpp_f32<DPP_ROW_HALF_MIRROR>(s);
+                const bool some = lane / SEGS < left;
+                s = some ? a.sm_log2 * s : -INFINITY;   // in all lanes of its token
+                const float M = fmaxf(m, wave_all_max(s)), f = exp2_diff(m, M), w = some ? exp2f(s - M) : 0.0f;
+                if (lane % SEGS == 0) weights[lane / SEGS] = w;
+                wave_lds_fence();
+                l = fmaf(f, l, wave_all_sum(lane % SEGS == 0 ? w : 0.0f));
+                m = M;
+                float acc[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+#pragma unroll
+                for (int i = 0; i < PER / 4; ++i) {
+                    const __half *hv = reinterpret_cast<const __half *>(&v[i]);
+                    const float wt = weights[(lane >> 4) + 4 * i];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) acc[e] = fmaf(wt, __half2float(hv[e]), acc[e]);
+                }
+                const float2 two = row_sums8(acc);
+                const float pmin = red[g][D];
+                wave_lds_fence();
+                const float2 before = *row;
+                *row = make_float2(fmaf(f, before.x + pmin, two.x), fmaf(f, before.y + pmin, two.y));
+                if (lane == 0) red[g][D] = 0.0f;
+                wave_lds_fence();
+            }
+            if (lane == 0) red[g][D + 1] = l, red[g][D + 2] = m;
+        }
+    }
+};
+
+// The waves' rows of a stream, tail included, to its outputs.
+template <int G, int WAVES>
+__device__ inline void attn_solo_store(const AArgs &a, const float (*red)[G][D + 4], int64_t head0) {
+    for (int i = threadIdx.x; i < G * D / 2; i += 64 * WAVES) {
+        const int g = i / (D / 2), d = 2 * (i % (D / 2));
+        float M = red[0][g][D + 2];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) M = fmaxf(M, red[w][g][D + 2]);
+        float x = 0.0f, y = 0.0f, l = 0.0f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const float f = exp2_diff(red[w][g][D + 2], M), pmin = red[w][g][D];
+            const float2 v = *reinterpret_cast<const float2 *>(&red[w][g][d]);
+            x = fmaf(f, v.x + pmin, x), y = fmaf(f, v.y + pmin, y), l = fmaf(f, red[w][g][D + 1], l);
+        }
+        const bool some = l > 0.0f;  // every block dropped and no tail: defined output
+        *reinterpret_cast<float2 *>(a.out + (head0 + g) * D + d) = make_float2(some ? x / l : 0.0f, some ? y / l : 0.0f);
+    }
+}
+
 // HIGH: the V codes of the cache may need four bits (a plane H exists).  The blocks of all streams form
 // one work list cut into equal ranges, one per workgroup and one round of resident workgroups
 // (FlatPlan), so no last round runs nearly empty; a workgroup whose range crosses a stream
 // boundary writes a partial row set per stream.
-template <int G, bool HIGH, bool FLAT, bool MERGE>
-__global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
+// SOLO > 0: a workgroup of that many waves to a stream, which does it all: no partial rows through memory, no counter and no
+// second kernel (solo_waves says where).
+template <int G, bool HIGH, bool FLAT, bool MERGE, int SOLO = 0>
+__global__ __launch_bounds__(SOLO ? 64 * SOLO : 256) void attn_kernel(AArgs a, FlatPlan plan) {
+    constexpr int WAVES = SOLO ? SOLO : 4;
+    static_assert(!SOLO || (!FLAT && !MERGE), "a stream of its own needs neither");
     // per wave: buffer 0 holds the K chunk (and then its tiles, k_planes.h), buffer 1 the V chunk of
     // the block in flight; between two streams the same memory holds the cross-wave reduction array
     // red[4][G][D + 4].  (A second K buffer, the next K chunk on its way while one is decoded: 41.7 -> 42.6 us for
     // 4 x 8 streams of 512 blocks at four heads, 69.3 -> 75.9 for twice as many: two workgroups per compute unit, not three.)
-    __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * 2 * CHUNK_LDS + LDS_TAIL_PAD];
+    __shared__ __attribute__((aligned(16))) uint8_t lds_all[WAVES * 2 * CHUNK_LDS + LDS_TAIL_PAD];
     constexpr int VB = vb_bytes<G>();
-    __shared__ __attribute__((aligned(16))) uint8_t vb_all[4 * VB];  // digit staging of the V phase
+    __shared__ __attribute__((aligned(16))) uint8_t vb_all[WAVES * VB];  // digit staging of the V phase
     __shared__ uint4 ktable[5];                                      // K chunks: plane layout, channel-major
     __shared__ uint4 vtable[PLANE_TABLE_ENTRIES];                    // V chunks: plane layout, group-major
     __shared__ uint32_t vhighs[PLANE_TABLE_ENTRIES];
-    static_assert(sizeof(float) * 4 * G * (D + 4) <= 4 * 2 * CHUNK_LDS, "reduction array must fit");
+    __shared__ __attribute__((aligned(16))) __half q_lds[SOLO ? G * D : 8];
+    static_assert(sizeof(float) * G * (D + 4) <= 2 * CHUNK_LDS, "reduction array must fit");
     static_assert(K_TILES_BYTES <= CHUNK_LDS && CHUNK_LDS % 16 == 0, "the K tiles are built in the K buffer");
     float(*red)[G][D + 4] = reinterpret_cast<float(*)[G][D + 4]>(lds_all);
     const int lane = threadIdx.x & 63;
@@ -295,6 +400,7 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
     uint8_t *vb = vb_all + wave * VB;
     bool tables = false;
     const int64_t range_end = FLAT ? plan.begin(grp + 1) : 1;
+    SoloTail<G, WAVES> tail;
 
     for (int64_t f = FLAT ? plan.begin(grp) : 0; f < range_end;) {
         FlatPlan::Segment seg;
@@ -327,8 +433,8 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
         // index words of up to 64 blocks of this wave
         auto load_index = [&](int first) {
             if (first >= blk_end) return;
-            ik.load(a.k_index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
-            iv.load(a.v_index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
+            ik.load(a.k_index, a.index_words, first, WAVES, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
+            iv.load(a.v_index, a.index_words, first, WAVES, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
             const int64_t tok0 = b * a.meta_stride + int64_t(first) * N + lane;
             kmt_next = a.k_meta[tok0], vmt_next = a.v_meta[tok0];
         };
@@ -345,8 +451,12 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
             issue_v(0);
         };
         load_index(blk_begin + wave);
+        if constexpr (SOLO > 0) {
+            tail.load(a, b, h, wave, lane);
+            for (int i = threadIdx.x; i < G * D / 8; i += 64 * WAVES) reinterpret_cast<uint4 *>(q_lds)[i] = reinterpret_cast<const uint4 *>(a.q + head0 * D)[i];
+        }
         if (!tables) {  // while the index words are on their way
-            for (int i = threadIdx.x; i < 4 * VB / 4; i += 256) reinterpret_cast<uint32_t *>(vb_all)[i] = 0;
+            for (int i = threadIdx.x; i < WAVES * VB / 4; i += 64 * WAVES) reinterpret_cast<uint32_t *>(vb_all)[i] = 0;
             build_k_plane_table<false>(ktable);
             build_plane_table<false>(vtable, vhighs);
             __syncthreads();
@@ -354,8 +464,8 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
         }
         issue_first(blk_begin + wave);
         kq.build(lane);  // while the first chunks are on their way
-        for (int first = blk_begin + wave; first < blk_end; first += 4 * 64) {
-            const int n_it = min(64, (blk_end - first + 3) / 4);
+        for (int first = blk_begin + wave; first < blk_end; first += WAVES * 64) {
+            const int n_it = min(64, (blk_end - first + WAVES - 1) / WAVES);
             for (int it = 0; it < n_it; ++it) {
                 // a block dropped by an arena overflow (in either tensor) takes no part
                 const bool valid = ik.end16(it) - ik.start16(it) >= uint32_t(HEADER / 16) &&
@@ -363,12 +473,15 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
                 wait_chunk_landed();  // K chunk of this block
                 uint32_t kmt = kmt_next, vmt = vmt_next;
                 consume_here(kmt), consume_here(vmt);
+                if constexpr (SOLO > 0) {
+                    if (it == 0) tail.consume();
+                }
                 if (it > 0) {
                     lds_reads_returned();  // the previous V chunk has been read completely
                     issue_v(it);
                 }
                 if (it + 1 < n_it) {
-                    const int64_t tok = b * a.meta_stride + int64_t(first + 4 * (it + 1)) * N + lane;
+                    const int64_t tok = b * a.meta_stride + int64_t(first + WAVES * (it + 1)) * N + lane;
                     kmt_next = a.k_meta[tok];
                     vmt_next = a.v_meta[tok];
                 }
@@ -398,8 +511,17 @@ __global__ __launch_bounds__(256) void attn_kernel(AArgs a, FlatPlan plan) {
             }
             wait_chunk_landed();
             lds_reads_returned();  // the last V chunk has been read before the next batch's first overwrites it
-            load_index(first + 4 * 64);
-            issue_first(first + 4 * 64);
+            load_index(first + WAVES * 64);
+            issue_first(first + WAVES * 64);
+        }
+        if constexpr (SOLO > 0) {
+            __syncthreads();  // every wave is done with its chunk buffers: reuse them as red[][][]
+            attn_store_state<G>(st, red[wave], lane, 0.0f);
+            wave_lds_fence();
+            tail.add(a, q_lds, red[wave], l_lane, m_ref, reinterpret_cast<float *>(vb), wave, lane);
+            __syncthreads();
+            attn_solo_store<G, WAVES>(a, red, head0);
+            return;
         }
         attn_store_partial<G, MERGE>(a, st, l_lane, m_ref, red, wave, lane, row_set);
         if constexpr (FLAT)
@@ -635,6 +757,20 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
     if (d < D) out[int64_t(r) * D + d] = l > 0.0f ? o / l : 0.0f;  // every block dropped and no tail: defined output
 }
 
+// Waves of a workgroup that has a stream to itself, 0: the streams are split.  A solo workgroup saves the way of the partial rows through
+// memory and the merge (2 us in the same kernel, 5 with a kernel of its own); against that stands that a stream cannot have more
+// than one compute unit.  Eight waves: every stream of up to four blocks; up to 72 where the streams fill three quarters of the
+// chip, 16 where they fill half of it.  Beyond one stream to a compute unit, four waves (one head; two workgroups fit): short contexts,
+// and up to 56 blocks where two workgroups to a stream would not all be resident.  Split / solo, replayed, us:
+// 32 streams, one head, 4 blocks 10.1 / 8.2, 8 blocks 10.2 / 10.2; 128 of 12 13.1 / 11.2, of 16 13.3 / 13.3; 208 of 10 15.2 / 11.2, of 56 28.6 / 26.1;
+// 256 of 3, 20, 60, 80, 95 blocks at four heads 13.6 / 11.1, 23.5 / 18.4, 37.6 / 34.9, 45.3 / 43.8, 49.9 / 50.3; 320 of 10 17.4 / 16.5, of 24 22.6 / 24.5;
+// 416 of 6, 16, 32, 56 18.5 / 14.0, 23.6 / 19.5, 33.0 / 29.7, 47.5 / 44.7.
+static int solo_waves(int n_blocks, int streams, int heads) {
+    const int cus = flat_groups_for(int64_t(1) << 40, 1, int64_t(1) << 30);
+    if (streams <= cus) return n_blocks <= (4 * streams >= 3 * cus ? 72 : 2 * streams >= cus ? 16 : 4) ? 8 : 0;
+    return heads == 1 && streams <= 2 * cus && n_blocks <= (2 * streams > 3 * cus ? 56 : 10) ? 4 : 0;
+}
+
 int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, float *out, hipStream_t s) {
     // Hs: kv-heads as the stream kernels count them (each dup times, see head_split); the combine
     // kernel works per query head and sees the real kv-head count and the whole group
@@ -644,7 +780,7 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
     float *partial = reinterpret_cast<float *>(ws + WS_VPART);
     const float sm_log2 = sm_scale * LOG2E;
     FlatPlan plan = FlatPlan::make(n_blocks, B, Hs);
-    int n_splits = 0;
+    int n_splits = 0, solo = 0;
     bool flat = false, merged = false;
     if (n_blocks > 0) {
         AArgs a;
@@ -695,6 +831,8 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         a.blocks_per_split = (n_blocks + n_splits - 1) / n_splits;
         n_splits = (n_blocks + a.blocks_per_split - 1) / a.blocks_per_split;
         merged = merge_in_kernel(int64_t(n_splits) * B * Hs, int64_t(B) * Hs, G, c->wide_k || c->wide_v);
+        solo = c->cfg.pack_size == PACK ? solo_waves(n_blocks, B * Hs, G) : 0;
+        if (solo) a.blocks_per_split = n_blocks;
         a.counters = ws + WS_STATUS + 4 * ST_COUNTERS + COUNT_ATTENTION;
         a.k_tail = static_cast<const __half *>(c->buf.k_tail);
         a.v_tail = static_cast<const __half *>(c->buf.v_tail);
@@ -713,7 +851,9 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
 #define PACKKV_LAUNCH_A8NW(g) PACKKV_LAUNCH_A8W(g, false, true)
 #define PACKKV_LAUNCH_A8WW(g) PACKKV_LAUNCH_A8W(g, true, true)
 #define PACKKV_LAUNCH_AX(g, high)                                                                            \
-    if (merged) hipLaunchKernelGGL((attn_kernel<g, high, false, true>), grid, dim3(256), 0, s, a, plan);     \
+    if (solo == 8) hipLaunchKernelGGL((attn_kernel<g, high, false, false, 8>), dim3(1, B * Hs), dim3(512), 0, s, a, plan); \
+    else if (solo) hipLaunchKernelGGL((attn_kernel<1, high, false, false, 4>), dim3(1, B * Hs), dim3(256), 0, s, a, plan); \
+    else if (merged) hipLaunchKernelGGL((attn_kernel<g, high, false, true>), grid, dim3(256), 0, s, a, plan);     \
     else hipLaunchKernelGGL((attn_kernel<g, high, false, false>), grid, dim3(256), 0, s, a, plan)
 #define PACKKV_LAUNCH_A(g) PACKKV_LAUNCH_AX(g, false)
 #define PACKKV_LAUNCH_AH(g) PACKKV_LAUNCH_AX(g, true)
@@ -733,7 +873,7 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
             hipLaunchKernelGGL((__VA_ARGS__), dim3(groups), dim3(256), 0, s, a, plan);                 \
         }                                                                                              \
     }
-        if (c->cfg.pack_size == 16 && G == 1) {
+        if (c->cfg.pack_size == 16 && G == 1 && !solo) {
             if (c->qmax_v > 7) PACKKV_LAUNCH_FLAT(attn_kernel<1, true, true, false>)
             else PACKKV_LAUNCH_FLAT(attn_kernel<1, false, true, false>)
         }
@@ -764,7 +904,7 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
 #undef PACKKV_LAUNCH_AH
 #undef PACKKV_LAUNCH_FLAT
     }
-    if (flat || !merged)
+    if (flat || !(merged || solo))
         hipLaunchKernelGGL(flat ? attn_combine_kernel<true> : attn_combine_kernel<false>, dim3(B * H * Gq), dim3(256), 0, s, partial,
                            n_splits, B * H * Gq, plan, q, static_cast<const __half *>(c->buf.k_tail),
                            static_cast<const __half *>(c->buf.v_tail), c->tail_tokens,

@@ -389,14 +389,18 @@ __device__ inline float row_pairs_sum(float x, float y) {
     return __uint_as_float(a) + __uint_as_float(b);
 }
 
-// The sums of macc[0 .. 7] over the four rows of a wave (lane = channels 8 (lane % 16) ..): row r's lanes write channels 2 r and
-// 2 r + 1 of their eight to `to` (one head's 128 outputs).
-__device__ inline void store_row_sums8(const float (&macc)[8], float *to, int lane) {
-    const int row = lane >> 4;
+// The sums of macc[0 .. 7] over the four rows of a wave (lane = channels 8 (lane % 16) ..): row r's lanes get channels 2 r and
+// 2 r + 1 of their eight, for their place in one head's 128 outputs.
+__device__ inline float2 row_sums8(const float (&macc)[8]) {
     float m[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k) m[k] = row_pairs_sum(halves_sum(macc[k], macc[4 + k]), halves_sum(macc[2 + k], macc[6 + k]));
-    *reinterpret_cast<float2 *>(to + 8 * (lane & 15) + 4 * (row >> 1) + 2 * (row & 1)) = make_float2(m[0], m[1]);
+    return make_float2(m[0], m[1]);
 }
+__device__ inline float2 *row_sums8_place(float *to, int lane) {
+    const int row = lane >> 4;
+    return reinterpret_cast<float2 *>(to + 8 * (lane & 15) + 4 * (row >> 1) + 2 * (row & 1));
+}
+__device__ inline void store_row_sums8(const float (&macc)[8], float *to, int lane) { *row_sums8_place(to, lane) = row_sums8(macc); }
 
 }  // namespace packkv
