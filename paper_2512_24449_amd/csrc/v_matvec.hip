@@ -113,6 +113,75 @@ __device__ inline void v_merge_stream(const VArgs &a, int stream, int b, int h, 
     }
 }
 
+// SOLO: a workgroup has its stream to itself, tail included.  Wave w of WAVES takes the tail's tokens 64 / WAVES * w ..; their values and
+// weights are loaded ahead of the first chunk and stay in registers.
+template <int G, int WAVES>
+struct VSoloTail {
+    static constexpr int PER = N / WAVES;
+    uint4 v[PER / 4];        // token lane / 16 + 4 i, channels 8 (lane % 16) ..
+    float w[G][PER / 4];
+    __device__ inline void load(const VArgs &a, const float *prow, int b, int h, int wave, int lane) {
+        const int Hkv = a.H / a.dup, left = a.n_tail - PER * wave;
+        const int64_t step = int64_t(Hkv) * D;
+        const __half *vrow = a.tail + ((int64_t(b) * a.tail_cap + PER * wave + (lane >> 4)) * Hkv + h / a.dup) * D + 8 * (lane & 15);
+#pragma unroll
+        for (int i = 0; i < PER / 4; ++i) {
+            const int t = (lane >> 4) + 4 * i;
+            v[i] = make_uint4(0, 0, 0, 0);
+            if (t < left) v[i] = *reinterpret_cast<const uint4 *>(vrow + 4 * i * step);
+#pragma unroll
+            for (int g = 0; g < G; ++g) w[g][i] = t < left ? prow[g * a.ld + a.packed_tokens + PER * wave + t] : 0.0f;
+        }
+    }
+    __device__ inline void consume() {
+#pragma unroll
+        for (int i = 0; i < PER / 4; ++i) {
+            consume_here(v[i].x), consume_here(v[i].y), consume_here(v[i].z), consume_here(v[i].w);
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                uint32_t bits = __float_as_uint(w[g][i]);
+                consume_here(bits);
+                w[g][i] = __uint_as_float(bits);
+            }
+        }
+    }
+    // Adds the wave's tail tokens to its rows red[g].
+    __device__ inline void add(const VArgs &a, float (*red)[D + 4], int wave, int lane) const {
+        if (a.n_tail <= PER * wave) return;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            float acc[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < PER / 4; ++i) {
+                const __half *hv = reinterpret_cast<const __half *>(&v[i]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[e] = fmaf(w[g][i], __half2float(hv[e]), acc[e]);
+            }
+            const float2 two = row_sums8(acc);
+            float2 *const place = row_sums8_place(red[g], lane);
+            const float2 before = *place;
+            *place = make_float2(before.x + two.x, before.y + two.y);
+        }
+    }
+};
+
+// The waves' rows of a stream, tail included, to its outputs.
+template <int G, int WAVES>
+__device__ inline void v_solo_store(const VArgs &a, const float (*red)[G][D + 4], int64_t head0) {
+    for (int i = threadIdx.x; i < G * D / 2; i += 64 * WAVES) {
+        const int g = i / (D / 2), d = 2 * (i % (D / 2));
+        float x = 0.0f, y = 0.0f, pmin = 0.0f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const float2 v = *reinterpret_cast<const float2 *>(&red[w][g][d]);
+            x += v.x, y += v.y, pmin += red[w][g][D];
+        }
+        *reinterpret_cast<float2 *>(a.out + (head0 + g) * D + d) = make_float2(x + pmin, y + pmin);
+    }
+}
+
 // Packs of 16 tokens, plane layout (v_planes.h).  HIGH: the codes of the cache may need four bits
 // (otherwise a chunk is at most 512 + 512 * 6 bytes).  The chunks of all streams form one work
 // list that is cut into equal ranges, one per workgroup (FlatPlan): a launch is one round of
@@ -122,8 +191,12 @@ __device__ inline void v_merge_stream(const VArgs &a, int stream, int b, int h, 
 // travel the same way (one dword per lane, global memory -> LDS, behind the chunk in its buffer):
 // no vector memory instruction of the loop is visible to the compiler, so the only waits are the
 // counted ones below.
-template <int G, bool HIGH, bool MERGE>
-__global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
+// SOLO > 0: a workgroup of that many waves to a stream (blockIdx.x), which does it all, tail included: no partial rows through memory and no second
+// kernel (v_solo_waves says where).
+template <int G, bool HIGH, bool MERGE, int SOLO = 0>
+__global__ __launch_bounds__(SOLO ? 64 * SOLO : 256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
+    constexpr int WAVES = SOLO ? SOLO : 4;
+    static_assert(!SOLO || !MERGE, "a stream of its own needs no merge");
     constexpr int CHUNK_BYTES = HIGH ? CHUNK_MAX : HEADER + PACKS * 6;
     constexpr int SLICES = (CHUNK_BYTES + 1023) / 1024;
     constexpr int SIDE = CHUNK_BYTES + LDS_TAIL_PAD;   // metadata row, then G weight rows
@@ -131,13 +204,13 @@ __global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
     constexpr int NBUF = PACKKV_V_NBUF;                // chunks n+1 .. n+NBUF-1 in flight
     static_assert(NBUF == 2 || NBUF == 3, "wait counts below");
     // between the ranges of two streams the chunk buffers hold the cross-wave reduction array
-    __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * NBUF * BUF];
+    __shared__ __attribute__((aligned(16))) uint8_t lds_all[WAVES * NBUF * BUF];
     constexpr int VB = vb_bytes<G>();
-    __shared__ __attribute__((aligned(16))) uint8_t vb_all[4 * VB];
+    __shared__ __attribute__((aligned(16))) uint8_t vb_all[WAVES * VB];
     __shared__ uint4 table[PLANE_TABLE_ENTRIES];
     __shared__ uint32_t highs[PLANE_TABLE_ENTRIES];
     __shared__ uint32_t merge_flag;
-    static_assert(sizeof(float) * 4 * G * (D + 4) <= 4 * NBUF * BUF, "reduction array must fit");
+    static_assert(sizeof(float) * G * (D + 4) <= NBUF * BUF, "reduction array must fit");
     static_assert(BUF % 16 == 0, "buffers are 16-byte aligned");
     float(*red)[G][D + 4] = reinterpret_cast<float(*)[G][D + 4]>(lds_all);
     const int lane = threadIdx.x & 63;
@@ -146,9 +219,10 @@ __global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
     bool tables = false;
     uint8_t *vb = vb_all + wave * VB;
     const int grp = blockIdx.x;
-    const int64_t range_end = plan.begin(grp + 1);
+    const int64_t range_end = SOLO ? int64_t(grp + 1) * a.n_blocks : plan.begin(grp + 1);
+    VSoloTail<G, WAVES> tail;
 
-    for (int64_t f = plan.begin(grp); f < range_end;) {
+    for (int64_t f = SOLO ? int64_t(grp) * a.n_blocks : plan.begin(grp); f < range_end;) {
         const FlatPlan::Segment seg = plan.segment(f, range_end);
         const int stream = seg.stream, b = seg.b, h = seg.h, blk_begin = seg.blk_begin, blk_end = seg.blk_end;
         f += blk_end - blk_begin;
@@ -170,20 +244,24 @@ __global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
 
         IndexBatch ib;
         auto load_index = [&](int first) {
-            if (first < blk_end) ib.load(a.index, a.index_words, first, 4, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
+            if (first < blk_end) ib.load(a.index, a.index_words, first, WAVES, blk_end, a.B, a.H / a.dup, b, h / a.dup, lane);
         };
         load_index(blk_begin + wave);
+        if constexpr (SOLO > 0) tail.load(a, prow, b, h, wave, lane);
         if (!tables) {  // while the index words are on their way
-            for (int i = threadIdx.x; i < 4 * VB / 4; i += 256) reinterpret_cast<uint32_t *>(vb_all)[i] = 0;
+            for (int i = threadIdx.x; i < WAVES * VB / 4; i += 64 * WAVES) reinterpret_cast<uint32_t *>(vb_all)[i] = 0;
             build_plane_table(table, highs);
             tables = true;
         }
-        for (int first = blk_begin + wave; first < blk_end; first += 4 * 64) {
-            const int n_it = min(64, (blk_end - first + 3) / 4);
+        for (int first = blk_begin + wave; first < blk_end; first += WAVES * 64) {
+            const int n_it = min(64, (blk_end - first + WAVES - 1) / WAVES);
             wait_chunk_landed();  // the index words (the only loads the compiler sees)
+            if constexpr (SOLO > 0) {
+                if (first == blk_begin + wave) tail.consume();
+            }
             issue(ib, 0, first, 0);
             int slices_next = 0;  // transfer instructions of chunk it + 1
-            if (NBUF == 3 && n_it > 1) slices_next = issue(ib, 1, first + 4, 1);
+            if (NBUF == 3 && n_it > 1) slices_next = issue(ib, 1, first + WAVES, 1);
             int slot = 0;         // buffer of chunk it
             for (int it = 0; it < n_it; ++it) {
                 const int cur = buf_base + slot * BUF;
@@ -197,7 +275,7 @@ __global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
                 if (it + NBUF - 1 < n_it) {
                     // into the buffer chunk it - 1 was decoded from: its LDS reads have returned
                     lds_reads_returned();
-                    slices_next = issue(ib, it + NBUF - 1, first + 4 * (it + NBUF - 1), slot == 0 ? NBUF - 1 : slot - 1);
+                    slices_next = issue(ib, it + NBUF - 1, first + WAVES * (it + NBUF - 1), slot == 0 ? NBUF - 1 : slot - 1);
                 }
                 slot = slot == NBUF - 1 ? 0 : slot + 1;
                 if (!valid) continue;  // a block dropped by an arena overflow contributes nothing
@@ -209,11 +287,18 @@ __global__ __launch_bounds__(256) void v_matvec_kernel(VArgs a, FlatPlan plan) {
                 v_planes_chunk<G, HIGH>(lds_all, cur, table, highs, vb, mt, pt, st);
             }
             wait_chunk_landed();
-            load_index(first + 4 * 64);
+            load_index(first + WAVES * 64);
         }
         __syncthreads();  // every wave is done with its chunk buffers: reuse them as red[][][]
 
         v_planes_store<G>(st, red[wave], lane);
+        if constexpr (SOLO > 0) {
+            wave_lds_fence();
+            tail.add(a, red[wave], wave, lane);
+            __syncthreads();
+            v_solo_store<G, WAVES>(a, red, int64_t(stream) * G);
+            return;
+        }
         __syncthreads();
         float *dst = a.partial + int64_t(grp + stream) * G * V_PART_STRIDE;
         v_store_partial<G, MERGE>(a, red, dst);
@@ -435,6 +520,19 @@ StreamSplits splits_for(int n_blocks, int streams, int per_cu, int most) {
     return stream_splits(n_blocks, streams, int(resident_room(1)), per_cu, most);
 }
 
+// Waves of a workgroup that has a stream to itself, 0: the streams are split (as in the fused attention, where a block is twice the
+// work; four waves only where eight would not let two workgroups share a compute unit).  Split, the reduction included / solo, replayed, us:
+// one stream, one head, 4 blocks 6.8 / 4.7, 16 6.8 / 6.2, 24 6.9 / 7.4; 8, four heads, 8 8.1 / 6.5, 16 8.2 / 8.3; 128 of 16 8.9 / 6.9, of 32 10.4 / 9.0,
+// of 60 12.3 / 12.7; 256 of 15 blocks at four heads 14.4 / 9.0, of 90 29.4 / 26.2; one head, 120 23.4 / 21.9, 160 27.9 / 27.9; 320 of 30 13.9 / 13.0, of 60 19.5 / 19.6;
+// 416 of 16 12.5 / 9.5, of 120 34.7 / 33.8; 384 at four heads 30 23.0 / 20.4, 60 31.8 / 32.9.
+static int v_solo_waves(int n_blocks, int streams, int heads) {
+    const int cus = int(resident_room(1));
+    if (streams <= cus) return n_blocks <= (4 * streams >= 3 * cus ? 120 : 2 * streams >= cus ? 32 : heads <= 2 ? 16 : 8) ? 8 : 0;
+    if (streams > 2 * cus) return 0;
+    if (heads <= 2) return n_blocks <= (2 * streams > 3 * cus ? 120 : 30) ? 8 : 0;
+    return n_blocks <= 30 ? 4 : 0;
+}
+
 // partial: [row sets][V_PART_STRIDE] floats for the split sums; max_split_rows: how many rows
 // (one per query head and split or row set) it can take; counter: COUNT_V or COUNT_V_NOALLOC.
 static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p, float *out, float *partial,
@@ -475,12 +573,15 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
         // one round of resident workgroups: how many fit a compute unit depends on the instance; at
         // most 62 per stream (the combine kernel takes up to 64 row sets per stream)
         const int64_t most_groups = std::min<int64_t>(int64_t(62) * B * Hs, max_split_rows / G - int64_t(B) * Hs);
+        const int solo = v_solo_waves(n_blocks, B * Hs, G);
 #define PACKKV_LAUNCH_VX(g, high)                                                                          \
     {                                                                                                      \
         static const int per_cu = resident_workgroups(reinterpret_cast<const void *>(v_matvec_kernel<g, high, false>)); \
         plan.split(plan_groups_for(n_blocks, B * Hs, per_cu, most_groups));                               \
-        merged = merge_in_kernel(plan.n_groups, int64_t(B) * Hs, G);                              \
-        if (merged) hipLaunchKernelGGL((v_matvec_kernel<g, high, true>), dim3(plan.n_groups), dim3(256), 0, s, a, plan); \
+        merged = solo || merge_in_kernel(plan.n_groups, int64_t(B) * Hs, G);                              \
+        if (solo == 8) hipLaunchKernelGGL((v_matvec_kernel<g, high, false, 8>), dim3(B * Hs), dim3(512), 0, s, a, plan); \
+        else if (solo) hipLaunchKernelGGL((v_matvec_kernel<(g < 3 ? 3 : g), high, false, 4>), dim3(B * Hs), dim3(256), 0, s, a, plan); \
+        else if (merged) hipLaunchKernelGGL((v_matvec_kernel<g, high, true>), dim3(plan.n_groups), dim3(256), 0, s, a, plan); \
         else hipLaunchKernelGGL((v_matvec_kernel<g, high, false>), dim3(plan.n_groups), dim3(256), 0, s, a, plan); \
     }
 #define PACKKV_LAUNCH_V(g) PACKKV_LAUNCH_VX(g, false)
