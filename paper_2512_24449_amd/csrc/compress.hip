@@ -2439,7 +2439,7 @@ int launch_tail_copy(const kv_cache *c, const __half *ksrc, const __half *vsrc, 
 
 // The V-median keys come with the token parameters (codes of the fixed-point rule).
 static bool keys_with_params(const kv_cache *c) {
-    return c->cfg.repack == KV_REPACK_V_MEDIAN && c->cfg.pack_size == 16 && c->qmax_v < 16;
+    return c->cfg.repack == KV_REPACK_V_MEDIAN && c->qmax_v < 16;
 }
 
 int launch_token_params(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, hipStream_t s) {
@@ -2506,11 +2506,15 @@ static bool fits_for_sure(const kv_cache *c, int n_chunks) {
 }
 
 // Whether a round of n_chunks chunks (per tensor) is staged, unless (packs of 16) the arena turns out to be too full.
-// Packs of 8: only where no arena can be too full, and for codes the fixed-point quantizer takes.
+// Packs of 8: only where no arena can be too full, and for codes the fixed-point quantizer takes; and not in many small parts, which
+// take longer than two passes over all of the round (one sequence of 30 000 tokens, two passes / staged: 4 heads, 8 parts of 256 chunks, 79 / 107 us,
+// wide and repacked 116 / 174; 8 heads, wide, 8 of 512 132 / 156; 2 heads, 4 of 256 56 / 53; 32 streams of 20 000, 5 of 2048, 352 / 157).
 static bool staged_rounds(const kv_cache *c, int n_chunks) {
     const int most = c->stage_chunks / 2;
     if (most < c->cfg.n_kv_heads || (c->pool && n_chunks > most)) return false;
-    return c->cfg.pack_size == 16 || (std::max(c->qmax_k, c->qmax_v) <= MOST_STAGED_CODE && fits_for_sure(c, n_chunks));
+    if (c->cfg.pack_size == 16) return true;
+    if (most < 1024 && n_chunks > 4 * most) return false;
+    return std::max(c->qmax_k, c->qmax_v) <= MOST_STAGED_CODE && fits_for_sure(c, n_chunks);
 }
 
 bool finds_params(const kv_cache *c, int n_chunks) {
