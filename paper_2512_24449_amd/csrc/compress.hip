@@ -13,7 +13,8 @@
 //   token_params   a workgroup or a wave per (token, batch)
 //   v_median_key, block_order   (V-median repacking only) sort key per token,
 //                  order of the 64 tokens of a block, metadata into storage order
-// else (two-pass path: large rounds of paged arenas, a nearly full arena, codes above 127), behind token_params:
+// else (two-pass path: large rounds of paged arenas or small staging areas, a nearly full arena, codes above 127):
+//   quantize       as above, metadata and width sums only; or token_params and
 //   chunk_sizes    one workgroup per chunk: quantize, per-pack width -> bytes
 //   scan_offsets / place_small, place_chunks (paged arena) one workgroup: chunk positions -> index;
 //                  paged: inside pages taken from a shared pool, index of (start, end) pairs
@@ -920,11 +921,13 @@ inline QuantRange quant_range(float rel, int qmax) {
 // and two header bytes to a pack.  One read of the input instead of three (parameters, sizes, bytes): 8 x 52 heads
 // of 8000 tokens 1603 -> 653 us, wide 1670 -> 947; 4 x 8 heads 134 -> 61; a block of 2 x 40 heads, V wide, 44.7 -> 16.1 (eight
 // launches before, two now).
+// SIZES: token metadata and width sums only, of a whole round that is written in a second pass over the input.
 // UNSURE: the round may not be staged, and the kernel finds out first (at run time the question alone cost sure rounds 1 %, a
 // block of 8 x 52 heads 16.0 -> 16.4 us).  Not staged, 8000 tokens of 8 x 52 heads take 1025 us, 4096 of 32 55; quantized
 // all the same, and thrown away, 1305 and 67.
-template <int HP, bool GIVEN, bool STREAM, bool UNSURE, bool MIXED, bool PACK8>
+template <int HP, bool GIVEN, bool STREAM, bool UNSURE, bool MIXED, bool PACK8, bool SIZES = false>
 __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_kernel(PackArgs a) {
+    static_assert(!SIZES || (!GIVEN && !UNSURE && !MIXED), "whole rounds that are written in a second pass");
     static_assert(!PACK8 || !UNSURE, "packs of 8 are staged in rounds that fit for sure");
     static_assert(!MIXED || (!GIVEN && !UNSURE), "the block of the tail: rounds that are staged for sure and find their parameters");
     constexpr int MOST_WAVES = HP < 4 ? 1 : GIVEN ? 4 : 16;
@@ -1128,12 +1131,12 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
             if (wide) {
                 const uint32_t m0 = m_lo & 0x7F7F7F7Fu, m1 = m_hi & 0x7F7F7F7Fu, w0 = width_bytes7(x_lo - m0), w1 = width_bytes7(x_hi - m1);
                 width_sum += w0 + w1;
-                if (present) *reinterpret_cast<uint2 *>(to) = make_uint2(w0, w1);
-                if (present) *reinterpret_cast<uint2 *>(to + HEADERW / 2) = make_uint2(m0, m1);
+                if (present && !SIZES) *reinterpret_cast<uint2 *>(to) = make_uint2(w0, w1);
+                if (present && !SIZES) *reinterpret_cast<uint2 *>(to + HEADERW / 2) = make_uint2(m0, m1);
             } else {
                 const uint32_t m0 = m_lo & 0x0F0F0F0Fu, m1 = m_hi & 0x0F0F0F0Fu, w0 = width_bytes(x_lo - m0), w1 = width_bytes(x_hi - m1);
                 width_sum += w0 + w1;
-                if (present) *reinterpret_cast<uint2 *>(to) = make_uint2((w0 << 4) | m0, (w1 << 4) | m1);
+                if (present && !SIZES) *reinterpret_cast<uint2 *>(to) = make_uint2((w0 << 4) | m0, (w1 << 4) | m1);
             }
         };
 #pragma unroll
@@ -1167,7 +1170,7 @@ __global__ __launch_bounds__(HP < 4 ? 64 : GIVEN ? 256 : 1024) void quantize16_k
             // what the quad leaves is computed here: moved to where it is used, it would keep all pairs in registers
 #pragma unroll
             for (int k = 0; k < 4; ++k) consume_here(mn2[k]), consume_here(mx2[k]), consume_here(codes[2 * k]), consume_here(codes[2 * k + 1]);
-            if (((quad & 1) || wide) && present) {
+            if (!SIZES && ((quad & 1) || wide) && present) {
                 const uint32_t place = wide ? HEADERW + 2048 * g + 512 * quad : (PACK8 ? HEADER8 : HEADER) + 1024 * g + 512 * (quad >> 1);
                 uint8_t *const to = a.staging + (at + place);
                 *reinterpret_cast<uint4 *>(to) = make_uint4(codes[0], codes[1], codes[2], codes[3]);
@@ -1578,9 +1581,18 @@ __global__ __launch_bounds__(1024) void scan_offsets_kernel(PackArgs a) {
     const int per = ((n + 15) / 16 + 255) & ~255;
     const int lo = min(wave * per, n), hi = min(lo + per, n);
     // sizes lo + 256 r + 4 lane .. + 3 (sizes16 is 256-byte aligned and its area a multiple of 16 bytes)
+    const uint2 *widths = reinterpret_cast<const uint2 *>(t.widths);   // or the width sums, where the round has those
     auto load4 = [&](int r) {
         const int i = lo + 256 * r + 4 * lane;
-        uint4 q = i < hi ? *reinterpret_cast<const uint4 *>(sizes16 + i) : make_uint4(0, 0, 0, 0);
+        uint4 q = make_uint4(0, 0, 0, 0);
+        if (widths) {
+            if (i < hi) {   // (the area goes on behind the last one)
+                const uint4 x = *reinterpret_cast<const uint4 *>(widths + i), y = *reinterpret_cast<const uint4 *>(widths + i + 2);
+                q.x = chunk_units(make_uint2(x.x, x.y), t.header16, t.unit_shift), q.y = chunk_units(make_uint2(x.z, x.w), t.header16, t.unit_shift);
+                q.z = chunk_units(make_uint2(y.x, y.y), t.header16, t.unit_shift), q.w = chunk_units(make_uint2(y.z, y.w), t.header16, t.unit_shift);
+            }
+        } else
+            q = i < hi ? *reinterpret_cast<const uint4 *>(sizes16 + i) : make_uint4(0, 0, 0, 0);
         if (i + 1 >= hi) q.y = 0;
         if (i + 2 >= hi) q.z = 0;
         if (i + 3 >= hi) q.w = 0;
@@ -1671,11 +1683,15 @@ __global__ __launch_bounds__(1024) void place_chunks_kernel(PackArgs a, int n_te
     const int64_t first_chunk = pt.round.first_chunk;
     uint32_t *const page_list = pt.page_list;
     const int64_t max_pages = pt.max_pages;
+    const uint2 *widths = reinterpret_cast<const uint2 *>(pt.widths);
     if (tensor) __syncthreads();  // the shared arrays and the pool's state of the tensor before are done with
 
-    // (1) exclusive prefix sums, in place
+    // (1) exclusive prefix sums, in place (width sums: both tensors use the same sizes, one after the other)
     uint32_t local = 0;
-    for (int i = lo; i < hi; ++i) local += sizes16[i];
+    for (int i = lo; i < hi; ++i) {
+        if (widths) sizes16[i] = chunk_units(widths[i], pt.header16, pt.unit_shift);
+        local += sizes16[i];
+    }
     uint32_t inc = local;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -2505,20 +2521,39 @@ static bool fits_for_sure(const kv_cache *c, int n_chunks) {
     return c->fill_bound16[0] + worst16(c->wide_k) <= arena_units(c->sizes.k_arena) && c->fill_bound16[1] + worst16(c->wide_v) <= arena_units(c->sizes.v_arena);
 }
 
+// Whether a round in two passes over the input finds its metadata and sizes with the staged path's quantizer (the width sums go to the
+// staging area): one read of the input for both, where token parameters and sizes took one each (pages, 8 x 10 heads of 22 090 tokens 847 -> 759 us, 3 x 1 of
+// 11 032 43.7 -> 29.9; packs of 8, 32 heads of 10 000 188 -> 150).
+static bool sizes_in_one(const kv_cache *c, int n_chunks) {
+    const size_t area = size_t(c->stage_chunks / 2) * stage_pair_bytes(c->cfg.pack_size, c->wide_k, c->wide_v);
+    return std::max(c->qmax_k, c->qmax_v) <= MOST_STAGED_CODE && c->cfg.n_kv_heads <= 64 && c->cfg.repack == KV_REPACK_NONE &&
+           area >= size_t(2) * 8 * (size_t(n_chunks) + 8);
+}
+
+// Whether a round that could be staged in parts of at most `most` chunks is better done in two passes over all of it: parts leave
+// the chip idle and cost two launches each; the second read comes from the last-level cache or costs less than they do.  Staged / two passes:
+// packs of 16, parts of 256 chunks (4 heads of 40 000 tokens) 128 / 50 us, 512 (8 heads of 13 000) 60 / 41, 1024 (2 x 8 of 30 000) 155 / 107, 2048 (32 of
+// 20 000) 151 / 137, two of 2048 58 / 65, 2560 (4 x 10 of 30 000) 274 / 252, 3328 (52 of 20 000) 214 / 227, 5120 (8 x 10 of 22 090) 327 / 384; packs of 8, whose second pass is
+// slower, 256 (4 heads of 13 000) 55 / 41, 512 (8 heads) 64 / 58, 1024 (2 x 8 of 20 000) 105 / 126.  Repacked packs of 8, whose token parameters
+// and sizes are two passes themselves, 4 heads of 30 000, wide, in 8 parts of 256 174 / 116.
+static bool two_passes_pay(const kv_cache *c, int n_chunks, int most) {
+    const int parts = (n_chunks + most - 1) / most;
+    if (!sizes_in_one(c, n_chunks)) return c->cfg.pack_size == 8 && most < 1024 && parts > 4;
+    if (c->cfg.pack_size == 8) return parts > 1 && most <= 640;
+    // (an arena that may be too full: the staged kernels find out before they have read anything twice)
+    return ((parts > 2 && most <= 2560) || (parts > 1 && most <= 512)) && fits_for_sure(c, n_chunks);
+}
+
 // Whether a round of n_chunks chunks (per tensor) is staged, unless (packs of 16) the arena turns out to be too full.
-// Packs of 8: only where no arena can be too full, and for codes the fixed-point quantizer takes; and not in many small parts, which
-// take longer than two passes over all of the round (one sequence of 30 000 tokens, two passes / staged: 4 heads, 8 parts of 256 chunks, 79 / 107 us,
-// wide and repacked 116 / 174; 8 heads, wide, 8 of 512 132 / 156; 2 heads, 4 of 256 56 / 53; 32 streams of 20 000, 5 of 2048, 352 / 157).
+// Packs of 8: only where no arena can be too full, and for codes the fixed-point quantizer takes.
 static bool staged_rounds(const kv_cache *c, int n_chunks) {
     const int most = c->stage_chunks / 2;
-    if (most < c->cfg.n_kv_heads || (c->pool && n_chunks > most)) return false;
-    if (c->cfg.pack_size == 16) return true;
-    if (most < 1024 && n_chunks > 4 * most) return false;
-    return std::max(c->qmax_k, c->qmax_v) <= MOST_STAGED_CODE && fits_for_sure(c, n_chunks);
+    if (most < c->cfg.n_kv_heads || (c->pool && n_chunks > most) || two_passes_pay(c, n_chunks, most)) return false;
+    return c->cfg.pack_size == 16 || (std::max(c->qmax_k, c->qmax_v) <= MOST_STAGED_CODE && fits_for_sure(c, n_chunks));
 }
 
 bool finds_params(const kv_cache *c, int n_chunks) {
-    return staged_rounds(c, n_chunks) && c->cfg.n_kv_heads <= 64 && c->cfg.repack == KV_REPACK_NONE;
+    return c->cfg.n_kv_heads <= 64 && c->cfg.repack == KV_REPACK_NONE && (staged_rounds(c, n_chunks) || sizes_in_one(c, n_chunks));
 }
 
 // A round of many small parts is left to the token parameters of the whole round and two kernels to a part, instead of three
@@ -2541,7 +2576,7 @@ static void launch_quantize_tokens(const PackArgs &a, int H, bool stream, hipStr
 }
 
 template <int HP, bool GIVEN, bool PACK8>
-static void launch_quantize16_as(PackArgs &a, int H, bool stream, bool unsure, bool mixed, hipStream_t s) {
+static void launch_quantize16_as(PackArgs &a, int H, bool stream, bool unsure, bool mixed, bool sizes, hipStream_t s) {
     const int waves = HP < 4 ? 1 : std::min((H + 3) / 4, GIVEN ? 4 : 16);
     // workgroups of that many waves that fit a compute unit (0: not asked yet)
     static std::atomic<int> per_cu_of[17];
@@ -2563,14 +2598,16 @@ static void launch_quantize16_as(PackArgs &a, int H, bool stream, bool unsure, b
         if (unsure) kernel = stream ? quantize16_kernel<HP, GIVEN, true, true, false, false> : quantize16_kernel<HP, GIVEN, false, true, false, false>;
     if constexpr (!GIVEN)
         if (mixed) kernel = quantize16_kernel<HP, false, false, false, true, PACK8>;
+    if constexpr (!GIVEN)
+        if (sizes) kernel = stream ? quantize16_kernel<HP, false, true, false, false, PACK8, true> : quantize16_kernel<HP, false, false, false, false, PACK8, true>;
     hipLaunchKernelGGL(kernel, dim3(groups), dim3(64 * waves), 0, s, a);
 }
 
 template <bool PACK8>
-static void launch_quantize16(PackArgs &a, int H, bool given, bool stream, bool unsure, bool mixed, hipStream_t s) {
+static void launch_quantize16(PackArgs &a, int H, bool given, bool stream, bool unsure, bool mixed, bool sizes, hipStream_t s) {
 #define PACKKV_LAUNCH_QUANTIZE(hp)                                        \
-    given ? launch_quantize16_as<hp, true, PACK8>(a, H, stream, unsure, false, s) \
-          : launch_quantize16_as<hp, false, PACK8>(a, H, stream, unsure, mixed, s)
+    given ? launch_quantize16_as<hp, true, PACK8>(a, H, stream, unsure, false, false, s) \
+          : launch_quantize16_as<hp, false, PACK8>(a, H, stream, unsure, mixed, sizes, s)
     if (H == 1) PACKKV_LAUNCH_QUANTIZE(1);
     else if (H == 2) PACKKV_LAUNCH_QUANTIZE(2);
     else PACKKV_LAUNCH_QUANTIZE(4);
@@ -2579,7 +2616,7 @@ static void launch_quantize16(PackArgs &a, int H, bool given, bool stream, bool 
 
 bool completes_in_place(const kv_cache *c) {
     const int n_chunks = c->cfg.batch * c->cfg.n_kv_heads;
-    return ((finds_params(c, n_chunks) && fits_for_sure(c, n_chunks)) || moves_codes(c, n_chunks)) && !larger_than_caches(n_chunks);
+    return ((staged_rounds(c, n_chunks) && finds_params(c, n_chunks) && fits_for_sure(c, n_chunks)) || moves_codes(c, n_chunks)) && !larger_than_caches(n_chunks);
 }
 
 int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &vjob, TailRest *rest, hipStream_t s) {
@@ -2666,7 +2703,7 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
                 launch_quantize_tokens(a, H, stream, s);
                 hipLaunchKernelGGL(planes ? move_codes_kernel<false> : move_codes_kernel<true>, dim3((a.n + 3) / 4, 2), dim3(256), 0, s, a);
             } else
-                (planes ? launch_quantize16<false> : launch_quantize16<true>)(a, H, !finds_params(c, n_chunks), stream, unsure, kjob.held > 0, s);
+                (planes ? launch_quantize16<false> : launch_quantize16<true>)(a, H, !finds_params(c, n_chunks), stream, unsure, kjob.held > 0, false, s);
             static_assert(PLACE_SMALL_CHUNKS >= 16384 / 2, "a staged round of a paged cache fits the placement kernel");
             static_assert(16384 * 8 + 64 <= WS_SIZES_BYTES, "the width sums of a part fit the sizes area");
             if (c->pool) hipLaunchKernelGGL(place_small_kernel, dim3(1), dim3(1024), 0, s, a);
@@ -2689,15 +2726,19 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
     }
     if (two_pass) {
         // both tensors per launch where the sizes area takes both (and, packs of 8, the layouts agree)
-        a.part_first = 0;
+        a.part_first = a.part_row = 0;
         a.n = n_chunks;
-        a.t[0].widths = a.t[1].widths = nullptr;
-        const bool both = 2 * ((n_chunks + 3) & ~3) <= MAX_NEW_CHUNKS;
+        a.rows = a.round_rows = n_chunks / H;
+        const bool sized = !staged && finds_params(c, n_chunks);
+        a.t[0].widths = sized ? reinterpret_cast<uint16_t *>(a.staging) : nullptr;
+        a.t[1].widths = sized ? a.t[0].widths + 4 * ((n_chunks + 7) & ~3) : nullptr;
+        const bool both = sized || 2 * ((n_chunks + 3) & ~3) <= MAX_NEW_CHUNKS;
         const bool same = planes || kjob.wide == vjob.wide;
+        if (sized) (planes ? launch_quantize16<false> : launch_quantize16<true>)(a, H, false, stream, false, false, true, s);
         for (int i = 0; i < 2; i += both ? 2 : 1) {
             a.first_tensor = i;
             a.t[0].sizes16 = sizes16;
-            a.t[1].sizes16 = both ? sizes16 + ((n_chunks + 3) & ~3) : sizes16;
+            a.t[1].sizes16 = both && !sized ? sizes16 + ((n_chunks + 3) & ~3) : sizes16;
             const int n_tensors = both ? 2 : 1;
             auto pass = [&](bool write) {
                 for (int j = i; j < i + n_tensors; j += same ? n_tensors : 1) {
@@ -2711,7 +2752,7 @@ int launch_pack(const kv_cache *c, const CompressJob &kjob, const CompressJob &v
                 }
                 a.first_tensor = i;
             };
-            pass(false);
+            if (!sized) pass(false);
             if (c->pool && n_tensors == 2 && n_chunks <= PLACE_SMALL_CHUNKS)
                 hipLaunchKernelGGL(place_small_kernel, dim3(1), dim3(1024), 0, s, a);
             else if (c->pool)
