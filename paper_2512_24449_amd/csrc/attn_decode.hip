@@ -50,6 +50,7 @@ struct AArgs {
     const __half *k_tail, *v_tail;
     int n_tail, tail_cap;
     float *out;
+    VCentre centre;         // wide V chunks
 };
 
 // Maximum over the 64 lanes of a wave, in every lane (see wave_all_sum).
@@ -71,9 +72,9 @@ __device__ inline float exp2_diff(float a, float b) { return a == -INFINITY ? 0.
 
 // Online softmax bookkeeping: raise a head's reference only when a score of this block runs
 // away from it, and rescale the running sums then.  s: this lane's scores (log2 units).
-template <int G>
+template <int G, bool FOLD>
 __device__ inline void attn_raise_reference(const float (&s)[G], float (&m_ref)[G], float (&l_lane)[G],
-                                            VState<G> &st, int col) {
+                                            VState<G, FOLD> &st, int col) {
     bool raise = false;
 #pragma unroll
     for (int g = 0; g < G; ++g) raise |= s[g] > m_ref[g] + RAISE_MARGIN;
@@ -88,7 +89,7 @@ __device__ inline void attn_raise_reference(const float (&s)[G], float (&m_ref)[
             m_ref[g] = m_new;
             l_lane[g] *= alpha;
             st.pm[g] *= alpha;
-            if constexpr (!fold_min<G>()) {
+            if constexpr (!FOLD) {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) st.macc[g][j] *= alpha;
             }
@@ -126,8 +127,8 @@ __device__ inline void attn_raise_reference(const float (&s)[G], float (&m_ref)[
     }
 }
 
-template <int G>
-__device__ inline void attn_store_state(const VState<G> &st, float (*red)[D + 4], int lane, float code_scale) {
+template <int G, bool FOLD>
+__device__ inline void attn_store_state(const VState<G, FOLD> &st, float (*red)[D + 4], int lane, float code_scale) {
     v_state_store<G>(st, red, lane, code_scale);
 }
 template <int G>
@@ -586,7 +587,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G <= 4 && K
     VLane<G> vl;
     vl.init(blds_all + wave * BLds<G>::BYTES, lane);
     vl.bslot = v8_bslot<G>(tok_in_blk);
-    VState<G> st;
+    VState<G, VW || fold_min<G>()> st;
     st.clear();
     float m_ref[G], l_lane[G];
 #pragma unroll
@@ -655,7 +656,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G <= 4 && K
                     l_lane[g] += pt[g];
                 }
                 if constexpr (VW)
-                    vw_chunk<G, true>(lds_all, vbuf, vtable, vl, vmt, pt, st);
+                    vw_chunk<G>(lds_all, vbuf, vtable, vl, vmt, pt, a.centre, st);
                 else
                     v8_chunk<G, true>(lds_all, vbuf, vtable, vl, vmt, pt, st);
             }
@@ -839,6 +840,7 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         a.n_tail = c->tail_tokens;
         a.tail_cap = c->cfg.tail_capacity;
         a.out = out;
+        a.centre = VCentre::of(c->qmax_v);
         const dim3 grid(n_splits, B * Hs);
 #define PACKKV_LAUNCH_A8X(g, kw, vw, mid)                                                                    \
     if (merged) hipLaunchKernelGGL((attn8_kernel<g, kw, vw, mid, (g <= MERGED_HEADS)>), grid, dim3(256), 0, s, a); \

@@ -271,8 +271,8 @@ __device__ inline void v8_chunk(const uint8_t *lds_all, int cur, const uint4 *ta
 // subnormals (code * 2^-24), so the K dot products stay exact.  The V path cannot lift them far
 // enough inside the subnormal range for the matrix cores (255 << 2 is the limit, and with two
 // bits the measured output error at 32 Ki tokens and 255 levels was 6e-3): it turns every
-// pair into the normal numbers `code` instead, exactly: OR in the bit pattern of 1024.0, then
-// subtract 1024.0 in packed fp16 -- two instructions per word.
+// pair into normal numbers instead, exactly: OR in the bit pattern of 1024.0, then
+// add minimum - mid - 1024 in packed fp16 -- two instructions per word.
 constexpr int CHUNKW_LDS = CHUNKW_MAX;
 // Codes of up to 31 (relative scales down to 1/31): widths of at most 5 bits, and a buffer two thirds as large, of which a wave
 // gets two where it gets one of the others.
@@ -280,6 +280,16 @@ constexpr int MID_QMAX = 31;
 constexpr int CHUNKM_MAX = HEADERW + N / 8 * D * 5, CHUNKM_LDS = CHUNKM_MAX;
 constexpr int WIDE_TABLE_ENTRIES = 9;   // widths 0..8
 typedef _Float16 vhalf2 __attribute__((ext_vector_type(2)));
+// What centres the codes of a wide V tensor (vw_chunk): an even number mid near half of its largest code, -(1024 + mid) and -(2048 + mid) as
+// pairs of fp16 numbers (in steps of 1 and 2 there).
+struct VCentre {
+    uint32_t code_zero, min_zero;
+    float mid;
+    static VCentre of(int qmax) {
+        const uint32_t quarter = uint32_t(qmax + 1) / 4;
+        return VCentre{(0xE400u + 2 * quarter) * 0x10001u, (0xE800u + quarter) * 0x10001u, float(2 * quarter)};
+    }
+};
 
 // K form: x = 2w in bits 0..4 (bit-field offset/width), w in byte 1, the w-bit mask in the high
 // half; y = 4w (64-bit shift amount).  V form: x = mask in both halves, y = w, z = 4w, w = 2w.
@@ -390,15 +400,20 @@ __device__ inline void kw_chunk(const uint8_t *lds0, int cur, const uint2 *ktabl
     kw_half<G>(lds0, ktable, lp1, kq, lane, u1);
 }
 
-// V, one wide chunk (both halves); the lane's token as in v8_chunk (K8_ORDER).  vtable:
-// build_wide_tables.  The A operand holds the codes as numbers: accumulators in units of 1.
-template <int G, bool K8_ORDER = false>
+// V, one wide chunk (both halves); the lane's token is the one whose place vl.bslot is.  vtable:
+// build_wide_tables.  The A operand holds centred codes as numbers: accumulators in units of 1.
+// Centred: code - mid, and token minimums raised by mid * scale, mid about half of the tensor's largest code.  Values on both sides of 0 are the
+// usual ones; of those the sums of w code and of p min, a few hundred times their sum at 25 600 tokens, showed
+// every difference in the order of the additions (64 streams of 400 blocks, codes up to 31, 12 workgroups to a stream against 16: more than 1e-5
+// of an output; centred 4e-7).  The pack minimum comes in with the constant that turns the codes into numbers, so it has no sum of its
+// own (1390 vector instructions of 1470 in the fused kernel with one head, 1865 of 2062 with three); from four heads on, where that form makes
+// the compiler spill (32 streams of 1000 blocks at four heads 109 -> 131 us), it is added to the codes as an integer.
+template <int G>
 __device__ inline void vw_chunk(const uint8_t *lds_all, int cur, const uint4 *vtable, const VLane<G> &vl,
-                                uint32_t mt, const float (&pt)[G], VState<G> &st) {
+                                uint32_t mt, const float (&pt)[G], VCentre centre, VState<G, true> &st) {
     const int lane = threadIdx.x & 63;
     const float scale = __half2float(__ushort_as_half(uint16_t(mt & 0xFFFFu)));
-    const float mn = __half2float(__ushort_as_half(uint16_t(mt >> 16)));
-    float wsum[2][G];
+    const float mn = fmaf(scale, centre.mid, __half2float(__ushort_as_half(uint16_t(mt >> 16))));
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         // the fp16 split holds weights below 2^15 (hi rounds toward zero, the residual times 2^11 stays
@@ -412,21 +427,6 @@ __device__ inline void vw_chunk(const uint8_t *lds_all, int cur, const uint4 *vt
         const _Float16 lo16 = _Float16(lo);  // to nearest: the residual's rounding error has no sign bias
         *reinterpret_cast<_Float16 *>(vl.blds + vl.bslot + (2 * g) * 16) = hi;
         *reinterpret_cast<_Float16 *>(vl.blds + vl.bslot + (2 * g + 1) * 16) = lo16;
-        if (!fold_min<G>()) {
-            if constexpr (K8_ORDER) {
-                // the eight tokens of group (half s, row) sit in the lanes of this row with i & 1 = s
-                float v = w + dpp_f32<DPP_ROW_ROR8>(w);
-                v += dpp_f32<DPP_ROW_ROR4>(v);
-                v += dpp_f32<DPP_QUAD_XOR2>(v);
-                const float other = dpp_f32<DPP_QUAD_XOR1>(v);
-                wsum[0][g] = (lane & 1) ? other : v;
-                wsum[1][g] = (lane & 1) ? v : other;
-            } else {
-                const float w8 = lanes8_all_reduce(w);
-                wsum[0][g] = __shfl(w8, 8 * (lane >> 4));
-                wsum[1][g] = __shfl(w8, 32 + 8 * (lane >> 4));
-            }
-        }
     }
     wave_lds_fence();
     const vhalf8 b0 = *reinterpret_cast<const vhalf8 *>(vl.blds + vl.bread0);
@@ -440,14 +440,17 @@ __device__ inline void vw_chunk(const uint8_t *lds_all, int cur, const uint4 *vt
         LanePacksW lp;
         lp.init(wb, mb, payload);
         payload = lp.end_all;
+        vhalf2 offset = __builtin_bit_cast(vhalf2, centre.code_zero);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
+            if (!fold_min<G>() && j % 2 == 0)   // minimum - mid - 1024 of packs j and j + 1, exact
+                offset = __builtin_bit_cast(vhalf2, __builtin_amdgcn_perm(0x64646464u, j < 4 ? lp.mlo : lp.mhi, j & 2 ? 0x04030402u : 0x04010400u)) +
+                         __builtin_bit_cast(vhalf2, centre.min_zero);
             const uint4 k = vtable[lp.width(j)];
             uint32_t A, R;
             fetch_window_wide(lds_all, lp.pos(j), k.z, A, R);
             const uint32_t w = k.y, M = k.x, s2 = k.w;
-            const uint32_t mj = lp.minimum(j);
-            const uint32_t fold = fold_min<G>() ? mj * 0x10001u : 0u;   // code + minimum < 256
+            const uint32_t fold = fold_min<G>() ? lp.minimum(j) * 0x10001u : 0u;   // code + minimum < 256
             // tokens (0,1 | 4,5) and (2,3 | 6,7): low half | high half
             const uint32_t Z0 = __builtin_amdgcn_perm(R, A, 0x05040100u);
             const uint32_t Z1 = __builtin_amdgcn_perm(R >> s2, A >> s2, 0x05040100u);
@@ -455,13 +458,8 @@ __device__ inline void vw_chunk(const uint8_t *lds_all, int cur, const uint4 *vt
             uint32_t P[4];   // tokens (0,4) (1,5) (2,6) (3,7) as fp16 numbers
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-                const uint32_t biased = ((raw[m] & M) | 0x64006400u) + fold;   // 1024 + code (+ minimum), exact
-                P[m] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(vhalf2, biased) - vhalf2{1024.0f16, 1024.0f16});
-            }
-            if constexpr (!fold_min<G>()) {
-                const float m = float(mj);
-#pragma unroll
-                for (int g = 0; g < G; ++g) st.macc[g][j] = fmaf(m, wsum[s][g], st.macc[g][j]);
+                const uint32_t biased = ((raw[m] & M) | 0x64006400u) + fold;   // 1024 + code above the minimum (+ minimum)
+                P[m] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(vhalf2, biased) + vhalf2{offset[j & 1], offset[j & 1]});
             }
             typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
             const vhalf8 a = __builtin_bit_cast(vhalf8, u32x4v{P[0], P[1], P[2], P[3]});

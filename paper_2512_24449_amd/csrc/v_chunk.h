@@ -50,10 +50,10 @@ struct VLane {
 
 // Running sums of one wave: MFMA tiles (lane = column col, rows 4*row+r of pack slot j), the
 // pack-minimum term (lane = token group row, channels 8*col+j) and sum p*min per head.
-template <int G>
+template <int G, bool FOLD = fold_min<G>()>
 struct VState {
     vfloat4 acc[8];
-    float macc[fold_min<G>() ? 1 : G][8];  // unused when the minimum is folded into the codes
+    float macc[FOLD ? 1 : G][8];  // unused when the minimum is folded into the codes
     float pm[G];
 
     __device__ inline void clear() {
@@ -62,7 +62,7 @@ struct VState {
 #pragma unroll
         for (int g = 0; g < G; ++g) pm[g] = 0.0f;
 #pragma unroll
-        for (int g = 0; g < (fold_min<G>() ? 1 : G); ++g)
+        for (int g = 0; g < (FOLD ? 1 : G); ++g)
 #pragma unroll
             for (int j = 0; j < 8; ++j) macc[g][j] = 0.0f;
     }
@@ -71,8 +71,8 @@ struct VState {
 // Writes this wave's sums as red[g][0..127] (outputs) and red[g][128] (sum p*min).
 // code_scale: what one unit of the A operand stands for (codes enter as code * 2^-24 * 2^lift).
 // (Lanes that took every output on its own and added the minimum terms by shuffles: see v_planes_store.)
-template <int G>
-__device__ inline void v_state_store(const VState<G> &st, float (*red)[D + 4], int lane,
+template <int G, bool FOLD>
+__device__ inline void v_state_store(const VState<G, FOLD> &st, float (*red)[D + 4], int lane,
                                      float code_scale = CODE_SCALE_LIFTED) {
     const int row = lane >> 4, col = lane & 15;
     const int head = col >> 1;
@@ -93,7 +93,7 @@ __device__ inline void v_state_store(const VState<G> &st, float (*red)[D + 4], i
         o[0][j] = (odd ? v2 : v0) + dpp_f32<DPP_QUAD_XOR1>(odd ? v0 : v2);
         o[1][j] = (odd ? v3 : v1) + dpp_f32<DPP_QUAD_XOR1>(odd ? v1 : v3);
     }
-    if constexpr (!fold_min<G>()) {
+    if constexpr (!FOLD) {
 #pragma unroll
         for (int g = 0; g < G; ++g) store_row_sums8(st.macc[g], red[g], lane);
         wave_lds_fence();
@@ -103,7 +103,7 @@ __device__ inline void v_state_store(const VState<G> &st, float (*red)[D + 4], i
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             float4 v = make_float4(o[k >> 1][4 * (k & 1)], o[k >> 1][4 * (k & 1) + 1], o[k >> 1][4 * (k & 1) + 2], o[k >> 1][4 * (k & 1) + 3]);
-            if constexpr (!fold_min<G>()) {
+            if constexpr (!FOLD) {
                 const float4 m = to[k];
                 v = make_float4(v.x + m.x, v.y + m.y, v.z + m.z, v.w + m.w);
             }

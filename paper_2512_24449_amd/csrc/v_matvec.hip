@@ -10,6 +10,7 @@
 // context axis is split over workgroups whose partial sums are combined by a second small kernel
 // -- no atomics, bitwise reproducible.  De-quantization is folded in:
 //   out_d = sum_t w_t code[t,d] + sum_g m[g,d] sum_{t in g} w_t + sum_t p_t min_t
+// (wide chunks: centred codes and minimums, vw_chunk).
 #include <algorithm>
 #include <mutex>
 
@@ -43,6 +44,7 @@ struct VArgs {
     int64_t packed_tokens;
     int n_tail, tail_cap;
     float *out;
+    VCentre centre;         // wide chunks
 };
 
 // The sums of a workgroup's four waves, red[4][G][..], to the partial rows dst[g].
@@ -344,7 +346,7 @@ __global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a) {
     VLane<G> vl;
     vl.init(blds_all + wave * BLds<G>::BYTES, lane);
     vl.bslot = v8_bslot<G>(lane);  // lane l is token l of the block
-    VState<G> st;
+    VState<G, MID || fold_min<G>()> st;
     st.clear();
 
     for (int first = blk_begin + wave; first < blk_end; first += 4 * 64) {
@@ -377,7 +379,7 @@ __global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a) {
                 for (int g = 0; g < G; ++g) p_next[g] = a.p[(int64_t(b) * a.H * G + h * G + g) * a.ld + tok];
             }
             if (!valid) continue;  // a block dropped by an arena overflow contributes nothing
-            if constexpr (MID) vw_chunk<G>(lds_all, cur, table, vl, mt, pt, st);
+            if constexpr (MID) vw_chunk<G>(lds_all, cur, table, vl, mt, pt, a.centre, st);
             else v8_chunk<G>(lds_all, cur, table, vl, mt, pt, st);
         }
         wait_chunk_landed();
@@ -421,7 +423,7 @@ __global__ __launch_bounds__(256) void vw_matvec_kernel(VArgs a) {
     VLane<G> vl;
     vl.init(blds_all + wave * BLds<G>::BYTES, lane);
     vl.bslot = v8_bslot<G>(lane);  // lane l is token l of the block
-    VState<G> st;
+    VState<G, true> st;
     st.clear();
 
     for (int first = blk_begin + wave; first < blk_end; first += 4 * 64) {
@@ -437,7 +439,7 @@ __global__ __launch_bounds__(256) void vw_matvec_kernel(VArgs a) {
             for (int g = 0; g < G; ++g) pt[g] = a.p[(int64_t(b) * a.H * G + h * G + g) * a.ld + tok];
             wait_chunk_landed();
             if (!valid) continue;  // a block dropped by an arena overflow contributes nothing
-            vw_chunk<G>(lds_all, buf, vtable, vl, mt, pt, st);
+            vw_chunk<G>(lds_all, buf, vtable, vl, mt, pt, a.centre, st);
         }
         load_index(first + 4 * 64);
     }
@@ -565,6 +567,7 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
     a.n_tail = c->tail_tokens;
     a.tail_cap = c->cfg.tail_capacity;
     a.out = out;
+    a.centre = VCentre::of(c->qmax_v);
     a.counters = static_cast<uint8_t *>(c->buf.workspace) + WS_STATUS + 4 * ST_COUNTERS + counter;
     bool merged = false;
     if (n_blocks > 0 && planes) {

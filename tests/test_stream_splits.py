@@ -42,3 +42,18 @@ def test_within_bounds(splits):
             n, cost, usual = splits(nb, streams, per_cu, most)
             assert 1 <= n <= max(1, min(most, (nb + 3) // 4)) and cost > 0
             assert usual or n * streams <= 256 * per_cu or n == 1
+
+
+# test_gpu_wide_buffers compares 32 streams of 400 blocks, which take the kernels with two smaller chunk buffers (two workgroups to a compute unit),
+# with 64, which must not.  The rules as launch_k_matvec and launch_decode_attention have them, three workgroups of the other kernels to a compute unit.
+@pytest.mark.parametrize("streams,small_buffers", [(32, True), (64, False)])
+def test_both_sides_of_the_line_between_wide_buffers(splits, streams, small_buffers):
+    blocks = 400
+    (_, cost, _), (n2, cost2, _) = splits(blocks, streams, 3), splits(blocks, streams, 2)
+    assert (n2 * streams <= 512 and cost2 <= cost) == small_buffers, "fused attention"
+    _, cost, _ = splits(blocks, streams, 3, 1 << 20)
+    n2, cost2, usual2 = splits(blocks, streams, 2, 1 << 20)
+    if usual2:
+        n2 = max(1, min(max(streams * blocks // 32, 512), 4096) // streams)
+    per_group = max(4, -(-(-(-blocks // n2)) // 4) * 4)
+    assert (cost2 <= cost and streams * -(-blocks // per_group) <= 512) == small_buffers, "K product"
