@@ -24,6 +24,7 @@
 #include <algorithm>
 #include <atomic>
 
+#include "quantize_value.h"
 #include "unpack.h"
 
 namespace packkv {
@@ -141,27 +142,6 @@ struct PackBits {
     uint64_t bits;
     int w, m;
 };
-
-// Token-wise quantization of one value (Sec. III-B.2) with the token's scale and minimum:
-// clamp(rint(fl((x - mn) / s)), 0, qmax), the quotient rounded to fp32 as an IEEE divide does.
-// r is the token's 1 / s from an IEEE divide (once per token).  The product (x - mn) * r lies
-// within 1.5 * 2^-23 relative of that rounded quotient (half an ulp for r, half for the product,
-// half for the quotient's own rounding), which is below 5e-5 in absolute terms for every quotient
-// that is not clamped anyway (<= 256.5; beyond that both round to at least 256 > qmax).  So unless
-// the product is within 1e-3 of a rounding tie k + 0.5, rint of the product IS rint of the
-// quotient; the rare value near a tie takes the divide.
-__device__ inline int quantize_value(float x, float s, float mn, float r, int qmax) {
-    int v = 0;
-    if (s != 0.0f) {
-        const float a = x - mn;
-        const float q1 = a * r;
-        float t = rintf(q1);  // ties to even
-        if (fabsf(fabsf(q1 - t) - 0.5f) < 1e-3f) t = rintf(a / s);  // IEEE fp32 divide
-        v = (int)t;
-        v = v < 0 ? 0 : (v > qmax ? qmax : v);
-    }
-    return v;
-}
 
 // A token's (scale, minimum, 1 / scale) from its metadata word (fp16 scale | fp16 minimum << 16).
 __device__ inline float4 token_scale_min(uint32_t mt) {
@@ -285,11 +265,13 @@ __global__ __launch_bounds__(256) void chunk_kernel(PackArgs a) {
     const int d = tau & 127;
 
     uint8_t *dst = nullptr;
+    uint32_t room16 = 0;
     if (WRITE) {
         const int64_t e = (t.round.first_chunk + cl) * a.index_words;
         uint32_t o0 = t.index[e], o1 = t.index[e + 1];
         if (o1 == o0) return;  // dropped: the arena was full
         dst = t.arena + size_t(o0) * 16;
+        room16 = o1 - o0;
     }
 
     // stage the block's 64 x 128 values in LDS with 16-byte loads, rows in storage order, and the
@@ -328,6 +310,12 @@ __global__ __launch_bounds__(256) void chunk_kernel(PackArgs a) {
 
     if (!WRITE) {
         if (tau == 0) t.sizes16[cl] = uint32_t(padded >> 4);
+        return;
+    }
+    // The sizes come from the same codes, so this never happens; should it all the same, nothing is written behind the chunk's place, and a
+    // header of zeros makes it 64 tokens of code 0.
+    if (uint32_t(padded) > 16 * room16) {
+        for (int i = tau; i < HDR && uint32_t(i) < 16 * room16; i += 256) dst[i] = 0;
         return;
     }
 #pragma unroll
@@ -455,8 +443,9 @@ __device__ inline ChunkInput load_chunk_input(const ChunkSource &cs, int cl) {
 // e >= 8) the quotient can only be on the other side of a rounding tie, or on one, if the fraction
 // field of t is below 2g: then the token's eight values take the divide.  A token whose offset is so
 // large against its scale that g reaches 1/2 always does, infinite offsets and scales among them.  A NaN
-// gets some code in range: its pattern is above the clamp's on the fast path, and the divide's minimum
-// takes qmax.  s = 0: r = 0, code 0.
+// gets qmax: its pattern is above the clamp's on the fast path, and the divide's minimum
+// takes qmax.  s = 0: r = 0, code 0; t is then 128 + (1 - 2^-16) for every number, at the guard, while a NaN, from infinite values too, lies below it (its
+// low 13 bits are 0) and takes the divide, which gives 0.
 struct TokenQuant {
     float r, c;
     uint32_t guard;  // 2g
@@ -468,8 +457,8 @@ __device__ inline float4 token_quant(uint32_t mt) {
     const float r = s != 0.0f ? __builtin_amdgcn_rcpf(s) : 0.0f;
     const int e = int((__float_as_uint(fmaf(-mn, r, 128.5f)) >> 23) & 0xFFu) - 127;
     const uint32_t g = 3u + (e >= 8 ? 2u << min(e - 8, 14) : 0u);
-    const float c = fmaf(-mn, r, 128.5f + float(g) * (1.0f / 65536.0f));
-    return make_float4(r, c, __uint_as_float(2u * g), __uint_as_float(mt));
+    const float c = s != 0.0f ? fmaf(-mn, r, 128.5f + float(g) * (1.0f / 65536.0f)) : __uint_as_float(0x4300FFFFu);
+    return make_float4(r, c, __uint_as_float(s != 0.0f ? 2u * g : 0xFFFFu), __uint_as_float(mt));
 }
 
 // x * r + c for the low (HI = false) or high half x of a word of two fp16 values, rounded once.
@@ -683,16 +672,18 @@ __global__ __launch_bounds__(256) void chunk16_kernel(PackArgs a) {
     if (staged_round(t.round, t.index)) return;  // the staged path writes this round
     const int cl = blockIdx.x;
     uint8_t *dst = nullptr;
+    int room16 = 0;
     if (WRITE) {
         const int64_t e = (t.round.first_chunk + cl) * a.index_words;
         uint32_t o0 = t.index[e], o1 = t.index[e + 1];
         if (o1 == o0) return;  // dropped: the arena was full
         dst = t.arena + size_t(o0) * 16;
+        room16 = int(o1 - o0);
     }
     __shared__ ChunkLds lds;
     const int n16 = build_plane_chunk<WRITE>(t.cs, load_chunk_input(t.cs, cl), lds);
     if (WRITE)
-        copy_image(lds, n16, dst);
+        copy_image(lds, min(n16, room16), dst);   // (they are equal; nothing is written behind the chunk's place in any case)
     else if (threadIdx.x == 0)
         t.sizes16[cl] = uint32_t(n16);
 }
