@@ -50,7 +50,6 @@ struct AArgs {
     const __half *k_tail, *v_tail;
     int n_tail, tail_cap;
     float *out;
-    VCentre centre;         // wide V chunks
 };
 
 // Maximum over the 64 lanes of a wave, in every lane (see wave_all_sum).
@@ -546,7 +545,7 @@ __global__ __launch_bounds__(SOLO ? 64 * SOLO : 256) void attn_kernel(AArgs a, F
 // 29.6 -> 28.4 us (4 x 8 streams of 156 blocks, four heads), 35.1 -> 33.0 (2 x 32 of 127, both tensors wide).
 // (Three waves per SIMD where the buffers leave room for them, two with more heads.)
 template <int G, bool KW, bool VW, bool MID, bool MERGE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G <= 4 && KW == VW && !MID ? 3 : 2))) void attn8_kernel(AArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G <= 4 && KW == VW && !MID ? 3 : 2))) void attn8_kernel(AArgs a, VCentre centre) {
     constexpr bool SHARED = KW && VW && !MID;
     constexpr int WLDS = MID ? CHUNKM_LDS : CHUNKW_LDS, WMAX = MID ? CHUNKM_MAX : CHUNKW_MAX;
     constexpr int KLDS = KW ? WLDS : CHUNK8_LDS, VLDS = SHARED ? 0 : (VW ? WLDS : CHUNK8_LDS);
@@ -656,7 +655,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G <= 4 && K
                     l_lane[g] += pt[g];
                 }
                 if constexpr (VW)
-                    vw_chunk<G>(lds_all, vbuf, vtable, vl, vmt, pt, a.centre, st);
+                    vw_chunk<G>(lds_all, vbuf, vtable, vl, vmt, pt, centre, st);
                 else
                     v8_chunk<G, true>(lds_all, vbuf, vtable, vl, vmt, pt, st);
             }
@@ -840,11 +839,10 @@ int launch_decode_attention(const kv_cache *c, const __half *q, float sm_scale, 
         a.n_tail = c->tail_tokens;
         a.tail_cap = c->cfg.tail_capacity;
         a.out = out;
-        a.centre = VCentre::of(c->qmax_v);
         const dim3 grid(n_splits, B * Hs);
 #define PACKKV_LAUNCH_A8X(g, kw, vw, mid)                                                                    \
-    if (merged) hipLaunchKernelGGL((attn8_kernel<g, kw, vw, mid, (g <= MERGED_HEADS)>), grid, dim3(256), 0, s, a); \
-    else hipLaunchKernelGGL((attn8_kernel<g, kw, vw, mid, false>), grid, dim3(256), 0, s, a)
+    if (merged) hipLaunchKernelGGL((attn8_kernel<g, kw, vw, mid, (g <= MERGED_HEADS)>), grid, dim3(256), 0, s, a, VCentre::of(c->qmax_v)); \
+    else hipLaunchKernelGGL((attn8_kernel<g, kw, vw, mid, false>), grid, dim3(256), 0, s, a, VCentre::of(c->qmax_v))
 #define PACKKV_LAUNCH_A8W(g, kw, vw)              \
     if (mid) { PACKKV_LAUNCH_A8X(g, kw, vw, true); } \
     else { PACKKV_LAUNCH_A8X(g, kw, vw, false); }

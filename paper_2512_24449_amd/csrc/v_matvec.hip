@@ -44,7 +44,6 @@ struct VArgs {
     int64_t packed_tokens;
     int n_tail, tail_cap;
     float *out;
-    VCentre centre;         // wide chunks
 };
 
 // The sums of a workgroup's four waves, red[4][G][..], to the partial rows dst[g].
@@ -319,7 +318,7 @@ __global__ __launch_bounds__(SOLO ? 64 * SOLO : 256) void v_matvec_kernel(VArgs 
 // MID: wide chunks without codes above 31, of which two fit as well (pack8.h; with one buffer, as below, 64 streams of 127
 // blocks took 22.6 us).
 template <int G, bool MID, bool MERGE>
-__global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a) {
+__global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a, VCentre centre) {
     constexpr int LDS = MID ? CHUNKM_LDS : CHUNK8_LDS, MAXB = MID ? CHUNKM_MAX : CHUNK8_MAX, HDR = MID ? HEADERW : HEADER8;
     // two chunk buffers per wave; after the main loop the same memory holds the
     // cross-wave reduction array red[4][G][D + 4]
@@ -379,7 +378,7 @@ __global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a) {
                 for (int g = 0; g < G; ++g) p_next[g] = a.p[(int64_t(b) * a.H * G + h * G + g) * a.ld + tok];
             }
             if (!valid) continue;  // a block dropped by an arena overflow contributes nothing
-            if constexpr (MID) vw_chunk<G>(lds_all, cur, table, vl, mt, pt, a.centre, st);
+            if constexpr (MID) vw_chunk<G>(lds_all, cur, table, vl, mt, pt, centre, st);
             else v8_chunk<G>(lds_all, cur, table, vl, mt, pt, st);
         }
         wait_chunk_landed();
@@ -400,7 +399,7 @@ __global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a) {
 // Wide chunks (codes above 15; pack8.h): one buffer per wave (a chunk is up to 10 KB), so the
 // transfer is waited for before the unpack; the other waves of the compute unit overlap with it.
 template <int G, bool MERGE>
-__global__ __launch_bounds__(256) void vw_matvec_kernel(VArgs a) {
+__global__ __launch_bounds__(256) void vw_matvec_kernel(VArgs a, VCentre centre) {
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * CHUNKW_LDS + LDS_TAIL_PAD];
     __shared__ __attribute__((aligned(16))) uint8_t blds_all[4 * BLds<G>::BYTES];
     __shared__ uint4 vtable[16];
@@ -439,7 +438,7 @@ __global__ __launch_bounds__(256) void vw_matvec_kernel(VArgs a) {
             for (int g = 0; g < G; ++g) pt[g] = a.p[(int64_t(b) * a.H * G + h * G + g) * a.ld + tok];
             wait_chunk_landed();
             if (!valid) continue;  // a block dropped by an arena overflow contributes nothing
-            vw_chunk<G>(lds_all, buf, vtable, vl, mt, pt, a.centre, st);
+            vw_chunk<G>(lds_all, buf, vtable, vl, mt, pt, centre, st);
         }
         load_index(first + 4 * 64);
     }
@@ -567,7 +566,6 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
     a.n_tail = c->tail_tokens;
     a.tail_cap = c->cfg.tail_capacity;
     a.out = out;
-    a.centre = VCentre::of(c->qmax_v);
     a.counters = static_cast<uint8_t *>(c->buf.workspace) + WS_STATUS + 4 * ST_COUNTERS + counter;
     bool merged = false;
     if (n_blocks > 0 && planes) {
@@ -621,11 +619,11 @@ static int launch_v_matvec_into(const kv_cache *c, const float *p, int64_t ld_p,
         dim3 grid(n_splits, B * Hs);
         merged = merge_in_kernel(int64_t(n_splits) * B * Hs, int64_t(B) * Hs, G, c->wide_v);
 #define PACKKV_LAUNCH_VW(g)                                                                     \
-    if (merged) hipLaunchKernelGGL((vw_matvec_kernel<g, (g <= MERGED_HEADS)>), grid, dim3(256), 0, s, a);      \
-    else hipLaunchKernelGGL((vw_matvec_kernel<g, false>), grid, dim3(256), 0, s, a)
+    if (merged) hipLaunchKernelGGL((vw_matvec_kernel<g, (g <= MERGED_HEADS)>), grid, dim3(256), 0, s, a, VCentre::of(c->qmax_v));      \
+    else hipLaunchKernelGGL((vw_matvec_kernel<g, false>), grid, dim3(256), 0, s, a, VCentre::of(c->qmax_v))
 #define PACKKV_LAUNCH_V8X(g, mid)                                                               \
-    if (merged) hipLaunchKernelGGL((v8_matvec_kernel<g, mid, (g <= MERGED_HEADS)>), grid, dim3(256), 0, s, a); \
-    else hipLaunchKernelGGL((v8_matvec_kernel<g, mid, false>), grid, dim3(256), 0, s, a)
+    if (merged) hipLaunchKernelGGL((v8_matvec_kernel<g, mid, (g <= MERGED_HEADS)>), grid, dim3(256), 0, s, a, VCentre::of(c->qmax_v)); \
+    else hipLaunchKernelGGL((v8_matvec_kernel<g, mid, false>), grid, dim3(256), 0, s, a, VCentre::of(c->qmax_v))
 #define PACKKV_LAUNCH_V8(g) PACKKV_LAUNCH_V8X(g, false)
 #define PACKKV_LAUNCH_VM(g) PACKKV_LAUNCH_V8X(g, true)
         if (mid) {
