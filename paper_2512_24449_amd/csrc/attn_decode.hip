@@ -320,7 +320,8 @@ struct SoloTail {
                 if constexpr (SEGS == 8) s += dpp_f32<DPP_ROW_HALF_MIRROR>(s);
                 const bool some = lane / SEGS < left;
                 s = some ? a.sm_log2 * s : -INFINITY;   // in all lanes of its token
-                const float M = fmaxf(m, wave_all_max(s)), f = exp2_diff(m, M), w = some ? exp2f(s - M) : 0.0f;
+                const float M = fmaxf(m, wave_all_max(s)), f = exp2_diff(m, M);
+                const float w = exp2_diff(s, M);   // (M too is -inf where the wave has no block and only such tokens)
                 if (lane % SEGS == 0) weights[lane / SEGS] = w;
                 wave_lds_fence();
                 l = fmaf(f, l, wave_all_sum(lane % SEGS == 0 ? w : 0.0f));
