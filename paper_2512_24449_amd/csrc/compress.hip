@@ -2292,6 +2292,10 @@ __global__ __launch_bounds__(256) void move_codes_kernel(PackArgs a) {
         if (PACK8) headers(2 * g + half);
     }
     if (!PACK8) headers(g);
+    // all codes are in registers before the first of them is overwritten, by whichever lane
+#pragma unroll
+    for (int t = 0; t < 16; ++t) asm volatile("" ::"v"(x[t]));
+    vmem_order_fence();
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
         uint32_t y[8];
