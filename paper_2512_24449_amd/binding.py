@@ -1,5 +1,6 @@
 """Thin binding of libpackkv.so -- argument marshalling only: ctypes, and for the calls of a decode step and of an append
-a native module (csrc/binding_native.cpp) that is tried first and leaves every argument it does not expect to the code here.
+a native module (csrc/binding_native.cpp) that is tried first and leaves every argument it does not expect to the code here,
+which makes every call where that module cannot be built or loaded.
 
 Function names follow the C ABI (include/packkv.h).  PyTorch is used for
 device memory and streams; every step of the path runs in the HIP kernels.
@@ -9,7 +10,10 @@ fails loudly.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
+import subprocess
+import warnings
 
 import torch
 
@@ -69,14 +73,41 @@ def library_path() -> str:
     return _build.LIB
 
 
+def _load_native(L):
+    """The native module on top of the library L, built first only if it does not exist; None where it cannot be had."""
+    try:
+        path = _build.native_path()
+        if not os.path.exists(path):
+            _build.build_native()
+        spec = importlib.util.spec_from_file_location(__package__ + "._native", path)
+        native = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(native)
+        native.bind(tuple(C.cast(getattr(L, name), C.c_void_p).value for name in _NATIVE_CALLS), _check,
+                    _current_device, _current_raw_stream, getattr(torch._C, "_cuda_isInBadFork", None))
+        return native
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        warnings.warn("the binding's native part is not available, calls are marshalled in Python: %s" % e, RuntimeWarning)
+        return None
+
+
+class _PythonCalls:
+    """In the place of the native module's Calls: leaves every call to the Python code."""
+
+    def set_handle(self, address):
+        pass
+
+    def append(self, *args):
+        return NotImplemented
+
+    k_matvec = softmax = v_matvec = attention = restore = release = append
+
+
 def lib():
     """Load libpackkv.so and the native module; build them first only if they do not exist."""
     global _lib, _native
     if _lib is None:
         if not os.path.exists(_build.LIB):
             _build.build()
-        if not os.path.exists(_build.NATIVE):
-            _build.build_native()
         L = C.CDLL(_build.LIB)
         vp, i32, i64, f32 = C.c_void_p, C.c_int32, C.c_int64, C.c_float
         L.kv_query_sizes.argtypes = [C.POINTER(kv_config_t), C.c_double, C.POINTER(kv_sizes_t)]
@@ -114,10 +145,7 @@ def lib():
             if name not in ("kv_cache_tokens", "kv_strerror", "kv_fp16_v_workspace_bytes",
                             "kv_page_pool_state_bytes"):
                 getattr(L, name).restype = C.c_int
-        from . import _native as native
-        native.bind(tuple(C.cast(getattr(L, name), vp).value for name in _NATIVE_CALLS), _check,
-                    _current_device, _current_raw_stream, getattr(torch._C, "_cuda_isInBadFork", None))
-        _lib, _native = L, native
+        _lib, _native = L, _load_native(L)
     return _lib
 
 
@@ -231,7 +259,7 @@ class PackedKVCache:
             else:
                 _check(lib().kv_cache_create(C.byref(self.cfg), C.byref(bufs), C.byref(self.sizes),
                                              C.byref(handle)), "kv_cache_create")
-        self._calls = _native.Calls(batch, n_kv_heads, n_q_heads, str(self.device))
+        self._calls = _native.Calls(batch, n_kv_heads, n_q_heads, str(self.device)) if _native else _PythonCalls()
         self.handle = handle
         self.batch, self.n_kv_heads, self.n_q_heads = batch, n_kv_heads, n_q_heads
         self._q_shape, self._row_shape = (batch, n_q_heads, HEAD_DIM), (batch, n_q_heads)

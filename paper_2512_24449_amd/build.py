@@ -1,16 +1,18 @@
-"""Builds libpackkv.so (HIP, gfx950 only) in-tree with hipcc, and the binding's native part with g++."""
+"""Builds libpackkv.so (HIP, gfx950 only) in-tree with hipcc, and the binding's native part with g++.  The library works
+without that part, whose name says which Python and torch it was built against."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
+import sys
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpackkv.so")
 NATIVE_SOURCE = os.path.join(CSRC, "binding_native.cpp")
-NATIVE = os.path.join(HERE, "_native.so")
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
@@ -26,12 +28,19 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def native_path() -> str:
+    """The module that marshals the binding's frequent calls, as built against this Python and this torch."""
+    import torch
+    return os.path.join(HERE, "_native-%s-torch%s.so" % (sys.implementation.cache_tag, torch.__version__))
+
+
 def build_native(verbose: bool = False) -> str:
-    """Compile the module that marshals the binding's frequent calls (against torch's headers)."""
+    """Compile that module (against torch's headers)."""
     import sysconfig
     import torch
     base = os.path.dirname(torch.__file__)
-    tmp = NATIVE + ".tmp%d" % os.getpid()
+    native = native_path()
+    tmp = native + ".tmp%d" % os.getpid()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
            "-isystem", os.path.join(base, "include"), "-I", sysconfig.get_paths()["include"], "-o", tmp, NATIVE_SOURCE,
@@ -39,13 +48,14 @@ def build_native(verbose: bool = False) -> str:
     if verbose:
         print(" ".join(cmd))
     subprocess.check_call(cmd)
-    os.replace(tmp, NATIVE)
-    return NATIVE
+    os.replace(tmp, native)
+    return native
 
 
 def build(verbose: bool = False) -> str:
     """Compile every HIP source (one hipcc process per file, in parallel) and link them into one
-    shared library, and the native module beside it; always recompiles."""
+    shared library, and the native module beside it (without a compiler or headers for that one the binding works in
+    Python alone); always recompiles."""
     import concurrent.futures
     import shutil
     import tempfile
@@ -65,7 +75,10 @@ def build(verbose: bool = False) -> str:
         with concurrent.futures.ThreadPoolExecutor(jobs) as pool:
             native = pool.submit(build_native, verbose)
             objs = list(pool.map(compile_one, sources()))
-            native.result()
+            try:
+                native.result()
+            except (OSError, subprocess.CalledProcessError) as e:
+                warnings.warn("the binding's native part was not built: %s" % e)
         tmp = LIB + ".tmp%d" % os.getpid()
         cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs
         if verbose:
@@ -78,9 +91,10 @@ def build(verbose: bool = False) -> str:
 
 
 def stale() -> bool:
-    if not (os.path.exists(LIB) and os.path.exists(NATIVE)):
+    native = native_path()
+    if not (os.path.exists(LIB) and os.path.exists(native)):
         return True
-    t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
+    t = min(os.path.getmtime(LIB), os.path.getmtime(native))
     deps = sources() + [NATIVE_SOURCE] + glob.glob(os.path.join(CSRC, "*.h")) + [os.path.join(ROOT, "include", "packkv.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
