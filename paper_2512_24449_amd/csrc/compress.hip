@@ -20,7 +20,9 @@
 //                  paged: inside pages taken from a shared pool, index of (start, end) pairs
 //   pack_chunks    one workgroup per chunk: quantize again and write header +
 //                  payload at its final place
-// K and V share every launch.  No atomics in either path: the arena bytes are a pure function of the input.
+// K and V share every launch.  The arena bytes are a pure function of the input, whichever way a round takes: the rules for a code agree on every
+// bit pattern (quantize_value.h), and the atomics are ORs and counts in LDS, in any order the same, and the page stack's update.
+// (Only the metadata of a token without a single number differs between the ways.)
 #include <algorithm>
 #include <atomic>
 

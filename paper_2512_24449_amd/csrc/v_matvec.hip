@@ -7,8 +7,8 @@
 // are stored (v_planes.h; packs of 8 tokens and wide chunks: fp16 operands, pack8.h), the
 // softmax weights times the token scales are the other operand, and the G query heads of a group
 // share one decode.  Accumulation is fp32 inside the matrix instruction, in a fixed order: the
-// context axis is split over workgroups whose partial sums are combined by a second small kernel
-// -- no atomics, bitwise reproducible.  De-quantization is folded in:
+// context axis is split over workgroups whose partial sums are combined by a second small kernel or the last workgroup of
+// a stream -- no floating-point atomics, bitwise reproducible.  De-quantization is folded in:
 //   out_d = sum_t w_t code[t,d] + sum_g m[g,d] sum_{t in g} w_t + sum_t p_t min_t
 // (wide chunks: centred codes and minimums, vw_chunk).
 #include <algorithm>
