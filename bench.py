@@ -35,7 +35,7 @@ ROTATE_BYTES = 1.1e9             # working set to rotate over so reads come from
 # kernel takes 20 % longer in the first milliseconds after an idle phase).  Every timed loop below is
 # therefore preceded by an untimed run of the same kernels for this long, before the W warmup steps.
 CLOCK_RAMP_S = 0.5
-DOM_KERNEL = {"k": "k_planes_kernel<1, 5>", "v": "v_matvec_kernel<1, false, false>"}   # names in the profiles
+DOM_KERNEL = {"k": "k_planes_kernel<1, 5>", "v": "v_matvec_kernel<1, false, false, 0>"}   # names in the profiles
 
 
 def stored_profile_numbers(workload, dom):
