@@ -1287,7 +1287,8 @@ __device__ inline void assemble_chunk(const StagedLane &in, bool channel_major, 
 }
 
 // New tokens behind the last full block to the start of the raw tail, by the workgroups behind those of the chunks, REST_UNITS
-// 16-byte units of a batch element each (a launch less: 4 x 3522 tokens of one head 19.4 -> 15.8 us).
+// 16-byte units of a batch element each (a launch less: 4 x 3522 tokens of one head 19.4 -> 15.8 us,
+// 2 x 40 heads of 26 blocks and 63 tokens 35.1 -> 33.0; of 58 blocks, 61.5 / 61.6, and more the copy costs what its launch did).
 constexpr int REST_UNITS = 512;
 __device__ inline void copy_rest(const PackArgs &a, const PackTensor &t, int wg) {
     const int B = t.cs.B, slice = wg / B, b = wg - slice * B;
