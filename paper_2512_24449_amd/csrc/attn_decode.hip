@@ -128,7 +128,7 @@ __device__ inline void attn_raise_reference(const float (&s)[G], float (&m_ref)[
 
 template <int G, bool FOLD>
 __device__ inline void attn_store_state(const VState<G, FOLD> &st, float (*red)[D + 4], int lane, float code_scale) {
-    v_state_store<G>(st, red, lane, code_scale);
+    v_state_store<G, false>(st, red, lane, code_scale);
 }
 template <int G>
 __device__ inline void attn_store_state(const VPlaneState<G> &st, float (*red)[D + 4], int lane, float) {

@@ -405,16 +405,21 @@ __device__ inline void kw_chunk(const uint8_t *lds0, int cur, const uint2 *ktabl
 // Centred: code - mid, and token minimums raised by mid * scale, mid about half of the tensor's largest code.  Values on both sides of 0 are the
 // usual ones; of those the sums of w code and of p min, a few hundred times their sum at 25 600 tokens, showed
 // every difference in the order of the additions (64 streams of 400 blocks, codes up to 31, 12 workgroups to a stream against 16: more than 1e-5
-// of an output; centred 4e-7).  Values on one side of their minimum and near it pay: 2 % of them above it, 8192 tokens, the V product is off by
-// 1.2e-5 at most, uncentred 2.0e-6 (normal values 3.0e-6, uncentred 2.5e-5).  The pack minimum comes in with the constant that turns the codes into numbers, so it has no sum of its
-// own (1390 vector instructions of 1470 in the fused kernel with one head, 1865 of 2062 with three); from four heads on, where that form makes
+// of an output; centred 4e-7).  The pack minimum comes in with the constant that turns the codes into numbers, so it has no sum of its
+// own (fused kernel with one head: 953 vector instructions per pair of chunks instead of 988); from four heads on, where that form makes
 // the compiler spill (32 streams of 1000 blocks at four heads 109 -> 131 us), it is added to the codes as an integer.
-template <int G>
+// SMALL: the weights are the caller's, and over long contexts so small that their fp16 residual is subnormal.  What a weight loses there is made
+// good for a value of 0, whose code, as far as codes go, is z = -min / scale: values near 0 would otherwise lose it times mid (8192 tokens, codes up to 255,
+// 98 % of the values 0 and the others above: V product off by 1.2e-5, with this 1.2e-6, uncentred 1.2e-6; 0.2 us of 14 to 20).  In the fused kernel weights are near 1.
+template <int G, bool SMALL = false>
 __device__ inline void vw_chunk(const uint8_t *lds_all, int cur, const uint4 *vtable, const VLane<G> &vl,
                                 uint32_t mt, const float (&pt)[G], VCentre centre, VState<G, true> &st) {
     const int lane = threadIdx.x & 63;
     const float scale = __half2float(__ushort_as_half(uint16_t(mt & 0xFFFFu)));
-    const float mn = fmaf(scale, centre.mid, __half2float(__ushort_as_half(uint16_t(mt >> 16))));
+    const float token_min = __half2float(__ushort_as_half(uint16_t(mt >> 16))), mn = fmaf(scale, centre.mid, token_min);
+    float zero = 0.0f;   // (z - mid) / 2^11; any number for a scale of 0, which leaves nothing to make good
+    if constexpr (SMALL)
+        zero = fminf(fmaxf(fmaf(-token_min, __builtin_amdgcn_rcpf(scale), -centre.mid), -centre.mid), centre.mid) * (1.0f / 2048.0f);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         // the fp16 split holds weights below 2^15 (hi rounds toward zero, the residual times 2^11 stays
@@ -426,6 +431,7 @@ __device__ inline void vw_chunk(const uint8_t *lds_all, int cur, const uint4 *vt
             _Float16, uint16_t(__builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(w, 0.0f)) & 0xFFFFu));
         const float lo = (w - float(hi)) * 2048.0f;
         const _Float16 lo16 = _Float16(lo);  // to nearest: the residual's rounding error has no sign bias
+        if constexpr (SMALL) st.pm[g] = fmaf(lo - float(lo16), zero, st.pm[g]);
         *reinterpret_cast<_Float16 *>(vl.blds + vl.bslot + (2 * g) * 16) = hi;
         *reinterpret_cast<_Float16 *>(vl.blds + vl.bslot + (2 * g + 1) * 16) = lo16;
     }

@@ -70,8 +70,11 @@ struct VState {
 
 // Writes this wave's sums as red[g][0..127] (outputs) and red[g][128] (sum p*min).
 // code_scale: what one unit of the A operand stands for (codes enter as code * 2^-24 * 2^lift).
+// CENTRED: the wave's sum p*min goes into its outputs and red[g][128] is 0.  Both parts of a centred sum are largest where the values
+// are all near their minimum (vw_chunk); met here they cancel before anything else is added to them (8192 tokens, 98 % of the values 0 and the
+// others above: V product off by 3e-7, 6e-6 with the two parts apart until the end).  The fused attention adds them wave by wave in any case.
 // (Lanes that took every output on its own and added the minimum terms by shuffles: see v_planes_store.)
-template <int G, bool FOLD>
+template <int G, bool CENTRED, bool FOLD>
 __device__ inline void v_state_store(const VState<G, FOLD> &st, float (*red)[D + 4], int lane,
                                      float code_scale = CODE_SCALE_LIFTED) {
     const int row = lane >> 4, col = lane & 15;
@@ -81,7 +84,12 @@ __device__ inline void v_state_store(const VState<G, FOLD> &st, float (*red)[D +
     for (int g = 0; g < G; ++g) pm[g] = wave_all_sum(st.pm[g]);
     if (lane == 0) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) red[g][D] = pm[g];
+        for (int g = 0; g < G; ++g) red[g][D] = CENTRED ? 0.0f : pm[g];
+    }
+    float mine = 0.0f;
+    if constexpr (CENTRED) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) mine = head == g ? pm[g] : mine;
     }
     // hi column + lo column: the even lane keeps rows 4 row, 4 row + 1 of every tile, the odd lane the two behind
     const bool odd = lane & 1;
@@ -107,6 +115,7 @@ __device__ inline void v_state_store(const VState<G, FOLD> &st, float (*red)[D +
                 const float4 m = to[k];
                 v = make_float4(v.x + m.x, v.y + m.y, v.z + m.z, v.w + m.w);
             }
+            if constexpr (CENTRED) v = make_float4(v.x + mine, v.y + mine, v.z + mine, v.w + mine);
             to[k] = v;
         }
     }

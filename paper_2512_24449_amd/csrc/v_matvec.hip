@@ -378,7 +378,7 @@ __global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a, VCentre centre)
                 for (int g = 0; g < G; ++g) p_next[g] = a.p[(int64_t(b) * a.H * G + h * G + g) * a.ld + tok];
             }
             if (!valid) continue;  // a block dropped by an arena overflow contributes nothing
-            if constexpr (MID) vw_chunk<G>(lds_all, cur, table, vl, mt, pt, centre, st);
+            if constexpr (MID) vw_chunk<G, true>(lds_all, cur, table, vl, mt, pt, centre, st);
             else v8_chunk<G>(lds_all, cur, table, vl, mt, pt, st);
         }
         wait_chunk_landed();
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(256) void v8_matvec_kernel(VArgs a, VCentre centre)
     }
     __syncthreads();  // every wave is done with its chunk buffers: reuse them as red[][][]
 
-    v_state_store<G>(st, red[wave], lane, MID ? 1.0f : CODE_SCALE_LIFTED);  // the wide path feeds the codes as numbers
+    v_state_store<G, MID>(st, red[wave], lane, MID ? 1.0f : CODE_SCALE_LIFTED);  // the wide path feeds the codes as numbers
     __syncthreads();
     const int64_t set_stride = int64_t(a.B) * a.H * G * V_PART_STRIDE;
     float *first_set = a.partial + int64_t(bh) * G * V_PART_STRIDE;
@@ -438,13 +438,13 @@ __global__ __launch_bounds__(256) void vw_matvec_kernel(VArgs a, VCentre centre)
             for (int g = 0; g < G; ++g) pt[g] = a.p[(int64_t(b) * a.H * G + h * G + g) * a.ld + tok];
             wait_chunk_landed();
             if (!valid) continue;  // a block dropped by an arena overflow contributes nothing
-            vw_chunk<G>(lds_all, buf, vtable, vl, mt, pt, centre, st);
+            vw_chunk<G, true>(lds_all, buf, vtable, vl, mt, pt, centre, st);
         }
         load_index(first + 4 * 64);
     }
     __syncthreads();  // every wave is done with its chunk buffer: reuse the memory as red[][][]
 
-    v_state_store<G>(st, red[wave], lane, 1.0f);  // the wide path feeds the codes as numbers
+    v_state_store<G, true>(st, red[wave], lane, 1.0f);  // the wide path feeds the codes as numbers
     __syncthreads();
     const int64_t set_stride = int64_t(a.B) * a.H * G * V_PART_STRIDE;
     float *first_set = a.partial + int64_t(bh) * G * V_PART_STRIDE;
